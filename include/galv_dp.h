@@ -82,7 +82,7 @@ typedef struct {
                                   storage only: results are identical); needs n_strategies <= 255.
                                   Shrinks the largest table of the workspace by 4x.  The sweep
                                   then keeps rolling cost rows (9 bytes per state); where the
-                                  single packed table applies (GALV_DP_FORCE_PACK) that form is
+                                  byte table applies (GALV_DP_FORCE_PACK) that form is
                                   the faster one, and this flag buys memory, not time */
 
 #define GALV_DP_NO_U32 4u      /* do not use the 32-bit integer-key kernels (see
@@ -98,12 +98,15 @@ typedef struct {
 #define GALV_DP_NO_PACK 32u    /* 32-bit-key instances: always keep the rolling cost rows and plain
                                   back-pointers (see GALV_DP_FORCE_PACK)                            */
 #define GALV_DP_FORCE_PACK 64u /* 32-bit-key instances, int32 back-pointers, at most 256 strategies:
-                                  keep a SINGLE table, in which the back-pointer word of a state also
-                                  carries its cost relative to the smallest former cost of its budget
-                                  column, plus one such minimum per column; no cost rows are written.
-                                  Half the bytes per state.  By default this is done when a layer has
-                                  enough workgroups to fill the chip (as for GALV_DP_FORCE_PEEK).
-                                  Results, exported tables included, are identical either way.       */
+                                  keep argmins of one byte each and, instead of cost rows, one former
+                                  minimum per budget column plus the relative costs of the few former
+                                  strategies that can win in a tile, from which the next layer rebuilds
+                                  the cells it reads; and store only the budget columns between the
+                                  first reachable one and the one from which a layer is constant.
+                                  1 to 2 bytes per state instead of 8.  By default this is done when a
+                                  layer has enough workgroups to fill the chip (as for
+                                  GALV_DP_FORCE_PEEK).  Results, exported tables included, are
+                                  identical either way.                                              */
 #define GALV_DP_FORCE_WIDE_TILES 128u   /* sweep workgroups take tiles of 256 budget columns instead of 128
                                            (17 to 256 strategies: the kernel variants that have such a twin).
                                            By default this is done when a layer has enough workgroups to
@@ -237,8 +240,8 @@ galv_status_t galv_dp_get_status(galv_dp_t *h, int32_t *status_dev, void *stream
 /*
  * Work statistics of the last solve, for instances on the 32-bit-key path (zeros otherwise):
  *   stats_dev [B][3] int64  [b][0] former-layer rows actually reduced, [b][1] usable rows listed,
- *                           [b][2] rows fetched from the cost table, each summed over the budget
- *                           tiles and the layers 1..L-1.
+ *                           [b][2] rows fetched from the cost table, each summed over the layers
+ *                           1..L-1 and the budget tiles swept (GALV_DP_FORCE_PACK leaves some out).
  * The sweep leaves out rows that cannot win any minimum of a tile (cost above the column minimum
  * by more than the largest transition cost, in every column of the tile), and does not even fetch
  * a row when two of its cells show as much; [b][0] / [b][1] is the share of the min-plus
@@ -249,7 +252,7 @@ galv_status_t galv_dp_get_stats(galv_dp_t *h, int64_t *stats_dev, void *stream);
 
 /*
  * What galv_dp_create chose for this handle from the shape and the flags (host call, no GPU work):
- *   config [4] HOST int32  [0] 1 if 32-bit-key instances keep the single packed table (see
+ *   config [4] HOST int32  [0] 1 if 32-bit-key instances keep the byte table (see
  *                              GALV_DP_FORCE_PACK), [1] 1 if the sweep peeks before it fetches a
  *                              row (GALV_DP_FORCE_PEEK), [2] internal streams the last solve used
  *                              (before any solve: what the first will use), [3] budget columns

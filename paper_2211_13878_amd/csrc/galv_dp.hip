@@ -31,10 +31,8 @@
 //    of layer costs some 90-95 % of the candidates fall away and the sweep is bound by HBM.
 //    The keys' width depends on the transition costs only; when the costs themselves outgrow
 //    32-bit cells, the same body runs over 64-bit cells (up to 256 strategies).
-//    Where a layer fills the chip, these instances keep a SINGLE table: the reduced key of a
-//    state, (cost relative to its column's former minimum) * 2^k + argmin, is what the
-//    back-pointer's 32-bit word stores, with one former minimum per budget column beside it;
-//    the next layer rebuilds the cells it reads, and no cost rows are written (half the bytes).
+//    Where a layer fills the chip, these instances keep argmins of one byte and what it takes to
+//    rebuild the few cells the next layer reads, instead of cost rows (see the byte-table sweep).
 //  * 64-bit keys: key = cost * 2^k + s' (k = ceil(log2 S)) lives in the mantissa of a double
 //    whose exponent is pinned, K = 2^52 + key; one v_add_f64 + one v_min_f64 per candidate,
 //    exact while K stays below 2^53.  Two storage widths: narrow (costs below 2^31 stored as
@@ -74,6 +72,7 @@ constexpr int kPrepThreads = 1024;     // prep_kernel: one workgroup per instanc
 constexpr int kWave = 64;
 constexpr int kEAlign = 1024;          // budget columns are padded to this
 constexpr int kMaxS = 1024;
+constexpr int kSample = 64;            // byte-table sweep: absolute costs are kept of every 64th budget column
 constexpr int kMaxSide = 16;          // internal streams per handle
 constexpr int kMaxPp = 16;            // pipeline degrees per reduce call
 #ifndef GALV_P1_BATCH
@@ -131,9 +130,8 @@ struct Layout {
     void *bp;             // argmin, un-shifted  [B][L-1][S][e_pad] of int32, or of uint8 (0xFF = none)
     int32_t bp_u8;        // 1: one-byte back-pointers
     int32_t peek;         // 1: the row-sharing sweep looks at two cells of a row before it fetches the row
-    int32_t packed;       // 1: instances on the 32-bit-key paths keep ONE table: the back-pointer word holds the
-                          //    reduced key (relative cost << k | argmin, all ones = unreachable) and the cost
-                          //    rows are replaced by one former minimum per budget column (see is_packed)
+    int32_t packed;       // 1: instances on the 32-bit-key paths keep the byte table: argmins in one byte, and
+                          //    instead of cost rows what it takes to rebuild a cell (see PackTables)
     int32_t synth_l1;     // 1: the 32-bit-key sweep makes up layer 0's cells (a constant per strategy)
                           //    when it sweeps layer 1, so layer 0's row is never written nor read
     int32_t b_off, b_step; // a sweep launch covers instances b_off + z * b_step (dealt over streams)
@@ -145,7 +143,8 @@ struct Layout {
     int32_t *nvalid;      // how many of them    [B][L]
     uint32_t *dclamp;     // 32-bit-key path: largest R + 1, the clamp of relative costs  [B]
     int32_t *hdr;         // what a sweep workgroup needs first, in one place: status, budget, usable strategies of
-                          // the former layer, clamp, transition matrix of the layer; 3 unused  [B][L][8]
+                          // the former layer, clamp, transition matrix of the layer, first reachable column,
+                          // last column worth sweeping (byte table), smallest usable memory  [B][L][8]
     int32_t *status;      // per instance        [B]
     int32_t *last;        // best last strategy  [B]
     int32_t *lead_mode;   // whose infinity leads the rows hold (lead_kind), 0 none  [B]
@@ -196,23 +195,27 @@ __device__ __forceinline__ int lead_kind(int st) {
     return 0;
 }
 
-// Whether instance status st keeps the single packed table (a handle-wide choice of kernels, and
+// Whether instance status st keeps the byte table (a handle-wide choice of kernels, and
 // the instance must be on a 32-bit-key path; one layer has no table at all).
 __device__ __forceinline__ bool is_packed(const Layout &a, int st) {
     return a.packed && a.L > 1 && (st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE);
 }
 
-// Back-pointer of un-shifted cell idx, whichever width the handle stores.
-__device__ __forceinline__ int32_t load_bp(const Layout &a, int st, int64_t idx) {
+// Back-pointer of un-shifted cell (layer l >= 1, strategy s, column x), whichever width the handle
+// stores.  The byte table holds the columns [first, last] of the layer's header record: below is
+// unreachable, above is constant.
+__device__ __forceinline__ int32_t load_bp(const Layout &a, int st, int b, int l, int64_t s, int64_t x) {
+    const int64_t row = (((int64_t)b * (a.L - 1) + (l - 1)) * a.S + s) * a.e_pad;
     if (is_packed(a, st)) {
-        const uint32_t w = static_cast<const uint32_t *>(a.bp)[idx];
-        return w == 0xffffffffu ? -1 : (int32_t)(w & ((1u << a.k_bits) - 1u));
+        const int32_t *h = a.hdr + ((int64_t)b * a.L + l) * 8;
+        if (x < h[5]) return -1;
+        return static_cast<const uint8_t *>(a.bp)[row + (x < h[6] ? x : h[6])];
     }
     if (a.bp_u8) {
-        const uint8_t v = static_cast<const uint8_t *>(a.bp)[idx];
+        const uint8_t v = static_cast<const uint8_t *>(a.bp)[row + x];
         return v == 0xFF ? -1 : (int32_t)v;
     }
-    return static_cast<const int32_t *>(a.bp)[idx];
+    return static_cast<const int32_t *>(a.bp)[row + x];
 }
 __device__ __forceinline__ void store_bp(const Layout &a, int64_t idx, int32_t v) {
     if (a.bp_u8)
@@ -297,6 +300,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
     __shared__ unsigned long long rmax[64];  // max of each transition matrix (64 at a time)
     __shared__ unsigned long long red[kPrepThreads];
     __shared__ unsigned long long bound_s;
+    __shared__ int m_top;                          // layer 0's largest usable memory
     if (tid == 0) bad = 0;
     __syncthreads();
 
@@ -457,6 +461,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
         h[2] = 0;
         h[3] = (int32_t)a.dclamp[b];
         h[4] = (ridx && l >= 1 && st >= 0) ? ridx[l] : 0;
+        h[5] = 0;
+        h[6] = budget;
     }
     __syncthreads();
     if (!narrow_cells(st) && st != GALV_INSTANCE_OK_FAST_WIDE && st != GALV_INSTANCE_OK_U32_WIDE) return;
@@ -502,7 +508,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
     for (int64_t l = wave; l < L; l += kPrepThreads / kWave) {
         uint64_t *lst = a.vlist + ((int64_t)b * L + l) * a.S_pad;
         uint64_t *lc = a.vcost + ((int64_t)b * L + l) * a.S_pad;
-        int n = 0;
+        int n = 0, m_lo = budget + 1, m_hi = 0;    // usable strategies, their smallest and largest memory
         uint64_t last_ent = 0, last_c = 0;         // the list's last entry so far (wave-uniform)
         for (int s0 = 0; s0 < (int)S; s0 += kWave) {
             const int sx = s0 + lane;
@@ -510,6 +516,10 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
             const int sh = in ? m[l * S + sx] : 0;
             const uint64_t cv = in ? (uint64_t)c[l * S + sx] : 0;
             const bool ok = in && sh <= budget;
+            if (ok) {
+                m_lo = min(m_lo, sh);
+                m_hi = max(m_hi, sh);
+            }
             const uint64_t ent = ((uint64_t)(uint32_t)sh << 32) | (uint32_t)sx;
             const uint64_t votes = __builtin_amdgcn_ballot_w64(ok);
             if (ok) {
@@ -524,9 +534,16 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
                 n += __builtin_popcountll(votes);
             }
         }
+#pragma unroll
+        for (int w = kWave / 2; w > 0; w >>= 1) {
+            m_lo = min(m_lo, __shfl_xor(m_lo, w, kWave));
+            m_hi = max(m_hi, __shfl_xor(m_hi, w, kWave));
+        }
         if (lane == 0) {
             a.nvalid[(int64_t)b * L + l] = n;
+            a.hdr[((int64_t)b * L + l) * 8 + 7] = m_lo;
             if (l + 1 < L) a.hdr[((int64_t)b * L + l + 1) * 8 + 2] = n;
+            if (l == 0) m_top = m_hi;
         }
         // Past the list's end its last entry repeats (it changes no minimum: min(x, x) = x), so
         // a sweep that walks a fixed number of entries needs no bound check; an empty list is
@@ -536,6 +553,30 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
                 lst[i] = last_ent;
                 lc[i] = last_c;
             }
+    }
+    if (!is_packed(a, st)) return;
+    // Columns of each layer that are worth sweeping (see the byte-table sweep): from the sum of the
+    // smallest memories before it, saturating above the budget (a wave's prefix sum, 64 layers at a
+    // time); layer 1 up to layer 0's largest memory, later layers as live_step finds.
+    __syncthreads();
+    if (wave != 0) return;
+    int64_t before = 0;
+    for (int l0 = 0; l0 < (int)L; l0 += kWave) {
+        const int l = l0 + lane;
+        int32_t *h = a.hdr + ((int64_t)b * L + (l < L ? l : L - 1)) * 8;
+        const int64_t mine = l < L ? h[7] : 0;
+        int64_t sum = mine;
+#pragma unroll
+        for (int w = 1; w < kWave; w <<= 1) {
+            const int64_t o = __shfl_up((long long)sum, w, kWave);
+            if (lane >= w) sum += o;
+        }
+        if (l < L) {
+            const int64_t y = before + sum - mine;
+            h[5] = (int32_t)(y <= budget ? y : (int64_t)budget + 1);
+            if (l == 1) h[6] = m_top < budget - (int)mine ? m_top : budget - (int)mine;
+        }
+        before += __shfl((long long)sum, kWave - 1, kWave);
     }
 }
 
@@ -1168,27 +1209,18 @@ constexpr int keep_rows(int ts, int ng, int wpe, int cols) {       // cols: budg
 //      and every wave reduces that list.
 // Only the survivors' keys live in LDS, as many rows as fit without costing a resident workgroup
 // (keep_rows), which is what lets three 8-wave workgroups share a CU at S = 128.
-//
-// PACK: the table of back-pointers is the ONLY table.  The reduced key of a state already holds
-// both results, (cost relative to the column's former minimum Cmin) << k | argmin, and
-//     U_l[e'][s] = Cmin_l[e'] + (key >> k) + c(l, s),
-// so the sweep stores the key where the back-pointer goes (all ones = unreachable), one Cmin
-// per budget column beside it (rolling, in the space of the cost rows, which it replaces), and
-// the next layer rebuilds the cells of the rows it fetches: 4 bytes written and at most 4 read
-// per state instead of 8 and 4.  The backtrack masks the index out of the word.
-template <int TS, int TE, int NG, class BP, class Cell, bool PACK, int KEEP>
+template <int TS, int TE, int NG, class BP, class Cell, int KEEP>
 __device__ __forceinline__ void sweep_u32_shared(const Layout &a, int g, int l, int b, int budget,
                                                  int64_t tile_start, bool add_stats, int n, uint32_t dmax,
                                                  int r_sel, uint64_t my_ent, uint64_t my_c0_64) {
     // n, dmax, r_sel: the former layer's usable strategies, the clamp and the layer's transition
     // matrix, from the header record.  my_ent, my_c0_64: lane r (and lane 32 + r) holds the list
-    // entry of this wave's row g + NG * r and that strategy's c(l-1, s'), which made-up and
-    // rebuilt cells add; the kernel requests them before it knows anything else (their addresses
+    // entry of this wave's row g + NG * r and that strategy's c(l-1, s'), which made-up
+    // cells hold; the kernel requests them before it knows anything else (their addresses
     // depend on the workgroup's position only), so that they arrive together with the header.
     // Fetched as scalars where they are used, one row at a time, they form a chain of dependent
     // round trips (entry, then c, then the cells) that costs more than everything else a tile
     // does.  Rows that turn out to be needed get their entry broadcast from its lane.
-    static_assert(!PACK || sizeof(BP) == 4, "a key needs the whole 32-bit word");
     // Cell: uint32_t (costs below 2^31, infinity = 2^31) or uint64_t (any cost up to the 2^62
     // precondition, infinity = 2^62).  Only RELATIVE costs enter the 32-bit keys, so the wide form
     // runs the same arithmetic and the same pruning; it moves 8-byte cells.
@@ -1219,44 +1251,18 @@ __device__ __forceinline__ void sweep_u32_shared(const Layout &a, int g, int l, 
     const ConstPtr<uint32_t> Rk =
         as_const(reinterpret_cast<const uint32_t *>(a.Rk + ((int64_t)b * a.nR + r_sel) * S * a.S_pad) + s0);
     const ConstPtr<uint64_t> ck = as_const(a.ck + ((int64_t)b * a.L + l) * a.S_pad + s0);
-    // PACK: the former layer's words (rows of e_pad, no lead: a column below the shift is tested
-    // for instead) and column minima, and this layer's column minima
-    const uint32_t *Wp = static_cast<const uint32_t *>(a.bp) +
-                         ((int64_t)b * (a.L - 1) + (l >= 2 ? l - 2 : 0)) * S * a.e_pad;
-    const Cell *Mp = reinterpret_cast<const Cell *>(a.U[(l - 1) & 1] + (int64_t)b * a.S_pad * a.row * 8);
-    Cell *Mn_tile = reinterpret_cast<Cell *>(a.U[l & 1] + (int64_t)b * a.S_pad * a.row * 8) + tile_start;
     const Cell my_c0 = (Cell)my_c0_64;
 
     // The shifted cells of one usable former strategy for this lane's columns.  Layer 0's table
     // is a constant per strategy, U_0[e'][s'] = c(0, s'), so when layer 1 is swept its cells are
     // made up here (infinity below the shift) instead of being read.
     const bool first = l == 1;                     // uniform
-    // (cp = c(l-1, s'): what a made-up or rebuilt cell adds; unused for stored cells)
+    // (cp = c(l-1, s'): what a made-up cell holds; unused for stored cells)
     auto load_row = [&](uint64_t ent, Cell cp, Cell (&out)[TE]) {
         const uint32_t sp = (uint32_t)ent, shift = (uint32_t)(ent >> 32);
         if (first) {
 #pragma unroll
             for (int j = 0; j < TE; ++j) out[j] = e0 + j * kWave >= (int64_t)shift ? cp : kInfCell;
-        } else if constexpr (PACK) {
-            const uint32_t *w = Wp + (int64_t)sp * a.e_pad;
-            uint32_t wv[TE];
-            Cell mv[TE];
-            bool ok[TE];
-#pragma unroll
-            for (int j = 0; j < TE; ++j) {
-                const int64_t idx = e0 + j * kWave - (int64_t)shift;
-                ok[j] = idx >= 0;
-                const uint32_t x = ok[j] ? (uint32_t)idx : 0u;       // idx < e_pad <= 2^31 + 1024
-                wv[j] = w[x];
-                mv[j] = Mp[x];
-            }
-#pragma unroll
-            for (int j = 0; j < TE; ++j) {
-                // (the sum first, then a select between two values: a load used in one arm only
-                // would be moved into that arm, behind the other load's round trip)
-                const Cell cell = mv[j] + (Cell)(wv[j] >> k) + cp;
-                out[j] = ok[j] && wv[j] != 0xffffffffu ? cell : kInfCell;
-            }
         } else {
             const Cell *p = Up + (int64_t)sp * pitch - (int64_t)shift;
 #pragma unroll
@@ -1310,13 +1316,6 @@ __device__ __forceinline__ void sweep_u32_shared(const Layout &a, int g, int l, 
         const int64_t idx = tile_start + (my_last ? kCols - 1 : -1) - (int64_t)my_shift;
         if (first) {
             mine = idx < 0 ? kInfCell : my_c0;     // this lane's column lies below the row's shift
-        } else if constexpr (PACK) {
-            const bool ok = idx >= 0;
-            const uint32_t x = ok ? (uint32_t)idx : 0u;
-            const uint32_t wv = Wp[(int64_t)my_sp * a.e_pad + x];
-            const Cell mv = Mp[x];
-            const Cell cell = mv + (Cell)(wv >> k) + my_c0;
-            mine = ok && wv != 0xffffffffu ? cell : kInfCell;
         } else {
             mine = Up[(int64_t)my_sp * pitch + (idx - tile_start)];   // (the lead holds infinity below the shift)
         }
@@ -1343,58 +1342,13 @@ __device__ __forceinline__ void sweep_u32_shared(const Layout &a, int g, int l, 
         Cell pm[TE];
 #pragma unroll
         for (int j = 0; j < TE; ++j) pm[j] = kAllOnes;
-        if (PACK && !first) {
-            // Rebuilt cells: the words and column minima of kChunk rows are requested before the
-            // first of them is used, so the rows' round trips overlap (a row that is not read
-            // counts as unreachable: it leaves every minimum alone).
-            constexpr int kChunk = 4;
 #pragma unroll
-            for (int r0 = 0; r0 < TS; r0 += kChunk) {
-                uint32_t wv[kChunk][TE];
-                Cell mv[kChunk][TE];
+        for (int r = 0; r < TS; ++r) {
+            if (keep >> r & 1) {
+                load_row(read_lane(my_ent, r), read_lane(my_c0, r), rowc[r]);
+            } else {
 #pragma unroll
-                for (int q = 0; q < kChunk; ++q) {
-                    const int r = r0 + q;
-                    if (r >= TS) break;
-                    if (keep >> r & 1) {
-                        const uint64_t e_r = read_lane(my_ent, r);
-                        const uint32_t *w = Wp + (int64_t)(uint32_t)e_r * a.e_pad;
-#pragma unroll
-                        for (int j = 0; j < TE; ++j) {
-                            const int64_t idx = e0 + j * kWave - (int64_t)(uint32_t)(e_r >> 32);
-                            const uint32_t x = idx >= 0 ? (uint32_t)idx : 0u;
-                            const uint32_t v = w[x];
-                            wv[q][j] = idx >= 0 ? v : 0xffffffffu;
-                            mv[q][j] = Mp[x];
-                        }
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < kChunk; ++q) {
-                    const int r = r0 + q;
-                    if (r >= TS) break;
-                    if (keep >> r & 1) {           // (wave-uniform: most rows are not read at all)
-                        const Cell cp = read_lane(my_c0, r);
-#pragma unroll
-                        for (int j = 0; j < TE; ++j) {
-                            const Cell cell = mv[q][j] + (Cell)(wv[q][j] >> k) + cp;
-                            rowc[r][j] = wv[q][j] != 0xffffffffu ? cell : kInfCell;
-                        }
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < TE; ++j) rowc[r][j] = kAllOnes;      // leaves every minimum alone
-                    }
-                }
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < TS; ++r) {
-                if (keep >> r & 1) {
-                    load_row(read_lane(my_ent, r), read_lane(my_c0, r), rowc[r]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < TE; ++j) rowc[r][j] = kAllOnes;          // leaves every minimum alone
-                }
+                for (int j = 0; j < TE; ++j) rowc[r][j] = kAllOnes;          // leaves every minimum alone
             }
         }
 #pragma unroll
@@ -1541,36 +1495,19 @@ __device__ __forceinline__ void sweep_u32_shared(const Layout &a, int g, int l, 
                 const uint32_t key = acc[s][j];
                 // (wave-uniform row address + the lane's offset: no per-store address arithmetic)
                 BP *bp_row = bp_tile + (int64_t)s * a.e_pad;
-                if constexpr (PACK) {
-                    // (a winning key is never all ones: the winner's relative cost is not clamped)
-                    bp_row[(uint32_t)lane + j * kWave] = (BP)(alive ? key : 0xffffffffu);
-                } else {
-                    Cell *un_row = Un_tile + (int64_t)s * pitch;
-                    un_row[(uint32_t)lane + j * kWave] = alive ? cmin[j] + (Cell)(key >> k) + cs : kInfCell;
-                    __builtin_nontemporal_store((BP)(alive ? (int32_t)(key & mask) : -1),
-                                                &bp_row[(uint32_t)lane + j * kWave]);
-                }
+                Cell *un_row = Un_tile + (int64_t)s * pitch;
+                un_row[(uint32_t)lane + j * kWave] = alive ? cmin[j] + (Cell)(key >> k) + cs : kInfCell;
+                __builtin_nontemporal_store((BP)(alive ? (int32_t)(key & mask) : -1),
+                                            &bp_row[(uint32_t)lane + j * kWave]);
             }
-        }
-    }
-    if constexpr (PACK) {
-        (void)mask;
-        (void)Un_tile;
-        if (g == 0) {
-            // (of an unreachable column every word is all ones and this value is never used)
-#pragma unroll
-            for (int j = 0; j < TE; ++j) Mn_tile[(uint32_t)lane + j * kWave] = cmin[j];
         }
     }
 }
 
 // UX: the 32-bit-key body keeps half-size accumulators, so it may take UX (1 or 2) times
 // the budget columns per lane; the 64-bit-key bodies then cover the same tile in UX steps.
-// PACK (row-sharing variants with int32 back-pointers): the 32-bit-key instances keep the single
-// packed table; the handle says so in Layout::packed and launches this instantiation.
-template <int TS, int TE, int NG, int WPE, class BP, int W, int UX, int SHARE, int PACK>
+template <int TS, int TE, int NG, int WPE, class BP, int W, int UX, int SHARE>
 __global__ __launch_bounds__(W * kWave, WPE) void sweep_kernel(Layout a, int l) {
-    static_assert(!PACK || (SHARE && sizeof(BP) == 4), "the packed table needs the row-sharing body and 32-bit words");
     const int wave = uniform(threadIdx.x >> 6);    // the only use of the thread-index register (see lane_id)
     const int b = a.b_off + blockIdx.z * a.b_step;
     // The row-sharing body's list entries (see there): requested first, ahead of the header.
@@ -1606,7 +1543,7 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_kernel(Layout a, int l) 
     if (tile_start > budget) return;
     if (st == GALV_INSTANCE_OK_FAST_U32) {
         if constexpr (SHARE)
-            sweep_u32_shared<TS, TE * UX, NG, BP, uint32_t, PACK != 0, keep_rows(TS, NG, WPE, kWave * TE * UX)>(a, wave, l, b, budget, tile_start, false, n_prev, dmax, r_sel, my_ent, my_c0);
+            sweep_u32_shared<TS, TE * UX, NG, BP, uint32_t, keep_rows(TS, NG, WPE, kWave * TE * UX)>(a, wave, l, b, budget, tile_start, false, n_prev, dmax, r_sel, my_ent, my_c0);
         else
             sweep_u32<TS, TE * UX, NG, BP>(a, wave, l, b, budget, tile_start);
     } else if (st == GALV_INSTANCE_OK_U32_WIDE) {
@@ -1616,7 +1553,7 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_kernel(Layout a, int l) 
             for (int h = 0; h < TE; ++h) {
                 if (tile_start + h * (kWave * UX) > budget) break;   // workgroup-uniform
                 if (h) __syncthreads();                              // the LDS of the part before is free again
-                sweep_u32_shared<TS, UX, NG, BP, uint64_t, PACK != 0, keep_rows(TS, NG, WPE, kWave * TE * UX)>(a, wave, l, b, budget, tile_start + h * (kWave * UX), h > 0, n_prev, dmax, r_sel, my_ent, my_c0);
+                sweep_u32_shared<TS, UX, NG, BP, uint64_t, keep_rows(TS, NG, WPE, kWave * TE * UX)>(a, wave, l, b, budget, tile_start + h * (kWave * UX), h > 0, n_prev, dmax, r_sel, my_ent, my_c0);
             }
         }
     } else if (st == GALV_INSTANCE_OK_FAST) {
@@ -1630,6 +1567,586 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_kernel(Layout a, int l) 
     }
 }
 
+// ------------------------------------------------------------ byte-table sweep
+//
+// The packed form of the 32-bit-key sweep, for handles whose layers fill the chip.  There the
+// sweep is bound by what it writes and by its chain of round trips, so it keeps little per state:
+//   * the argmin, one byte: the only table that lives on after the next layer;
+//   * and, per budget column, the former minimum Cmin and the clamped relative costs
+//     rel(s') = C[l-1][e'][s'] - Cmin of those former strategies that are alive in the tile (a few
+//     of S when the pruning bites).
+// That is enough to rebuild any cell, because its argmin is always one of the alive strategies:
+//     U_l[e'][s] = Cmin_l[e'] + rel_l(s')[e'] + R_l(s', s) + c(l, s)   with s' = argmin byte.
+// The next layer fetches few rows, so rebuilding them (two dependent loads) costs less than
+// writing every cell: 1 byte + 4 bytes x (share of rows alive) are written per state, where a
+// 32-bit key per state was 4.  A lane owns TE consecutive columns, so the bytes of a row leave as
+// one word per lane.  For the peek, absolute costs of every 64th column are kept too ("samples",
+// 1/16 byte per state): rows are non-increasing along the budget axis, so the sample at or after a
+// tile's last column bounds the row's cells in the tile from below and the one at or before the
+// column in front of the tile bounds every column minimum of the tile from above, in one load each.
+//
+// Only the columns [Y_l, X_l] of layer l are swept and stored:
+//   * below Y_l = sum of the smallest memories of the layers before l nothing is reachable;
+//   * from X_l = max_s (memory of the best plan without any memory limit that ends in s) on, every
+//     row is constant, costs and argmins alike: the unlimited optimum fits, no column offers a
+//     candidate below it, and the lowest-index minimiser is the same.  Readers clamp to X_l.
+//     (And columns beyond budget - min_s m(l, s) are read by nobody.)
+// 55-65 % of the columns of 22 strategies x 32-48 layers fall away, 35-40 % of 44 x 96, 16 % of
+// 128 x 128.  live_step() runs the unlimited recurrence one layer ahead of the sweep.
+//
+// Measured, before (a 32-bit key per state, all columns, 2 / 6 / 16 streams) and after (1 / 2 / 2), whole
+// solves: 22 strategies x 24576 columns x 48 layers x 32 instances 1.30 -> 0.82 ms, 44 x 32768 x 96 x 64
+// (budgets of a quarter up) 6.7 -> 3.6 ms, 128 x 65536 x 128 x 16 20.7 -> 12.4 ms.
+struct PackTables {                                // of one instance, in the space of the cost rows
+    uint32_t *rel;                                 // [S_pad][e_pad]
+    char *cost;                                    // samples [S_pad][e_pad / 64] of Cell
+    char *cmin;                                    // [e_pad] of Cell
+    uint64_t *V;                                   // [S_pad] unlimited optimum ending in s
+    int32_t *mem;                                  // [S_pad] its memory in the layers before
+};
+__device__ __forceinline__ PackTables pack_tables(const Layout &a, int parity, int b) {
+    char *base = a.U[parity] + (int64_t)b * a.S_pad * a.row * 8;
+    PackTables t;
+    t.rel = reinterpret_cast<uint32_t *>(base);
+    t.cost = base + (int64_t)a.S_pad * a.e_pad * 4;
+    t.cmin = t.cost + (int64_t)a.S_pad * (a.e_pad / kSample) * 8;
+    t.V = reinterpret_cast<uint64_t *>(t.cmin + a.e_pad * 8);
+    t.mem = reinterpret_cast<int32_t *>(t.V + a.S_pad);
+    return t;                                      // (rows reserve 8 bytes per column, leads included: ample)
+}
+__device__ __forceinline__ const uint32_t *rkeys(const Layout &a, int b, int r) {
+    return reinterpret_cast<const uint32_t *>(a.Rk + ((int64_t)b * a.nR + r) * a.S * a.S_pad);
+}
+
+// Smallest value over the wave's lanes, in every lane.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+#define GALV_DPP_MIN(ctrl) v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, ctrl, 0xf, 0xf, false))
+    GALV_DPP_MIN(0x111);                           // row_shr 1, 2, 4, 8: minimum of each row of 16 in its last lane
+    GALV_DPP_MIN(0x112);
+    GALV_DPP_MIN(0x114);
+    GALV_DPP_MIN(0x118);
+#undef GALV_DPP_MIN
+    return min(min(read_lane(v, 15), read_lane(v, 31)), min(read_lane(v, 47), read_lane(v, 63)));
+}
+__device__ __forceinline__ uint64_t wave_min(uint64_t v) {
+#pragma unroll
+    for (int w = kWave / 2; w > 0; w >>= 1) {
+        const uint64_t o = (uint64_t)__shfl_xor((long long)v, w, kWave);
+        if (o < v) v = o;
+    }
+    return read_lane(v, 0);
+}
+
+// One step of the recurrence without a memory limit, for layer l of instance b: V_l(s) and the
+// memory its plan takes before layer l, from those of layer l - 1; then (tell) the last column of
+// layer l that has to be swept.  Same keys, same tie-break as the sweep.  One workgroup; S <= 16 * NG.
+template <int NG>
+__device__ __forceinline__ void live_step(const Layout &a, int wave, int b, int l, bool tell) {
+    int32_t *h = a.hdr + ((int64_t)b * a.L + l) * 8;
+    const int lane = lane_id(), tid = wave * kWave + lane;
+    const int S = a.S, k = a.k_bits;
+    const int budget = h[1], n = h[2];
+    const uint32_t dmax = (uint32_t)h[3];
+    const PackTables from = pack_tables(a, (l - 1) & 1, b), to = pack_tables(a, l & 1, b);
+    const uint64_t *list = a.vlist + ((int64_t)b * a.L + (l - 1)) * a.S_pad;
+    const uint64_t *lcost = a.vcost + ((int64_t)b * a.L + (l - 1)) * a.S_pad;
+    uint32_t *dv = lds_cells, *sp = dv + a.S_pad, *mem = sp + a.S_pad, *part = mem + a.S_pad;   // part [NG][S_pad]
+    uint32_t *top = part + NG * a.S_pad;
+    if (n == 0) {                                  // nothing reachable from here on
+        if (tid == 0 && tell) h[6] = -1;
+        return;
+    }
+    // (list entry i belongs to thread i of every wave's view: each wave takes the minimum itself)
+    uint64_t vmin = ~0ull;
+    for (int i = lane; i < n; i += kWave) {
+        const uint32_t s = (uint32_t)list[i];
+        const uint64_t v = l == 1 ? lcost[i] : from.V[s];
+        vmin = v < vmin ? v : vmin;
+    }
+    vmin = wave_min(vmin);
+    if (tid < n) {
+        const uint64_t ent = list[tid];
+        const uint32_t s = (uint32_t)ent;
+        const uint64_t rel = (l == 1 ? lcost[tid] : from.V[s]) - vmin;
+        dv[tid] = (rel < dmax ? (uint32_t)rel : dmax) << k;
+        sp[tid] = s;
+        // (memories saturate just above the budget)
+        const int64_t x = (int64_t)(l == 1 ? 0 : from.mem[s]) + (int64_t)(ent >> 32);
+        mem[s] = (uint32_t)(x <= budget ? x : (int64_t)budget + 1);
+    }
+    if (tid == 0) *top = 0;
+    __syncthreads();
+    const uint32_t *Rk = rkeys(a, b, h[4]);
+    constexpr int kQ = (16 * NG + kWave - 1) / kWave;
+    uint32_t best[kQ];
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) best[q] = 0xffffffffu;
+#pragma unroll 4
+    for (int i = wave; i < n; i += NG) {
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+            const int s = q * kWave + lane;
+            best[q] = min(best[q], dv[i] + Rk[(int64_t)sp[i] * a.S_pad + (s < S ? s : S - 1)]);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kQ; ++q)
+        if (q * kWave + lane < S) part[wave * a.S_pad + q * kWave + lane] = best[q];
+    __syncthreads();
+    if (tid < S) {
+        uint32_t key = 0xffffffffu;
+        for (int w = 0; w < NG && w < n; ++w) key = min(key, part[w * a.S_pad + tid]);
+        const uint32_t x = mem[key & ((1u << k) - 1u)];
+        to.V[tid] = vmin + (key >> k) + (uint64_t)a.c[((int64_t)b * a.L + l) * S + tid];
+        to.mem[tid] = (int32_t)x;
+        if (a.m[((int64_t)b * a.L + l) * S + tid] <= budget) atomicMax(top, x);
+    }
+    __syncthreads();
+    if (tid == 0 && tell) {
+        const int64_t fits = (int64_t)budget - h[7];         // beyond it nobody reads layer l
+        h[6] = (int32_t)((int64_t)*top < fits ? (int64_t)*top : fits);
+    }
+}
+
+// Rows of cells a tile keeps in LDS, out of a resident workgroup's share of the 160 KB.
+constexpr int byte_keep_rows(int ts, int ng, int wpe, int cols) {
+    const int wgs = wpe * 4 / ng > 0 ? wpe * 4 / ng : 1;
+    const int share = 160 * 1024 / wgs < 128 * 1024 ? 160 * 1024 / wgs : 128 * 1024;
+    int rows = (share - ng * cols * 4 - ts * ng * 16 - 512) / (cols * 4 + 4);
+    if (rows > ts * ng) rows = ts * ng;
+    rows -= rows % ng;
+    return rows < ng ? ng : rows;
+}
+constexpr unsigned byte_lds(int ts, int ng, int wpe, int cols) {
+    const int keep = byte_keep_rows(ts, ng, wpe, cols);
+    const unsigned tile = (unsigned)(ng * cols * 4 + keep * cols * 4 + ts * ng * 16 + keep * 4 + 16);
+    const unsigned live = (unsigned)((3 + ng) * ts * ng * 4 + 4);       // live_step
+    return tile > live ? tile : live;
+}
+
+// What a tile needs to know of its layer and of the former one.
+struct TileHdr {
+    int n;                                         // usable strategies of the former layer
+    uint32_t dmax;
+    int r, r_prev;                                 // transition matrices of this layer and of the former
+    int y_prev, x_prev;                            // reachable from / stored up to, former layer
+};
+
+// The kernel's Layout argument, read again from the argument segment: pointers derived from this
+// copy are computed where they are used.  (Derived once at the top they would outlive the
+// min-plus loop, whose transition keys take 64 of the scalar registers, and be spilled around it.)
+__device__ __forceinline__ const Layout &layout_again() {
+    ConstPtr<Layout> p = (ConstPtr<Layout>)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const Layout *)p;
+}
+
+// What rebuilding the former layer's cells takes.
+template <class Cell>
+struct Former {
+    const uint8_t *bp;
+    const Cell *cmin;
+    const uint32_t *rel, *R;
+    int64_t e_pad;
+    int S_pad, k;
+    __device__ __forceinline__ Former(const Layout &a, int b, int l, int r) {
+        const PackTables t = pack_tables(a, (l - 1) & 1, b);
+        bp = static_cast<const uint8_t *>(a.bp) + ((int64_t)b * (a.L - 1) + (l == 1 ? 0 : l - 2)) * a.S * a.e_pad;
+        cmin = reinterpret_cast<const Cell *>(t.cmin);
+        rel = t.rel;
+        R = rkeys(a, b, r);
+        e_pad = a.e_pad;
+        S_pad = a.S_pad;
+        k = a.k_bits;
+    }
+};
+
+template <int TS, int TE, int NG, class Cell, int KEEP, int TILE>
+__device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b, int tile_start, bool add_stats,
+                                            const TileHdr &h, const uint64_t (&ent)[(TS * NG + kWave - 1) / kWave],
+                                            const uint64_t (&c0_64)[(TS * NG + kWave - 1) / kWave]) {
+    constexpr Cell kInfCell = sizeof(Cell) == 8 ? (Cell)kInf : (Cell)kInf32;
+    constexpr Cell kAllOnes = ~(Cell)0;
+    constexpr int kCols = kWave * TE;
+    constexpr int kQ = (TS * NG + kWave - 1) / kWave;
+    static_assert(TS <= 16, "one scalar load fetches the R keys of a row");
+    typedef uint32_t relv __attribute__((ext_vector_type(TE)));
+    typedef Cell cellv __attribute__((ext_vector_type(TE)));
+    __builtin_amdgcn_s_setprio(3);                 // (a wave with loads to issue goes first, as in sweep_u32_shared)
+    const int lane = lane_id();
+    const int e0 = tile_start + lane * TE;
+    const int s0 = g * TS;
+    const bool first = l == 1;
+
+    Cell *part = reinterpret_cast<Cell *>(lds_cells);                   // [NG][kCols] partial column minima
+    Cell *cells = part + NG * kCols;                                    // [KEEP][kCols] fetched rows, then their keys
+    uint64_t *row_ent = reinterpret_cast<uint64_t *>(cells + KEEP * kCols);   // [TS * NG] kept rows: list entry
+    uint64_t *row_c0 = row_ent + TS * NG;                               // [TS * NG] and c(l-1, s')
+    uint32_t *live = reinterpret_cast<uint32_t *>(row_c0 + TS * NG);    // [KEEP] slot << 16 | strategy
+    uint32_t *count = live + KEEP;                                      // [3] live rows, by pass modulo 3
+    if (g == 0 && lane == 0) count[0] = 0;
+
+    // Peek.  Lane i holds list entry i (and i + 64, ...): every wave does all rows itself, so no
+    // exchange is needed and all waves agree on which rows are fetched and who fetches them.
+    const int64_t n_samples = a.e_pad / kSample;
+    const Cell *prev_cost = reinterpret_cast<const Cell *>(pack_tables(a, (l - 1) & 1, b).cost);
+    Cell lower[kQ], upper = kAllOnes;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+        const int shift = (int)(uint32_t)(ent[q] >> 32);
+        const int last = tile_start + kCols - 1 - shift, before = tile_start - 1 - shift;
+        const bool listed = q * kWave + lane < h.n;
+        Cell lo, up;
+        if (first) {
+            lo = last >= 0 ? (Cell)c0_64[q] : kInfCell;
+            up = before >= 0 ? (Cell)c0_64[q] : kInfCell;
+        } else {
+            const Cell *row = prev_cost + (int64_t)(uint32_t)ent[q] * n_samples;
+            const int at_last = min(last, h.x_prev) / kSample;                  // (ends at or after the column)
+            const int at_before = (min(before, h.x_prev) + 1) / kSample - 1;    // (ends at or before it)
+            const bool lo_ok = last >= h.y_prev;
+            const bool up_ok = before >= 0 && at_before >= h.y_prev / TILE * (TILE / kSample);
+            const int last_stored = h.x_prev / kSample;
+            const Cell v_lo = row[lo_ok ? at_last : last_stored], v_up = row[up_ok ? at_before : last_stored];
+            lo = lo_ok ? v_lo : kInfCell;
+            up = up_ok ? v_up : kInfCell;
+        }
+        lower[q] = listed ? lo : kAllOnes;
+        upper = min(upper, listed ? up : kAllOnes);
+    }
+    const Cell bound = wave_min(upper);
+    // (no bound without a reachable column in front of the tile; rows without a reachable cell are out either way)
+    const Cell limit = a.peek && bound < kInfCell ? bound + (Cell)h.dmax : kInfCell;
+    int nk = 0;                                    // rows to fetch
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+        const bool kept = lower[q] < limit;
+        const uint64_t votes = __builtin_amdgcn_ballot_w64(kept);
+        if (kept) {                                // (all waves write the same words)
+            const int at = nk + __builtin_popcountll(votes & ((1ull << lane) - 1ull));
+            row_ent[at] = ent[q];
+            row_c0[at] = c0_64[q];
+        }
+        nk += __builtin_popcountll(votes);
+    }
+
+    // The shifted cells of kept row i for this lane's columns.
+    struct Fetch {
+        uint32_t sp[TE];                           // argmin bytes
+        Cell cmin[TE];
+        bool ok[TE];
+        int x[TE];
+    };
+    auto row_entry = [&](int i, uint32_t &sp, int &shift, Cell &cp) {
+        const uint64_t en = row_ent[i], cv = row_c0[i];
+        sp = (uint32_t)uniform((int)(uint32_t)en);
+        shift = uniform((int)(uint32_t)(en >> 32));
+        cp = (Cell)((uint64_t)(uint32_t)uniform((int)(uint32_t)(cv >> 32)) << 32 | (uint32_t)uniform((int)(uint32_t)cv));
+    };
+    auto fetch_row = [&](const Former<Cell> &t, uint32_t sp, int shift, Fetch &f) {
+        const uint8_t *w = t.bp + (int64_t)sp * t.e_pad;
+#pragma unroll
+        for (int j = 0; j < TE; ++j) {
+            const int idx = e0 + j - shift;
+            f.ok[j] = idx >= h.y_prev;
+            f.x[j] = f.ok[j] ? min(idx, h.x_prev) : h.x_prev;
+            f.sp[j] = w[(uint32_t)f.x[j]];
+            f.cmin[j] = t.cmin[(uint32_t)f.x[j]];
+        }
+    };
+    auto finish_row = [&](const Former<Cell> &t, uint32_t sp, Cell cp, const Fetch &f, Cell (&out)[TE]) {
+        uint32_t rel[TE], r[TE];
+#pragma unroll
+        for (int j = 0; j < TE; ++j) {
+            rel[j] = t.rel[(int64_t)f.sp[j] * t.e_pad + f.x[j]];
+            r[j] = t.R[f.sp[j] * (uint32_t)t.S_pad + sp];
+        }
+#pragma unroll
+        for (int j = 0; j < TE; ++j) {
+            const Cell v = f.cmin[j] + (Cell)rel[j] + (Cell)(r[j] >> t.k) + cp;
+            out[j] = f.ok[j] ? v : kInfCell;
+        }
+    };
+    auto made_up = [&](int shift, Cell cp, Cell (&out)[TE]) {
+#pragma unroll
+        for (int j = 0; j < TE; ++j) out[j] = e0 + j >= shift ? cp : kInfCell;
+    };
+
+    // Wave g fetches kept rows g, g + NG, ...: two at a time, so that their round trips overlap.
+    Cell cmin[TE];
+    {
+        const Former<Cell> former(a, b, l, h.r_prev);
+        Cell pm[TE];
+#pragma unroll
+        for (int j = 0; j < TE; ++j) pm[j] = kAllOnes;
+        auto take = [&](int i, const Cell (&v)[TE]) {
+            cellv out;
+#pragma unroll
+            for (int j = 0; j < TE; ++j) {
+                pm[j] = min(pm[j], v[j]);
+                out[j] = v[j];
+            }
+            if (i < KEEP) *reinterpret_cast<cellv *>(cells + i * kCols + lane * TE) = out;
+        };
+        for (int i = g; i < nk; i += 2 * NG) {
+            uint32_t spa, spb;
+            int sha, shb;
+            Cell ca, cb, va[TE], vb[TE];
+            row_entry(i, spa, sha, ca);
+            const bool two = i + NG < nk;
+            if (two) row_entry(i + NG, spb, shb, cb);
+            if (first) {
+                made_up(sha, ca, va);
+                if (two) made_up(shb, cb, vb);
+            } else if (two) {
+                Fetch fa, fb;
+                fetch_row(former, spa, sha, fa);
+                fetch_row(former, spb, shb, fb);
+                finish_row(former, spa, ca, fa, va);
+                finish_row(former, spb, cb, fb, vb);
+            } else {
+                Fetch fa;
+                fetch_row(former, spa, sha, fa);
+                finish_row(former, spa, ca, fa, va);
+            }
+            take(i, va);
+            if (two) take(i + NG, vb);
+        }
+        if (g < nk) {
+            cellv out;
+#pragma unroll
+            for (int j = 0; j < TE; ++j) out[j] = pm[j];
+            *reinterpret_cast<cellv *>(part + g * kCols + lane * TE) = out;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < TE; ++j) cmin[j] = kAllOnes;
+#pragma unroll
+        for (int w = 0; w < NG; ++w)
+            if (w < nk) {
+                const cellv v = *reinterpret_cast<const cellv *>(part + w * kCols + lane * TE);
+#pragma unroll
+                for (int j = 0; j < TE; ++j) cmin[j] = min(cmin[j], v[j]);
+            }
+    }
+
+    // Keys of the alive rows, and the min-plus product over them, KEEP kept rows at a time (one
+    // pass unless transition costs dwarf the spread of the layer costs).
+    uint32_t acc[TS][TE];
+#pragma unroll
+    for (int s = 0; s < TS; ++s)
+#pragma unroll
+        for (int j = 0; j < TE; ++j) acc[s][j] = 0xffffffffu;
+    const Layout &a1 = layout_again();
+    const int S_pad = a1.S_pad, k = a1.k_bits;
+    const bool idle = s0 >= a1.S;                  // an idle strategy group only fetches rows
+    const ConstPtr<uint32_t> Rk = as_const(rkeys(a1, b, h.r) + s0);
+    uint32_t rows_reduced = 0;
+    int pass = 0;
+    for (int base = 0; base < nk; base += KEEP) {
+        uint32_t *counter = count + pass % 3;
+        for (int i = base + g; i < nk && i < base + KEEP; i += NG) {
+            uint32_t sp;
+            int shift;
+            Cell cp, v[TE];
+            row_entry(i, sp, shift, cp);
+            const int slot = i - base;
+            if (base == 0) {
+                const cellv in = *reinterpret_cast<const cellv *>(cells + slot * kCols + lane * TE);
+#pragma unroll
+                for (int j = 0; j < TE; ++j) v[j] = in[j];
+            } else if (first) {
+                made_up(shift, cp, v);
+            } else {
+                const Former<Cell> former(layout_again(), b, l, h.r_prev);
+                Fetch f;
+                fetch_row(former, sp, shift, f);
+                finish_row(former, sp, cp, f, v);
+            }
+            relv d, key;
+            bool alive = false;
+#pragma unroll
+            for (int j = 0; j < TE; ++j) {
+                const Cell rel = v[j] - cmin[j];
+                d[j] = (uint32_t)min(rel, (Cell)h.dmax);
+                key[j] = d[j] << k;
+                alive |= rel < (Cell)h.dmax && cmin[j] < kInfCell;
+            }
+            if (__builtin_amdgcn_ballot_w64(alive) != 0) {   // wave-uniform
+                // (keys take the first words of the slot; wide cells leave the rest unused)
+                *reinterpret_cast<relv *>(reinterpret_cast<uint32_t *>(cells + slot * kCols) + lane * TE) = key;
+                const Layout &ar = layout_again();
+                *reinterpret_cast<relv *>(pack_tables(ar, l & 1, b).rel + (int64_t)sp * ar.e_pad + e0) = d;
+                if (lane == 0) live[atomicAdd(counter, 1u)] = (uint32_t)slot << 16 | sp;
+            }
+        }
+        if (g == 0 && lane == 0) count[(pass + 1) % 3] = 0;
+        __syncthreads();
+        if (pass == 0) __builtin_amdgcn_s_setprio(0);
+        const int cnt = uniform((int)*counter);
+        rows_reduced += (uint32_t)cnt;
+        if (!idle && cnt > 0) {
+            const int npair = (cnt + 1) / 2;       // an odd tail repeats its entry: min(x, x) = x
+            uint32_t va[2][TE], vb[2][TE];
+            uint32_t spa[2], spb[2];
+            R32Row<TS> ra[2], rb[2];
+            auto request = [&](int q, int pr) {
+                const uint32_t la = (uint32_t)uniform((int)live[2 * pr < cnt ? 2 * pr : cnt - 1]);
+                const uint32_t lb = (uint32_t)uniform((int)live[2 * pr + 1 < cnt ? 2 * pr + 1 : cnt - 1]);
+                spa[q] = la & 0xffffu;
+                spb[q] = lb & 0xffffu;
+                const relv ka = *reinterpret_cast<const relv *>(reinterpret_cast<const uint32_t *>(cells + (la >> 16) * kCols) + lane * TE);
+                const relv kb = *reinterpret_cast<const relv *>(reinterpret_cast<const uint32_t *>(cells + (lb >> 16) * kCols) + lane * TE);
+#pragma unroll
+                for (int j = 0; j < TE; ++j) {
+                    va[q][j] = ka[j];
+                    vb[q][j] = kb[j];
+                }
+            };
+            auto reduce_pair = [&](int q) {
+                // keys of the next pair's rows, in flight under this pair's arithmetic
+                ra[q ^ 1].request(Rk + (int64_t)uniform((int)spa[q ^ 1]) * S_pad);
+                rb[q ^ 1].request(Rk + (int64_t)uniform((int)spb[q ^ 1]) * S_pad);
+#pragma unroll
+                for (int s = 0; s < TS; ++s)
+                    minplus_u32x2<TE>(acc[s], va[q], vb[q], ra[q].at(s), rb[q].at(s), ra[q ^ 1], rb[q ^ 1]);
+                r32_await(ra[q ^ 1], rb[q ^ 1]);
+            };
+            request(0, 0);
+            request(1, 1);
+            ra[0].request(Rk + (int64_t)uniform((int)spa[0]) * S_pad);
+            rb[0].request(Rk + (int64_t)uniform((int)spb[0]) * S_pad);
+            r32_await(ra[0], rb[0]);
+            int pr = 0;
+            for (; pr + 2 <= npair; pr += 2) {
+                reduce_pair(0);
+                request(0, pr + 2);
+                reduce_pair(1);
+                request(1, pr + 3);
+            }
+            if (pr < npair) reduce_pair(0);
+        }
+        ++pass;
+        if (base + KEEP < nk) __syncthreads();     // the slots and the list are free again
+    }
+    const Layout &a2 = layout_again();
+    const PackTables now = pack_tables(a2, l & 1, b);
+    const int64_t e_pad = a2.e_pad;
+    if (g == 0 && lane == 0) {                     // statistics: how much the pruning removed
+        uint32_t *st = a2.stats + 2 * (((int64_t)b * (a2.L - 1) + (l - 1)) * a2.n_tiles + tile_start / TILE);
+        const uint32_t rows = rows_reduced << 16 | (uint32_t)h.n;
+        st[0] = add_stats ? st[0] + rows : rows;   // (a tile swept in several parts adds them up)
+        st[1] = add_stats ? st[1] + (uint32_t)nk : (uint32_t)nk;
+    }
+    if (g == 0) {
+        cellv out;
+#pragma unroll
+        for (int j = 0; j < TE; ++j) out[j] = cmin[j];
+        *reinterpret_cast<cellv *>(reinterpret_cast<Cell *>(now.cmin) + e0) = out;
+    }
+    if (idle) return;
+    const int S = a2.S;
+    uint8_t *bp = static_cast<uint8_t *>(a2.bp) + (((int64_t)b * (a2.L - 1) + (l - 1)) * S + s0) * e_pad + tile_start;
+
+    // (of an unreachable column the bytes are never used: readers compare with Y_l)
+    const uint32_t mask = ((1u << k) - 1u) * 0x01010101u;
+    auto store = [&](auto full) {                  // (whole groups of strategies: no test per row)
+#pragma unroll
+        for (int s = 0; s < TS; ++s)
+            if (full || s0 + s < S) {
+                uint8_t *row = bp + (int64_t)s * e_pad;
+                if constexpr (TE == 4) {
+                    const uint32_t p01 = __builtin_amdgcn_perm(acc[s][1], acc[s][0], 0x0c0c0400u);
+                    const uint32_t p23 = __builtin_amdgcn_perm(acc[s][3], acc[s][2], 0x0c0c0400u);
+                    reinterpret_cast<uint32_t *>(row)[lane] = __builtin_amdgcn_perm(p23, p01, 0x05040100u) & mask;
+                } else if constexpr (TE == 2) {
+                    reinterpret_cast<uint16_t *>(row)[lane] =
+                        (uint16_t)(__builtin_amdgcn_perm(acc[s][1], acc[s][0], 0x0c0c0400u) & mask);
+                } else {
+                    row[lane] = (uint8_t)(acc[s][0] & mask);
+                }
+            }
+        // the last column of every 64: samples for the next layer's peek
+        constexpr int kLanes = kSample / TE;
+        if ((lane & (kLanes - 1)) == kLanes - 1) {
+            const ConstPtr<uint64_t> ck = as_const(a2.ck + ((int64_t)b * a2.L + l) * S_pad + s0);
+            const uint32_t n_samples = (uint32_t)(e_pad / kSample);
+            Cell *out = reinterpret_cast<Cell *>(now.cost) + (int64_t)s0 * n_samples + e0 / kSample;
+#pragma unroll
+            for (int s = 0; s < TS; ++s)
+                if (full || s0 + s < S)
+                    out[(uint32_t)s * n_samples] =
+                        cmin[TE - 1] < kInfCell ? cmin[TE - 1] + (Cell)(acc[s][TE - 1] >> k) + (Cell)ck[s] : kInfCell;
+        }
+    };
+    if (s0 + TS <= S)
+        store(std::true_type{});
+    else
+        store(std::false_type{});
+}
+
+// The sweep of handles that keep the byte table (Layout::packed).  Grid: (8 + tiles, 1, instances);
+// the first workgroup of an instance runs live_step for the layer after this one.
+template <int TS, int TE, int NG, int WPE, int W, int UX>
+__global__ __launch_bounds__(W * kWave, WPE) void sweep_bytes_kernel(Layout a, int l) {
+    constexpr int kTile = kWave * TE * UX;
+    constexpr int kQ = (TS * NG + kWave - 1) / kWave;
+    constexpr int kKeep = byte_keep_rows(TS, NG, WPE, kTile);
+    const int wave = uniform(threadIdx.x >> 6);    // the only use of the thread-index register (see lane_id)
+    const int b = a.b_off + blockIdx.z * a.b_step;
+    // List entries of the former layer, lane i those of entry i, i + 64, ...: requested ahead of the header.
+    uint64_t ent[kQ], c0[kQ];
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+        const int i = q * kWave + lane_id();
+        const int64_t at = ((int64_t)b * a.L + (l - 1)) * a.S_pad + (i < TS * NG ? i : TS * NG - 1);
+        ent[q] = a.vlist[at];
+        c0[q] = a.vcost[at];
+    }
+    const ConstPtr<int32_t> hdr = as_const(a.hdr + ((int64_t)b * a.L + l) * 8);
+    const int st = hdr[0], budget = hdr[1];
+    if (st < 0) return;
+    const bool packed = st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE;
+    const int slot = (int)(blockIdx.x >> 3) - 1;
+    if (slot < 0) {
+        if ((blockIdx.x & 7) == 0 && packed) {
+            if (l == 1) {                          // (layer 1 itself is being swept, up to prep_kernel's bound)
+                live_step<NG>(layout_again(), wave, b, 1, false);
+                __syncthreads();
+            }
+            if (l + 1 < a.L) live_step<NG>(layout_again(), wave, b, l + 1, true);
+        }
+        return;
+    }
+    const TileHdr h = {hdr[2], (uint32_t)hdr[3], hdr[4], hdr[4 - 8], hdr[5 - 8], hdr[6 - 8]};
+    const int y = packed ? hdr[5] : 0, x = packed ? hdr[6] : budget;
+    if (y > x) return;
+    // Each XCD takes a contiguous eighth of the tiles to sweep (see sweep_kernel).
+    const int lo = y / kTile, nt = x / kTile - lo + 1;
+    const int per = (nt + 7) >> 3;
+    const int t = (int)(blockIdx.x & 7) * per + slot;
+    if (slot >= per || t >= nt) return;
+    const int tile_start = (lo + t) * kTile;
+    if (st == GALV_INSTANCE_OK_FAST_U32) {
+        sweep_bytes<TS, TE * UX, NG, uint32_t, kKeep, kTile>(layout_again(), wave, l, b, tile_start, false, h, ent, c0);
+    } else if (st == GALV_INSTANCE_OK_U32_WIDE) {
+        // 8-byte cells: a part of the tile at a time keeps registers and LDS within what the narrow form uses
+        for (int p = 0; p < TE; ++p) {
+            if (tile_start + p * (kWave * UX) > x) break;    // workgroup-uniform
+            if (p) __syncthreads();                          // the LDS of the part before is free again
+            sweep_bytes<TS, UX, NG, uint64_t, kKeep, kTile>(layout_again(), wave, l, b, tile_start + p * (kWave * UX), p > 0, h, ent, c0);
+        }
+    } else if (st == GALV_INSTANCE_OK_FAST) {
+        for (int u = 0; u < UX; ++u)
+            sweep_fast<TS, TE, NG, Narrow, int32_t>(layout_again(), wave, l, b, budget, tile_start + u * (kTile / UX));
+    } else if (st == GALV_INSTANCE_OK_FAST_WIDE) {
+        for (int u = 0; u < UX; ++u)
+            sweep_fast<TS, TE, NG, Wide, int32_t>(layout_again(), wave, l, b, budget, tile_start + u * (kTile / UX));
+    } else {
+        sweep_int64<8>(layout_again(), wave, l, b, budget, tile_start);
+    }
+}
+
 // ------------------------------------------------- final minimum and backtrack
 
 // C[L-1][e][s] from the un-shifted last row, as an integer (GALV_INF if none).
@@ -1638,14 +2155,15 @@ __device__ __forceinline__ int64_t last_layer_cost(const Layout &a, int b, int s
     const int64_t shift = a.m[((int64_t)b * a.L + (a.L - 1)) * a.S + s];
     if (shift > e) return kInf;
     if (is_packed(a, st)) {
-        // U_{L-1}[e'][s] = Cmin[e'] + (key >> k) + c(L-1, s) with e' = e - shift
-        const int64_t x = e - shift;
-        const uint32_t w = static_cast<const uint32_t *>(a.bp)[(((int64_t)b * (a.L - 1) + (a.L - 2)) * a.S + s) * a.e_pad + x];
-        if (w == 0xffffffffu) return kInf;
-        const char *M = a.U[(a.L - 1) & 1] + (int64_t)b * a.S_pad * a.row * 8;
-        const int64_t cmin = st == GALV_INSTANCE_OK_U32_WIDE ? (int64_t)reinterpret_cast<const uint64_t *>(M)[x]
-                                                             : (int64_t)reinterpret_cast<const uint32_t *>(M)[x];
-        return cmin + (int64_t)(w >> a.k_bits) + a.c[((int64_t)b * a.L + (a.L - 1)) * a.S + s];
+        const int32_t *h = a.hdr + ((int64_t)b * a.L + (a.L - 1)) * 8;
+        if (e - shift < h[5]) return kInf;
+        const int64_t x = e - shift < h[6] ? e - shift : h[6];
+        const PackTables t = pack_tables(a, (a.L - 1) & 1, b);
+        const uint32_t sp = static_cast<const uint8_t *>(a.bp)[(((int64_t)b * (a.L - 1) + (a.L - 2)) * a.S + s) * a.e_pad + x];
+        const int64_t cmin = st == GALV_INSTANCE_OK_U32_WIDE ? (int64_t)reinterpret_cast<const uint64_t *>(t.cmin)[x]
+                                                             : (int64_t)reinterpret_cast<const uint32_t *>(t.cmin)[x];
+        return cmin + (int64_t)t.rel[(int64_t)sp * a.e_pad + x] + (int64_t)(rkeys(a, b, h[4])[(int64_t)sp * a.S_pad + s] >> a.k_bits) +
+               a.c[((int64_t)b * a.L + (a.L - 1)) * a.S + s];
     }
     const char *U = a.U[(a.L - 1) & 1] + ((int64_t)b * a.S_pad + s) * a.row * 8;
     const int64_t x = a.lead + e - shift;
@@ -1684,7 +2202,7 @@ __global__ __launch_bounds__(kThreads) void final_kernel(Layout a, int64_t *best
         best_last[b] = last;
         a.last[b] = last;
         // every block of init_kernel has long finished: safe to record what the leads hold
-        // (a packed instance keeps its column minima where the first row's lead was)
+        // (an instance with the byte table keeps other things there)
         a.lead_mode[b] = st < 0 || is_packed(a, st) ? 0 : lead_kind(st);
     }
 }
@@ -1706,7 +2224,7 @@ __device__ __forceinline__ void walk_plan(const Layout &a, int b, int64_t e, int
             for (int q = 0; q < a.L; ++q) out[q] = -1;
             return;
         }
-        s = load_bp(a, st, (((int64_t)b * (a.L - 1) + (l - 1)) * a.S + s) * a.e_pad + e);
+        s = load_bp(a, st, b, l, s, e);
         if (s < 0 || s >= a.S) {
             for (int q = 0; q < a.L; ++q) out[q] = -1;
             return;
@@ -1724,6 +2242,10 @@ __global__ __launch_bounds__(kThreads) void stats_kernel(Layout a, int64_t *out)
     if (a.status[b] == GALV_INSTANCE_OK_FAST_U32 || a.status[b] == GALV_INSTANCE_OK_U32_WIDE) {
         const int nt = a.budget[b] / a.tile_e + 1;
         for (int64_t i = threadIdx.x; i < (int64_t)(a.L - 1) * nt; i += kThreads) {
+            if (a.packed) {                        // only the layer's tiles in its header's range are swept
+                const int32_t *h = a.hdr + ((int64_t)b * a.L + i / nt + 1) * 8;
+                if (h[5] > h[6] || i % nt < h[5] / a.tile_e || i % nt > h[6] / a.tile_e) continue;
+            }
             const uint32_t *v = a.stats + 2 * (((int64_t)b * (a.L - 1) + i / nt) * a.n_tiles + i % nt);
             done += v[0] >> 16;
             listed += v[0] & 0xffffu;
@@ -1773,7 +2295,7 @@ __global__ __launch_bounds__(kWave) void backtrack_kernel(Layout a, int32_t *pla
             for (int q = 0; q < a.L; ++q) out[q] = -1;
             return;
         }
-        s = load_bp(a, st, (((int64_t)b * (a.L - 1) + (l - 1)) * a.S + s) * a.e_pad + e);
+        s = load_bp(a, st, b, l, s, e);
         if (s < 0 || s >= a.S) {
             for (int q = 0; q < a.L; ++q) out[q] = -1;
             return;
@@ -1850,7 +2372,7 @@ __global__ __launch_bounds__(kThreads) void export_kernel(Layout a, int b, int64
         if (live && l >= 1) {
             const int64_t shift = a.m[((int64_t)b * a.L + l) * a.S + s];
             if (shift <= e)
-                v = load_bp(a, st, (((int64_t)b * (a.L - 1) + (l - 1)) * a.S + s) * a.e_pad + (e - shift));
+                v = load_bp(a, st, b, l, s, e - shift);
         }
         dst[s] = v;
     }
@@ -2039,7 +2561,7 @@ using SweepFn = void (*)(Layout, int);
 struct VariantEntry {
     Variant v;
     SweepFn fn, fn_u8;     // int32 and one-byte back-pointers
-    SweepFn fn_pack;       // int32, single packed table (row-sharing variants; else null)
+    SweepFn fn_pack;       // byte table (row-sharing variants; else null)
 };
 template <int TS, int TE, int NG, int WPE, int W, int UX, int SHARE>
 VariantEntry variant_entry() {
@@ -2048,10 +2570,10 @@ VariantEntry variant_entry() {
     static_assert(!SHARE || W == NG, "the row-sharing body has one budget tile per workgroup");
     static_assert((UX == 1 || UX == 2) && TE * UX <= 4, "budget columns per lane");
     SweepFn pack = nullptr;
-    if constexpr (SHARE != 0) pack = sweep_kernel<TS, TE, NG, WPE, int32_t, W, UX, SHARE, 1>;
+    if constexpr (SHARE != 0) pack = sweep_bytes_kernel<TS, TE, NG, WPE, W, UX>;
     return {{TS, TE, NG, W, UX, WPE, SHARE},
-            sweep_kernel<TS, TE, NG, WPE, int32_t, W, UX, SHARE, 0>,
-            sweep_kernel<TS, TE, NG, WPE, uint8_t, W, UX, SHARE, 0>,
+            sweep_kernel<TS, TE, NG, WPE, int32_t, W, UX, SHARE>,
+            sweep_kernel<TS, TE, NG, WPE, uint8_t, W, UX, SHARE>,
             pack};
 }
 
@@ -2166,7 +2688,8 @@ galv_status_t make_plan(const galv_dp_desc_t *d, Plan *p) {
         const size_t wide = ((size_t)v.ng * wcols + v.ng) * sizeof(uint64_t) + (4 + keep + keep * wcols) * sizeof(uint32_t);
         p->lds_bytes = (unsigned)(narrow > wide ? narrow : wide);
     }
-    if (p->lds_bytes > 160u * 1024u)
+    const unsigned lds_packed = v.share ? byte_lds(v.ts, v.ng, v.wpe, kWave * v.te * v.ux) : 0;
+    if (p->lds_bytes > 160u * 1024u || lds_packed > 160u * 1024u)
         return fail(GALV_ERR_RANGE, "internal: staging variant needs %u bytes of LDS", p->lds_bytes);
     a.e_pad = (int64_t)round_up((size_t)a.E_max + 1, kEAlign);
     a.n_tiles = (int32_t)((a.E_max + a.tile_e) / a.tile_e);   // ceil((E_max+1)/tile_e)
@@ -2174,12 +2697,12 @@ galv_status_t make_plan(const galv_dp_desc_t *d, Plan *p) {
     a.peek = fills_chip ? 1 : 0;
     if (d->flags & GALV_DP_NO_PEEK) a.peek = 0;
     if (d->flags & GALV_DP_FORCE_PEEK) a.peek = 1;
-    // The single packed table halves the bytes of a state but rebuilds every cell it reads from
-    // two loads: measured, it gains 15-25 % where the peek leaves few rows to read (configs 2-4)
-    // and loses 15 % where every row is read and latency binds (config 1): same switch as the peek.
+    // The byte table writes a quarter of the bytes or less but rebuilds every cell it reads in two
+    // dependent steps: it pays where the peek leaves few rows to read, so it has the same switch.
     bool packed = v.share && !u8 && fills_chip;
     if (d->flags & GALV_DP_NO_PACK) packed = false;
     if ((d->flags & GALV_DP_FORCE_PACK) && v.share && !u8) packed = true;
+    if (packed) p->lds_bytes = lds_packed;
     p->sweep = packed ? ve.fn_pack : (u8 ? ve.fn_u8 : ve.fn);
     a.packed = packed ? 1 : 0;
     a.seen = nullptr;
@@ -2220,7 +2743,11 @@ galv_status_t make_plan(const galv_dp_desc_t *d, Plan *p) {
 }
 
 // grid.x of a sweep launch for n budget tiles.
-inline unsigned kGridTiles(int n) { return GALV_XCD_MAP ? (unsigned)((n + 7) / 8 * 8) : (unsigned)n; }
+// (the byte-table sweep's first eight workgroups are not for tiles)
+inline unsigned kGridTiles(const Layout &a) {
+    const unsigned n = (unsigned)a.n_tiles;
+    return (GALV_XCD_MAP || a.packed ? (n + 7) / 8 * 8 : n) + (a.packed ? 8 : 0);
+}
 
 // Point a layout's table pointers into a workspace laid out by make_plan.
 void bind_workspace(Layout &a, const Plan &p, char *ws) {
@@ -2255,6 +2782,12 @@ int pick_streams(const galv_dp *h, int64_t tiles) {
     if (h->n_side <= 1) return 1;
     if (!h->auto_streams) return h->n_side;
     const Layout &a = h->lay;
+    // The byte-table sweep: every launch costs ~4 us on the host and the same again on the queue, so
+    // one stream, or two where a layer holds enough states for the overlap of two launches to pay:
+    // 17 M states (22 x 24576 columns x 32 instances) 0.82 / 0.94 ms with 1 / 2 streams, 58 M (44 x
+    // 20480 x 64) 4.05 / 3.59 / 3.72 / 4.5 ms with 1 / 2 / 3 / 6, 134 M (128 x 65536 x 16) 13.3 / 12.4 /
+    // 12.5 / 16.3 ms with 1 / 2 / 3 / 16.
+    if (a.packed) return (double)tiles * a.tile_e * a.S >= 20e6 && a.B > 1 ? 2 : 1;
     const double wgs = (double)tiles * h->groups_y;
     int n = (int)(wgs / (0.66 * h->resident) + 0.5);
     const double us = (double)tiles * a.tile_e * a.S * 8.0 / 5.5e12 * 1e6;   // a layer at 8 B per state
@@ -2300,7 +2833,7 @@ galv_status_t enqueue_solve(galv_dp *h, const int64_t *c_dev, const int32_t *m_d
     a.b_off = 0;
     a.b_step = 1;
     if (n_use <= 1) {
-        const dim3 grid(kGridTiles(a.n_tiles), h->groups_y, a.B);
+        const dim3 grid(kGridTiles(a), h->groups_y, a.B);
         for (int l = 1; l < a.L; ++l) h->sweep<<<grid, h->var.w * kWave, h->lds_bytes, st>>>(a, l);
     } else {
         // Instances are independent, so their layer chains need no common barrier: each
@@ -2318,7 +2851,7 @@ galv_status_t enqueue_solve(galv_dp *h, const int64_t *c_dev, const int32_t *m_d
             Layout ag = a;
             ag.b_off = g;
             ag.b_step = n_use;
-            const dim3 grid(kGridTiles(a.n_tiles), h->groups_y, count);
+            const dim3 grid(kGridTiles(a), h->groups_y, count);
             for (int l = 1; l < a.L; ++l) h->sweep<<<grid, h->var.w * kWave, h->lds_bytes, h->side[g]>>>(ag, l);
             err = hipEventRecord(h->join[g], h->side[g]);
             const hipError_t e2 = err == hipSuccess ? hipStreamWaitEvent(st, h->join[g], 0) : err;
