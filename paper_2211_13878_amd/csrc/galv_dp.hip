@@ -201,6 +201,12 @@ __device__ __forceinline__ bool is_packed(const Layout &a, int st) {
     return a.packed && a.L > 1 && (st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE);
 }
 
+// First row of layer l (>= 1) in the byte table.  An instance's bytes start where its 32-bit back-pointers
+// would: the same batch may hold instances that keep those.
+__device__ __forceinline__ uint8_t *byte_rows(const Layout &a, int b, int l) {
+    return static_cast<uint8_t *>(a.bp) + ((int64_t)b * 4 * (a.L - 1) + (l - 1)) * a.S * a.e_pad;
+}
+
 // Back-pointer of un-shifted cell (layer l >= 1, strategy s, column x), whichever width the handle
 // stores.  The byte table holds the columns [first, last] of the layer's header record: below is
 // unreachable, above is constant.
@@ -209,7 +215,7 @@ __device__ __forceinline__ int32_t load_bp(const Layout &a, int st, int b, int l
     if (is_packed(a, st)) {
         const int32_t *h = a.hdr + ((int64_t)b * a.L + l) * 8;
         if (x < h[5]) return -1;
-        return static_cast<const uint8_t *>(a.bp)[row + (x < h[6] ? x : h[6])];
+        return byte_rows(a, b, l)[s * a.e_pad + (x < h[6] ? x : h[6])];
     }
     if (a.bp_u8) {
         const uint8_t v = static_cast<const uint8_t *>(a.bp)[row + x];
@@ -1751,7 +1757,7 @@ struct Former {
     int S_pad, k;
     __device__ __forceinline__ Former(const Layout &a, int b, int l, int r) {
         const PackTables t = pack_tables(a, (l - 1) & 1, b);
-        bp = static_cast<const uint8_t *>(a.bp) + ((int64_t)b * (a.L - 1) + (l == 1 ? 0 : l - 2)) * a.S * a.e_pad;
+        bp = byte_rows(a, b, l == 1 ? 1 : l - 1);
         cmin = reinterpret_cast<const Cell *>(t.cmin);
         rel = t.rel;
         R = rkeys(a, b, r);
@@ -2046,7 +2052,7 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
     }
     if (idle) return;
     const int S = a2.S;
-    uint8_t *bp = static_cast<uint8_t *>(a2.bp) + (((int64_t)b * (a2.L - 1) + (l - 1)) * S + s0) * e_pad + tile_start;
+    uint8_t *bp = byte_rows(a2, b, l) + (int64_t)s0 * e_pad + tile_start;
 
     // (of an unreachable column the bytes are never used: readers compare with Y_l)
     const uint32_t mask = ((1u << k) - 1u) * 0x01010101u;
@@ -2159,7 +2165,7 @@ __device__ __forceinline__ int64_t last_layer_cost(const Layout &a, int b, int s
         if (e - shift < h[5]) return kInf;
         const int64_t x = e - shift < h[6] ? e - shift : h[6];
         const PackTables t = pack_tables(a, (a.L - 1) & 1, b);
-        const uint32_t sp = static_cast<const uint8_t *>(a.bp)[(((int64_t)b * (a.L - 1) + (a.L - 2)) * a.S + s) * a.e_pad + x];
+        const uint32_t sp = byte_rows(a, b, a.L - 1)[(int64_t)s * a.e_pad + x];
         const int64_t cmin = st == GALV_INSTANCE_OK_U32_WIDE ? (int64_t)reinterpret_cast<const uint64_t *>(t.cmin)[x]
                                                              : (int64_t)reinterpret_cast<const uint32_t *>(t.cmin)[x];
         return cmin + (int64_t)t.rel[(int64_t)sp * a.e_pad + x] + (int64_t)(rkeys(a, b, h[4])[(int64_t)sp * a.S_pad + s] >> a.k_bits) +

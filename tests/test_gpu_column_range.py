@@ -44,3 +44,15 @@ def test_two_layers_and_one_handle_after_another_instance_mix(S):
         for b, ref in enumerate(oracle.solve_workload(w, threads=4)):
             assert int(cost[b]) == ref.best_cost and (plan[b] == np.asarray(ref.plan)).all()
     sol.close()
+
+
+@pytest.mark.parametrize("S", [6, 22, 128])
+def test_one_batch_with_and_without_the_byte_table(S):
+    """Instances on 64-bit integers keep 32-bit back-pointers beside the bytes of the others."""
+    w = workloads.random_workload(S, 6, 5, S, 900, nR=2, m_range=(0, 200), c_range=(0, 5000), r_range=(0, 300),
+                                  infeasible=0.05, zero_diagonal=False)
+    w.c[::2] += 1 << 58
+    w.R[::2] += 1 << 50
+    w.budget[:] = 900
+    _, _, _, status = check_against_oracle(w, flags=PACK | PEEK, table_instances=range(6))
+    assert (status[::2] == binding.GALV_INSTANCE_OK_INT64).all() and (status[1::2] == binding.GALV_INSTANCE_OK_FAST_U32).all()
