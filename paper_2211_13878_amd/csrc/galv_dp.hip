@@ -31,8 +31,9 @@
 //    of layer costs some 90-95 % of the candidates fall away and the sweep is bound by HBM.
 //    The keys' width depends on the transition costs only; when the costs themselves outgrow
 //    32-bit cells, the same body runs over 64-bit cells (up to 256 strategies).
-//    Where a layer fills the chip, these instances keep argmins of one byte and what it takes to
-//    rebuild the few cells the next layer reads, instead of cost rows (see the byte-table sweep).
+//    Where a layer has many tiles, these instances keep argmins of one byte and what it takes to
+//    rebuild the few cells the next layer reads, instead of cost rows (see the byte-table sweep);
+//    so do the instances on 64-bit keys whose transition costs fit 32 bits.
 //  * 64-bit keys: key = cost * 2^k + s' (k = ceil(log2 S)) lives in the mantissa of a double
 //    whose exponent is pinned, K = 2^52 + key; one v_add_f64 + one v_min_f64 per candidate,
 //    exact while K stays below 2^53.  Two storage widths: narrow (costs below 2^31 stored as
@@ -130,7 +131,7 @@ struct Layout {
     void *bp;             // argmin, un-shifted  [B][L-1][S][e_pad] of int32, or of uint8 (0xFF = none)
     int32_t bp_u8;        // 1: one-byte back-pointers
     int32_t peek;         // 1: the row-sharing sweep looks at two cells of a row before it fetches the row
-    int32_t packed;       // 1: instances on the 32-bit-key paths keep the byte table: argmins in one byte, and
+    int32_t packed;       // 1: instances of byte_status() keep the byte table: argmins in one byte, and
                           //    instead of cost rows what it takes to rebuild a cell (see PackTables)
     int32_t synth_l1;     // 1: the 32-bit-key sweep makes up layer 0's cells (a constant per strategy)
                           //    when it sweeps layer 1, so layer 0's row is never written nor read
@@ -141,7 +142,7 @@ struct Layout {
                           // up to the row's end  [B][L][S_pad]
     uint64_t *vcost;      // c(l, s') of the listed strategies, in the list's order (padded the same way)  [B][L][S_pad]
     int32_t *nvalid;      // how many of them    [B][L]
-    uint32_t *dclamp;     // 32-bit-key path: largest R + 1, the clamp of relative costs  [B]
+    uint32_t *dclamp;     // largest R + 1, the clamp of relative costs; 0 when it does not fit  [B]
     int32_t *hdr;         // what a sweep workgroup needs first, in one place: status, budget, usable strategies of
                           // the former layer, clamp, transition matrix of the layer, first reachable column,
                           // last column worth sweeping (byte table), smallest usable memory  [B][L][8]
@@ -195,10 +196,15 @@ __device__ __forceinline__ int lead_kind(int st) {
     return 0;
 }
 
-// Whether instance status st keeps the byte table (a handle-wide choice of kernels, and
-// the instance must be on a 32-bit-key path; one layer has no table at all).
-__device__ __forceinline__ bool is_packed(const Layout &a, int st) {
-    return a.packed && a.L > 1 && (st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE);
+// Whether an instance of status st keeps the byte table (a handle-wide choice of kernels; one
+// layer has no table at all).  That takes packed keys, and relative costs of 32 bits: clamp is
+// R_max + 1, or 0 when that does not fit.
+__device__ __forceinline__ bool byte_status(int st, uint32_t clamp) {
+    return st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE ||
+           ((st == GALV_INSTANCE_OK_FAST || st == GALV_INSTANCE_OK_FAST_WIDE) && clamp != 0);
+}
+__device__ __forceinline__ bool is_packed(const Layout &a, int st, int b) {
+    return a.packed && a.L > 1 && byte_status(st, a.dclamp[b]);
 }
 
 // First row of layer l (>= 1) in the byte table.  An instance's bytes start where its 32-bit back-pointers
@@ -210,9 +216,9 @@ __device__ __forceinline__ uint8_t *byte_rows(const Layout &a, int b, int l) {
 // Back-pointer of un-shifted cell (layer l >= 1, strategy s, column x), whichever width the handle
 // stores.  The byte table holds the columns [first, last] of the layer's header record: below is
 // unreachable, above is constant.
-__device__ __forceinline__ int32_t load_bp(const Layout &a, int st, int b, int l, int64_t s, int64_t x) {
+__device__ __forceinline__ int32_t load_bp(const Layout &a, bool packed, int b, int l, int64_t s, int64_t x) {
     const int64_t row = (((int64_t)b * (a.L - 1) + (l - 1)) * a.S + s) * a.e_pad;
-    if (is_packed(a, st)) {
+    if (packed) {
         const int32_t *h = a.hdr + ((int64_t)b * a.L + l) * 8;
         if (x < h[5]) return -1;
         return byte_rows(a, b, l)[s * a.e_pad + (x < h[6] ? x : h[6])];
@@ -440,18 +446,17 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
             const bool u32 = !(flags & GALV_DP_NO_U32) &&
                              ((2 * rmax_all + 2) << a.k_bits) <= (1ull << 32);
             st = u32 ? GALV_INSTANCE_OK_FAST_U32 : GALV_INSTANCE_OK_FAST;
-            a.dclamp[b] = (uint32_t)(rmax_all + 1);
         } else if (a.synth_l1 && !(flags & GALV_DP_NO_U32) &&
                    ((2 * rmax_all + 2) << a.k_bits) <= (1ull << 32)) {
             // costs need 64-bit cells, but only RELATIVE costs (clamped at R_max + 1) enter the keys:
             // the 32-bit-key arithmetic and its pruning apply all the same (row-sharing variants)
             st = GALV_INSTANCE_OK_U32_WIDE;
-            a.dclamp[b] = (uint32_t)(rmax_all + 1);
         } else if (bound + 1 <= (1ull << (52 - a.k_bits))) {
             st = GALV_INSTANCE_OK_FAST_WIDE;    // keys fit the 52-bit mantissa
         } else {
             st = GALV_INSTANCE_OK_INT64;
         }
+        a.dclamp[b] = rmax_all < 0xffffffffull ? (uint32_t)(rmax_all + 1) : 0u;
         status_s = st;
         a.status[b] = st;
     }
@@ -500,7 +505,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
     // c(l,s) in the form the epilogue adds: the integer itself (integer cells) or the
     // double c * 2^k (cells that hold 64-bit keys).
     uint64_t *ck = a.ck + (int64_t)b * L * S_pad;
-    const bool c_int = narrow_cells(st) || st == GALV_INSTANCE_OK_U32_WIDE;
+    const bool c_int = narrow_cells(st) || st == GALV_INSTANCE_OK_U32_WIDE || is_packed(a, st, b);
     for (int64_t l = wave; l < L; l += kWaves)
         for (int sx = lane; sx < S_pad; sx += kWave) {
             const int64_t v = (sx < (int)S) ? c[l * S + sx] : 0;
@@ -560,7 +565,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
                 lc[i] = last_c;
             }
     }
-    if (!is_packed(a, st)) return;
+    if (!is_packed(a, st, b)) return;
     // Columns of each layer that are worth sweeping (see the byte-table sweep): from the sum of the
     // smallest memories before it, saturating above the budget (a wave's prefix sum, 64 layers at a
     // time); layer 1 up to layer 0's largest memory, later layers as live_step finds.
@@ -605,7 +610,7 @@ __global__ __launch_bounds__(kThreads) void init_kernel(Layout a, int fresh) {
         for (int64_t x = a.lead + x0; x < a.row; x += step) reinterpret_cast<int64_t *>(a.U[0] + base)[x] = c0;
         return;
     }
-    if (is_packed(a, st)) return;                  // no cost rows: layer 0 is made up, the sweeps test the shift
+    if (is_packed(a, st, b)) return;               // no cost rows: layer 0 is made up, the sweeps test the shift
     const bool leads = fresh || a.lead_mode[b] != lead_kind(st);
     const bool u32_keys = st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE;
     const bool row0 = !(u32_keys && a.synth_l1 && a.L > 1);
@@ -1575,7 +1580,7 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_kernel(Layout a, int l) 
 
 // ------------------------------------------------------------ byte-table sweep
 //
-// The packed form of the 32-bit-key sweep, for handles whose layers fill the chip.  There the
+// The packed form of the pruning sweep, for handles whose layers have many tiles.  There the
 // sweep is bound by what it writes and by its chain of round trips, so it keeps little per state:
 //   * the argmin, one byte: the only table that lives on after the next layer;
 //   * and, per budget column, the former minimum Cmin and the clamped relative costs
@@ -1620,9 +1625,34 @@ __device__ __forceinline__ PackTables pack_tables(const Layout &a, int parity, i
     t.mem = reinterpret_cast<int32_t *>(t.V + a.S_pad);
     return t;                                      // (rows reserve 8 bytes per column, leads included: ample)
 }
-__device__ __forceinline__ const uint32_t *rkeys(const Layout &a, int b, int r) {
-    return reinterpret_cast<const uint32_t *>(a.Rk + ((int64_t)b * a.nR + r) * a.S * a.S_pad);
+template <class T>
+__device__ __forceinline__ const T *rkeys(const Layout &a, int b, int r) {
+    return reinterpret_cast<const T *>(a.Rk + ((int64_t)b * a.nR + r) * a.S * a.S_pad);
 }
+
+// The two kinds of keys, (relative cost + R) * 2^k + s': 32-bit words where twice the largest
+// relative cost fits them, else whole numbers below 2^42 held in doubles (the add and the minimum
+// of doubles run at the same rate as two 32-bit ones, and there is no 64-bit integer minimum).
+// Costs outgrow the 32-bit key with the unit of time: 44 strategies and transitions of 0.1 s,
+// counted in nanoseconds.  Over cost rows such instances take every candidate of every column: 44
+// strategies x 16384 columns x 48 layers x 16 instances 3.06 ms, and with the byte table 1.27 ms.
+struct Key32 {
+    using T = uint32_t;
+    static __device__ __forceinline__ T none() { return 0xffffffffu; }
+    static __device__ __forceinline__ T make(uint32_t rel, int k) { return rel << k; }
+    static __device__ __forceinline__ uint32_t low(T key) { return key; }
+    static __device__ __forceinline__ uint64_t cost(T key, int k) { return key >> k; }
+};
+struct Key64 {
+    using T = double;
+    static __device__ __forceinline__ T none() { return 0x1p51; }
+    static __device__ __forceinline__ T make(uint32_t rel, int k) { return __builtin_ldexp((double)rel, k); }
+    static __device__ __forceinline__ uint64_t bits(T key) {     // (below 2^52: the sum's mantissa is the number)
+        return (uint64_t)__double_as_longlong(key + 0x1p52) & 0x000fffffffffffffull;
+    }
+    static __device__ __forceinline__ uint32_t low(T key) { return (uint32_t)bits(key); }
+    static __device__ __forceinline__ uint64_t cost(T key, int k) { return bits(key) >> k; }
+};
 
 // Smallest value over the wave's lanes, in every lane.
 __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
@@ -1646,7 +1676,7 @@ __device__ __forceinline__ uint64_t wave_min(uint64_t v) {
 // One step of the recurrence without a memory limit, for layer l of instance b: V_l(s) and the
 // memory its plan takes before layer l, from those of layer l - 1; then (tell) the last column of
 // layer l that has to be swept.  Same keys, same tie-break as the sweep.  One workgroup; S <= 16 * NG.
-template <int NG>
+template <int NG, class Key>
 __device__ __forceinline__ void live_step(const Layout &a, int wave, int b, int l, bool tell) {
     int32_t *h = a.hdr + ((int64_t)b * a.L + l) * 8;
     const int lane = lane_id(), tid = wave * kWave + lane;
@@ -1656,8 +1686,10 @@ __device__ __forceinline__ void live_step(const Layout &a, int wave, int b, int 
     const PackTables from = pack_tables(a, (l - 1) & 1, b), to = pack_tables(a, l & 1, b);
     const uint64_t *list = a.vlist + ((int64_t)b * a.L + (l - 1)) * a.S_pad;
     const uint64_t *lcost = a.vcost + ((int64_t)b * a.L + (l - 1)) * a.S_pad;
-    uint32_t *dv = lds_cells, *sp = dv + a.S_pad, *mem = sp + a.S_pad, *part = mem + a.S_pad;   // part [NG][S_pad]
-    uint32_t *top = part + NG * a.S_pad;
+    using KeyT = typename Key::T;
+    KeyT *part = reinterpret_cast<KeyT *>(lds_cells);               // [NG][S_pad]
+    uint32_t *dv = reinterpret_cast<uint32_t *>(part + NG * a.S_pad), *sp = dv + a.S_pad, *mem = sp + a.S_pad;
+    uint32_t *top = mem + a.S_pad;
     if (n == 0) {                                  // nothing reachable from here on
         if (tid == 0 && tell) h[6] = -1;
         return;
@@ -1674,7 +1706,7 @@ __device__ __forceinline__ void live_step(const Layout &a, int wave, int b, int 
         const uint64_t ent = list[tid];
         const uint32_t s = (uint32_t)ent;
         const uint64_t rel = (l == 1 ? lcost[tid] : from.V[s]) - vmin;
-        dv[tid] = (rel < dmax ? (uint32_t)rel : dmax) << k;
+        dv[tid] = rel < dmax ? (uint32_t)rel : dmax;
         sp[tid] = s;
         // (memories saturate just above the budget)
         const int64_t x = (int64_t)(l == 1 ? 0 : from.mem[s]) + (int64_t)(ent >> 32);
@@ -1682,17 +1714,18 @@ __device__ __forceinline__ void live_step(const Layout &a, int wave, int b, int 
     }
     if (tid == 0) *top = 0;
     __syncthreads();
-    const uint32_t *Rk = rkeys(a, b, h[4]);
+    const KeyT *Rk = rkeys<KeyT>(a, b, h[4]);
     constexpr int kQ = (16 * NG + kWave - 1) / kWave;
-    uint32_t best[kQ];
+    KeyT best[kQ];
 #pragma unroll
-    for (int q = 0; q < kQ; ++q) best[q] = 0xffffffffu;
+    for (int q = 0; q < kQ; ++q) best[q] = Key::none();
 #pragma unroll 4
     for (int i = wave; i < n; i += NG) {
 #pragma unroll
         for (int q = 0; q < kQ; ++q) {
             const int s = q * kWave + lane;
-            best[q] = min(best[q], dv[i] + Rk[(int64_t)sp[i] * a.S_pad + (s < S ? s : S - 1)]);
+            const KeyT key = Key::make(dv[i], k) + Rk[(int64_t)sp[i] * a.S_pad + (s < S ? s : S - 1)];
+            best[q] = key < best[q] ? key : best[q];
         }
     }
 #pragma unroll
@@ -1700,10 +1733,13 @@ __device__ __forceinline__ void live_step(const Layout &a, int wave, int b, int 
         if (q * kWave + lane < S) part[wave * a.S_pad + q * kWave + lane] = best[q];
     __syncthreads();
     if (tid < S) {
-        uint32_t key = 0xffffffffu;
-        for (int w = 0; w < NG && w < n; ++w) key = min(key, part[w * a.S_pad + tid]);
-        const uint32_t x = mem[key & ((1u << k) - 1u)];
-        to.V[tid] = vmin + (key >> k) + (uint64_t)a.c[((int64_t)b * a.L + l) * S + tid];
+        KeyT key = Key::none();
+        for (int w = 0; w < NG && w < n; ++w) {
+            const KeyT o = part[w * a.S_pad + tid];
+            key = o < key ? o : key;
+        }
+        const uint32_t x = mem[Key::low(key) & ((1u << k) - 1u)];
+        to.V[tid] = vmin + Key::cost(key, k) + (uint64_t)a.c[((int64_t)b * a.L + l) * S + tid];
         to.mem[tid] = (int32_t)x;
         if (a.m[((int64_t)b * a.L + l) * S + tid] <= budget) atomicMax(top, x);
     }
@@ -1726,7 +1762,7 @@ constexpr int byte_keep_rows(int ts, int ng, int wpe, int cols) {
 constexpr unsigned byte_lds(int ts, int ng, int wpe, int cols) {
     const int keep = byte_keep_rows(ts, ng, wpe, cols);
     const unsigned tile = (unsigned)(ng * cols * 4 + keep * cols * 4 + ts * ng * 16 + keep * 4 + 16);
-    const unsigned live = (unsigned)((3 + ng) * ts * ng * 4 + 4);       // live_step
+    const unsigned live = (unsigned)((3 + 2 * ng) * ts * ng * 4 + 4);   // live_step
     return tile > live ? tile : live;
 }
 
@@ -1748,11 +1784,12 @@ __device__ __forceinline__ const Layout &layout_again() {
 }
 
 // What rebuilding the former layer's cells takes.
-template <class Cell>
+template <class Cell, class Key>
 struct Former {
     const uint8_t *bp;
     const Cell *cmin;
-    const uint32_t *rel, *R;
+    const uint32_t *rel;
+    const typename Key::T *R;
     int64_t e_pad;
     int S_pad, k;
     __device__ __forceinline__ Former(const Layout &a, int b, int l, int r) {
@@ -1760,14 +1797,14 @@ struct Former {
         bp = byte_rows(a, b, l == 1 ? 1 : l - 1);
         cmin = reinterpret_cast<const Cell *>(t.cmin);
         rel = t.rel;
-        R = rkeys(a, b, r);
+        R = rkeys<typename Key::T>(a, b, r);
         e_pad = a.e_pad;
         S_pad = a.S_pad;
         k = a.k_bits;
     }
 };
 
-template <int TS, int TE, int NG, class Cell, int KEEP, int TILE>
+template <int TS, int TE, int NG, class Cell, class Key, int KEEP, int TILE>
 __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b, int tile_start, bool add_stats,
                                             const TileHdr &h, const uint64_t (&ent)[(TS * NG + kWave - 1) / kWave],
                                             const uint64_t (&c0_64)[(TS * NG + kWave - 1) / kWave]) {
@@ -1776,6 +1813,8 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
     constexpr int kCols = kWave * TE;
     constexpr int kQ = (TS * NG + kWave - 1) / kWave;
     static_assert(TS <= 16, "one scalar load fetches the R keys of a row");
+    using KeyT = typename Key::T;
+    constexpr bool kDouble = sizeof(KeyT) == 8;
     typedef uint32_t relv __attribute__((ext_vector_type(TE)));
     typedef Cell cellv __attribute__((ext_vector_type(TE)));
     __builtin_amdgcn_s_setprio(3);                 // (a wave with loads to issue goes first, as in sweep_u32_shared)
@@ -1849,7 +1888,7 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
         shift = uniform((int)(uint32_t)(en >> 32));
         cp = (Cell)((uint64_t)(uint32_t)uniform((int)(uint32_t)(cv >> 32)) << 32 | (uint32_t)uniform((int)(uint32_t)cv));
     };
-    auto fetch_row = [&](const Former<Cell> &t, uint32_t sp, int shift, Fetch &f) {
+    auto fetch_row = [&](const Former<Cell, Key> &t, uint32_t sp, int shift, Fetch &f) {
         const uint8_t *w = t.bp + (int64_t)sp * t.e_pad;
 #pragma unroll
         for (int j = 0; j < TE; ++j) {
@@ -1860,8 +1899,9 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
             f.cmin[j] = t.cmin[(uint32_t)f.x[j]];
         }
     };
-    auto finish_row = [&](const Former<Cell> &t, uint32_t sp, Cell cp, const Fetch &f, Cell (&out)[TE]) {
-        uint32_t rel[TE], r[TE];
+    auto finish_row = [&](const Former<Cell, Key> &t, uint32_t sp, Cell cp, const Fetch &f, Cell (&out)[TE]) {
+        uint32_t rel[TE];
+        KeyT r[TE];
 #pragma unroll
         for (int j = 0; j < TE; ++j) {
             rel[j] = t.rel[(int64_t)f.sp[j] * t.e_pad + f.x[j]];
@@ -1869,7 +1909,7 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
         }
 #pragma unroll
         for (int j = 0; j < TE; ++j) {
-            const Cell v = f.cmin[j] + (Cell)rel[j] + (Cell)(r[j] >> t.k) + cp;
+            const Cell v = f.cmin[j] + (Cell)rel[j] + (Cell)Key::cost(r[j], t.k) + cp;
             out[j] = f.ok[j] ? v : kInfCell;
         }
     };
@@ -1881,7 +1921,7 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
     // Wave g fetches kept rows g, g + NG, ...: two at a time, so that their round trips overlap.
     Cell cmin[TE];
     {
-        const Former<Cell> former(a, b, l, h.r_prev);
+        const Former<Cell, Key> former(a, b, l, h.r_prev);
         Cell pm[TE];
 #pragma unroll
         for (int j = 0; j < TE; ++j) pm[j] = kAllOnes;
@@ -1938,15 +1978,15 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
 
     // Keys of the alive rows, and the min-plus product over them, KEEP kept rows at a time (one
     // pass unless transition costs dwarf the spread of the layer costs).
-    uint32_t acc[TS][TE];
+    KeyT acc[TS][TE];
 #pragma unroll
     for (int s = 0; s < TS; ++s)
 #pragma unroll
-        for (int j = 0; j < TE; ++j) acc[s][j] = 0xffffffffu;
+        for (int j = 0; j < TE; ++j) acc[s][j] = Key::none();
     const Layout &a1 = layout_again();
     const int S_pad = a1.S_pad, k = a1.k_bits;
     const bool idle = s0 >= a1.S;                  // an idle strategy group only fetches rows
-    const ConstPtr<uint32_t> Rk = as_const(rkeys(a1, b, h.r) + s0);
+    const ConstPtr<KeyT> Rk = as_const(rkeys<KeyT>(a1, b, h.r) + s0);
     uint32_t rows_reduced = 0;
     int pass = 0;
     for (int base = 0; base < nk; base += KEEP) {
@@ -1964,7 +2004,7 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
             } else if (first) {
                 made_up(shift, cp, v);
             } else {
-                const Former<Cell> former(layout_again(), b, l, h.r_prev);
+                const Former<Cell, Key> former(layout_again(), b, l, h.r_prev);
                 Fetch f;
                 fetch_row(former, sp, shift, f);
                 finish_row(former, sp, cp, f, v);
@@ -1975,7 +2015,7 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
             for (int j = 0; j < TE; ++j) {
                 const Cell rel = v[j] - cmin[j];
                 d[j] = (uint32_t)min(rel, (Cell)h.dmax);
-                key[j] = d[j] << k;
+                key[j] = kDouble ? d[j] : d[j] << k;
                 alive |= rel < (Cell)h.dmax && cmin[j] < kInfCell;
             }
             if (__builtin_amdgcn_ballot_w64(alive) != 0) {   // wave-uniform
@@ -1991,7 +2031,43 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
         if (pass == 0) __builtin_amdgcn_s_setprio(0);
         const int cnt = uniform((int)*counter);
         rows_reduced += (uint32_t)cnt;
-        if (!idle && cnt > 0) {
+        if constexpr (kDouble) {
+            if (!idle && cnt > 0) {
+                using Group = std::conditional_t<(TS > 8 && TS <= 12), RGroupMid, RGroup<(TS > 8 ? 2 : 1)>>;
+                uint32_t rel[2][TE];
+                uint32_t sp[2];
+                Group buf[2];
+                auto request = [&](int q, int i) {
+                    const uint32_t row = (uint32_t)uniform((int)live[i < cnt ? i : cnt - 1]);
+                    sp[q] = row & 0xffffu;
+                    const relv in = *reinterpret_cast<const relv *>(reinterpret_cast<const uint32_t *>(cells + (row >> 16) * kCols) + lane * TE);
+#pragma unroll
+                    for (int j = 0; j < TE; ++j) rel[q][j] = in[j];
+                };
+                auto reduce_row = [&](int q) {     // the next row's transition keys in flight under this one's arithmetic
+                    rgroup_request(buf[q ^ 1], Rk + (int64_t)uniform((int)sp[q ^ 1]) * S_pad);
+                    double key[TE];
+#pragma unroll
+                    for (int j = 0; j < TE; ++j) key[j] = Key::make(rel[q][j], k);
+#pragma unroll
+                    for (int s = 0; s < TS; ++s)
+                        minplus<TE>(acc[s], key, rgroup_key(buf[q], s), rgroup_keep0(buf[q ^ 1]), rgroup_keep1(buf[q ^ 1]));
+                    rgroup_await(buf[q ^ 1]);
+                };
+                request(0, 0);
+                request(1, 1);
+                rgroup_request(buf[0], Rk + (int64_t)uniform((int)sp[0]) * S_pad);
+                rgroup_await(buf[0]);
+                int i = 0;
+                for (; i + 2 <= cnt; i += 2) {
+                    reduce_row(0);
+                    request(0, i + 2);
+                    reduce_row(1);
+                    request(1, i + 3);
+                }
+                if (i < cnt) reduce_row(0);
+            }
+        } else if (!idle && cnt > 0) {
             const int npair = (cnt + 1) / 2;       // an odd tail repeats its entry: min(x, x) = x
             uint32_t va[2][TE], vb[2][TE];
             uint32_t spa[2], spb[2];
@@ -2061,15 +2137,18 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
         for (int s = 0; s < TS; ++s)
             if (full || s0 + s < S) {
                 uint8_t *row = bp + (int64_t)s * e_pad;
+                uint32_t low[TE];
+#pragma unroll
+                for (int j = 0; j < TE; ++j) low[j] = Key::low(acc[s][j]);
                 if constexpr (TE == 4) {
-                    const uint32_t p01 = __builtin_amdgcn_perm(acc[s][1], acc[s][0], 0x0c0c0400u);
-                    const uint32_t p23 = __builtin_amdgcn_perm(acc[s][3], acc[s][2], 0x0c0c0400u);
+                    const uint32_t p01 = __builtin_amdgcn_perm(low[1], low[0], 0x0c0c0400u);
+                    const uint32_t p23 = __builtin_amdgcn_perm(low[3], low[2], 0x0c0c0400u);
                     reinterpret_cast<uint32_t *>(row)[lane] = __builtin_amdgcn_perm(p23, p01, 0x05040100u) & mask;
                 } else if constexpr (TE == 2) {
                     reinterpret_cast<uint16_t *>(row)[lane] =
-                        (uint16_t)(__builtin_amdgcn_perm(acc[s][1], acc[s][0], 0x0c0c0400u) & mask);
+                        (uint16_t)(__builtin_amdgcn_perm(low[1], low[0], 0x0c0c0400u) & mask);
                 } else {
-                    row[lane] = (uint8_t)(acc[s][0] & mask);
+                    row[lane] = (uint8_t)(low[0] & mask);
                 }
             }
         // the last column of every 64: samples for the next layer's peek
@@ -2082,7 +2161,7 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
             for (int s = 0; s < TS; ++s)
                 if (full || s0 + s < S)
                     out[(uint32_t)s * n_samples] =
-                        cmin[TE - 1] < kInfCell ? cmin[TE - 1] + (Cell)(acc[s][TE - 1] >> k) + (Cell)ck[s] : kInfCell;
+                        cmin[TE - 1] < kInfCell ? cmin[TE - 1] + (Cell)Key::cost(acc[s][TE - 1], k) + (Cell)ck[s] : kInfCell;
         }
     };
     if (s0 + TS <= S)
@@ -2112,15 +2191,23 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_bytes_kernel(Layout a, i
     const ConstPtr<int32_t> hdr = as_const(a.hdr + ((int64_t)b * a.L + l) * 8);
     const int st = hdr[0], budget = hdr[1];
     if (st < 0) return;
-    const bool packed = st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE;
+    const bool keys32 = st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE;
+    const bool packed = byte_status(st, (uint32_t)hdr[3]);
     const int slot = (int)(blockIdx.x >> 3) - 1;
     if (slot < 0) {
         if ((blockIdx.x & 7) == 0 && packed) {
-            if (l == 1) {                          // (layer 1 itself is being swept, up to prep_kernel's bound)
-                live_step<NG>(layout_again(), wave, b, 1, false);
-                __syncthreads();
-            }
-            if (l + 1 < a.L) live_step<NG>(layout_again(), wave, b, l + 1, true);
+            auto step = [&](auto key) {
+                using Key = decltype(key);
+                if (l == 1) {                      // (layer 1 itself is being swept, up to prep_kernel's bound)
+                    live_step<NG, Key>(layout_again(), wave, b, 1, false);
+                    __syncthreads();
+                }
+                if (l + 1 < a.L) live_step<NG, Key>(layout_again(), wave, b, l + 1, true);
+            };
+            if (keys32)
+                step(Key32{});
+            else
+                step(Key64{});
         }
         return;
     }
@@ -2134,13 +2221,16 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_bytes_kernel(Layout a, i
     if (slot >= per || t >= nt) return;
     const int tile_start = (lo + t) * kTile;
     if (st == GALV_INSTANCE_OK_FAST_U32) {
-        sweep_bytes<TS, TE * UX, NG, uint32_t, kKeep, kTile>(layout_again(), wave, l, b, tile_start, false, h, ent, c0);
-    } else if (st == GALV_INSTANCE_OK_U32_WIDE) {
+        sweep_bytes<TS, TE * UX, NG, uint32_t, Key32, kKeep, kTile>(layout_again(), wave, l, b, tile_start, false, h, ent, c0);
+    } else if (packed) {
         // 8-byte cells: a part of the tile at a time keeps registers and LDS within what the narrow form uses
         for (int p = 0; p < TE; ++p) {
             if (tile_start + p * (kWave * UX) > x) break;    // workgroup-uniform
             if (p) __syncthreads();                          // the LDS of the part before is free again
-            sweep_bytes<TS, UX, NG, uint64_t, kKeep, kTile>(layout_again(), wave, l, b, tile_start + p * (kWave * UX), p > 0, h, ent, c0);
+            if (keys32)
+                sweep_bytes<TS, UX, NG, uint64_t, Key32, kKeep, kTile>(layout_again(), wave, l, b, tile_start + p * (kWave * UX), p > 0, h, ent, c0);
+            else
+                sweep_bytes<TS, UX, NG, uint64_t, Key64, kKeep, kTile>(layout_again(), wave, l, b, tile_start + p * (kWave * UX), p > 0, h, ent, c0);
         }
     } else if (st == GALV_INSTANCE_OK_FAST) {
         for (int u = 0; u < UX; ++u)
@@ -2160,16 +2250,19 @@ __device__ __forceinline__ int64_t last_layer_cost(const Layout &a, int b, int s
                                                    int64_t s) {
     const int64_t shift = a.m[((int64_t)b * a.L + (a.L - 1)) * a.S + s];
     if (shift > e) return kInf;
-    if (is_packed(a, st)) {
+    if (is_packed(a, st, b)) {
         const int32_t *h = a.hdr + ((int64_t)b * a.L + (a.L - 1)) * 8;
         if (e - shift < h[5]) return kInf;
         const int64_t x = e - shift < h[6] ? e - shift : h[6];
         const PackTables t = pack_tables(a, (a.L - 1) & 1, b);
         const uint32_t sp = byte_rows(a, b, a.L - 1)[(int64_t)s * a.e_pad + x];
-        const int64_t cmin = st == GALV_INSTANCE_OK_U32_WIDE ? (int64_t)reinterpret_cast<const uint64_t *>(t.cmin)[x]
-                                                             : (int64_t)reinterpret_cast<const uint32_t *>(t.cmin)[x];
-        return cmin + (int64_t)t.rel[(int64_t)sp * a.e_pad + x] + (int64_t)(rkeys(a, b, h[4])[(int64_t)sp * a.S_pad + s] >> a.k_bits) +
-               a.c[((int64_t)b * a.L + (a.L - 1)) * a.S + s];
+        const bool keys32 = st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE;
+        const int64_t cmin = st == GALV_INSTANCE_OK_FAST_U32 ? (int64_t)reinterpret_cast<const uint32_t *>(t.cmin)[x]
+                                                             : (int64_t)reinterpret_cast<const uint64_t *>(t.cmin)[x];
+        const uint64_t at = (uint64_t)sp * (uint32_t)a.S_pad + (uint32_t)s;
+        const uint64_t r = keys32 ? Key32::cost(rkeys<uint32_t>(a, b, h[4])[at], a.k_bits)
+                                  : Key64::cost(rkeys<double>(a, b, h[4])[at], a.k_bits);
+        return cmin + (int64_t)t.rel[(int64_t)sp * a.e_pad + x] + (int64_t)r + a.c[((int64_t)b * a.L + (a.L - 1)) * a.S + s];
     }
     const char *U = a.U[(a.L - 1) & 1] + ((int64_t)b * a.S_pad + s) * a.row * 8;
     const int64_t x = a.lead + e - shift;
@@ -2209,18 +2302,18 @@ __global__ __launch_bounds__(kThreads) void final_kernel(Layout a, int64_t *best
         a.last[b] = last;
         // every block of init_kernel has long finished: safe to record what the leads hold
         // (an instance with the byte table keeps other things there)
-        a.lead_mode[b] = st < 0 || is_packed(a, st) ? 0 : lead_kind(st);
+        a.lead_mode[b] = st < 0 || is_packed(a, st, b) ? 0 : lead_kind(st);
     }
 }
 
 // Walk the un-shifted argmin table of instance b from (L-1, e, s) down to layer 0:
 // L dependent loads.  Writes the plan, or all -1 when s < 0.
 __device__ __forceinline__ void walk_plan(const Layout &a, int b, int64_t e, int s, int32_t *out) {
-    const int st = a.status[b];
     if (s < 0) {
         for (int l = 0; l < a.L; ++l) out[l] = -1;
         return;
     }
+    const bool packed = is_packed(a, a.status[b], b);
     for (int l = a.L - 1; l >= 1; --l) {
         out[l] = s;
         e -= a.m[((int64_t)b * a.L + l) * a.S + s];
@@ -2230,7 +2323,7 @@ __device__ __forceinline__ void walk_plan(const Layout &a, int b, int64_t e, int
             for (int q = 0; q < a.L; ++q) out[q] = -1;
             return;
         }
-        s = load_bp(a, st, b, l, s, e);
+        s = load_bp(a, packed, b, l, s, e);
         if (s < 0 || s >= a.S) {
             for (int q = 0; q < a.L; ++q) out[q] = -1;
             return;
@@ -2293,7 +2386,7 @@ __global__ __launch_bounds__(kWave) void backtrack_kernel(Layout a, int32_t *pla
         return;
     }
     int64_t e = a.budget[b];
-    const int st = a.status[b];
+    const bool packed = is_packed(a, a.status[b], b);
     for (int l = a.L - 1; l >= 1; --l) {
         out[l] = s;
         e -= m_lds[(int64_t)l * a.S + s];
@@ -2301,7 +2394,7 @@ __global__ __launch_bounds__(kWave) void backtrack_kernel(Layout a, int32_t *pla
             for (int q = 0; q < a.L; ++q) out[q] = -1;
             return;
         }
-        s = load_bp(a, st, b, l, s, e);
+        s = load_bp(a, packed, b, l, s, e);
         if (s < 0 || s >= a.S) {
             for (int q = 0; q < a.L; ++q) out[q] = -1;
             return;
@@ -2366,6 +2459,7 @@ __global__ __launch_bounds__(kThreads) void export_kernel(Layout a, int b, int64
     const int st = uniform(a.status[b]);
     const int budget = uniform(a.budget[b]);
     const bool live = st >= 0 && e <= budget;
+    const bool packed = is_packed(a, st, b);
     if (l == a.L) {
         for (int s = 0; s < a.S; ++s)
             C_last[e * a.S + s] = live ? last_layer_cost(a, b, st, e, s) : kInf;
@@ -2378,7 +2472,7 @@ __global__ __launch_bounds__(kThreads) void export_kernel(Layout a, int b, int64
         if (live && l >= 1) {
             const int64_t shift = a.m[((int64_t)b * a.L + l) * a.S + s];
             if (shift <= e)
-                v = load_bp(a, st, b, l, s, e - shift);
+                v = load_bp(a, packed, b, l, s, e - shift);
         }
         dst[s] = v;
     }
@@ -2699,13 +2793,20 @@ galv_status_t make_plan(const galv_dp_desc_t *d, Plan *p) {
         return fail(GALV_ERR_RANGE, "internal: staging variant needs %u bytes of LDS", p->lds_bytes);
     a.e_pad = (int64_t)round_up((size_t)a.E_max + 1, kEAlign);
     a.n_tiles = (int32_t)((a.E_max + a.tile_e) / a.tile_e);   // ceil((E_max+1)/tile_e)
-    // measured: with ~1000 workgroups per layer (config 1) the peek costs 9 %, with ~6000 (config 2) it gains 14 %
-    a.peek = fills_chip ? 1 : 0;
+    // The byte table pays before that: it sweeps half the columns, and prunes for 64-bit keys too.  Whole solves over
+    // cost rows / with the byte table, by tiles of 128 columns: 78 (29 strategies x 37 layers) 0.348 / 0.335 ms,
+    // 272 (44 x 48) 0.57 / 0.82, 1032 (22 x 32) 0.370 / 0.334, 1256 (22 x 24) 0.289 / 0.233, 1548 (44 x 48, hardly
+    // anything to prune) 1.59 / 1.60, 2064 (44 x 48, 64-bit keys) 3.06 / 1.27 (1.08 with the 256-column twin).
+    // (Not where a tile is wider than a layer's share of the budget: rows then fall steeply within a tile and the
+    // peek leaves too many.)
+    const bool many_tiles = fills_chip || (((int64_t)d->max_budget / 128 + 1) * d->n_instances >= 1024 &&
+                                           d->max_budget / 128 >= d->n_layers);
+    a.peek = many_tiles ? 1 : 0;
     if (d->flags & GALV_DP_NO_PEEK) a.peek = 0;
     if (d->flags & GALV_DP_FORCE_PEEK) a.peek = 1;
     // The byte table writes a quarter of the bytes or less but rebuilds every cell it reads in two
     // dependent steps: it pays where the peek leaves few rows to read, so it has the same switch.
-    bool packed = v.share && !u8 && fills_chip;
+    bool packed = v.share && !u8 && many_tiles;
     if (d->flags & GALV_DP_NO_PACK) packed = false;
     if ((d->flags & GALV_DP_FORCE_PACK) && v.share && !u8) packed = true;
     if (packed) p->lds_bytes = lds_packed;

@@ -1,0 +1,24 @@
+"""The byte-table sweep with 64-bit keys: transition costs too large for a 32-bit key, up to the
+largest that a 32-bit relative cost holds (2^32 - 2) and one above it, where the sweep over cost
+rows takes over.  Whole tables are compared with the oracle's."""
+import pytest
+
+from paper_2211_13878_amd import binding, workloads
+from test_gpu_parity import check_against_oracle
+
+pytestmark = pytest.mark.gpu
+PACK, PEEK, NO_PEEK, WIDE = (binding.GALV_DP_FORCE_PACK, binding.GALV_DP_FORCE_PEEK, binding.GALV_DP_NO_PEEK,
+                             binding.GALV_DP_FORCE_WIDE_TILES)
+
+
+@pytest.mark.parametrize("S", [1, 6, 16, 22, 29, 44, 64, 128, 200])
+@pytest.mark.parametrize("c_hi,r_hi", [(5000, 1 << 27), (1 << 36, 1 << 30), (1 << 36, (1 << 32) - 2), (1 << 36, (1 << 32) - 1)])
+def test_large_transition_costs(S, c_hi, r_hi):
+    w = workloads.random_workload(9 * S + r_hi % 97, 4, 5, S, 900, nR=2, m_range=(0, 200), c_range=(0, c_hi),
+                                  r_range=(0, r_hi), infeasible=0.1, zero_diagonal=False)
+    w.R[0, 0, 0, 0] = r_hi                    # the largest value itself is met
+    w.R[1:] //= 64                            # and three instances where rows can be ruled out
+    w.R[1, 1, 0, S - 1] = r_hi
+    w.budget[:] = (900, 255, 256, 511)
+    for flags in (PACK | PEEK, PACK | NO_PEEK, PACK | PEEK | WIDE, PACK | PEEK | binding.GALV_DP_NO_U32):
+        check_against_oracle(w, flags=flags, table_instances=[0, 1, 2, 3], allow_vacuous=S == 1)
