@@ -2277,26 +2277,37 @@ __device__ __forceinline__ int64_t last_layer_cost(const Layout &a, int b, int s
     return reinterpret_cast<const int64_t *>(U)[x];
 }
 
-// One workgroup per instance: min over s at e = budget, lowest s first.
-__global__ __launch_bounds__(kThreads) void final_kernel(Layout a, int64_t *best_cost,
-                                                         int32_t *best_last) {
+// min_s C[L-1][e][s] and the lowest minimising s for one (instance, budget column), by a whole wave:
+// a lane per strategy, so that the dependent loads of a cell (argmin, relative cost) are waited for once.
+__device__ __forceinline__ void best_at_wave(const Layout &a, int b, int st, int64_t e, int64_t &opt, int32_t &last) {
+    opt = kInf;
+    last = -1;
+    for (int s = lane_id(); s < a.S; s += kWave) {
+        const int64_t v = last_layer_cost(a, b, st, e, s);
+        if (v < opt) {
+            opt = v;
+            last = s;
+        }
+    }
+#pragma unroll
+    for (int w = kWave / 2; w > 0; w >>= 1) {
+        const int64_t v = (int64_t)__shfl_xor((long long)opt, w, kWave);
+        const int32_t s = __shfl_xor(last, w, kWave);
+        if (v < opt || (v == opt && (uint32_t)s < (uint32_t)last)) {   // (-1, nothing reachable, is the largest)
+            opt = v;
+            last = s;
+        }
+    }
+}
+
+// One wave per instance: min over s at e = budget, lowest s first.
+__global__ __launch_bounds__(kWave) void final_kernel(Layout a, int64_t *best_cost, int32_t *best_last) {
     const int b = blockIdx.x;
     const int st = uniform(a.status[b]);
-    __shared__ int64_t val[kMaxS];
-    if (st >= 0) {
-        const int budget = uniform(a.budget[b]);
-        for (int s = threadIdx.x; s < a.S; s += kThreads) val[s] = last_layer_cost(a, b, st, budget, s);
-    }
-    __syncthreads();
+    int64_t opt = kInf;
+    int32_t last = -1;
+    if (st >= 0) best_at_wave(a, b, st, uniform(a.budget[b]), opt, last);
     if (threadIdx.x == 0) {
-        int64_t opt = kInf;
-        int32_t last = -1;
-        if (st >= 0)
-            for (int s = 0; s < a.S; ++s)
-                if (val[s] < opt) {
-                    opt = val[s];
-                    last = s;
-                }
         best_cost[b] = opt;
         best_last[b] = last;
         a.last[b] = last;
@@ -2332,6 +2343,108 @@ __device__ __forceinline__ void walk_plan(const Layout &a, int b, int64_t e, int
     out[0] = s;
 }
 
+// The same walk by a whole wave, two layers per round trip.  The column that layer l - 1 is left at
+// depends on layer l's choice but not on layer l - 1's own, so while the argmin that names strategy
+// s' of layer l - 1 is under way, lane s' already fetches the argmin that s' would lead to; memories and
+// column ranges of the next two layers are fetched meanwhile.  S <= 64 * Q.
+// (Before, one dependent load per layer after a copy of the memory table to LDS: 29 strategies x 37 layers
+// 22 -> 21 us, 44 x 48 x 16 instances 37 -> 30 us; 32 queries of 22 x 24, once a thread each, 37 -> 15 us.)
+template <int Q>
+__device__ __forceinline__ void walk_wave(const Layout &a, bool packed, int b, int64_t e0, int s, int32_t *out) {
+    const int lane = lane_id();
+    const int S = a.S, L = a.L;
+    const int32_t *m = a.m + (int64_t)b * L * S;
+    const int32_t *hdr = a.hdr + (int64_t)b * L * 8;
+    const int64_t bp0 = (int64_t)b * (L - 1) * S * a.e_pad;
+    struct Row {                                   // of one layer: memories, and the columns the byte table holds
+        int m[Q];
+        int y, x;
+    };
+    auto load = [&](int l, Row &r) {
+        l = l > 0 ? l : 0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int sx = q * kWave + lane;
+            r.m[q] = m[(int64_t)l * S + (sx < S ? sx : S - 1)];
+        }
+        r.y = packed ? hdr[l * 8 + 5] : 0;
+        r.x = packed ? hdr[l * 8 + 6] : 0x7fffffff;
+    };
+    auto cell = [&](int l, const Row &r, int sx, int x) -> int {   // layer l >= 1, a column of the table
+        const int64_t at = bp0 + ((int64_t)(l - 1) * S + sx) * a.e_pad;
+        if (packed) return x < r.y ? -1 : (int)byte_rows(a, b, l)[(int64_t)sx * a.e_pad + (x < r.x ? x : r.x)];
+        if (a.bp_u8) {
+            const uint8_t v = static_cast<const uint8_t *>(a.bp)[at + x];
+            return v == 0xFF ? -1 : (int)v;
+        }
+        return static_cast<const int32_t *>(a.bp)[at + x];
+    };
+    auto pick = [&](const int (&v)[Q], int sx) {   // strategy sx's value, wave-uniform
+        int r = __builtin_amdgcn_readlane(v[0], sx & (kWave - 1));
+#pragma unroll
+        for (int q = 1; q < Q; ++q) {
+            const int o = __builtin_amdgcn_readlane(v[q], sx & (kWave - 1));
+            if (sx >> 6 == q) r = o;
+        }
+        return r;
+    };
+    int e = uniform((int)e0);
+    s = uniform(s);
+    int l = L - 1;
+    Row now, below;
+    load(l, now);
+    load(l - 1, below);
+    // A reachable cell always points at a reachable cell; the guards only keep the walk inside the
+    // table if that invariant were ever broken.
+    while (s >= 0 && l >= 1) {
+        const int x = e - pick(now.m, s);
+        if (x < 0 || x > a.E_max) {
+            s = -1;
+            break;
+        }
+        const int first = cell(l, now, s, x);
+        int second[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int sx = q * kWave + lane, x2 = x - below.m[q];
+            second[q] = l >= 2 && sx < S && x2 >= 0 && x2 <= a.E_max ? cell(l - 1, below, sx, x2) : -1;
+        }
+        Row next, next_below;
+        load(l - 2, next);
+        load(l - 3, next_below);
+        if (lane == 0) out[l] = s;
+        s = uniform(first);
+        if (s < 0 || s >= S) {
+            s = -1;
+            break;
+        }
+        if (--l == 0) break;
+        if (lane == 0) out[l] = s;
+        e = x - pick(below.m, s);
+        s = pick(second, s);
+        if (s < 0 || s >= S) {
+            s = -1;
+            break;
+        }
+        --l;
+        now = next;
+        below = next_below;
+    }
+    if (s < 0)
+        for (int q = lane; q < L; q += kWave) out[q] = -1;
+    else if (lane == 0)
+        out[0] = s;
+}
+__device__ __forceinline__ void walk_any(const Layout &a, int b, int64_t e, int s, int32_t *out) {
+    const bool packed = is_packed(a, a.status[b], b);
+    if (a.S <= kWave)
+        walk_wave<1>(a, packed, b, e, s, out);
+    else if (a.S <= 4 * kWave)
+        walk_wave<4>(a, packed, b, e, s, out);
+    else if (lane_id() == 0)
+        walk_plan(a, b, e, s, out);
+}
+
 // Per instance: the tiles' (rows reduced, rows listed) summed over the tiles within the budget
 // and the layers; zeros for an instance that is not on the 32-bit-key path.
 __global__ __launch_bounds__(kThreads) void stats_kernel(Layout a, int64_t *out) {
@@ -2364,43 +2477,10 @@ __global__ __launch_bounds__(kThreads) void stats_kernel(Layout a, int64_t *out)
         for (int q = 0; q < 3; ++q) out[3 * b + q] = (int64_t)red[q][0];
 }
 
-// One wave per instance, from the full budget and the stored best last strategy.  The walk is
-// a chain of dependent loads, two per layer (the memory of the chosen strategy, then the
-// back-pointer it leads to); when the instance's memory table fits LDS the wave copies it there
-// first, coalesced, which leaves one global load per layer in the chain.
-constexpr int kWalkLds = 16384;                  // int32 words of m(l, s) kept in LDS
+// One wave per instance, from the full budget and the stored best last strategy.
 __global__ __launch_bounds__(kWave) void backtrack_kernel(Layout a, int32_t *plan) {
     const int b = blockIdx.x;
-    __shared__ int32_t m_lds[kWalkLds];
-    const int64_t n = (int64_t)a.L * a.S;
-    const int32_t *m = a.m + (int64_t)b * n;
-    const bool in_lds = n <= kWalkLds;
-    int s = a.last[b];
-    if (in_lds && s >= 0)
-        for (int64_t i = threadIdx.x; i < n; i += kWave) m_lds[i] = m[i];
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    int32_t *out = plan + (int64_t)b * a.L;
-    if (!in_lds || s < 0) {
-        walk_plan(a, b, a.budget[b], s, out);
-        return;
-    }
-    int64_t e = a.budget[b];
-    const bool packed = is_packed(a, a.status[b], b);
-    for (int l = a.L - 1; l >= 1; --l) {
-        out[l] = s;
-        e -= m_lds[(int64_t)l * a.S + s];
-        if (e < 0 || e > a.E_max) {             // cannot happen for a reachable cell; keeps the walk inside the table
-            for (int q = 0; q < a.L; ++q) out[q] = -1;
-            return;
-        }
-        s = load_bp(a, packed, b, l, s, e);
-        if (s < 0 || s >= a.S) {
-            for (int q = 0; q < a.L; ++q) out[q] = -1;
-            return;
-        }
-    }
-    out[0] = s;
+    walk_any(a, b, a.budget[b], a.last[b], plan + (int64_t)b * a.L);
 }
 
 // min_s C[L-1][e][s] and the lowest minimising s for one (instance, budget column).
@@ -2431,22 +2511,22 @@ __global__ __launch_bounds__(kThreads) void best_per_budget_kernel(Layout a, int
     if (best_last) best_last[(int64_t)b * (a.E_max + 1) + e] = last;
 }
 
-// One thread per (instance, budget) query: final minimum at that column, then the walk.
+// One wave per (instance, budget) query: final minimum at that column, then the walk.
 __global__ __launch_bounds__(kWave) void backtrack_queries_kernel(Layout a, int n, const int32_t *inst,
-                                                                  const int32_t *budgets,
-                                                                  int64_t *cost, int32_t *plan) {
-    const int q = blockIdx.x * kWave + threadIdx.x;
-    if (q >= n) return;
-    const int b = inst[q];
-    const int64_t e = budgets[q];
-    int64_t opt = kInf;
-    int32_t last = -1;
-    if (b >= 0 && b < a.B) {
-        const int st = uniform(a.status[b]);
-        if (st >= 0 && e >= 0 && e <= a.budget[b]) best_at(a, b, st, e, opt, last);
+                                                                  const int32_t *budgets, int64_t *cost,
+                                                                  int32_t *plan) {
+    for (int64_t q = blockIdx.x; q < n; q += gridDim.x) {
+        const int b = uniform(inst[q]);
+        const int64_t e = uniform(budgets[q]);
+        int64_t opt = kInf;
+        int32_t last = -1;
+        if (b >= 0 && b < a.B) {
+            const int st = uniform(a.status[b]);
+            if (st >= 0 && e >= 0 && e <= a.budget[b]) best_at_wave(a, b, st, e, opt, last);
+        }
+        if (cost && threadIdx.x == 0) cost[q] = opt;
+        walk_any(a, b < 0 || b >= a.B ? 0 : b, e, last, plan + q * a.L);
     }
-    if (cost) cost[q] = opt;
-    walk_plan(a, b < 0 || b >= a.B ? 0 : b, e, last, plan + (int64_t)q * a.L);
 }
 
 // Canonical-order tables of one instance.  Grid: (e tiles, L + 1); row L of the
@@ -2972,7 +3052,7 @@ galv_status_t enqueue_solve(galv_dp *h, const int64_t *c_dev, const int32_t *m_d
             return fail(GALV_ERR_HIP, "forking the layer sweeps over internal streams failed: %s",
                         hipGetErrorString(err));
     }
-    final_kernel<<<a.B, kThreads, 0, st>>>(a, best_cost_dev, best_last_dev);
+    final_kernel<<<a.B, kWave, 0, st>>>(a, best_cost_dev, best_last_dev);
     HIP_TRY(hipGetLastError());
     h->solved = true;
     h->fresh = false;
@@ -3207,9 +3287,9 @@ galv_status_t galv_dp_backtrack_queries(galv_dp_t *h, int32_t n_queries, const i
     if (!instance_dev || !budget_dev || !plan_dev)
         return fail(GALV_ERR_INVALID_ARG, "a required device pointer is NULL");
     if (!h->solved) return fail(GALV_ERR_STATE, "backtrack_queries before a successful solve");
-    backtrack_queries_kernel<<<(n_queries + kWave - 1) / kWave, kWave, 0,
-                               static_cast<hipStream_t>(stream)>>>(h->lay, n_queries, instance_dev,
-                                                                   budget_dev, cost_dev, plan_dev);
+    const unsigned blocks = (unsigned)(n_queries < 1 << 20 ? n_queries : 1 << 20);
+    backtrack_queries_kernel<<<blocks, kWave, 0, static_cast<hipStream_t>(stream)>>>(h->lay, n_queries, instance_dev,
+                                                                                     budget_dev, cost_dev, plan_dev);
     HIP_TRY(hipGetLastError());
     return GALV_OK;
 }
