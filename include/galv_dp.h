@@ -95,23 +95,25 @@ typedef struct {
                                   sweep is then bound by bytes; below that it is bound by latency
                                   and the extra dependent step costs more than it saves).  Results
                                   are identical either way.                                          */
-#define GALV_DP_NO_PACK 32u    /* 32-bit-key instances: always keep the rolling cost rows and plain
-                                  back-pointers (see GALV_DP_FORCE_PACK)                            */
-#define GALV_DP_FORCE_PACK 64u /* 32-bit-key instances, int32 back-pointers, at most 256 strategies:
+#define GALV_DP_NO_PACK 32u    /* always keep the rolling cost rows and plain back-pointers (see
+                                  GALV_DP_FORCE_PACK)                                               */
+#define GALV_DP_FORCE_PACK 64u /* packed-key instances with transition costs below 2^32 - 1, int32
+                                  back-pointers, at most 256 strategies:
                                   keep argmins of one byte each and, instead of cost rows, one former
                                   minimum per budget column plus the relative costs of the few former
                                   strategies that can win in a tile, from which the next layer rebuilds
                                   the cells it reads; and store only the budget columns between the
                                   first reachable one and the one from which a layer is constant.
                                   1 to 2 bytes per state instead of 8.  By default this is done when a
-                                  layer has enough workgroups to fill the chip (as for
-                                  GALV_DP_FORCE_PEEK).  Results, exported tables included, are
+                                  layer has many states and its share of the budget spans a tile, and
+                                  the sweep then peeks (GALV_DP_FORCE_PEEK) too.  Results, exported tables included, are
                                   identical either way.                                              */
 #define GALV_DP_FORCE_WIDE_TILES 128u   /* sweep workgroups take tiles of 256 budget columns instead of 128
                                            (17 to 256 strategies: the kernel variants that have such a twin).
                                            By default this is done when a layer has enough workgroups to
                                            fill the chip, as for GALV_DP_FORCE_PEEK.  Results are identical. */
-#define GALV_DP_NO_WIDE_TILES 0x2000u   /* always 128-column tiles                                           */
+#define GALV_DP_NO_WIDE_TILES 0x2000u   /* always 128-column tiles of the plain shape: neither wide tiles nor, on
+                                           launches that leave wavefront slots idle, more waves per tile      */
 #define GALV_DP_STREAMS_SHIFT 8 /* bits 8..12: how many internal streams the layer sweeps are   */
 #define GALV_DP_STREAMS_MASK 0x1f00u /* spread over; 1 = none, at most 16; 0 = chosen by the library:
                                         galv_dp_create makes as many as the shape could use with every

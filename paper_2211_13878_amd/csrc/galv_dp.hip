@@ -2496,6 +2496,37 @@ __device__ __forceinline__ void best_at(const Layout &a, int b, int st, int64_t 
         }
     }
 }
+// The same from the byte table: no branch per strategy, so that the two dependent loads of several cells are
+// under way together (8 x 20002 columns x 22 strategies took 27 us with the branches).
+template <class Cell, class Key>
+__device__ __forceinline__ void best_at_bytes(const Layout &a, int b, int e, int64_t &opt, int32_t &last) {
+    const int32_t *h = a.hdr + ((int64_t)b * a.L + (a.L - 1)) * 8;
+    const int y = h[5], top = h[6];
+    opt = kInf;
+    last = -1;
+    if (y > top) return;                           // nothing reachable, nothing stored
+    const PackTables t = pack_tables(a, (a.L - 1) & 1, b);
+    const uint8_t *bp = byte_rows(a, b, a.L - 1);
+    const Cell *cmin = reinterpret_cast<const Cell *>(t.cmin);
+    const typename Key::T *R = rkeys<typename Key::T>(a, b, h[4]);
+    const int32_t *m = a.m + ((int64_t)b * a.L + (a.L - 1)) * a.S;
+    const int64_t *c = a.c + ((int64_t)b * a.L + (a.L - 1)) * a.S;
+    const int mask = (1 << a.k_bits) - 1;
+#pragma unroll 4
+    for (int s = 0; s < a.S; ++s) {
+        const int at = e - m[s];
+        const bool ok = at >= y;                   // (memories are not negative, and y is not)
+        const int x = ok && at < top ? at : top;
+        const uint32_t sp = bp[(int64_t)s * a.e_pad + x] & (uint32_t)mask;
+        const uint32_t in = sp < (uint32_t)a.S ? sp : 0;        // (bytes of unreachable columns may be anything)
+        const int64_t v = (int64_t)cmin[x] + (int64_t)t.rel[(int64_t)in * a.e_pad + x] +
+                          (int64_t)Key::cost(R[(int64_t)in * a.S_pad + s], a.k_bits) + c[s];
+        if (ok && v < opt) {
+            opt = v;
+            last = s;
+        }
+    }
+}
 
 // The optimum of every budget column.  Grid: (column tiles, B).
 __global__ __launch_bounds__(kThreads) void best_per_budget_kernel(Layout a, int64_t *best_cost,
@@ -2506,7 +2537,16 @@ __global__ __launch_bounds__(kThreads) void best_per_budget_kernel(Layout a, int
     const int st = uniform(a.status[b]);
     int64_t opt = kInf;
     int32_t last = -1;
-    if (st >= 0 && e <= a.budget[b]) best_at(a, b, st, e, opt, last);
+    if (st >= 0 && e <= a.budget[b]) {
+        if (!is_packed(a, st, b))
+            best_at(a, b, st, e, opt, last);
+        else if (st == GALV_INSTANCE_OK_FAST_U32)
+            best_at_bytes<uint32_t, Key32>(a, b, (int)e, opt, last);
+        else if (st == GALV_INSTANCE_OK_U32_WIDE)
+            best_at_bytes<uint64_t, Key32>(a, b, (int)e, opt, last);
+        else
+            best_at_bytes<uint64_t, Key64>(a, b, (int)e, opt, last);
+    }
     best_cost[(int64_t)b * (a.E_max + 1) + e] = opt;
     if (best_last) best_last[(int64_t)b * (a.E_max + 1) + e] = last;
 }
@@ -2623,6 +2663,36 @@ __global__ __launch_bounds__(kThreads) void export_kernel(Layout a, int b, int64
 #endif
 #ifndef GALV_V7X
 #define GALV_V7X 16, 2, 16, 4, 16, 2, 1
+#endif
+// Twins with the same tiles and more, thinner waves, for launches that leave wavefront slots idle: a
+// tile's time is then a chain of round trips, two per row that a wave rebuilds or one per row that it
+// loads, and of the additions of the strategies it owns, and more waves shorten both.
+#ifndef GALV_S0
+#define GALV_S0 2, 2, 4, 8, 4, 1, 1
+#endif
+#ifndef GALV_S1
+#define GALV_S1 4, 2, 4, 8, 4, 1, 1
+#endif
+#ifndef GALV_S2
+#define GALV_S2 6, 2, 4, 8, 4, 1, 1
+#endif
+#ifndef GALV_S3
+#define GALV_S3 8, 2, 4, 8, 4, 1, 1
+#endif
+#ifndef GALV_S4
+#define GALV_S4 6, 2, 8, 8, 8, 1, 1
+#endif
+#ifndef GALV_S5
+#define GALV_S5 8, 2, 8, 8, 8, 1, 1
+#endif
+#ifndef GALV_S6
+#define GALV_S6 8, 2, 16, 8, 16, 1, 1
+#endif
+#ifndef GALV_F2
+#define GALV_F2 3, 2, 8, 8, 8, 1, 1
+#endif
+#ifndef GALV_F3
+#define GALV_F3 4, 2, 8, 8, 8, 1, 1
 #endif
 
 // ---------------------------------------------------------------------------------------------
@@ -2757,8 +2827,21 @@ VariantEntry variant_entry() {
             pack};
 }
 
-// `wide_tiles`: the launch fills the chip; take the 256-column twin where there is one.
-const VariantEntry &pick_variant(int S, bool wide_tiles) {
+enum class Tiles { wide, normal, split, fine };
+
+// wide: the launch fills the chip; take the 256-column twin where there is one.  split, fine: it
+// leaves wavefront slots idle; take the twin with more waves per tile.
+const VariantEntry &pick_variant(int S, Tiles tiles) {
+    static const VariantEntry splits[] = {
+        variant_entry<GALV_S0>(), variant_entry<GALV_S1>(), variant_entry<GALV_S2>(), variant_entry<GALV_S3>(),
+        variant_entry<GALV_S4>(), variant_entry<GALV_S5>(), variant_entry<GALV_S6>()};
+    static const VariantEntry fines[] = {variant_entry<GALV_F2>(), variant_entry<GALV_F3>()};
+    if (tiles == Tiles::fine)
+        for (const VariantEntry &t : fines)
+            if (S > 16 && S <= t.v.ts * t.v.ng) return t;
+    if (tiles == Tiles::split || tiles == Tiles::fine)
+        for (const VariantEntry &t : splits)
+            if (S <= t.v.ts * t.v.ng) return t;
     static const VariantEntry table[] = {
         variant_entry<GALV_V0>(), variant_entry<GALV_V1>(), variant_entry<GALV_V2>(),
         variant_entry<GALV_V3>(), variant_entry<GALV_V4>(), variant_entry<GALV_V5>(),
@@ -2769,7 +2852,7 @@ const VariantEntry &pick_variant(int S, bool wide_tiles) {
     constexpr int n = sizeof table / sizeof table[0];
     for (int i = 0; i < n; ++i)
         if (S <= table[i].v.ts * table[i].v.ng) {
-            if (wide_tiles)
+            if (tiles == Tiles::wide)
                 for (const VariantEntry &t : twins)
                     if (t.v.ts == table[i].v.ts && t.v.ng == table[i].v.ng) return t;
             return table[i];
@@ -2811,7 +2894,7 @@ struct Plan {
     unsigned lds_bytes;
 };
 
-galv_status_t make_plan(const galv_dp_desc_t *d, Plan *p) {
+galv_status_t make_plan(const galv_dp_desc_t *d, bool may_split, Plan *p) {
     if (!d) return fail(GALV_ERR_INVALID_ARG, "desc is NULL");
     if (d->n_instances < 1 || d->n_layers < 1 || d->n_strategies < 1 || d->max_budget < 0 ||
         d->n_transition < 1)
@@ -2838,10 +2921,45 @@ galv_status_t make_plan(const galv_dp_desc_t *d, Plan *p) {
         return fail(GALV_ERR_RANGE, "max_budget %d exceeds 2^30", d->max_budget);
 
     memset(p, 0, sizeof *p);
-    // enough workgroups per layer to fill the chip several times over (counted in 128-column tiles)?
-    const bool fills_chip = ((int64_t)d->max_budget / 128 + 1) * d->n_instances >= 3072;
-    const bool wide_tiles = (fills_chip || (d->flags & GALV_DP_FORCE_WIDE_TILES)) && !(d->flags & GALV_DP_NO_WIDE_TILES);
-    const VariantEntry &ve = pick_variant(d->n_strategies, wide_tiles);
+    const int64_t tiles = ((int64_t)d->max_budget / 128 + 1) * d->n_instances;    // of 128 columns, in one layer
+    const int S = d->n_strategies;
+    // Enough workgroups per layer to fill the chip several times over?
+    const bool fills_chip = tiles >= 3072;
+    // Byte table or cost rows.  The byte table sweeps half the columns and writes a quarter of the bytes or less,
+    // but rebuilds every cell it reads in two dependent steps, so a tile takes longer: it pays where a layer has
+    // many states.  Whole solves of 12 layers over cost rows / with the byte table, in us:
+    //   14 strategies:  504 tiles  96 / 100   1008 tiles 114 / 105      44:   94 tiles  98 / 100    252 tiles 115 / 108
+    //   22:             252 tiles  87 /  93    504 tiles 108 / 103      64:   94 tiles 111 / 106
+    //   29:             252 tiles  96 / 104    504 tiles 119 / 111     120:   94 tiles 158 / 140
+    // (costs in nanoseconds, that is 64-bit keys: 44 x 504 260 / 196, 120 x 504 917 / 357).  Not where a tile
+    // is wider than a layer's share of the budget: rows then fall steeply within a tile and the peek leaves too
+    // many (12 layers, cost rows / byte table: 22 x 512 tiles of 1000 columns 120 / 131, of 2040 columns 116 / 115; 120
+    // x 512 of 1000 258 / 362, of 2040 261 / 238).
+    // (Where the chip is full, down to half a tile, beyond 16 strategies: 3200 to 4000 tiles, cost rows / byte table,
+    // share 49: 22 2.41 / 2.84 ms, 44 3.70 / 4.03; share 83 to 98: 14 0.90 / 1.11, 22 1.19 / 1.10 and 1.94 / 2.02,
+    // 44 3.60 / 2.54.)
+    const int64_t share = d->max_budget / d->n_layers;
+    const bool rows_asked = u8 || (d->flags & GALV_DP_NO_PACK);
+    const bool pays = !rows_asked && tiles * S >= 10000 && (share >= 128 || (fills_chip && S > 16 && share >= 64));
+    // Tiles of 256 columns where the launch fills the chip with them (normal / wide, in us: 44 x 1008 tiles 137 /
+    // 146, x 2016 172 / 172 and with 64-bit keys 282 / 244; 64 x 2016 227 / 204; 120 x 504 242 / 241, x 1008 319 /
+    // 270; in the byte table not where a layer's share is small and many rows are kept: 22 x 4032 tiles at 83 columns
+    // 2.02 / 3.08 ms); more waves per tile where even those would leave wavefront slots idle (normal / split: 22 x 1008 114 /
+    // 108, x 2016 142 / 142, x 2640 141 / 153; 29 x 2016 158 / 148; 44 x 504 127 / 128, x 1008 137 / 149; 64 x 504
+    // 136 / 131; 120 x 252 171 / 160); up to 16 strategies the normal shape has one wave per tile and loses until the
+    // chip is full (14 x 2640 158 / 143, x 3200 over cost rows 902 / 1026).  Very few tiles of 17 to 32 strategies take eight waves each (split / fine, cost rows:
+    // 22 x 94 88 / 82, 29 x 252 106 / 96, 22 x 1008 142 / 152).
+    Tiles shape = Tiles::normal;
+    if (fills_chip ? rows_asked || share >= 128 : pays && tiles * S >= 80000 && share >= 256)
+        shape = Tiles::wide;
+    else if (S > 16 && S <= 32 && tiles <= 256)
+        shape = Tiles::fine;
+    else if ((S <= 16 && !fills_chip) || tiles * (S <= 32 ? 4 : S <= 64 ? 8 : 16) <= 7168)
+        shape = Tiles::split;
+    if (d->flags & GALV_DP_FORCE_WIDE_TILES) shape = Tiles::wide;
+    if (d->flags & GALV_DP_NO_WIDE_TILES) shape = Tiles::normal;
+    if (!may_split && (shape == Tiles::split || shape == Tiles::fine)) shape = Tiles::normal;
+    const VariantEntry &ve = pick_variant(S, shape);
     const Variant v = ve.v;
     Layout &a = p->lay;
     a.B = d->n_instances;
@@ -2873,21 +2991,11 @@ galv_status_t make_plan(const galv_dp_desc_t *d, Plan *p) {
         return fail(GALV_ERR_RANGE, "internal: staging variant needs %u bytes of LDS", p->lds_bytes);
     a.e_pad = (int64_t)round_up((size_t)a.E_max + 1, kEAlign);
     a.n_tiles = (int32_t)((a.E_max + a.tile_e) / a.tile_e);   // ceil((E_max+1)/tile_e)
-    // The byte table pays before that: it sweeps half the columns, and prunes for 64-bit keys too.  Whole solves over
-    // cost rows / with the byte table, by tiles of 128 columns: 78 (29 strategies x 37 layers) 0.348 / 0.335 ms,
-    // 272 (44 x 48) 0.57 / 0.82, 1032 (22 x 32) 0.370 / 0.334, 1256 (22 x 24) 0.289 / 0.233, 1548 (44 x 48, hardly
-    // anything to prune) 1.59 / 1.60, 2064 (44 x 48, 64-bit keys) 3.06 / 1.27 (1.08 with the 256-column twin).
-    // (Not where a tile is wider than a layer's share of the budget: rows then fall steeply within a tile and the
-    // peek leaves too many.)
-    const bool many_tiles = fills_chip || (((int64_t)d->max_budget / 128 + 1) * d->n_instances >= 1024 &&
-                                           d->max_budget / 128 >= d->n_layers);
-    a.peek = many_tiles ? 1 : 0;
+    // measured over cost rows: with ~1000 workgroups per layer the peek costs 9 %, with ~6000 it gains 14 %
+    a.peek = fills_chip || pays ? 1 : 0;
     if (d->flags & GALV_DP_NO_PEEK) a.peek = 0;
     if (d->flags & GALV_DP_FORCE_PEEK) a.peek = 1;
-    // The byte table writes a quarter of the bytes or less but rebuilds every cell it reads in two
-    // dependent steps: it pays where the peek leaves few rows to read, so it has the same switch.
-    bool packed = v.share && !u8 && many_tiles;
-    if (d->flags & GALV_DP_NO_PACK) packed = false;
+    bool packed = v.share && pays;
     if ((d->flags & GALV_DP_FORCE_PACK) && v.share && !u8) packed = true;
     if (packed) p->lds_bytes = lds_packed;
     p->sweep = packed ? ve.fn_pack : (u8 ? ve.fn_u8 : ve.fn);
@@ -2927,6 +3035,16 @@ galv_status_t make_plan(const galv_dp_desc_t *d, Plan *p) {
     p->off_stats = take((size_t)a.B * (a.L > 1 ? a.L - 1 : 1) * a.n_tiles * 2 * sizeof(uint32_t));
     p->total = off;
     return GALV_OK;
+}
+
+galv_status_t make_plan(const galv_dp_desc_t *d, Plan *p) {
+    const galv_status_t st = make_plan(d, true, p);
+    // (the twins with more waves pad the strategies to a little more: not at the price of the fixed workspace)
+    Plan q;
+    if (st == GALV_OK && p->total > (size_t)GALV_DP_STATIC_BYTES && make_plan(d, false, &q) == GALV_OK &&
+        q.total <= (size_t)GALV_DP_STATIC_BYTES)
+        *p = q;
+    return st;
 }
 
 // grid.x of a sweep launch for n budget tiles.
