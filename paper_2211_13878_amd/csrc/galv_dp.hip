@@ -302,19 +302,39 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
     const int b = blockIdx.x;
     const int tid = threadIdx.x;
     const int64_t L = a.L, S = a.S, nR = a.nR;
-    const int64_t *c = a.c + (int64_t)b * L * S;
-    const int32_t *m = a.m + (int64_t)b * L * S;
-    const int64_t *R = a.R + (int64_t)b * nR * S * S;
+    // (the inputs through the constant address space: their loads may then pass the stores of the lists)
+    const ConstPtr<int64_t> c = as_const(a.c + (int64_t)b * L * S);
+    const ConstPtr<int32_t> m = as_const(a.m + (int64_t)b * L * S);
+    const ConstPtr<int64_t> R = as_const(a.R + (int64_t)b * nR * S * S);
     const int32_t *ridx = a.r_idx ? a.r_idx + (int64_t)b * L : nullptr;
     const unsigned long long cap = (unsigned long long)kInf;
 
     __shared__ int bad;
     __shared__ unsigned long long rmax[64];  // max of each transition matrix (64 at a time)
-    __shared__ unsigned long long red[kPrepThreads];
-    __shared__ unsigned long long bound_s;
+    __shared__ unsigned long long red[2][kPrepThreads / kWave];
     __shared__ int m_top;                          // layer 0's largest usable memory
     if (tid == 0) bad = 0;
     __syncthreads();
+    const int wave = tid >> 6, lane = tid & 63;
+    // A value of every thread, reduced over the workgroup, in every thread: one barrier (a tree in LDS took ten; the
+    // slots take turns, and nobody can be two reductions ahead of a barrier).
+    int turn = 0;
+    auto reduce = [&](unsigned long long v, auto op) {
+#pragma unroll
+        for (int w = kWave / 2; w > 0; w >>= 1) v = op(v, (unsigned long long)__shfl_xor((long long)v, w, kWave));
+        if (lane == 0) red[turn][wave] = v;
+        __syncthreads();
+        v = red[turn][lane & (kPrepThreads / kWave - 1)];
+#pragma unroll
+        for (int w = kPrepThreads / kWave / 2; w > 0; w >>= 1)
+            v = op(v, (unsigned long long)__shfl_xor((long long)v, w, kWave));
+        turn ^= 1;
+        return v;
+    };
+    auto largest = [](unsigned long long x, unsigned long long y) { return x > y ? x : y; };
+    auto sum_to_cap = [](unsigned long long x, unsigned long long y) {     // each at most 2^62: no wrap
+        return x + y > cap ? cap : x + y;
+    };
 
     const int budget = uniform(a.budget[b]);
     if (tid == 0 && (budget < 0 || budget > a.E_max)) bad = 1;
@@ -328,22 +348,15 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
             const int e = a.budget[i];
             if (e >= 0 && e <= a.E_max) tiles += (unsigned)(e / a.tile_e + 1);
         }
-        red[tid] = tiles;
-        __syncthreads();
-        for (int w = kPrepThreads / 2; w > 0; w >>= 1) {
-            if (tid < w) red[tid] += red[tid + w];
-            __syncthreads();
-        }
+        tiles = reduce(tiles, sum_to_cap);
         if (tid == 0)
-            __hip_atomic_store(a.seen, (int32_t)(red[0] < 0x7fffffffull ? red[0] : 0x7fffffffull),
+            __hip_atomic_store(a.seen, (int32_t)(tiles < 0x7fffffffull ? tiles : 0x7fffffffull),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __syncthreads();
     }
 
     // sum over layers of max_s c(l,s), saturating at 2^62: a wave per layer, a lane per strategy
     // (one thread walking a layer's strategies is a chain of loads, and with few layers most of
     // the workgroup would idle)
-    const int wave = tid >> 6, lane = tid & 63;
     unsigned long long part = 0;
     for (int64_t l = wave; l < L; l += kPrepThreads / kWave) {
         unsigned long long mx = 0;
@@ -367,25 +380,15 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
             if (part > cap) part = cap;
         }
     }
-    red[tid] = part;
-    __syncthreads();
-    for (int w = kPrepThreads / 2; w > 0; w >>= 1) {
-        if (tid < w) {
-            const unsigned long long t = red[tid] + red[tid + w];
-            red[tid] = t > cap ? cap : t;
-        }
-        __syncthreads();
-    }
-    if (tid == 0) bound_s = red[0];
-    __syncthreads();
+    const unsigned long long bound_c = reduce(part, sum_to_cap);
 
     // plus, for every layer transition, the max of the matrix it uses
-    unsigned long long rsum = 0, rmax_all = 0;  // valid in thread 0 only
+    unsigned long long rsum = 0, rmax_all = 0;
     for (int64_t k0 = 0; k0 < nR; k0 += 64) {
         const int64_t kn = (nR - k0 < 64) ? nR - k0 : 64;
         for (int64_t k = 0; k < kn; ++k) {
             unsigned long long mx = 0;
-            const int64_t *Rm = R + (k0 + k) * S * S;
+            const ConstPtr<int64_t> Rm = R + (k0 + k) * S * S;
             bool off = false;
 #pragma unroll 4
             for (int64_t i = tid; i < S * S; i += kPrepThreads) {
@@ -394,18 +397,11 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
                 if ((unsigned long long)v > mx) mx = (unsigned long long)v;
             }
             if (off) bad = 1;
-            red[tid] = mx;
-            __syncthreads();
-            for (int w = kPrepThreads / 2; w > 0; w >>= 1) {
-                if (tid < w && red[tid + w] > red[tid]) red[tid] = red[tid + w];
-                __syncthreads();
-            }
-            if (tid == 0) {
-                rmax[k] = red[0];
-                if (red[0] > rmax_all) rmax_all = red[0];
-            }
-            __syncthreads();
+            mx = reduce(mx, largest);
+            if (tid == 0) rmax[k] = mx;
+            rmax_all = largest(rmax_all, mx);
         }
+        __syncthreads();
         // (every thread adds up the layers it owns, saturating; one thread walking all layers is
         // a chain of dependent loads that takes longer than the rest of this kernel)
         unsigned long long part_r = 0;
@@ -416,25 +412,12 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
                 if (part_r > cap) part_r = cap;
             }
         }
-        red[tid] = part_r;
-        __syncthreads();
-        for (int w = kPrepThreads / 2; w > 0; w >>= 1) {
-            if (tid < w) {
-                const unsigned long long t = red[tid] + red[tid + w];      // each <= 2^62: no wrap
-                red[tid] = t > cap ? cap : t;
-            }
-            __syncthreads();
-        }
-        if (tid == 0) {
-            rsum += red[0];
-            if (rsum > cap) rsum = cap;
-        }
-        __syncthreads();
+        rsum = sum_to_cap(rsum, reduce(part_r, sum_to_cap));
     }
 
     __shared__ int status_s;
     if (tid == 0) {
-        const unsigned long long bound = bound_s + rsum;   // each <= 2^62: no wrap
+        const unsigned long long bound = bound_c + rsum;   // each <= 2^62: no wrap
         int st;
         if (bad || bound >= cap) {
             st = GALV_INSTANCE_BAD_VALUE;
@@ -488,7 +471,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
     const bool keys32 = st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE;
     for (int64_t k = 0; k < nR; ++k) {
         for (int sp = wave; sp < (int)S; sp += kWaves) {
-            const int64_t *src = R + (k * S + sp) * S;
+            const ConstPtr<int64_t> src = R + (k * S + sp) * S;
             if (keys32) {
                 // 32-bit keys in the first half of each matrix's slot: rows of S_pad words, one
                 // matrix every S * S_pad doubles; padded columns hold the largest word.
