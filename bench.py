@@ -20,10 +20,10 @@ searches/s and the exact candidate rate are reported beside it.
 of the time).  Two sides are computed per layer step, and the one that needs
 more time at its peak is the binding one (`roofline.bound`):
   * HBM: the table bytes of a state within the budgets, against 8 TB/s.  With the
-    single packed table (the library's choice when a layer fills the chip, as on
-    configurations 2-4) that is 8 bytes: one 32-bit word read and one written,
-    the word holding the back-pointer and the cost relative to its column's
-    former minimum, plus one minimum per budget column.  With rolling cost rows
+    byte table (the library's choice when a layer has many states, as on
+    configurations 1-4) that is one byte for the back-pointer, and per budget column
+    one former minimum and the relative costs of the few strategies that are alive,
+    1.5 to 2 bytes in all.  With rolling cost rows
     (small shapes, --no-pack, one-byte back-pointers) it is 12: cost cell read,
     cost cell written, int32 back-pointer written (20 with 64-bit cells);
   * ALU: the min-plus candidates the sweep evaluates (the library counts them:
@@ -71,7 +71,7 @@ BYTES_PER_STATE = {3: 4 + 4 + 4, 0: 4 + 4 + 4, 4: 8 + 8 + 4, 2: 8 + 8 + 4, 1: 8 
 # HBM bytes per sweep launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, each scaled by the
 # same counter's reading for a 1 GiB copy: the `traffic_bytes_per_launch` line of
 # profiles/sweep_kernel_config<N>.md (tests/test_profiles.py keeps the two equal); None where not measured.
-MEASURED_TRAFFIC_BYTES = {3: 322060786, 4: 659360817}
+MEASURED_TRAFFIC_BYTES = {3: 85643264, 4: 179496960}
 
 
 def cpu_baseline(w):
@@ -353,11 +353,15 @@ def run_config(cfg, args, torch, binding, workloads):
     evaluated = sum(f * (int(e) + 1) * w.S * w.S for e, f in zip(w.budget, share))     # per layer
     ops = OPS_PER_CANDIDATE.get(int(status[0]), 0.0)
     sweep_ms, achieved = alu(solve_ms)
-    # single packed table (the library's default with int32 back-pointers and S <= 256): 32-bit-key instances
-    # read and write one 4-byte word per state, plus one former minimum per budget column
+    # byte table (the library's default for layers of many states, S <= 256): one byte written per state, the
+    # samples of every 64th column, one former minimum per budget column and the relative costs of the rows
+    # that are alive, each written and read once (counted for all columns, though some need no sweep)
     packed = bool(main_leg["packed"])
-    per_state = [(4 + 4 + 2 * (4 if int(st) == 3 else 8) / w.S) if packed and int(st) in (3, 4)
-                 else BYTES_PER_STATE.get(int(st), 0) - (3 if args.bp_u8 else 0) for st in status]
+    def byte_table(st, alive):
+        cell = 4 if st == 3 else 8
+        return 1 + 2 * cell / 64 + 2 * cell / w.S + 8 * alive
+    per_state = [byte_table(int(st), f) if packed and int(st) in (0, 2, 3, 4)
+                 else BYTES_PER_STATE.get(int(st), 0) - (3 if args.bp_u8 else 0) for st, f in zip(status, share)]
     hbm_bytes = sum(p * (int(e) + 1) * w.S for p, e in zip(per_state, w.budget))   # per layer
     hbm_gbs = hbm_bytes / (sweep_ms * 1e-3) / 1e9
     # The same kernel with every layer as ONE launch on one stream: the per-launch figure that
