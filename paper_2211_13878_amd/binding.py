@@ -125,15 +125,15 @@ def _dev_ptr(t, dtype, shape=None, allow_none=False):
         raise GalvError(GALV_ERR_INVALID_ARG, "a required tensor is None")
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous() and t.dtype == dtype):
         raise GalvError(GALV_ERR_INVALID_ARG, f"expected a contiguous device tensor of {dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise GalvError(GALV_ERR_INVALID_ARG, f"expected shape {tuple(shape)}, got {tuple(t.shape)}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream_ptr(stream):
     if stream is None:
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def make_desc(B, L, S, E_max, nR=1, flags=0) -> Desc:
@@ -280,13 +280,14 @@ class Solver:
     def solve(self, c, m, R, r_idx, budget, stream=None):
         """Enqueue the sweep; returns (best_cost[B], best_last[B]) device tensors."""
         B, L, S, nR = self.B, self.L, self.S, self.nR
-        _dev_ptr(c, torch.int64, (B, L, S)); _dev_ptr(m, torch.int32, (B, L, S))
-        _dev_ptr(R, torch.int64, (B, nR, S, S)); _dev_ptr(budget, torch.int32, (B,))
-        if r_idx is not None:
-            _dev_ptr(r_idx, torch.int32, (B, L))
+        ptrs = (_dev_ptr(c, torch.int64, (B, L, S)), _dev_ptr(m, torch.int32, (B, L, S)),
+                _dev_ptr(R, torch.int64, (B, nR, S, S)), _dev_ptr(r_idx, torch.int32, (B, L), allow_none=True),
+                _dev_ptr(budget, torch.int32, (B,)))
         self._inputs = (c, m, R, r_idx, budget)      # keep alive for backtrack / export
-        galv_dp_solve_batched(self.handle, c, m, R, r_idx, budget, self.best_cost,
-                              self.best_last, stream)
+        # (each tensor looked at once: on a small search the calls' host time is the whole time)
+        _check(load_library().galv_dp_solve_batched(
+            self.handle, *ptrs, _dev_ptr(self.best_cost, torch.int64), _dev_ptr(self.best_last, torch.int32),
+            _stream_ptr(stream)))
         return self.best_cost, self.best_last
 
     def backtrack(self, stream=None):
