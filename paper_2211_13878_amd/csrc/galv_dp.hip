@@ -2923,17 +2923,19 @@ galv_status_t make_plan(const galv_dp_desc_t *d, bool may_split, Plan *p) {
     // 44 3.60 / 2.54.)
     const int64_t share = d->max_budget / d->n_layers;
     const bool rows_asked = u8 || (d->flags & GALV_DP_NO_PACK);
-    const bool pays = !rows_asked && tiles * S >= 10000 && (share >= 128 || (fills_chip && S > 16 && share >= 64));
+    const bool pays = !rows_asked && tiles * S >= 10000 && (S > 8 || fills_chip) && (share >= 128 || (fills_chip && S > 16 && share >= 64));
     // Tiles of 256 columns where the launch fills the chip with them (normal / wide, in us: 44 x 1008 tiles 137 /
     // 146, x 2016 172 / 172 and with 64-bit keys 282 / 244; 64 x 2016 227 / 204; 120 x 504 242 / 241, x 1008 319 /
     // 270; in the byte table not where a layer's share is small and many rows are kept: 22 x 4032 tiles at 83 columns
-    // 2.02 / 3.08 ms); more waves per tile where even those would leave wavefront slots idle (normal / split: 22 x 1008 114 /
+    // 2.02 / 3.08 ms; nor for up to 32 strategies, where the list of kept rows holds 12 or 16 of them: with a third of the
+    // rows kept 22 x 4240 221 / 510, 32 x 4240 279 / 601, with a seventh 22 x 6176 263 / 256, 29 x 10048 669 / 669); more
+    // waves per tile where even those would leave wavefront slots idle (normal / split: 22 x 1008 114 /
     // 108, x 2016 142 / 142, x 2640 141 / 153; 29 x 2016 158 / 148; 44 x 504 127 / 128, x 1008 137 / 149; 64 x 504
     // 136 / 131; 120 x 252 171 / 160); up to 16 strategies the normal shape has one wave per tile and loses until the
     // chip is full (14 x 2640 158 / 143, x 3200 over cost rows 902 / 1026).  Very few tiles of 17 to 32 strategies take eight waves each (split / fine, cost rows:
     // 22 x 94 88 / 82, 29 x 252 106 / 96, 22 x 1008 142 / 152).
     Tiles shape = Tiles::normal;
-    if (fills_chip ? rows_asked || share >= 128 : pays && tiles * S >= 80000 && share >= 256)
+    if (rows_asked ? fills_chip : pays && S > 32 && (fills_chip ? share >= 128 : tiles * S >= 80000 && share >= 256))
         shape = Tiles::wide;
     else if (S > 16 && S <= 32 && tiles <= 256)
         shape = Tiles::fine;
