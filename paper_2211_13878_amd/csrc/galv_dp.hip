@@ -2245,7 +2245,9 @@ __device__ __forceinline__ int64_t last_layer_cost(const Layout &a, int b, int s
         const uint64_t at = (uint64_t)sp * (uint32_t)a.S_pad + (uint32_t)s;
         const uint64_t r = keys32 ? Key32::cost(rkeys<uint32_t>(a, b, h[4])[at], a.k_bits)
                                   : Key64::cost(rkeys<double>(a, b, h[4])[at], a.k_bits);
-        return cmin + (int64_t)t.rel[(int64_t)sp * a.e_pad + x] + (int64_t)r + a.c[((int64_t)b * a.L + (a.L - 1)) * a.S + s];
+        // (c(l, s) from the solve's own copy: the caller's costs may be gone by the time an optimum is asked for)
+        const uint64_t cs = a.ck[((int64_t)b * a.L + (a.L - 1)) * a.S_pad + s];
+        return cmin + (int64_t)t.rel[(int64_t)sp * a.e_pad + x] + (int64_t)r + (int64_t)cs;
     }
     const char *U = a.U[(a.L - 1) & 1] + ((int64_t)b * a.S_pad + s) * a.row * 8;
     const int64_t x = a.lead + e - shift;
@@ -2493,7 +2495,7 @@ __device__ __forceinline__ void best_at_bytes(const Layout &a, int b, int e, int
     const Cell *cmin = reinterpret_cast<const Cell *>(t.cmin);
     const typename Key::T *R = rkeys<typename Key::T>(a, b, h[4]);
     const int32_t *m = a.m + ((int64_t)b * a.L + (a.L - 1)) * a.S;
-    const int64_t *c = a.c + ((int64_t)b * a.L + (a.L - 1)) * a.S;
+    const uint64_t *c = a.ck + ((int64_t)b * a.L + (a.L - 1)) * a.S_pad;    // (not the caller's: see last_layer_cost)
     const int mask = (1 << a.k_bits) - 1;
 #pragma unroll 4
     for (int s = 0; s < a.S; ++s) {
@@ -2503,7 +2505,7 @@ __device__ __forceinline__ void best_at_bytes(const Layout &a, int b, int e, int
         const uint32_t sp = bp[(int64_t)s * a.e_pad + x] & (uint32_t)mask;
         const uint32_t in = sp < (uint32_t)a.S ? sp : 0;        // (bytes of unreachable columns may be anything)
         const int64_t v = (int64_t)cmin[x] + (int64_t)t.rel[(int64_t)in * a.e_pad + x] +
-                          (int64_t)Key::cost(R[(int64_t)in * a.S_pad + s], a.k_bits) + c[s];
+                          (int64_t)Key::cost(R[(int64_t)in * a.S_pad + s], a.k_bits) + (int64_t)c[s];
         if (ok && v < opt) {
             opt = v;
             last = s;
