@@ -1743,6 +1743,7 @@ constexpr int byte_keep_rows(int ts, int ng, int wpe, int cols) {
     return rows < ng ? ng : rows;
 }
 constexpr unsigned byte_lds(int ts, int ng, int wpe, int cols) {
+    // (the two halves of an overfull tile take no more: half the columns, and twice the rows of half the size)
     const int keep = byte_keep_rows(ts, ng, wpe, cols);
     const unsigned tile = (unsigned)(ng * cols * 4 + keep * cols * 4 + ts * ng * 16 + keep * 4 + 16);
     const unsigned live = (unsigned)((3 + 2 * ng) * ts * ng * 4 + 4);   // live_step
@@ -1787,8 +1788,10 @@ struct Former {
     }
 };
 
-template <int TS, int TE, int NG, class Cell, class Key, int KEEP, int TILE>
-__device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b, int tile_start, bool add_stats,
+// Returns true when the tile has been swept.  With MAY_REFUSE a tile that keeps more rows than the list
+// holds is left untouched instead (all waves agree; nothing but LDS has been written).
+template <int TS, int TE, int NG, class Cell, class Key, int KEEP, int TILE, bool MAY_REFUSE = false>
+__device__ __forceinline__ bool sweep_bytes(const Layout &a, int g, int l, int b, int tile_start, bool add_stats,
                                             const TileHdr &h, const uint64_t (&ent)[(TS * NG + kWave - 1) / kWave],
                                             const uint64_t (&c0_64)[(TS * NG + kWave - 1) / kWave]) {
     constexpr Cell kInfCell = sizeof(Cell) == 8 ? (Cell)kInf : (Cell)kInf32;
@@ -1857,6 +1860,7 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
         }
         nk += __builtin_popcountll(votes);
     }
+    if (MAY_REFUSE && nk > KEEP) return false;
 
     // The shifted cells of kept row i for this lane's columns.
     struct Fetch {
@@ -2109,7 +2113,7 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
         for (int j = 0; j < TE; ++j) out[j] = cmin[j];
         *reinterpret_cast<cellv *>(reinterpret_cast<Cell *>(now.cmin) + e0) = out;
     }
-    if (idle) return;
+    if (idle) return true;
     const int S = a2.S;
     uint8_t *bp = byte_rows(a2, b, l) + (int64_t)s0 * e_pad + tile_start;
 
@@ -2151,6 +2155,7 @@ __device__ __forceinline__ void sweep_bytes(const Layout &a, int g, int l, int b
         store(std::true_type{});
     else
         store(std::false_type{});
+    return true;
 }
 
 // The sweep of handles that keep the byte table (Layout::packed).  Grid: (8 + tiles, 1, instances);
@@ -2204,7 +2209,20 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_bytes_kernel(Layout a, i
     if (slot >= per || t >= nt) return;
     const int tile_start = (lo + t) * kTile;
     if (st == GALV_INSTANCE_OK_FAST_U32) {
-        sweep_bytes<TS, TE * UX, NG, uint32_t, Key32, kKeep, kTile>(layout_again(), wave, l, b, tile_start, false, h, ent, c0);
+        // A tile of 256 columns that keeps more rows than its list holds (24 of 44, 32 of 64) would rebuild the rest
+        // twice, in further passes: it is swept as two halves, for which the same LDS holds twice the rows.  Passes /
+        // halves, in us, where a third to a half of the rows is kept: 44 strategies x 4805 tiles x 32 layers 1056 / 897,
+        // 35 x 4805 x 96 3135 / 2880, 64 x 3768 x 20 610 / 572; a list that overflows by little pays more for the
+        // second half than for the pass (56 x 2893 x 15 949 / 979).
+        const bool done = sweep_bytes<TS, TE * UX, NG, uint32_t, Key32, kKeep, kTile, (UX > 1)>(
+            layout_again(), wave, l, b, tile_start, false, h, ent, c0);
+        if constexpr (UX > 1)
+            for (int p = 0; p < UX && !done; ++p) {
+                const int part = tile_start + p * (kTile / UX);
+                if (part > x) break;                             // workgroup-uniform
+                __syncthreads();                                 // the LDS of the part before is free again
+                sweep_bytes<TS, TE, NG, uint32_t, Key32, UX * kKeep, kTile>(layout_again(), wave, l, b, part, p > 0, h, ent, c0);
+            }
     } else if (packed) {
         // 8-byte cells: a part of the tile at a time keeps registers and LDS within what the narrow form uses
         for (int p = 0; p < TE; ++p) {

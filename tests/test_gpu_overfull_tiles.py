@@ -1,0 +1,48 @@
+"""Tiles of 256 columns that keep more rows than their list holds are swept as two halves.  Transition
+costs around the spread of the layer costs put tiles of both kinds in one launch; budgets end before, at
+and behind the middle of a tile.  Whole tables are compared with the oracle's."""
+import numpy as np
+import pytest
+
+from paper_2211_13878_amd import binding, workloads
+from test_gpu_parity import check_against_oracle, oracle_refs
+
+pytestmark = pytest.mark.gpu
+PACK, PEEK, NO_PEEK, WIDE = (binding.GALV_DP_FORCE_PACK, binding.GALV_DP_FORCE_PEEK, binding.GALV_DP_NO_PEEK,
+                             binding.GALV_DP_FORCE_WIDE_TILES)
+
+
+def check_statistics(w, flags):
+    sol = binding.Solver(w.B, w.L, w.S, w.E_max, w.nR, flags)
+    sol.solve(*binding.upload(w))
+    reduced, listed, fetched = sol.stats().cpu().numpy().T
+    columns = sol.config()["tile_columns"]
+    sol.close()
+    usable = sum((w.m[:, l] <= w.budget[:, None]).sum(axis=1) for l in range(w.L - 1))
+    tiles = w.budget // columns + 1
+    assert (0 < reduced).all() and (reduced <= fetched).all() and (fetched <= listed).all()
+    assert (listed <= 2 * tiles * usable).all()              # (a tile in two halves lists its rows twice)
+    return columns, reduced, listed
+
+
+@pytest.mark.parametrize("S", [17, 24, 25, 33, 44, 64, 65, 100, 128, 129, 256])
+@pytest.mark.parametrize("r_hi", [300, 3000])
+def test_some_tiles_in_halves(S, r_hi):
+    w = workloads.random_workload(11 * S + r_hi, 5, 5, S, 1100, nR=2, m_range=(0, 160), c_range=(0, 2000),
+                                  r_range=(0, r_hi), infeasible=0.05, zero_diagonal=False)
+    w.budget[:] = (1100, 1023, 1024, 895, 896)               # tiles end at 1023; their halves at 895 and 1023
+    refs = oracle_refs(w, range(5), range(5), (), 8)
+    for flags in (PACK | PEEK | WIDE, PACK | NO_PEEK | WIDE, PACK | PEEK | WIDE | binding.GALV_DP_STREAMS(2)):
+        check_against_oracle(w, flags=flags, table_instances=range(5), refs=refs,
+                             expect_status=binding.GALV_INSTANCE_OK_FAST_U32)
+        assert check_statistics(w, flags)[0] == 256
+
+
+@pytest.mark.parametrize("S", [33, 64])
+def test_halves_without_flags(S):
+    w = workloads.random_workload(S, 64, 3, S, 6200, nR=1, m_range=(0, 2500), c_range=(0, 2000), r_range=(0, 900),
+                                  infeasible=0.05, zero_diagonal=False)
+    w.budget[:] = np.linspace(5900, 6200, 64).astype(np.int32)
+    check_against_oracle(w, table_instances=[0, 31, 63], threads=8, expect_status=binding.GALV_INSTANCE_OK_FAST_U32)
+    columns, reduced, listed = check_statistics(w, 0)
+    assert columns == 256 and (reduced > 0.2 * listed).all()
