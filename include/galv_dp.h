@@ -106,8 +106,10 @@ typedef struct {
                                   first reachable one and the one from which a layer is constant.
                                   1 to 2 bytes per state instead of 8.  By default this is done when a
                                   layer has many states and its share of the budget spans a tile, and
-                                  the sweep then peeks (GALV_DP_FORCE_PEEK) too.  Results, exported tables included, are
-                                  identical either way.                                              */
+                                  the sweep then peeks (GALV_DP_FORCE_PEEK) too; an instance on 64-bit
+                                  keys whose transition costs let nearly no strategy be left out keeps
+                                  cost rows all the same, unless this flag is given.  Results, exported
+                                  tables included, are identical either way.                          */
 #define GALV_DP_FORCE_WIDE_TILES 128u   /* sweep workgroups take tiles of 256 budget columns instead of 128
                                            (17 to 256 strategies: the kernel variants that have such a twin).
                                            By default this is done when a layer has enough workgroups to

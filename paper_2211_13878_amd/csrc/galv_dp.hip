@@ -131,6 +131,7 @@ struct Layout {
     void *bp;             // argmin, un-shifted  [B][L-1][S][e_pad] of int32, or of uint8 (0xFF = none)
     int32_t bp_u8;        // 1: one-byte back-pointers
     int32_t peek;         // 1: the row-sharing sweep looks at two cells of a row before it fetches the row
+    int32_t rows_if_alive; // 1: of those on 64-bit keys, the ones where most rows stay alive do not (see prep_kernel)
     int32_t packed;       // 1: instances of byte_status() keep the byte table: argmins in one byte, and
                           //    instead of cost rows what it takes to rebuild a cell (see PackTables)
     int32_t synth_l1;     // 1: the 32-bit-key sweep makes up layer 0's cells (a constant per strategy)
@@ -142,7 +143,7 @@ struct Layout {
                           // up to the row's end  [B][L][S_pad]
     uint64_t *vcost;      // c(l, s') of the listed strategies, in the list's order (padded the same way)  [B][L][S_pad]
     int32_t *nvalid;      // how many of them    [B][L]
-    uint32_t *dclamp;     // largest R + 1, the clamp of relative costs; 0 when it does not fit  [B]
+    uint32_t *dclamp;     // largest R + 1, the clamp of relative costs; 0 when it does not fit (or see byte_status)  [B]
     int32_t *hdr;         // what a sweep workgroup needs first, in one place: status, budget, usable strategies of
                           // the former layer, clamp, transition matrix of the layer, first reachable column,
                           // last column worth sweeping (byte table), smallest usable memory  [B][L][8]
@@ -198,7 +199,7 @@ __device__ __forceinline__ int lead_kind(int st) {
 
 // Whether an instance of status st keeps the byte table (a handle-wide choice of kernels; one
 // layer has no table at all).  That takes packed keys, and relative costs of 32 bits: clamp is
-// R_max + 1, or 0 when that does not fit.
+// R_max + 1, or 0 when that does not fit or does not pay.
 __device__ __forceinline__ bool byte_status(int st, uint32_t clamp) {
     return st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE ||
            ((st == GALV_INSTANCE_OK_FAST || st == GALV_INSTANCE_OK_FAST_WIDE) && clamp != 0);
@@ -445,6 +446,37 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
     }
     __syncthreads();
     const int st = status_s;
+    // The byte table saves what the pruning lets it save.  Where transition costs dwarf the spread of the layer
+    // costs, hardly a row is left out, and an instance on 64-bit keys rebuilds every cell that it could have read:
+    // it keeps cost rows instead (clamp 0 says so, see byte_status), as long as these stay in the caches.  Rows of
+    // a layer differ in cost by about what their strategies do there, so a strategy counts as alive that costs less
+    // than the layer's cheapest plus the largest transition cost.  Whole solves of 10 layers over cost rows / with the
+    // byte table, in us, share of alive strategies 1.0: 22 strategies x 1512 tiles 201 / 258, 44 x 1512 379 / 493, 14 x
+    // 3760 250 / 374; 0.55: 34 x 582 97 / 101; 0.35: 22 x 1512 202 / 180, 44 x 1512 379 / 254.
+    if (a.packed && a.rows_if_alive && (st == GALV_INSTANCE_OK_FAST || st == GALV_INSTANCE_OK_FAST_WIDE)) {
+        unsigned long long seen = 0;               // usable << 32 | alive
+        for (int64_t l = wave; l + 1 < L; l += kPrepThreads / kWave) {
+            unsigned long long v[4], least = ~0ull;           // (the byte table has at most 256 strategies)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t s = q * kWave + lane, at = l * S + (s < S ? s : 0);
+                const unsigned long long cost = (unsigned long long)c[at];
+                v[q] = s < S && m[at] <= budget ? cost : ~0ull;
+                least = v[q] < least ? v[q] : least;
+            }
+#pragma unroll
+            for (int w = kWave / 2; w > 0; w >>= 1) {
+                const unsigned long long o = (unsigned long long)__shfl_xor((long long)least, w, kWave);
+                least = o < least ? o : least;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (v[q] != ~0ull) seen += (1ull << 32) + (v[q] - least <= rmax_all ? 1 : 0);
+        }
+        seen = reduce(seen, [](unsigned long long x, unsigned long long y) { return x + y; });
+        if (tid == 0 && 4 * (seen & 0xffffffffull) > 3 * (seen >> 32)) a.dclamp[b] = 0;
+        __syncthreads();
+    }
     // One record per layer with what a sweep workgroup needs before anything else, so that it
     // takes one load instead of a chain of them.  (The count of the former layer's usable
     // strategies is filled in below, by the thread that builds that layer's list.)
@@ -3005,6 +3037,9 @@ galv_status_t make_plan(const galv_dp_desc_t *d, bool may_split, Plan *p) {
     if (packed) p->lds_bytes = lds_packed;
     p->sweep = packed ? ve.fn_pack : (u8 ? ve.fn_u8 : ve.fn);
     a.packed = packed ? 1 : 0;
+    // (up to 30 strategies x 3000 tiles: two tables of 8-byte cells take 184 MB, and the caches hold 256.  With all
+    // rows alive, cost rows / byte table: 30 x 3760 tiles 904 / 658 us, 34 x 3760 957 / 675, 64 x 1512 919 / 833)
+    a.rows_if_alive = !(d->flags & GALV_DP_FORCE_PACK) && tiles * S < 90000 ? 1 : 0;
     a.seen = nullptr;
     a.lead = (int64_t)round_up((size_t)a.E_max + 1, 64);
     a.row = a.lead + a.e_pad;
