@@ -16,7 +16,7 @@ INF = binding.GALV_INF
 assert INF == oracle.INF
 # the three arithmetic paths a small-valued instance can be sent down: 32-bit integer keys
 # (default), 64-bit keys in 32-bit cells, general 64-bit integers
-# single packed table (forced: small shapes would not choose it), cost rows with 32-bit keys, 64-bit keys, int64
+# byte table (forced: small shapes would not choose it), cost rows with 32-bit keys, 64-bit keys, int64
 ALL_PATHS = (binding.GALV_DP_FORCE_PACK, binding.GALV_DP_NO_PACK, binding.GALV_DP_NO_U32, binding.GALV_DP_FORCE_INT64)
 THREADS = max(1, min(16, os.cpu_count() or 1))      # oracle instances solved side by side
 
@@ -388,13 +388,17 @@ def test_large_costs_with_small_transition_costs_keep_32bit_keys(S):
 
 
 def test_wide_integer_keys_when_nothing_can_be_pruned_and_at_the_cost_limit():
-    """Same path with transition costs above the cost spread (the kept-row list overflows: full
-    loop over 8-byte cells) and with costs close to the 2^62 precondition."""
+    """Same path with transition costs above the cost spread (in the plain and the wide shape more rows stay
+    alive than the list holds: passes over 8-byte cells) and with costs close to the 2^62 precondition."""
+    from test_gpu_pruning import NO_PACK, NORMAL, PACK, WIDE, list_capacity, usable_rows
     w = workloads.random_workload(77, 3, 5, 44, 500, nR=2, m_range=(0, 120), c_range=(1 << 36, (1 << 36) + 9),
                                   r_range=(1000, 5000), infeasible=0.05, zero_diagonal=False)
     w.budget[0] = 500
     for flags in (binding.GALV_DP_FORCE_PEEK | binding.GALV_DP_FORCE_PACK, binding.GALV_DP_FORCE_PEEK | binding.GALV_DP_NO_PACK,
-                  binding.GALV_DP_FORCE_PACK):
+                  binding.GALV_DP_FORCE_PACK, PACK | NORMAL, NO_PACK | NORMAL, PACK | WIDE, NO_PACK | WIDE,
+                  PACK | NORMAL | binding.GALV_DP_FORCE_PEEK, NO_PACK | WIDE | binding.GALV_DP_FORCE_PEEK):
+        if flags & (NORMAL | WIDE):
+            assert usable_rows(w) > list_capacity(44, flags)
         _, _, _, status = check_against_oracle(w, flags=flags, table_instances=[0, 1, 2])
         assert (status == binding.GALV_INSTANCE_OK_U32_WIDE).all()
     w = workloads.random_workload(78, 2, 4, 9, 300, m_range=(0, 90), c_range=(0, (1 << 59) - 1), r_range=(0, 99))
@@ -423,7 +427,7 @@ def test_path_limits_by_transition_cost():
 def test_largest_possible_key_is_a_candidate_but_never_a_stored_word(L, expect):
     """S = 16 (four index bits) and the largest R the 32-bit keys allow, 2^27 - 1: a former
     strategy 15 that is clamped (relative cost R_max + 1) and pays R_max yields the key 2^32 - 1,
-    the very pattern the packed table uses for "unreachable".  It can never win (the strategy
+    the very pattern that the running minima start from.  It can never win (the strategy
     that attains the column's minimum offers a smaller key), so tables and plans must come out
     the same in both table forms."""
     rmax = (1 << 27) - 1
