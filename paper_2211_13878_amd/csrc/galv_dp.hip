@@ -2960,38 +2960,52 @@ galv_status_t make_plan(const galv_dp_desc_t *d, bool may_split, Plan *p) {
     const int S = d->n_strategies;
     // Enough workgroups per layer to fill the chip several times over?
     const bool fills_chip = tiles >= 3072;
+    const int64_t share = d->max_budget / d->n_layers;
+    const bool rows_asked = u8 || (d->flags & GALV_DP_NO_PACK);
     // Byte table or cost rows.  The byte table sweeps half the columns and writes a quarter of the bytes or less,
     // but rebuilds every cell it reads in two dependent steps, so a tile takes longer: it pays where a layer has
-    // many states.  Whole solves of 12 layers over cost rows / with the byte table, in us:
+    // many states, and where its share of the budget spans a tile (rows otherwise fall steeply within one and the
+    // peek leaves too many).  Whole solves of 12 layers over cost rows / with the byte table, in us:
     //   14 strategies:  504 tiles  96 / 100   1008 tiles 114 / 105      44:   94 tiles  98 / 100    252 tiles 115 / 108
     //   22:             252 tiles  87 /  93    504 tiles 108 / 103      64:   94 tiles 111 / 106
     //   29:             252 tiles  96 / 104    504 tiles 119 / 111     120:   94 tiles 158 / 140
-    // (costs in nanoseconds, that is 64-bit keys: 44 x 504 260 / 196, 120 x 504 917 / 357).  Not where a tile
-    // is wider than a layer's share of the budget: rows then fall steeply within a tile and the peek leaves too
-    // many (12 layers, cost rows / byte table: 22 x 512 tiles of 1000 columns 120 / 131, of 2040 columns 116 / 115; 120
-    // x 512 of 1000 258 / 362, of 2040 261 / 238).
-    // (Where the chip is full, down to half a tile, beyond 16 strategies: 3200 to 4000 tiles, cost rows / byte table,
-    // share 49: 22 2.41 / 2.84 ms, 44 3.70 / 4.03; share 83 to 98: 14 0.90 / 1.11, 22 1.19 / 1.10 and 1.94 / 2.02,
-    // 44 3.60 / 2.54.)
-    const int64_t share = d->max_budget / d->n_layers;
-    const bool rows_asked = u8 || (d->flags & GALV_DP_NO_PACK);
+    //   140, 200, 256:  126 tiles 179 / 169, 247 / 241, 246 / 228 on deep stacks of layers, 255 / 272, 357 / 374, 417 / 433
+    //                   on independent layers; 752 tiles 474 / 416, 610 / 564, 748 / 564 and 655 / 444, 892 / 663, 1102 / 798
+    // (costs in nanoseconds, that is 64-bit keys: 44 x 504 260 / 196, 120 x 504 917 / 357).  Between the two, the kind
+    // of input decides: time with the byte table over that with cost rows, each in its better shape, on independent
+    // layers / layers alike / deep stacks, at a share of 140: 32 x 352 1.38 1.20 0.96, x 1080 1.08 1.01 0.83, 100 x 352
+    // 0.99 0.99 0.85; of 700: 32 x 657 1.00 0.90 0.80.
+    // Below a share of 128, 22 x 512 tiles of 1000 columns 120 / 131, of 2040 columns 116 / 115; 120 x 512 of 1000 258 /
+    // 362, of 2040 261 / 238.  Where the chip is full, down to half a tile, beyond 16 strategies: 3200 to 4000 tiles, in
+    // ms, share 49: 22 2.41 / 2.84, 44 3.70 / 4.03; share 83 to 98: 14 0.90 / 1.11, 22 1.19 / 1.10 and 1.94 / 2.02, 44
+    // 3.60 / 2.54.
     const bool pays = !rows_asked && tiles * S >= 10000 && (S > 8 || fills_chip) && (share >= 128 || (fills_chip && S > 16 && share >= 64));
-    // Tiles of 256 columns where the launch fills the chip with them (normal / wide, in us: 44 x 1008 tiles 137 /
-    // 146, x 2016 172 / 172 and with 64-bit keys 282 / 244; 64 x 2016 227 / 204; 120 x 504 242 / 241, x 1008 319 /
-    // 270; in the byte table not where a layer's share is small and many rows are kept: 22 x 4032 tiles at 83 columns
-    // 2.02 / 3.08 ms; nor for up to 32 strategies, where the list of kept rows holds 12 or 16 of them: with a third of the
-    // rows kept 22 x 4240 221 / 510, 32 x 4240 279 / 601, with a seventh 22 x 6176 263 / 256, 29 x 10048 669 / 669); more
-    // waves per tile where even those would leave wavefront slots idle (normal / split: 22 x 1008 114 /
-    // 108, x 2016 142 / 142, x 2640 141 / 153; 29 x 2016 158 / 148; 44 x 504 127 / 128, x 1008 137 / 149; 64 x 504
-    // 136 / 131; 120 x 252 171 / 160); up to 16 strategies the normal shape has one wave per tile and loses until the
-    // chip is full (14 x 2640 158 / 143, x 3200 over cost rows 902 / 1026).  Very few tiles of 17 to 32 strategies take eight waves each (split / fine, cost rows:
-    // 22 x 94 88 / 82, 29 x 252 106 / 96, 22 x 1008 142 / 152).
+    // Tiles of 256 columns where the launch fills the chip with them (normal / wide, in us: 44 x 16448 tiles 4190 /
+    // 3440, 128 x 8208 3136 / 2263; with 64-bit keys, which sweep a tile in two parts, from 80000 tile-strategies on: 44 x
+    // 2064 1205 / 1077, 64 x 2064 1556 / 1282).  Where many rows are kept they lose (44 x 4805 613 / 897), all the more where
+    // their list holds 12 or 16: not for up to 32 strategies over the byte table (a third of the rows kept: 22 x 4240 221
+    // / 510, 32 x 4240 279 / 601; a seventh: 22 x 6176 263 / 256, 29 x 10048 669 / 669), nor where a layer's share
+    // is small (22 x 4032 tiles at 83 columns 2.02 / 3.08 ms).  Cost rows: 140 strategies x 3528 tiles 1907 / 1551; at a
+    // share of 48 to 63, 3200 tiles, 22 strategies 1839 / 1972, 44 2876 / 3181, 100 8109 / 8761.
+    const bool wide = pays ? S > 32 && (fills_chip ? share >= 128 : tiles * S >= 80000 && share >= 256)
+                           : fills_chip && share >= 64;
+    // More waves per tile where the normal shape would leave wavefront slots idle.  Normal / split over cost rows,
+    // relative: 6 strategies x 1520 tiles 1.00 / 0.98, x 1752 1.00 / 1.02, x 1980 1.00 / 1.15
+    // (64-bit keys, which take every row in every wave: 8 x 1128 1.00 / 0.77, x 1407 1.00 / 1.17); 16 and 32 x 1752 1.00 / 0.88,
+    // x 2120 1.00 / 1.02; 44 and 64 x 760 1.00 / 0.96, x 1060 1.00 / 1.09; 100 x 352 1.00 / 0.96, x 540 1.00 / 1.15.  Over the
+    // byte table, in us, on independent layers / layers alike / deep stacks: 11 x 3080 166 145 153 / 124 139 156, x 3520 172
+    // 145 156 / 129 142 168, x 4400 174 160 167 / 137 168 186; 24 x 2640 0.79 0.77 0.82 / 0.62 0.66 0.80 of the time over cost
+    // rows, x 3960 0.84 0.77 0.82 / 0.66 0.75 0.81, x 5640 0.77 0.72 0.83 / 0.61 0.74 0.88; 44 x 1080 1.14 0.88 0.79 / 0.97 0.92
+    // 0.95; 100 x 760 1.04 0.83 0.90 / 0.87 0.86 0.89, x 882 287 - 289 / 256 - 285 (64-bit keys: x 564 310 / 336 on deep stacks).
+    // Very few tiles of 17 to 32 strategies take eight waves each (split / fine, cost rows: 22 x 94 88 / 82 us, 29 x 252
+    // 106 / 96, 22 x 1008 142 / 152).
+    const int64_t split_to = S <= 32 ? (pays && S > 8 ? 3584 : 1792) : S <= 64 || pays ? 896 : 448;
     Tiles shape = Tiles::normal;
-    if (rows_asked ? fills_chip : pays && S > 32 && (fills_chip ? share >= 128 : tiles * S >= 80000 && share >= 256))
+    if (wide)
         shape = Tiles::wide;
     else if (S > 16 && S <= 32 && tiles <= 256)
         shape = Tiles::fine;
-    else if ((S <= 16 && !fills_chip) || tiles * (S <= 32 ? 4 : S <= 64 ? 8 : 16) <= 7168)
+    else if (tiles <= split_to)
         shape = Tiles::split;
     if (d->flags & GALV_DP_FORCE_WIDE_TILES) shape = Tiles::wide;
     if (d->flags & GALV_DP_NO_WIDE_TILES) shape = Tiles::normal;

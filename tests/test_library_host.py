@@ -67,6 +67,32 @@ def test_create_rejects_null_small_and_misaligned_workspace(lib):
     assert rc == binding.GALV_ERR_INVALID_ARG
 
 
+def create(lib, desc, n_bytes):
+    """A handle over a workspace that nothing touches (no solve is enqueued), or the error code."""
+    h = ctypes.c_void_p(None)
+    rc = lib.galv_dp_create(ctypes.byref(desc), ctypes.c_void_p(4096), n_bytes, ctypes.byref(h))
+    if rc == binding.GALV_OK:
+        config = binding.galv_dp_get_config(h)
+        lib.galv_dp_destroy(h)
+        return rc, config
+    return rc, None
+
+
+@pytest.mark.parametrize("S", [22, 44, 100])
+@pytest.mark.parametrize("L,columns", [(130, 128), (40, 256)])
+def test_cost_rows_take_the_same_tiles_by_default_and_on_request(lib, S, L, columns):
+    """A launch that fills the chip: cost rows are the default where a layer's share of the budget is below half a
+    tile; above that they have to be asked for."""
+    rows = []
+    for flags in (0, binding.GALV_DP_NO_PACK, binding.GALV_DP_BP_U8):
+        desc = binding.make_desc(64, L, S, 6300, 1, flags | binding.GALV_DP_STREAMS(1))
+        rc, config = create(lib, desc, 1 << 62)
+        assert rc == binding.GALV_OK
+        if not config[0]:
+            rows.append(config[3])
+    assert rows == [columns] * (3 if columns == 128 else 2)
+
+
 def test_null_handle_calls(lib):
     assert lib.galv_dp_solve_batched(*([None] * 9)) == binding.GALV_ERR_INVALID_ARG
     assert lib.galv_dp_backtrack(None, None, None) == binding.GALV_ERR_INVALID_ARG
