@@ -2929,7 +2929,12 @@ struct Plan {
     unsigned lds_bytes;
 };
 
-galv_status_t make_plan(const galv_dp_desc_t *d, bool may_split, Plan *p) {
+// Tiles of 128 columns in one layer of the whole batch; from kFullChip on they fill the chip several times over.
+int64_t launch_tiles(const galv_dp_desc_t &d) { return ((int64_t)d.max_budget / 128 + 1) * d.n_instances; }
+constexpr int64_t kFullChip = 3072;
+
+// `only`: the shape to take instead of the one the rules below choose (the flags still override it).
+galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, Plan *p) {
     if (!d) return fail(GALV_ERR_INVALID_ARG, "desc is NULL");
     if (d->n_instances < 1 || d->n_layers < 1 || d->n_strategies < 1 || d->max_budget < 0 ||
         d->n_transition < 1)
@@ -2956,10 +2961,9 @@ galv_status_t make_plan(const galv_dp_desc_t *d, bool may_split, Plan *p) {
         return fail(GALV_ERR_RANGE, "max_budget %d exceeds 2^30", d->max_budget);
 
     memset(p, 0, sizeof *p);
-    const int64_t tiles = ((int64_t)d->max_budget / 128 + 1) * d->n_instances;    // of 128 columns, in one layer
+    const int64_t tiles = launch_tiles(*d);
     const int S = d->n_strategies;
-    // Enough workgroups per layer to fill the chip several times over?
-    const bool fills_chip = tiles >= 3072;
+    const bool fills_chip = tiles >= kFullChip;
     const int64_t share = d->max_budget / d->n_layers;
     const bool rows_asked = u8 || (d->flags & GALV_DP_NO_PACK);
     // Byte table or cost rows.  The byte table sweeps half the columns and writes a quarter of the bytes or less,
@@ -3007,9 +3011,9 @@ galv_status_t make_plan(const galv_dp_desc_t *d, bool may_split, Plan *p) {
         shape = Tiles::fine;
     else if (tiles <= split_to)
         shape = Tiles::split;
+    if (only) shape = *only;
     if (d->flags & GALV_DP_FORCE_WIDE_TILES) shape = Tiles::wide;
     if (d->flags & GALV_DP_NO_WIDE_TILES) shape = Tiles::normal;
-    if (!may_split && (shape == Tiles::split || shape == Tiles::fine)) shape = Tiles::normal;
     const VariantEntry &ve = pick_variant(S, shape);
     const Variant v = ve.v;
     Layout &a = p->lay;
@@ -3091,14 +3095,23 @@ galv_status_t make_plan(const galv_dp_desc_t *d, bool may_split, Plan *p) {
     return GALV_OK;
 }
 
-galv_status_t make_plan(const galv_dp_desc_t *d, Plan *p) {
-    const galv_status_t st = make_plan(d, true, p);
-    // (the twins with more waves pad the strategies to a little more: not at the price of the fixed workspace)
-    Plan q;
-    if (st == GALV_OK && p->total > (size_t)GALV_DP_STATIC_BYTES && make_plan(d, false, &q) == GALV_OK &&
-        q.total <= (size_t)GALV_DP_STATIC_BYTES)
-        *p = q;
-    return st;
+// The plan of a handle: the shape that the rules choose, or, where it does not fit `bytes` of workspace, the plain
+// one, and where the launch fills the chip the wide one, if that does.  (The twins with more waves pad the strategies
+// to a little more, and narrow tiles take more statistics: a workspace of the size that these shapes need, which
+// were once all there were, stays large enough.)
+galv_status_t make_plan(const galv_dp_desc_t *d, size_t bytes, Plan *p) {
+    const galv_status_t st = make_plan(d, nullptr, p);
+    if (st != GALV_OK || p->total <= bytes) return st;
+    const bool fills_chip = launch_tiles(*d) >= kFullChip;
+    for (Tiles only : {Tiles::normal, Tiles::wide}) {
+        if (only == Tiles::wide && !fills_chip) continue;
+        Plan q;
+        if (make_plan(d, &only, &q) == GALV_OK && q.total <= bytes) {
+            *p = q;
+            break;
+        }
+    }
+    return GALV_OK;
 }
 
 // grid.x of a sweep launch for n budget tiles.
@@ -3261,7 +3274,7 @@ extern "C" {
 galv_status_t galv_dp_workspace_bytes(const galv_dp_desc_t *desc, size_t *bytes) {
     if (!bytes) return fail(GALV_ERR_INVALID_ARG, "bytes is NULL");
     Plan p;
-    galv_status_t st = make_plan(desc, &p);
+    galv_status_t st = make_plan(desc, (size_t)GALV_DP_STATIC_BYTES, &p);
     if (st != GALV_OK) return st;
     *bytes = p.total;
     return GALV_OK;
@@ -3272,7 +3285,7 @@ galv_status_t galv_dp_create(const galv_dp_desc_t *desc, void *workspace_dev,
     if (!out) return fail(GALV_ERR_INVALID_ARG, "out is NULL");
     *out = nullptr;
     Plan p;
-    galv_status_t st = make_plan(desc, &p);
+    galv_status_t st = make_plan(desc, workspace_bytes, &p);
     if (st != GALV_OK) return st;
     if (!workspace_dev) return fail(GALV_ERR_WORKSPACE, "workspace is NULL");
     if (reinterpret_cast<uintptr_t>(workspace_dev) % 256 != 0)
@@ -3394,7 +3407,7 @@ galv_status_t galv_dp_solve_static(const galv_dp_desc_t *desc, const int64_t *c_
                                    int64_t *best_cost_dev, int32_t *best_last_dev, int32_t *plan_dev,
                                    void *stream) {
     Plan p;
-    galv_status_t rc = make_plan(desc, &p);
+    galv_status_t rc = make_plan(desc, (size_t)GALV_DP_STATIC_BYTES, &p);
     if (rc != GALV_OK) return rc;
     if (((desc->flags & GALV_DP_STREAMS_MASK) >> GALV_DP_STREAMS_SHIFT) > 1u)
         return fail(GALV_ERR_INVALID_ARG, "galv_dp_solve_static runs on the caller's stream only "

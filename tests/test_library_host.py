@@ -78,6 +78,22 @@ def create(lib, desc, n_bytes):
     return rc, None
 
 
+@pytest.mark.parametrize("B,L,S,E", [(1, 37, 29, 9973), (8, 24, 22, 20001), (16, 48, 44, 2048), (4, 12, 64, 8000), (6, 10, 120, 9000),
+                                     (24, 20, 22, 16500), (40, 40, 44, 16384), (2, 300, 12, 3000), (3, 6, 22, 1500)])
+def test_workspace_of_the_plain_shapes_is_enough(lib, B, L, S, E):
+    """Shapes that pad the strategies to more (22 to 24, 44 to 48, 100 to 128) or count more tiles need a larger
+    workspace; one of the size of the plain shape, or of the wide one where the launch fills the chip, is taken."""
+    one = binding.GALV_DP_STREAMS(1)
+    need = binding.galv_dp_workspace_bytes(binding.make_desc(B, L, S, E, 2, one))
+    full = (E // 128 + 1) * B >= 3072
+    flags = binding.GALV_DP_FORCE_WIDE_TILES if full else binding.GALV_DP_NO_WIDE_TILES
+    former = binding.galv_dp_workspace_bytes(binding.make_desc(B, L, S, E, 2, one | flags))
+    desc = binding.make_desc(B, L, S, E, 2, one)
+    for n_bytes in {need, max(need, former), min(need, former)}:
+        assert create(lib, desc, n_bytes)[0] == binding.GALV_OK
+    assert create(lib, desc, min(need, former) - 256)[0] == binding.GALV_ERR_WORKSPACE
+
+
 @pytest.mark.parametrize("S", [22, 44, 100])
 @pytest.mark.parametrize("L,columns", [(130, 128), (40, 256)])
 def test_cost_rows_take_the_same_tiles_by_default_and_on_request(lib, S, L, columns):
