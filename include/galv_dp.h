@@ -91,10 +91,10 @@ typedef struct {
 #define GALV_DP_FORCE_PEEK 16u /* 32-bit-key sweep: look at a row's cells in a tile's first and last
                                   column before fetching the row, and skip the fetch when they show
                                   that the row cannot win any minimum of the tile.  By default this
-                                  is done when a layer has enough workgroups to fill the chip (the
-                                  sweep is then bound by bytes; below that it is bound by latency
-                                  and the extra dependent step costs more than it saves).  Results
-                                  are identical either way.                                          */
+                                  is done when a layer has enough workgroups to fill the chip (over
+                                  cost rows the extra dependent step costs more than it saves below
+                                  that), and wherever the library chooses the byte table
+                                  (GALV_DP_FORCE_PACK).  Results are identical either way.           */
 #define GALV_DP_NO_PACK 32u    /* always keep the rolling cost rows and plain back-pointers (see
                                   GALV_DP_FORCE_PACK)                                               */
 #define GALV_DP_FORCE_PACK 64u /* packed-key instances with transition costs below 2^32 - 1, int32
@@ -104,7 +104,7 @@ typedef struct {
                                   strategies that can win in a tile, from which the next layer rebuilds
                                   the cells it reads; and store only the budget columns between the
                                   first reachable one and the one from which a layer is constant.
-                                  1 to 2 bytes per state instead of 8.  By default this is done when a
+                                  1 to 2 bytes per state instead of 12.  By default this is done when a
                                   layer has many states and its share of the budget spans a tile, and
                                   the sweep then peeks (GALV_DP_FORCE_PEEK) too; an instance on 64-bit
                                   keys whose transition costs let nearly no strategy be left out keeps
@@ -113,7 +113,10 @@ typedef struct {
 #define GALV_DP_FORCE_WIDE_TILES 128u   /* sweep workgroups take tiles of 256 budget columns instead of 128
                                            (17 to 256 strategies: the kernel variants that have such a twin).
                                            By default this is done when a layer has enough workgroups to
-                                           fill the chip, as for GALV_DP_FORCE_PEEK.  Results are identical. */
+                                           fill the chip and its share of the budget is large enough: half a
+                                           tile of 128 columns over cost rows; one over the byte table, and
+                                           only beyond 32 strategies (there also for somewhat smaller launches
+                                           with a share of two).  Results are identical. */
 #define GALV_DP_NO_WIDE_TILES 0x2000u   /* always 128-column tiles of the plain shape: neither wide tiles nor, on
                                            launches that leave wavefront slots idle, more waves per tile      */
 #define GALV_DP_STREAMS_SHIFT 8 /* bits 8..12: how many internal streams the layer sweeps are   */
@@ -143,7 +146,9 @@ typedef struct {
 /*
  * Bytes of device workspace a handle for `desc` needs (rolling cost rows,
  * back-pointers for layers 1..L-1, packed transition tables, per-instance
- * state): roughly B * S * (E_max + 1) * (4 * (L - 1) + 32) bytes.
+ * state): roughly B * S * (E_max + 1) * (4 * (L - 1) + 32) bytes.  Of the kernels that suit a
+ * shape some pad the strategies to a little more than others: galv_dp_create also takes less, down to
+ * what the plain ones need (the size with GALV_DP_NO_WIDE_TILES), and then chooses among those that fit.
  */
 galv_status_t galv_dp_workspace_bytes(const galv_dp_desc_t *desc, size_t *bytes);
 

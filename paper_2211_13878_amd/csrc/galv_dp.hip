@@ -28,7 +28,8 @@
 //    is also what lets the sweep PRUNE: a former-layer row that is clamped in every column of
 //    a tile is left out of the inner loop, and (rows being non-increasing along the budget
 //    axis) two of its cells tell whether it needs to be fetched at all.  With the usual spread
-//    of layer costs some 90-95 % of the candidates fall away and the sweep is bound by HBM.
+//    of layer costs some 90-95 % of the candidates fall away and the sweep is bound by the chain of memory
+//    round trips of a tile.
 //    The keys' width depends on the transition costs only; when the costs themselves outgrow
 //    32-bit cells, the same body runs over 64-bit cells (up to 256 strategies).
 //    Where a layer has many tiles, these instances keep argmins of one byte and what it takes to
@@ -2352,14 +2353,14 @@ __global__ __launch_bounds__(kWave) void final_kernel(Layout a, int64_t *best_co
     }
 }
 
-// Walk the un-shifted argmin table of instance b from (L-1, e, s) down to layer 0:
-// L dependent loads.  Writes the plan, or all -1 when s < 0.
+// Walk the un-shifted argmin table of instance b from (L-1, e, s) down to layer 0, where
+// there are more strategies than walk_wave takes: L dependent loads.  Writes the plan, or
+// all -1 when s < 0.
 __device__ __forceinline__ void walk_plan(const Layout &a, int b, int64_t e, int s, int32_t *out) {
     if (s < 0) {
         for (int l = 0; l < a.L; ++l) out[l] = -1;
         return;
     }
-    const bool packed = is_packed(a, a.status[b], b);
     for (int l = a.L - 1; l >= 1; --l) {
         out[l] = s;
         e -= a.m[((int64_t)b * a.L + l) * a.S + s];
@@ -2369,7 +2370,7 @@ __device__ __forceinline__ void walk_plan(const Layout &a, int b, int64_t e, int
             for (int q = 0; q < a.L; ++q) out[q] = -1;
             return;
         }
-        s = load_bp(a, packed, b, l, s, e);
+        s = load_bp(a, false, b, l, s, e);         // (more strategies than a byte table has)
         if (s < 0 || s >= a.S) {
             for (int q = 0; q < a.L; ++q) out[q] = -1;
             return;
@@ -2644,9 +2645,8 @@ __global__ __launch_bounds__(kThreads) void export_kernel(Layout a, int b, int64
 // owning TS rows and TS strategies of one tile of 64 * TE * UX columns; it needs
 // TS * NG >= S, so the last variant, which serves any S, uses the plain body; the one before
 // it covers up to 256 strategies with 16-wave workgroups).
-// Measured on MI355X: with the dominated rows pruned the sweep is bound by HBM, and tiles of
-// 128 columns beat 64 (longer contiguous row segments) while larger register tiles gain
-// nothing; 8 waves per SIMD do not build for TS = 16 (the compiler then spills scalar
+// Measured over cost rows: tiles of 128 columns beat 64 (longer contiguous row segments) while larger register
+// tiles gain nothing; 8 waves per SIMD do not build for TS = 16 (the compiler then spills scalar
 // registers that a hand-issued load still targets, which the build refuses).
 #ifndef GALV_V0
 #define GALV_V0 8, 2, 1, 8, 1, 1, 1
@@ -2677,10 +2677,9 @@ __global__ __launch_bounds__(kThreads) void export_kernel(Layout a, int b, int64
 #endif
 // Twins with tiles of 256 budget columns (UX = 2: four columns per lane) and fewer, fatter waves,
 // for launches that fill the chip anyway: what a tile costs beside its min-plus arithmetic (its
-// chain of round trips, its addresses and bookkeeping) is spread over twice the states.
-// Measured against the 128-column variants: 3.5 % (44 strategies x 32768 columns x 64 instances),
-// 5 % (128 x 65536 x 16), 2 % (22 x 24576 x 32), 3-6 % at 32, 64, 200 and 256 strategies; 3 %
-// slower on 22 x 16384 x 8, which does not fill the chip and keeps the narrow tiles.
+// chain of round trips, its addresses and bookkeeping) is spread over twice the states, for half the
+// rows in its list.  Which launches take them, and what both shapes measured, stands in make_plan.  (Up to 32
+// strategies only cost rows take them by themselves; over the byte table they have to be asked for.)
 #ifndef GALV_V2X
 #define GALV_V2X 11, 2, 2, 5, 2, 2, 1
 #endif
@@ -2699,7 +2698,7 @@ __global__ __launch_bounds__(kThreads) void export_kernel(Layout a, int b, int64
 #ifndef GALV_V7X
 #define GALV_V7X 16, 2, 16, 4, 16, 2, 1
 #endif
-// Twins with the same tiles and more, thinner waves, for launches that leave wavefront slots idle: a
+// Twins with the plain shape's tiles and more, thinner waves, for launches that leave wavefront slots idle: a
 // tile's time is then a chain of round trips, two per row that a wave rebuilds or one per row that it
 // loads, and of the additions of the strategies it owns, and more waves shorten both.
 #ifndef GALV_S0
