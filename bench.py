@@ -17,29 +17,32 @@ configuration (int32 back-pointers, internal streams chosen from the shape);
 searches/s and the exact candidate rate are reported beside it.
 
 `roofline` is for the layer-sweep kernel (the only kernel that matters: > 95 %
-of the time).  Two sides are computed per layer step, and the one that needs
-more time at its peak is the binding one (`roofline.bound`):
-  * HBM: the table bytes of a state within the budgets, against 8 TB/s.  With the
-    byte table (the library's choice when a layer has many states, as on
-    configurations 1-4) that is one byte for the back-pointer, and per budget column
-    one former minimum and the relative costs of the few strategies that are alive,
-    1.5 to 2 bytes in all.  With rolling cost rows
-    (small shapes, --no-pack, one-byte back-pointers) it is 12: cost cell read,
-    cost cell written, int32 back-pointer written (20 with 64-bit cells);
-  * ALU: the min-plus candidates the sweep evaluates (the library counts them:
-    on the 32-bit-key path former strategies that cannot win any minimum of a
-    tile are pruned; `candidates_evaluated_share`) times the lane-operations
-    each needs on its instance's arithmetic path (1.5 with 32-bit keys: two adds
-    and one three-way minimum per two candidates; 2 with 64-bit keys), plus 7 per
-    table state on the 32-bit-key path, against the VALU issue peak of
-    256 CUs x 64 lanes x 2.4 GHz = 39.3 T lane-ops/s.
+of the time; `roofline.kernel` names the one that ran).  Two sides are computed
+per layer step, and the one that needs more time at its peak is the binding one
+(`roofline.bound`).  Both count what the chosen form of the tables does:
+  * with the byte table (the library's choice when a layer has many states, as on
+    configurations 1-4), only the budget columns that are swept (`columns_swept_share`:
+    the library counts usable rows per swept tile, and the inputs say how many are
+    usable per layer).  Bytes per swept column: one argmin byte per strategy, the
+    samples of every 64th column, the former minimum written and read, 8 bytes per row
+    alive (its relative cost written and read), 1 per row fetched.  Operations: 1.5 per candidate (two adds and one
+    three-way minimum per two of them; the candidates are the rows reduced times the
+    strategies), 6 per fetched cell (three additions that rebuild it, column minimum,
+    relative cost, clamp), 1 per state (its byte put beside its neighbours');
+  * with rolling cost rows (small shapes, --no-pack, one-byte back-pointers), all
+    columns within the budgets.  Bytes per state: 12, that is cost cell read, cost cell
+    written, int32 back-pointer written (20 with 64-bit cells).  Operations: 1.5 per
+    candidate evaluated with 32-bit keys, 2 with 64-bit keys, plus 7 per state on the
+    32-bit-key path.
+Peaks: 8 TB/s, and a VALU issue rate of 256 CUs x 64 lanes x 2.4 GHz = 39.3 T
+lane-ops/s.
 The sweep time per layer comes from events on the caller's stream around the
 solve, / (L-1).  With internal streams a layer is several overlapping launches,
 so that figure rests on event timing; `roofline.single_stream` is a second timed
 leg with one launch per layer, the kernel's own figure, which a kernel trace of
 `--streams 1` shows directly.
 `variant_bp_u8` is a third leg with one-byte back-pointers (same results; rolling
-cost rows, 9 B/state: it saves workspace, not time, where the packed table applies).
+cost rows, 9 B/state: it saves workspace, not time, where the byte table applies).
 `cpu_baseline` times the serial CPU oracle (test infrastructure, never tuned) on a
 bounded sample of the same workload: one instance on one thread, and one instance
 per thread on the host cores this process may use.
@@ -61,9 +64,12 @@ HBM_PEAK_GBS = 8000.0
 # (status code): 32-bit keys fold two candidates into two adds and one three-way minimum;
 # 64-bit keys take one add and one minimum each; the general integer path about six.
 OPS_PER_CANDIDATE = {3: 1.5, 4: 1.5, 0: 2.0, 2: 2.0, 1: 6.0}
-# lane-operations per table state that do not depend on the number of candidates, 32-bit-key path:
-# column minimum (1), relative cost and clamp test (2), new cell and back-pointer (4)
+# lane-operations per table state that do not depend on the number of candidates, 32-bit-key path over
+# cost rows: column minimum (1), relative cost and clamp test (2), new cell and back-pointer (4)
 FIXED_OPS_PER_STATE = {3: 7.0, 4: 12.0}
+# and with the byte table: per swept state, and per cell of a fetched former row
+BYTE_TABLE_OPS_PER_STATE = 1.0
+BYTE_TABLE_OPS_PER_FETCHED_CELL = 6.0
 # table bytes per state: cost cell read + cost cell written + int32 back-pointer written
 BYTES_PER_STATE = {3: 4 + 4 + 4, 0: 4 + 4 + 4, 4: 8 + 8 + 4, 2: 8 + 8 + 4, 1: 8 + 8 + 4}   # by per-instance status code
 
@@ -71,7 +77,7 @@ BYTES_PER_STATE = {3: 4 + 4 + 4, 0: 4 + 4 + 4, 4: 8 + 8 + 4, 2: 8 + 8 + 4, 1: 8 
 # HBM bytes per sweep launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, each scaled by the
 # same counter's reading for a 1 GiB copy: the `traffic_bytes_per_launch` line of
 # profiles/sweep_kernel_config<N>.md (tests/test_profiles.py keeps the two equal); None where not measured.
-MEASURED_TRAFFIC_BYTES = {3: 85643264, 4: 179496960}
+MEASURED_TRAFFIC_BYTES = {3: 85653504, 4: 179487744}
 
 
 def cpu_baseline(w):
@@ -128,8 +134,8 @@ def main():
     ap.add_argument("--force-int64", action="store_true", help="time the general integer kernels")
     ap.add_argument("--no-u32", action="store_true", help="keep 64-bit keys (GALV_DP_NO_U32)")
     ap.add_argument("--no-pack", action="store_true",
-                    help="rolling cost rows and plain back-pointers instead of the single packed table (GALV_DP_NO_PACK)")
-    ap.add_argument("--force-pack", action="store_true", help="the single packed table whatever the shape (GALV_DP_FORCE_PACK)")
+                    help="rolling cost rows and plain back-pointers instead of the byte table (GALV_DP_NO_PACK)")
+    ap.add_argument("--force-pack", action="store_true", help="the byte table whatever the shape (GALV_DP_FORCE_PACK)")
     ap.add_argument("--no-wide-tiles", action="store_true", help="128-column tiles whatever the shape (GALV_DP_NO_WIDE_TILES)")
     ap.add_argument("--bp-u8", action="store_true",
                     help="store back-pointers in one byte (GALV_DP_BP_U8): 9 instead of 12 B per state")
@@ -281,7 +287,7 @@ def run_config(cfg, args, torch, binding, workloads):
         torch.cuda.synchronize()
         del src, dst
 
-    chosen = {}       # what the handle of the last timed leg chose (packed table, peek, streams)
+    chosen = {}       # what the handle of the last timed leg chose (byte table, peek, streams)
 
     def timed(flags, steps, warmup):
         """K steps (solve + backtrack) on a fresh handle: wall ms per step, solve ms per step."""
@@ -345,24 +351,32 @@ def run_config(cfg, args, torch, binding, workloads):
     share = [float(r) / float(n) if n > 0 else 1.0 for r, n, _ in stats]
     fetched_share = (float(sum(f for _, _, f in stats)) / float(sum(n for _, n, _ in stats))
                      if sum(n for _, n, _ in stats) > 0 else 1.0)
-    # lane-ops of one layer: per instance and table state the fixed work of its path, plus its
-    # (E_b + 1) * S^2 candidates, as far as they were evaluated, times the path's cost per candidate
-    lane_ops_per_layer = sum((FIXED_OPS_PER_STATE.get(int(st), 0.0) +
-                              f * w.S * OPS_PER_CANDIDATE.get(int(st), 0.0)) * (int(e) + 1) * w.S
-                             for st, e, f in zip(status, w.budget, share))
-    evaluated = sum(f * (int(e) + 1) * w.S * w.S for e, f in zip(w.budget, share))     # per layer
-    ops = OPS_PER_CANDIDATE.get(int(status[0]), 0.0)
-    sweep_ms, achieved = alu(solve_ms)
-    # byte table (the library's default for layers of many states, S <= 256): one byte written per state, the
-    # samples of every 64th column, one former minimum per budget column and the relative costs of the rows
-    # that are alive, each written and read once (counted for all columns, though some need no sweep)
+    # What one layer takes, per instance on average: candidates, lane-operations, table bytes, swept columns.
     packed = bool(main_leg["packed"])
-    def byte_table(st, alive):
-        cell = 4 if st == 3 else 8
-        return 1 + 2 * cell / 64 + 2 * cell / w.S + 8 * alive
-    per_state = [byte_table(int(st), f) if packed and int(st) in (0, 2, 3, 4)
-                 else BYTES_PER_STATE.get(int(st), 0) - (3 if args.bp_u8 else 0) for st, f in zip(status, share)]
-    hbm_bytes = sum(p * (int(e) + 1) * w.S for p, e in zip(per_state, w.budget))   # per layer
+    ops = OPS_PER_CANDIDATE.get(int(status[0]), 0.0)
+
+    def layer_work(b):
+        st, e, (reduced, listed, fetched) = int(status[b]), int(w.budget[b]), stats[b]
+        columns = float(e + 1)
+        if packed and st in (3, 4) and listed > 0:
+            # a tile counts its rows once, and once per part where it is swept in parts: 8-byte cells take a
+            # tile in two (so do the few tiles of 256 columns that keep too many rows: counted as whole ones)
+            part = main_leg["tile_columns"] / (2 if st == 4 else 1)
+            usable = float((w.m[b, :-1] <= e).sum(axis=1).mean())
+            rows, got, cell = reduced * part, fetched * part, 4 if st == 3 else 8        # row-columns, all layers
+            swept = listed * part / usable
+            work = (rows * w.S * OPS_PER_CANDIDATE[st] + got * BYTE_TABLE_OPS_PER_FETCHED_CELL +
+                    swept * w.S * BYTE_TABLE_OPS_PER_STATE)
+            moved = swept * (w.S * (1 + cell / 64) + 2 * cell) + 8 * rows + got
+            return tuple(x / n_layer_steps for x in (rows * w.S, work, moved, swept))
+        f = share[b]
+        per_state = FIXED_OPS_PER_STATE.get(st, 0.0) + f * w.S * OPS_PER_CANDIDATE.get(st, 0.0)
+        size = BYTES_PER_STATE.get(st, 0) - (3 if args.bp_u8 else 0)
+        return f * columns * w.S * w.S, per_state * columns * w.S, size * columns * w.S, columns
+
+    evaluated, lane_ops_per_layer, hbm_bytes, columns_swept = (
+        sum(x) for x in zip(*(layer_work(b) for b in range(w.B))))
+    sweep_ms, achieved = alu(solve_ms)
     hbm_gbs = hbm_bytes / (sweep_ms * 1e-3) / 1e9
     # The same kernel with every layer as ONE launch on one stream: the per-launch figure that
     # a kernel trace shows directly (with several streams the launches overlap in time).
@@ -377,16 +391,16 @@ def run_config(cfg, args, torch, binding, workloads):
 
     # Which roofline binds: the one that needs more time at its peak for one layer's work.
     alu_obj = {"achieved": achieved, "peak": VALU_PEAK_TLANEOPS, "unit": "Tlane-op/s",
-               "frac": achieved / VALU_PEAK_TLANEOPS, "lane_ops_per_candidate": ops,
-               "lane_ops_per_state_fixed": FIXED_OPS_PER_STATE.get(int(status[0]), 0.0),
+               "frac": achieved / VALU_PEAK_TLANEOPS, "lane_ops_per_layer": lane_ops_per_layer,
+               "lane_ops_per_candidate": ops,
                "candidates_evaluated_share": evaluated / max(1.0, exact / n_layer_steps)}
     hbm_obj = {"achieved": hbm_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": hbm_gbs / HBM_PEAK_GBS,
-               "bytes_per_launch": hbm_bytes, "bytes_per_state": max(per_state)}
+               "bytes_per_launch": hbm_bytes, "bytes_per_state_swept": hbm_bytes / (columns_swept * w.S)}
     t_alu = lane_ops_per_layer / (VALU_PEAK_TLANEOPS * 1e12)
     t_hbm = hbm_bytes / (HBM_PEAK_GBS * 1e9)
     bound = "alu" if t_alu >= t_hbm else "hbm"
     binding_obj = alu_obj if bound == "alu" else hbm_obj
-    roofline = {"bound": bound, "kernel": "sweep_kernel", "achieved": binding_obj["achieved"],
+    roofline = {"bound": bound, "kernel": "sweep_bytes_kernel" if packed else "sweep_kernel", "achieved": binding_obj["achieved"],
                 "peak": binding_obj["peak"], "unit": binding_obj["unit"], "frac": binding_obj["frac"],
                 "traffic": (MEASURED_TRAFFIC_BYTES.get(cfg) if base_flags == 0 and args.r_scale == 1 and args.c_scale == 1
                             else None),
@@ -397,8 +411,14 @@ def run_config(cfg, args, torch, binding, workloads):
                         "figure rests on event timing only; single_stream is the kernel's own figure (one "
                         "launch per layer, the duration a kernel trace of --streams 1 shows). The ALU side "
                         "counts only the candidates the sweep evaluates (rows that cannot win any minimum "
-                        "of a tile are pruned; alu.candidates_evaluated_share, from galv_dp_get_stats)",
+                        "of a tile are pruned, and columns below the first reachable one or above the last one "
+                        "that differs are not swept; alu.candidates_evaluated_share, from galv_dp_get_stats)",
                 "single_stream": single, "alu": alu_obj, "hbm": hbm_obj}
+
+    if packed and any(int(st) in (0, 2) for st in status):
+        roofline = {"bound": None, "kernel": "sweep_bytes_kernel", "launch_ms": sweep_ms,
+                    "single_stream": single and {"launch_ms": single["launch_ms"]},
+                    "note": "not priced: the library counts no rows for instances on 64-bit keys"}
 
     kinds = {3: "u32", 4: "u32", 0: "f64", 2: "f64", 1: "int64"}
     used = sorted({kinds[int(st)] for st in status if int(st) in kinds})
@@ -415,8 +435,8 @@ def run_config(cfg, args, torch, binding, workloads):
         "data": "synthetic",
         "config": {"workload": f"config {cfg} '{w.name}': B={w.B} L={w.L} S={w.S} "
                                f"E_max={w.E_max} budgets {int(w.budget.min())}..{int(w.budget.max())}",
-                   "back_pointer_bytes": 1 if args.bp_u8 else 4,
-                   "single_packed_table": bool(packed and any(int(st) in (3, 4) for st in status)),
+                   "back_pointer_bytes": 1 if args.bp_u8 or packed else 4,
+                   "byte_table": packed,
                    "internal_streams": main_leg["streams"],
                    "peek_before_fetch": bool(main_leg["peek"]),
                    "tile_columns": main_leg["tile_columns"],
@@ -426,7 +446,8 @@ def run_config(cfg, args, torch, binding, workloads):
         "searches_per_sec": w.B / (ms_per_step * 1e-3),
         "exact_candidates_per_sec": exact / (ms_per_step * 1e-3),
         "candidates_evaluated_share": evaluated / max(1.0, exact / n_layer_steps),
-        "cost_rows_fetched_share": fetched_share,
+        "columns_swept_share": columns_swept / sum(int(e) + 1 for e in w.budget),
+        "rows_fetched_share": fetched_share,
         "solve_ms_median": solve_ms[len(solve_ms) // 2],
         "instances_by_path": {"u32_keys": int((status == binding.GALV_INSTANCE_OK_FAST_U32).sum()),
                               "u32_keys_64bit_cells": int((status == binding.GALV_INSTANCE_OK_U32_WIDE).sum()),
