@@ -359,8 +359,7 @@ def run_config(cfg, args, torch, binding, workloads):
         st, e, (reduced, listed, fetched) = int(status[b]), int(w.budget[b]), stats[b]
         columns = float(e + 1)
         if packed and st in (3, 4) and listed > 0:
-            # a tile counts its rows once, and once per part where it is swept in parts: 8-byte cells take a
-            # tile in two (so do the few tiles of 256 columns that keep too many rows: counted as whole ones)
+            # a tile counts its rows once, with 8-byte cells once per part, of which there are two
             part = main_leg["tile_columns"] / (2 if st == 4 else 1)
             usable = float((w.m[b, :-1] <= e).sum(axis=1).mean())
             rows, got, cell = reduced * part, fetched * part, 4 if st == 3 else 8        # row-columns, all layers

@@ -1783,6 +1783,10 @@ constexpr unsigned byte_lds(int ts, int ng, int wpe, int cols) {
     return tile > live ? tile : live;
 }
 
+// How a part of a tile enters the tile's statistics: alone, added to the part before, or, for the second half of
+// an overfull tile, which otherwise counts as one, as the mean of the two.
+enum PartStats { kSetStats, kAddStats, kMeanStats };
+
 // What a tile needs to know of its layer and of the former one.
 struct TileHdr {
     int n;                                         // usable strategies of the former layer
@@ -1824,7 +1828,7 @@ struct Former {
 // Returns true when the tile has been swept.  With MAY_REFUSE a tile that keeps more rows than the list
 // holds is left untouched instead (all waves agree; nothing but LDS has been written).
 template <int TS, int TE, int NG, class Cell, class Key, int KEEP, int TILE, bool MAY_REFUSE = false>
-__device__ __forceinline__ bool sweep_bytes(const Layout &a, int g, int l, int b, int tile_start, bool add_stats,
+__device__ __forceinline__ bool sweep_bytes(const Layout &a, int g, int l, int b, int tile_start, PartStats part_stats,
                                             const TileHdr &h, const uint64_t (&ent)[(TS * NG + kWave - 1) / kWave],
                                             const uint64_t (&c0_64)[(TS * NG + kWave - 1) / kWave]) {
     constexpr Cell kInfCell = sizeof(Cell) == 8 ? (Cell)kInf : (Cell)kInf32;
@@ -2136,9 +2140,14 @@ __device__ __forceinline__ bool sweep_bytes(const Layout &a, int g, int l, int b
     const int64_t e_pad = a2.e_pad;
     if (g == 0 && lane == 0) {                     // statistics: how much the pruning removed
         uint32_t *st = a2.stats + 2 * (((int64_t)b * (a2.L - 1) + (l - 1)) * a2.n_tiles + tile_start / TILE);
-        const uint32_t rows = rows_reduced << 16 | (uint32_t)h.n;
-        st[0] = add_stats ? st[0] + rows : rows;   // (a tile swept in several parts adds them up)
-        st[1] = add_stats ? st[1] + (uint32_t)nk : (uint32_t)nk;
+        if (part_stats == kMeanStats) {
+            st[0] = ((st[0] >> 16) + rows_reduced + 1) / 2 << 16 | (uint32_t)h.n;
+            st[1] = (st[1] + (uint32_t)nk + 1) / 2;
+        } else {
+            const uint32_t rows = rows_reduced << 16 | (uint32_t)h.n;
+            st[0] = part_stats == kAddStats ? st[0] + rows : rows;
+            st[1] = part_stats == kAddStats ? st[1] + (uint32_t)nk : (uint32_t)nk;
+        }
     }
     if (g == 0) {
         cellv out;
@@ -2248,13 +2257,14 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_bytes_kernel(Layout a, i
         // 35 x 4805 x 96 3135 / 2880, 64 x 3768 x 20 610 / 572; a list that overflows by little pays more for the
         // second half than for the pass (56 x 2893 x 15 949 / 979).
         const bool done = sweep_bytes<TS, TE * UX, NG, uint32_t, Key32, kKeep, kTile, (UX > 1)>(
-            layout_again(), wave, l, b, tile_start, false, h, ent, c0);
+            layout_again(), wave, l, b, tile_start, kSetStats, h, ent, c0);
         if constexpr (UX > 1)
             for (int p = 0; p < UX && !done; ++p) {
                 const int part = tile_start + p * (kTile / UX);
                 if (part > x) break;                             // workgroup-uniform
                 __syncthreads();                                 // the LDS of the part before is free again
-                sweep_bytes<TS, TE, NG, uint32_t, Key32, UX * kKeep, kTile>(layout_again(), wave, l, b, part, p > 0, h, ent, c0);
+                sweep_bytes<TS, TE, NG, uint32_t, Key32, UX * kKeep, kTile>(
+                    layout_again(), wave, l, b, part, p ? kMeanStats : kSetStats, h, ent, c0);
             }
     } else if (packed) {
         // 8-byte cells: a part of the tile at a time keeps registers and LDS within what the narrow form uses
@@ -2262,9 +2272,9 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_bytes_kernel(Layout a, i
             if (tile_start + p * (kWave * UX) > x) break;    // workgroup-uniform
             if (p) __syncthreads();                          // the LDS of the part before is free again
             if (keys32)
-                sweep_bytes<TS, UX, NG, uint64_t, Key32, kKeep, kTile>(layout_again(), wave, l, b, tile_start + p * (kWave * UX), p > 0, h, ent, c0);
+                sweep_bytes<TS, UX, NG, uint64_t, Key32, kKeep, kTile>(layout_again(), wave, l, b, tile_start + p * (kWave * UX), p ? kAddStats : kSetStats, h, ent, c0);
             else
-                sweep_bytes<TS, UX, NG, uint64_t, Key64, kKeep, kTile>(layout_again(), wave, l, b, tile_start + p * (kWave * UX), p > 0, h, ent, c0);
+                sweep_bytes<TS, UX, NG, uint64_t, Key64, kKeep, kTile>(layout_again(), wave, l, b, tile_start + p * (kWave * UX), p ? kAddStats : kSetStats, h, ent, c0);
         }
     } else if (st == GALV_INSTANCE_OK_FAST) {
         for (int u = 0; u < UX; ++u)

@@ -21,7 +21,7 @@ def check_statistics(w, flags):
     usable = sum((w.m[:, l] <= w.budget[:, None]).sum(axis=1) for l in range(w.L - 1))
     tiles = w.budget // columns + 1
     assert (0 < reduced).all() and (reduced <= fetched).all() and (fetched <= listed).all()
-    assert (listed <= 2 * tiles * usable).all()              # (a tile in two halves lists its rows twice)
+    assert (listed <= tiles * usable).all()                  # (a tile in two halves counts as one)
     return columns, reduced, listed
 
 
