@@ -118,7 +118,10 @@ struct Variant {
     int share;             // 1: the row-sharing 32-bit-key body (one tile per workgroup, LDS for the kept rows)
 };
 
-// Everything the kernels need to find their data.  Passed by value.
+enum : int32_t { kAllBytes = 1, kRowsIfAlive = 2 };      // Layout::packed
+
+// Everything the kernels need to find their data.  Passed by value.  (One more 4-byte field shifts the pointers behind
+// it and costs every sweep launch 0.2 us.)
 struct Layout {
     int32_t B, L, S, E_max, nR;
     int32_t S_pad;        // strategies rounded up to the variant's group size
@@ -132,9 +135,9 @@ struct Layout {
     void *bp;             // argmin, un-shifted  [B][L-1][S][e_pad] of int32, or of uint8 (0xFF = none)
     int32_t bp_u8;        // 1: one-byte back-pointers
     int32_t peek;         // 1: the row-sharing sweep looks at two cells of a row before it fetches the row
-    int32_t rows_if_alive; // 1: of those on 64-bit keys, the ones where most rows stay alive do not (see prep_kernel)
-    int32_t packed;       // 1: instances of byte_status() keep the byte table: argmins in one byte, and
-                          //    instead of cost rows what it takes to rebuild a cell (see PackTables)
+    int32_t packed;       // not 0: instances of byte_status() keep the byte table: argmins in one byte, and
+                          //    instead of cost rows what it takes to rebuild a cell (see PackTables); kAllBytes,
+                          //    or kRowsIfAlive: those on 64-bit keys not where most rows stay alive (see prep_kernel)
     int32_t synth_l1;     // 1: the 32-bit-key sweep makes up layer 0's cells (a constant per strategy)
                           //    when it sweeps layer 1, so layer 0's row is never written nor read
     int32_t b_off, b_step; // a sweep launch covers instances b_off + z * b_step (dealt over streams)
@@ -454,7 +457,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
     // than the layer's cheapest plus the largest transition cost.  Whole solves of 10 layers over cost rows / with the
     // byte table, in us, share of alive strategies 1.0: 22 strategies x 1512 tiles 201 / 258, 44 x 1512 379 / 493, 14 x
     // 3760 250 / 374; 0.55: 34 x 582 97 / 101; 0.35: 22 x 1512 202 / 180, 44 x 1512 379 / 254.
-    if (a.packed && a.rows_if_alive && (st == GALV_INSTANCE_OK_FAST || st == GALV_INSTANCE_OK_FAST_WIDE)) {
+    if (a.packed == kRowsIfAlive && (st == GALV_INSTANCE_OK_FAST || st == GALV_INSTANCE_OK_FAST_WIDE)) {
         unsigned long long seen = 0;               // usable << 32 | alive
         for (int64_t l = wave; l + 1 < L; l += kPrepThreads / kWave) {
             unsigned long long v[4], least = ~0ull;           // (the byte table has at most 256 strategies)
@@ -3063,10 +3066,9 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, Plan *p) {
     if ((d->flags & GALV_DP_FORCE_PACK) && v.share && !u8) packed = true;
     if (packed) p->lds_bytes = lds_packed;
     p->sweep = packed ? ve.fn_pack : (u8 ? ve.fn_u8 : ve.fn);
-    a.packed = packed ? 1 : 0;
     // (up to 30 strategies x 3000 tiles: two tables of 8-byte cells take 184 MB, and the caches hold 256.  With all
     // rows alive, cost rows / byte table: 30 x 3760 tiles 904 / 658 us, 34 x 3760 957 / 675, 64 x 1512 919 / 833)
-    a.rows_if_alive = !(d->flags & GALV_DP_FORCE_PACK) && tiles * S < 90000 ? 1 : 0;
+    a.packed = !packed ? 0 : !(d->flags & GALV_DP_FORCE_PACK) && tiles * S < 90000 ? kRowsIfAlive : kAllBytes;
     a.seen = nullptr;
     a.lead = (int64_t)round_up((size_t)a.E_max + 1, 64);
     a.row = a.lead + a.e_pad;
@@ -3525,7 +3527,7 @@ galv_status_t galv_dp_get_stats(galv_dp_t *h, int64_t *stats_dev, void *stream) 
 galv_status_t galv_dp_get_config(const galv_dp_t *h, int32_t *config) {
     if (!h) return fail(GALV_ERR_INVALID_ARG, "handle is NULL");
     if (!config) return fail(GALV_ERR_INVALID_ARG, "config is NULL");
-    config[0] = h->lay.packed;
+    config[0] = h->lay.packed ? 1 : 0;
     config[1] = h->lay.peek && h->var.share ? 1 : 0;
     config[2] = h->n_used > 0 ? h->n_used : (h->lay.L < 2 ? 1 : pick_streams(h, tiles_at_most(h)));
     config[3] = h->lay.tile_e;

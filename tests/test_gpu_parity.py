@@ -473,7 +473,7 @@ def test_call_order_and_reuse():
 
 def test_one_handle_through_every_storage_form():
     """The same handle solves, in turn, problems that land on different arithmetic paths and
-    table forms (single packed table, narrow and wide cost rows with their infinity leads,
+    table forms (byte table, narrow and wide cost rows with their infinity leads,
     64-bit integers): whatever one solve leaves in the workspace must not leak into the next."""
     shape = dict(B=3, L=6, S=23, E_max=900, nR=2)
     kinds = {
