@@ -13,7 +13,8 @@ largest that one GPU holds: the headline `value`, `ms_per_step`, `roofline` and
 `cpu_baseline`) and 3; `per_config` carries the full record of each.  `--config N`
 times that configuration alone.  `value` is DP cell-updates/s with the metric's
 nominal count sum_b L * E_b * S^2 per batch, in the library's default
-configuration (int32 back-pointers, internal streams chosen from the shape);
+configuration (int32 back-pointers asked for, which the byte table stores in one byte; internal streams
+chosen from the shape);
 searches/s and the exact candidate rate are reported beside it.
 
 `roofline` is for the layer-sweep kernel (the only kernel that matters: > 95 %
@@ -95,7 +96,7 @@ def cpu_baseline(w):
         host = min(host, len(os.sched_getaffinity(0)))
     except (AttributeError, OSError):
         pass
-    # a GPU machine gives one GPU's job a share of 16 cores whatever the core count it shows
+    # (a host of several GPUs gives one GPU's job a share of its cores, whatever the count it shows: at most 16 here)
     threads = max(1, min(host, 16, w.B))
     per_core = 2.0e9                                   # rough oracle rate used only to size the sample
     cap = int(15.0 * per_core / (w.L * w.S * w.S))     # budget columns one thread sweeps in ~15 s
