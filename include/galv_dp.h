@@ -153,6 +153,13 @@ typedef struct {
 galv_status_t galv_dp_workspace_bytes(const galv_dp_desc_t *desc, size_t *bytes);
 
 /*
+ * Bytes of device workspace with which galv_dp_create takes the kernels that suit the shape best, at least
+ * galv_dp_workspace_bytes.  Small searches run all their layers in one launch where the workspace holds every layer's
+ * rows: roughly B * S * (E_max + 1) * (4 * (L - 1) + 8 * L) bytes.
+ */
+galv_status_t galv_dp_workspace_bytes_preferred(const galv_dp_desc_t *desc, size_t *bytes);
+
+/*
  * Create a handle over caller-owned workspace (256-byte aligned device memory
  * of at least galv_dp_workspace_bytes).  The handle keeps the pointer; the
  * workspace must outlive it.  The device that is current at this call is the

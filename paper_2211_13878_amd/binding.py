@@ -41,7 +41,7 @@ GALV_INSTANCE_OK_FAST, GALV_INSTANCE_OK_INT64, GALV_INSTANCE_OK_FAST_WIDE, GALV_
 GALV_INSTANCE_OK_U32_WIDE = 4
 GALV_INSTANCE_BAD_VALUE = -1
 
-EXPORTS = ("galv_dp_workspace_bytes", "galv_dp_create", "galv_dp_solve_batched",
+EXPORTS = ("galv_dp_workspace_bytes", "galv_dp_workspace_bytes_preferred", "galv_dp_create", "galv_dp_solve_batched",
            "galv_dp_backtrack", "galv_dp_solve_static", "galv_dp_best_per_budget", "galv_dp_backtrack_queries",
            "galv_dp_export_tables", "galv_dp_get_status", "galv_dp_get_stats", "galv_dp_get_config", "galv_alg1_reduce",
            "galv_dp_coarsen", "galv_dp_expand_plan",
@@ -84,6 +84,7 @@ def load_library() -> ctypes.CDLL:
                               f"(build stamp: {text!r}): its device code is unverified and must not run")
         vp, i32 = ctypes.c_void_p, ctypes.c_int32
         lib.galv_dp_workspace_bytes.argtypes = [ctypes.POINTER(Desc), ctypes.POINTER(ctypes.c_size_t)]
+        lib.galv_dp_workspace_bytes_preferred.argtypes = [ctypes.POINTER(Desc), ctypes.POINTER(ctypes.c_size_t)]
         lib.galv_dp_create.argtypes = [ctypes.POINTER(Desc), vp, ctypes.c_size_t, ctypes.POINTER(vp)]
         lib.galv_dp_solve_batched.argtypes = [vp] * 9
         lib.galv_dp_backtrack.argtypes = [vp, vp, vp]
@@ -143,6 +144,12 @@ def make_desc(B, L, S, E_max, nR=1, flags=0) -> Desc:
 def galv_dp_workspace_bytes(desc: Desc) -> int:
     n = ctypes.c_size_t(0)
     _check(load_library().galv_dp_workspace_bytes(ctypes.byref(desc), ctypes.byref(n)))
+    return n.value
+
+
+def galv_dp_workspace_bytes_preferred(desc: Desc) -> int:
+    n = ctypes.c_size_t(0)
+    _check(load_library().galv_dp_workspace_bytes_preferred(ctypes.byref(desc), ctypes.byref(n)))
     return n.value
 
 
@@ -268,7 +275,7 @@ class Solver:
         self.device = torch.device(device)
         self.B, self.L, self.S, self.E_max, self.nR = B, L, S, E_max, nR
         self.desc = make_desc(B, L, S, E_max, nR, flags)
-        self.workspace_bytes = galv_dp_workspace_bytes(self.desc)
+        self.workspace_bytes = galv_dp_workspace_bytes_preferred(self.desc)
         with torch.cuda.device(self.device):
             self.workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=self.device)
             self.handle = galv_dp_create(self.desc, self.workspace)

@@ -77,6 +77,8 @@ constexpr int kMaxS = 1024;
 constexpr int kSample = 64;            // byte-table sweep: absolute costs are kept of every 64th budget column
 constexpr int kMaxSide = 16;          // internal streams per handle
 constexpr int kMaxPp = 16;            // pipeline degrees per reduce call
+constexpr int kWordStep = 16;         // chained sweep: 32-bit words from one flag to the next
+constexpr int32_t kUnset = INT32_MIN; // chained sweep: the last column of a layer is not told yet
 #ifndef GALV_P1_BATCH
 #define GALV_P1_BATCH 8
 #endif
@@ -118,7 +120,7 @@ struct Variant {
     int share;             // 1: the row-sharing 32-bit-key body (one tile per workgroup, LDS for the kept rows)
 };
 
-enum : int32_t { kAllBytes = 1, kRowsIfAlive = 2 };      // Layout::packed
+enum : int32_t { kAllBytes = 1, kRowsIfAlive = 2, kChain = 3 };      // Layout::packed
 
 // Everything the kernels need to find their data.  Passed by value.  (One more 4-byte field shifts the pointers behind
 // it and costs every sweep launch 0.2 us.)
@@ -137,7 +139,9 @@ struct Layout {
     int32_t peek;         // 1: the row-sharing sweep looks at two cells of a row before it fetches the row
     int32_t packed;       // not 0: instances of byte_status() keep the byte table: argmins in one byte, and
                           //    instead of cost rows what it takes to rebuild a cell (see PackTables); kAllBytes,
-                          //    or kRowsIfAlive: those on 64-bit keys not where most rows stay alive (see prep_kernel)
+                          //    or kRowsIfAlive: those on 64-bit keys not where most rows stay alive (see prep_kernel).
+                          //    kChain: one launch for all layers (see the chained sweep): argmins in one byte, whole
+                          //    cost rows of every layer at U[0], the workgroups' words at U[1]
     int32_t synth_l1;     // 1: the 32-bit-key sweep makes up layer 0's cells (a constant per strategy)
                           //    when it sweeps layer 1, so layer 0's row is never written nor read
     int32_t b_off, b_step; // a sweep launch covers instances b_off + z * b_step (dealt over streams)
@@ -347,6 +351,11 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
     // What the batch's sweeps really cover: the budget tiles of all instances, told to the host (a
     // word of pinned memory that the NEXT solve reads when it sizes its launches; the budgets live
     // on the device, and a solve never waits for one).
+    if (a.packed == kChain) {                      // nothing told yet (see chain_words)
+        int32_t *words = reinterpret_cast<int32_t *>(a.U[1]);
+        if (b == 0 && tid == 0) words[0] = 0;
+        for (int i = tid; i < a.n_tiles; i += kPrepThreads) words[kWave + ((int64_t)b * a.n_tiles + i) * kWordStep] = 0;
+    }
     if (a.seen && b == 0) {
         unsigned long long tiles = 0;
         for (int i = tid; i < a.B; i += kPrepThreads) {
@@ -492,7 +501,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
         h[3] = (int32_t)a.dclamp[b];
         h[4] = (ridx && l >= 1 && st >= 0) ? ridx[l] : 0;
         h[5] = 0;
-        h[6] = budget;
+        h[6] = a.packed == kChain && l > 1 && is_packed(a, st, b) ? kUnset : budget;
     }
     __syncthreads();
     if (!narrow_cells(st) && st != GALV_INSTANCE_OK_FAST_WIDE && st != GALV_INSTANCE_OK_U32_WIDE) return;
@@ -1661,6 +1670,7 @@ struct Key32 {
     static __device__ __forceinline__ T make(uint32_t rel, int k) { return rel << k; }
     static __device__ __forceinline__ uint32_t low(T key) { return key; }
     static __device__ __forceinline__ uint64_t cost(T key, int k) { return key >> k; }
+    static __device__ __forceinline__ T least(T x, T y) { return min(x, y); }
 };
 struct Key64 {
     using T = double;
@@ -1671,6 +1681,7 @@ struct Key64 {
     }
     static __device__ __forceinline__ uint32_t low(T key) { return (uint32_t)bits(key); }
     static __device__ __forceinline__ uint64_t cost(T key, int k) { return bits(key) >> k; }
+    static __device__ __forceinline__ T least(T x, T y) { return __builtin_fmin(x, y); }
 };
 
 // Smallest value over the wave's lanes, in every lane.
@@ -2290,6 +2301,574 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_bytes_kernel(Layout a, i
     }
 }
 
+// ------------------------------------------------------------- chained sweep
+//
+// All layers of a search in one launch, for launches whose layers are too small to hide what a launch per layer costs
+// (2.5 us from one empty launch to the next, 4 us with a kernel's first loads).  A workgroup owns 128
+// budget columns of one instance and takes them through the layers; layer l of its columns needs layer l - 1 of
+// columns at or below them only, so a workgroup waits for its left neighbours and never for a right one.
+//   * Workgroups take their places in the order in which they start (a counter, cleared by prep_kernel), columns
+//     ascending.  Whoever waits, waits for a place below its own, that is for a workgroup that runs already: the wait
+//     ends however few workgroups the GPU holds at a time, whatever else runs on it.
+//   * Costs pass between workgroups at agent scope, past the caches that other XCDs do not see; when all of a
+//     workgroup's stores have arrived it writes its word of the flags, and a reader reads its cells after it has
+//     seen the words of the blocks it needs.  (A fence per layer would write back and invalidate whole caches: 5 us
+//     with 64 workgroups, 18 with 256, against 1.3 for the words.)  One wave asks for all, and every word has a line
+//     of its own: with a word per wave and every wave asking, a layer of `single` below took 4.9 us instead of 3.6.
+//   * Every layer has rows of its own (no two layers share memory): nobody has to wait until others have read.
+// Rows are whole costs, [B][L][S_pad][e_pad], argmins one byte as in the byte table, and as there only the columns
+// [Y_l, X_l] are swept and stored: the first places of the order belong to one wave per instance that runs the
+// recurrence without a memory limit ahead of the sweep and tells each layer's X_l.
+//
+// What bounds it is the latency of a layer's chain: words 0.6 us, rows 0.8, column minima and alive rows 0.6, min-plus and
+// new cells 0.5, until the cells have arrived 0.5.  Whole searches, a launch per layer / chained, in us: 29 strategies x 78 tiles
+// x 37 layers (`single`) 248 / 166, 22 x 1032 x 32 281 / 215, 22 x 1256 x 24 with all budgets 239 / 200, 44 x 272 x 48 482 / 327.
+constexpr int kChainCols = 128;
+constexpr int kSpins = 1 << 21;                    // of some 0.6 us: no wait ends this way unless the memory order is broken
+
+template <class T>
+__device__ __forceinline__ T agent_load(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ void agent_store(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Words that workgroups tell each other: the counter of places, then [B][n_tiles] the last layer finished, each in a
+// line of its own (a line that many ask for answers them one after the other).
+__device__ __forceinline__ int32_t *chain_words(const Layout &a) { return reinterpret_cast<int32_t *>(a.U[1]); }
+__device__ __forceinline__ int32_t *chain_flags(const Layout &a, int b) {
+    return chain_words(a) + kWave + (int64_t)b * a.n_tiles * kWordStep;
+}
+template <class Cell>
+__device__ __forceinline__ Cell *chain_rows(const Layout &a, int b, int l) {
+    return reinterpret_cast<Cell *>(a.U[0] + ((int64_t)b * a.L + l) * a.S_pad * a.e_pad * 8);
+}
+
+// Until the blocks from `lo` to `hi` have finished layer `want`.
+__device__ __forceinline__ bool chain_wait(const int32_t *flags, int lo, int hi, int32_t want) {
+    const int lane = lane_id();
+    for (; lo <= hi; lo += kWave) {
+        bool waits = lo + lane <= hi;
+        for (int n = 0;; ++n) {
+            if (waits) waits = agent_load(flags + (int64_t)(lo + lane) * kWordStep) < want;   // (not asked for again)
+            if (__builtin_amdgcn_ballot_w64(waits) == 0) break;
+            if (n == kSpins) return false;
+            if (n >= 64)
+                __builtin_amdgcn_s_sleep(8);
+            else if (n >= 16)
+                __builtin_amdgcn_s_sleep(2);
+        }
+    }
+    asm volatile("" ::: "memory");
+    return true;
+}
+// X_l, once it is told.
+__device__ __forceinline__ bool chain_last_column(const int32_t *p, int32_t &x) {
+    for (int n = 0; x == kUnset; ++n) {
+        if (n == kSpins) return false;
+        __builtin_amdgcn_s_sleep(4);
+        x = uniform(agent_load(p));
+    }
+    return true;
+}
+
+// The recurrence without a memory limit for instance b, all layers (see live_step), by one wave with a lane per strategy:
+// no exchange, the transition keys in LDS.  (1.7 us a layer at 29 strategies, half of what the sweep takes.)
+template <int ROWS, class Key>
+__device__ __forceinline__ void chain_live(const Layout &a, int b, uint32_t dmax, int budget) {
+    using KeyT = typename Key::T;
+    const int lane = lane_id();
+    const int S = a.S, k = a.k_bits, L = a.L;
+    KeyT *Rl = reinterpret_cast<KeyT *>(lds_cells);                     // [S][ROWS]
+    int32_t *hdr = a.hdr + (int64_t)b * L * 8;
+    const uint64_t *costs = a.ck + (int64_t)b * L * ROWS;
+    const int32_t *mems = a.m + (int64_t)b * L * S;
+    const bool in = lane < S;
+    const uint32_t at = (uint32_t)(in ? lane : S - 1);         // this lane's strategy
+    struct Step {                                  // a layer's inputs, requested a layer ahead
+        uint64_t c;
+        int32_t m, r, least;
+    };
+    auto load = [&](int l, Step &to) {
+        l = l < L ? l : L - 1;
+        to.c = (costs + (int64_t)l * ROWS)[at];
+        to.m = (mems + (int64_t)l * S)[at];
+        to.r = (hdr + l * 8)[4];
+        to.least = (hdr + l * 8)[7];
+    };
+    Step now, next;
+    load(0, now);
+    load(1, next);
+    uint64_t V = now.c;
+    int32_t mem = 0, m = now.m;                    // memory in the layers before; of the layer at hand
+    int r_now = -1;
+    for (int l = 1; l < L; ++l) {
+        now = next;
+        const int r = uniform(now.r);
+        if (r != r_now) {
+            const KeyT *Rk = rkeys<KeyT>(a, b, r);
+            for (int i0 = 0; i0 < S; i0 += 8) {    // (eight rows under way at a time, the last one repeated)
+                KeyT row[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) row[u] = (Rk + (i0 + u < S ? i0 + u : S - 1) * ROWS)[at];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (i0 + u < S && in) Rl[(i0 + u) * ROWS + lane] = row[u];
+            }
+            r_now = r;
+        }
+        load(l + 1, next);
+        const bool usable = in && m <= budget;
+        const uint64_t mine = usable ? V : ~0ull;
+        const uint32_t hi = wave_min((uint32_t)(mine >> 32));
+        const uint32_t lo = wave_min((uint32_t)(mine >> 32) == hi ? (uint32_t)mine : 0xffffffffu);
+        const uint64_t vmin = (uint64_t)hi << 32 | lo;
+        if (vmin == ~0ull) {                       // nothing reachable from here on
+            if (lane == 0)
+                for (int q = l > 1 ? l : 2; q < L; ++q) agent_store(hdr + q * 8 + 6, -1);
+            return;
+        }
+        const int64_t with = (int64_t)mem + m;     // memory with the former layer, saturating just above the budget
+        const int32_t upto = (int32_t)(with <= budget ? with : (int64_t)budget + 1);
+        // (an unusable strategy costs as much as one that is ruled out)
+        const uint64_t rel = V - vmin;
+        const uint32_t dv = usable && rel < dmax ? (uint32_t)rel : dmax;
+        KeyT best = Key::none();
+        for (int i0 = 0; i0 < S; i0 += 8) {
+            KeyT row[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) row[u] = Rl[(i0 + u < S ? i0 + u : S - 1) * ROWS + at];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) best = Key::least(best, Key::make(read_lane(dv, i0 + u < S ? i0 + u : S - 1), k) + row[u]);
+        }
+        const int32_t x = __shfl(upto, (int)(Key::low(best) & ((1u << k) - 1u)), kWave);
+        V = vmin + Key::cost(best, k) + now.c;
+        mem = x;
+        m = now.m;
+        const uint32_t top = ~wave_min(~(in && m <= budget ? (uint32_t)x : 0u));
+        const int64_t fits = (int64_t)budget - uniform(now.least);       // beyond it nobody reads layer l
+        // (layer 1 is being swept up to prep_kernel's bound: every wave has to see the same one)
+        if (l > 1 && lane == 0) agent_store(hdr + l * 8 + 6, (int32_t)((int64_t)top < fits ? (int64_t)top : fits));
+    }
+}
+
+// A buffer over the rows of one layer, for loads and stores at agent scope of several cells at once: a wave-uniform offset
+// and one that no row changes per lane cost no address arithmetic.
+constexpr int kAgent = 16;                         // (the sc1 bit: what relaxed atomics at agent scope carry)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t chain_buffer(void *rows) {
+    return __builtin_amdgcn_make_buffer_rsrc(rows, 0, 0xffffffffu, 0x00020000);
+}
+template <class Cell>
+__device__ __forceinline__ void buffer_cells(__amdgpu_buffer_rsrc_t rows, uint32_t lane_off, uint32_t off, Cell (&out)[2]) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    if constexpr (sizeof(Cell) == 4) {
+        const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rows, (int)lane_off, (int)off, kAgent));
+        out[0] = v[0];
+        out[1] = v[1];
+    } else {
+        const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, (int)lane_off, (int)off, kAgent));
+        out[0] = (uint64_t)v[1] << 32 | v[0];
+        out[1] = (uint64_t)v[3] << 32 | v[2];
+    }
+}
+template <class Cell>
+__device__ __forceinline__ void buffer_store_cells(__amdgpu_buffer_rsrc_t rows, uint32_t lane_off, uint32_t off, const Cell (&in)[2]) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    if constexpr (sizeof(Cell) == 4) {
+        const u32x2 v = {in[0], in[1]};
+        __builtin_amdgcn_raw_buffer_store_b64(v, rows, (int)lane_off, (int)off, kAgent);
+    } else {
+        // (the whole offset per lane: behind a store of 16 bytes with a scalar offset the compiler leaves no wait states
+        // before the data registers are written again, and the first cell of some lanes was then lost)
+        const u32x4 v = {(uint32_t)in[0], (uint32_t)(in[0] >> 32), (uint32_t)in[1], (uint32_t)(in[1] >> 32)};
+        __builtin_amdgcn_raw_buffer_store_b128(v, rows, (int)(lane_off + off), 0, kAgent);
+    }
+}
+
+// What a layer's sweep needs to know, requested a layer ahead.
+struct ChainIn {
+    uint64_t ent;                                  // list entry `lane` of the former layer
+    int32_t h;                                     // header record, lane i word i
+    uint64_t ck;                                   // c(l, first strategy of the wave + lane)
+    int32_t x;                                     // X_l as far as told (wave 0)
+};
+template <int TS, int NG>
+__device__ __forceinline__ void chain_load(const Layout &a, int wave, int b, int l, ChainIn &in) {
+    const int lane = lane_id();
+    const int64_t row = (int64_t)b * a.L + l;
+    const uint64_t *list = a.vlist + (row - 1) * (TS * NG), *cost = a.ck + row * (TS * NG) + wave * TS;
+    int32_t *record = a.hdr + row * 8;
+    in.ent = list[(uint32_t)(lane < TS * NG ? lane : TS * NG - 1)];
+    in.h = record[(uint32_t)lane & 7];
+    in.ck = cost[(uint32_t)(lane < TS ? lane : TS - 1)];
+    in.x = 0;
+    if (wave == 0) in.x = agent_load(record + 6);
+}
+
+// One workgroup's columns, layers 1 to L - 1: byte_status() instances.  As in sweep_u32_shared a wave owns the rows
+// g, g + NG, ... of the former layer's list and the strategies g * TS on; the column minima meet in LDS, and the rows
+// that are alive in the tile, all of which fit, are reduced by every wave, with the transition keys from LDS.  Wave 0 does the waiting for all.
+template <int TS, int NG, class Cell, class Key>
+__device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, int t, uint32_t dmax, ChainIn &in, uint64_t c0) {
+    constexpr Cell kInfCell = sizeof(Cell) == 8 ? (Cell)kInf : (Cell)kInf32;
+    constexpr Cell kAllOnes = ~(Cell)0;
+    constexpr int kCols = kChainCols, TE = kCols / kWave, kRows = TS * NG;
+    static_assert(kRows <= kWave, "list positions by lane");
+    using KeyT = typename Key::T;
+    using Word = std::conditional_t<sizeof(Cell) == 8, unsigned long long, uint32_t>;
+    typedef uint32_t relv __attribute__((ext_vector_type(TE)));
+    const int lane = lane_id();
+    const int S = a.S, S_pad = kRows, L = a.L, k = a.k_bits;
+    const int start = t * kCols, e0 = start + lane * TE;
+    const uint32_t lane_off = (uint32_t)lane * TE * (uint32_t)sizeof(Cell);
+    int32_t *flags = chain_flags(a, b);
+    Word *minima = reinterpret_cast<Word *>(lds_cells);                     // [2][kCols] of the columns, in turns
+    unsigned long long *alive_of = reinterpret_cast<unsigned long long *>(minima + 2 * kCols);   // [2] list positions
+    KeyT *Rl = reinterpret_cast<KeyT *>(alive_of + 2);                      // [kRows][kRows] transition keys
+    uint32_t *keys = reinterpret_cast<uint32_t *>(Rl + kRows * kRows);      // [kRows][kCols] relative costs by list position
+    int32_t *last_of = reinterpret_cast<int32_t *>(keys + kRows * kCols);   // [2] X_l, by layer modulo 2
+
+    auto load = [&](int l, ChainIn &in) { chain_load<TS, NG>(layout_again(), wave, b, l < L ? l : L - 1, in); };
+    // (Here the loads have arrived.  Left to itself the compiler waits for them at the top of the loop, where it cannot
+    // tell them from the stores behind them and waits for those too.)
+    auto settle = [&](ChainIn &in) { asm volatile("" : "+v"(in.ent), "+v"(in.h), "+v"(in.ck), "+v"(in.x)); };
+    settle(in);
+    int32_t *records = a.hdr + (int64_t)b * L * 8;
+    int r_now = -1;
+    int y_prev = 0, x_prev = 0;
+    int turn = 0;
+    auto clear = [&](int h) {
+        Word *p = minima + h * kCols + lane * TE;
+#pragma unroll
+        for (int j = 0; j < TE; ++j) p[j] = kAllOnes;
+        if (lane == 0) alive_of[h] = 0;
+    };
+    if (wave == 0) {                               // (the first layer's barrier is ahead)
+        clear(0);
+        clear(1);
+    }
+    uint32_t bytes[TS];                            // the former layer's argmins, not stored yet
+    int unstored = 0;                              // of which layer (0: none)
+    auto store_bytes = [&] {
+        const Layout &al = layout_again();
+        const uint32_t pitch = (uint32_t)al.e_pad;
+        const int s0 = wave * TS;
+        const __amdgpu_buffer_rsrc_t to = chain_buffer(byte_rows(al, b, unstored) + (int64_t)s0 * pitch + start);
+#pragma unroll
+        for (int s = 0; s < TS; ++s)
+            if (s0 + s < S) __builtin_amdgcn_raw_buffer_store_b16((short)bytes[s], to, lane * 2, (int)(s * pitch), 0);
+    };
+    for (int l = 1; l < L; ++l) {
+        // (What follows from these is worked out where it is used: kept from before the loop it would fill the scalar
+        // registers and be spilled into vector lanes.)
+        int g = wave;
+        uint32_t pitch = (uint32_t)a.e_pad;        // (a layer's rows are below 4 GB, see make_plan)
+        asm volatile("" : "+s"(g), "+s"(pitch));
+        const int s0 = g * TS;
+        const int n = (int)read_lane((uint32_t)in.h, 2), r_sel = (int)read_lane((uint32_t)in.h, 4);
+        const int y = (int)read_lane((uint32_t)in.h, 5);
+        if (start + kCols - 1 < y) break;          // nothing reachable here, in this layer and from it on
+        if (g == 0) {
+            int x = uniform(in.x);
+            bool told = chain_last_column(records + l * 8 + 6, x);
+            if (told && l > 1 && start <= x && y <= x) {
+                // the former layer's blocks from the largest memory's shift to the smallest one's, but for the own one
+                const uint32_t shift = (uint32_t)(in.ent >> 32);
+                const int sh_lo = (int)wave_min(shift), sh_hi = (int)~wave_min(~shift);
+                const int lo = min(max(start - sh_hi, y_prev), x_prev) / kCols;
+                const int hi = start + kCols - 1 - sh_lo < y_prev ? -1 : min(min(start + kCols - 1 - sh_lo, x_prev) / kCols, t - 1);
+                told = chain_wait(flags, lo, hi, l - 1);
+            }
+            if (lane == 0) last_of[l & 1] = told ? x : kUnset;
+        }
+        // (meanwhile: which rows of the list lie inside the stored columns, and which nowhere reachable; where they begin)
+        const int shift_of = (int)(uint32_t)(in.ent >> 32);
+        const uint64_t inside = __builtin_amdgcn_ballot_w64(start - shift_of >= y_prev && start + kCols - 1 - shift_of <= x_prev);
+        const uint64_t dead = __builtin_amdgcn_ballot_w64(start + kCols - 1 - shift_of < y_prev);
+        const uint32_t off = ((uint32_t)in.ent * pitch + (uint32_t)(start - shift_of)) * (uint32_t)sizeof(Cell);
+        __syncthreads();
+        const int x = uniform(last_of[l & 1]);
+        if (x == kUnset) {
+            a.status[b] = GALV_INSTANCE_BAD_VALUE;
+            return;
+        }
+        if (y > x) break;                          // nothing reachable anywhere
+        if (start > x) {                           // constant here: nothing to store
+            load(l + 1, in);
+            settle(in);
+            y_prev = y;
+            x_prev = x;
+            continue;
+        }
+        const KeyT *Rk = rkeys<KeyT>(layout_again(), b, r_sel);
+        if (r_sel != r_now) {                      // (used two barriers on; last read before the latest one)
+            for (int i = g; i < S; i += NG)
+                if (lane < kRows) Rl[i * kRows + lane] = (Rk + (int64_t)i * S_pad)[lane];
+            r_now = r_sel;
+        }
+        Cell row[TS][TE];
+        if (l == 1) {
+#pragma unroll
+            for (int r = 0; r < TS; ++r) {
+                const int shift = (int)read_lane((uint32_t)(in.ent >> 32), g + NG * r);
+                const Cell cp = (Cell)read_lane(c0, g + NG * r);
+#pragma unroll
+                for (int j = 0; j < TE; ++j) row[r][j] = e0 + j >= shift ? cp : kInfCell;
+            }
+        } else {
+            // (past its end the list repeats its last entry)
+            const __amdgpu_buffer_rsrc_t rows = chain_buffer(chain_rows<Cell>(a, b, l - 1));
+#pragma unroll
+            for (int r = 0; r < TS; ++r) {
+                const int i = g + NG * r;
+                if (inside >> i & 1) {
+                    buffer_cells(rows, lane_off, read_lane(off, i), row[r]);
+                } else if (dead >> i & 1) {
+#pragma unroll
+                    for (int j = 0; j < TE; ++j) row[r][j] = kInfCell;
+                } else {
+                    const uint64_t en = read_lane(in.ent, i);
+                    const uint32_t first = (uint32_t)en * pitch * (uint32_t)sizeof(Cell);
+                    const int at = e0 - (int)(uint32_t)(en >> 32);
+#pragma unroll
+                    for (int j = 0; j < TE; ++j) {
+                        const uint32_t cell = (uint32_t)(at + j >= y_prev ? min(at + j, x_prev) : x_prev) * (uint32_t)sizeof(Cell);
+                        if constexpr (sizeof(Cell) == 4)
+                            row[r][j] = (Cell)__builtin_amdgcn_raw_buffer_load_b32(rows, (int)cell, (int)first, kAgent);
+                        else
+                            row[r][j] = __builtin_bit_cast(Cell, __builtin_amdgcn_raw_buffer_load_b64(rows, (int)cell, (int)first, kAgent));
+                    }
+#pragma unroll
+                    for (int j = 0; j < TE; ++j)
+                        if (at + j < y_prev) row[r][j] = kInfCell;
+                }
+            }
+            if (unstored) store_bytes();           // (behind the loads: nobody waits for them)
+            unstored = 0;
+        }
+        const uint32_t list = (uint32_t)in.ent;
+        const uint64_t ck = in.ck;
+        load(l + 1, in);
+        Word *now = minima + turn * kCols + lane * TE;
+#pragma unroll
+        for (int j = 0; j < TE; ++j) {
+            Cell v = row[0][j];
+#pragma unroll
+            for (int r = 1; r < TS; ++r) v = min(v, row[r][j]);
+            atomicMin(now + j, (Word)v);
+        }
+        __syncthreads();
+        // (an unreachable column's rows are far above 0, so that none of them counts as alive there)
+        Cell cmin[TE], from[TE];
+#pragma unroll
+        for (int j = 0; j < TE; ++j) {
+            cmin[j] = (Cell)now[j];
+            from[j] = cmin[j] < kInfCell ? cmin[j] : 0;
+        }
+        unsigned long long mine = 0;
+#pragma unroll
+        for (int r = 0; r < TS; ++r) {
+            relv d;
+            uint32_t least = dmax;
+#pragma unroll
+            for (int j = 0; j < TE; ++j) {
+                d[j] = (uint32_t)min(row[r][j] - from[j], (Cell)dmax);
+                least = min(least, d[j]);
+            }
+            *reinterpret_cast<relv *>(keys + (g + NG * r) * kCols + lane * TE) = d;
+            if (__builtin_amdgcn_ballot_w64(least < dmax) != 0 && g + NG * r < n)      // wave-uniform
+                mine |= 1ull << (g + NG * r);
+        }
+        if (lane == 0 && mine) atomicOr(alive_of + turn, mine);
+        __syncthreads();
+        const uint64_t alive = read_lane((uint64_t)alive_of[turn], 0);
+        KeyT acc[TS][TE];
+#pragma unroll
+        for (int s = 0; s < TS; ++s)
+#pragma unroll
+            for (int j = 0; j < TE; ++j) acc[s][j] = Key::none();
+        for (uint64_t left = alive; left;) {       // two rows at a time; an odd one twice
+            const int i = __builtin_ctzll(left);
+            left &= left - 1;
+            const int i2 = left ? __builtin_ctzll(left) : i;
+            left &= left - 1;                      // (0 stays 0)
+            const relv da = *reinterpret_cast<const relv *>(keys + i * kCols + lane * TE);
+            const relv db = *reinterpret_cast<const relv *>(keys + i2 * kCols + lane * TE);
+            const KeyT *Ra = Rl + read_lane(list, i) * kRows + s0, *Rb = Rl + read_lane(list, i2) * kRows + s0;
+            KeyT va[TE], vb[TE], ra[TS], rb[TS];
+#pragma unroll
+            for (int s = 0; s < TS; ++s) {
+                ra[s] = Ra[s];
+                rb[s] = Rb[s];
+            }
+#pragma unroll
+            for (int j = 0; j < TE; ++j) {
+                va[j] = Key::make(da[j], k);
+                vb[j] = Key::make(db[j], k);
+            }
+#pragma unroll
+            for (int s = 0; s < TS; ++s)
+#pragma unroll
+                for (int j = 0; j < TE; ++j) acc[s][j] = Key::least(Key::least(acc[s][j], va[j] + ra[s]), vb[j] + rb[s]);
+        }
+        if (s0 < S) {
+            const __amdgpu_buffer_rsrc_t out = chain_buffer(chain_rows<Cell>(a, b, l) + (int64_t)s0 * pitch + start);
+            const uint32_t mask = ((1u << k) - 1u) * 0x0101u;
+#pragma unroll
+            for (int s = 0; s < TS; ++s)
+                if (s0 + s < S) {
+                    const Cell cs = (Cell)read_lane(ck, s);
+                    Cell v[TE];
+#pragma unroll
+                    for (int j = 0; j < TE; ++j) v[j] = cmin[j] < kInfCell ? cmin[j] + (Cell)Key::cost(acc[s][j], k) + cs : kInfCell;
+                    buffer_store_cells(out, lane_off, (uint32_t)s * pitch * (uint32_t)sizeof(Cell), v);
+                }
+#pragma unroll
+            for (int s = 0; s < TS; ++s)
+                bytes[s] = __builtin_amdgcn_perm(Key::low(acc[s][1]), Key::low(acc[s][0]), 0x0c0c0400u) & mask;
+            unstored = l;
+        }
+        if (g == NG - 1 && lane == 0) {            // statistics: every listed row is read
+            const Layout &al = layout_again();
+            uint32_t *st = al.stats + 2 * (((int64_t)b * (L - 1) + (l - 1)) * al.n_tiles + t);
+            st[0] = (uint32_t)__builtin_popcountll(alive) << 16 | (uint32_t)n;
+            st[1] = (uint32_t)n;
+        }
+        turn ^= 1;
+        if (g == NG / 2) clear(turn);              // (read a layer ago; the barrier below is before its next use)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the cells have arrived
+        settle(in);
+        __syncthreads();
+        if (g == 0 && lane == 0) agent_store(flags + (int64_t)t * kWordStep, l);
+        y_prev = y;
+        x_prev = x;
+    }
+    if (unstored) store_bytes();
+}
+
+// The same for the other instances: 64-bit integers, every candidate, plain back-pointers.
+template <int TS, int NG>
+__device__ __forceinline__ void chain_int64(const Layout &a, int g, int b, int t, int budget) {
+    const int lane = lane_id();
+    const int S = a.S, L = a.L;
+    const int64_t pitch = a.e_pad;
+    constexpr int TE = kChainCols / kWave;
+    const int start = t * kChainCols, s0 = g * TS;
+    if (start > budget) return;
+    int32_t *flags = chain_flags(a, b);
+    int32_t *ready = reinterpret_cast<int32_t *>(lds_cells);   // [2] by layer modulo 2
+    for (int l = 1; l < L; ++l) {
+        if (g == 0) {
+            const bool ok = l == 1 || chain_wait(flags, 0, t - 1, l - 1);
+            if (lane == 0) ready[l & 1] = ok ? 1 : 0;
+        }
+        __syncthreads();
+        if (uniform(ready[l & 1]) == 0) {
+            a.status[b] = GALV_INSTANCE_BAD_VALUE;
+            return;
+        }
+        const int64_t row0 = (int64_t)b * L + l - 1;
+        const int32_t *m = a.m + row0 * S;
+        const int64_t *c = a.c + row0 * S;
+        const int r_sel = a.r_idx ? a.r_idx[row0 + 1] : 0;
+        const int64_t *R = a.R + ((int64_t)b * a.nR + r_sel) * S * S;
+        const int64_t *rows = chain_rows<int64_t>(a, b, l - 1);
+        int64_t best[TS][TE];
+        int32_t arg[TS][TE];
+#pragma unroll
+        for (int s = 0; s < TS; ++s)
+#pragma unroll
+            for (int j = 0; j < TE; ++j) {
+                best[s][j] = kInf;
+                arg[s][j] = -1;
+            }
+        for (int sp = 0; sp < S && s0 < S; ++sp) {
+            const int shift = uniform(m[sp]);
+            if (shift > budget) continue;          // whole column is infinity
+            int64_t v[TE];
+#pragma unroll
+            for (int j = 0; j < TE; ++j) {
+                const int e = start + lane * TE + j;
+                if (l == 1)
+                    v[j] = e >= shift ? c[sp] : kInf;
+                else
+                    v[j] = e >= shift && e <= budget ? agent_load(rows + (int64_t)sp * pitch + (e - shift)) : kInf;
+            }
+#pragma unroll
+            for (int s = 0; s < TS; ++s) {
+                const int64_t rk = R[(int64_t)sp * S + (s0 + s < S ? s0 + s : S - 1)];
+#pragma unroll
+                for (int j = 0; j < TE; ++j)
+                    if (v[j] + rk < best[s][j]) {  // strict: lowest s' keeps ties
+                        best[s][j] = v[j] + rk;
+                        arg[s][j] = sp;
+                    }
+            }
+        }
+        int64_t *out = chain_rows<int64_t>(a, b, l);
+        const int64_t bp0 = ((int64_t)b * (L - 1) + (l - 1)) * S * pitch;
+#pragma unroll
+        for (int s = 0; s < TS; ++s)
+            if (s0 + s < S) {
+                const int64_t cs = c[S + s0 + s];
+#pragma unroll
+                for (int j = 0; j < TE; ++j) {
+                    const int e = start + lane * TE + j;
+                    const bool dead = best[s][j] >= kInf;
+                    agent_store(out + (int64_t)(s0 + s) * pitch + e, dead ? kInf : best[s][j] + cs);
+                    static_cast<int32_t *>(a.bp)[bp0 + (int64_t)(s0 + s) * pitch + e] = dead ? -1 : arg[s][j];
+                }
+            }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the cells have arrived
+        __syncthreads();
+        if (g == 0 && lane == 0) agent_store(flags + (int64_t)t * kWordStep, l);
+    }
+}
+
+// (4 waves per SIMD at least: no vector register is spilled)
+template <int TS, int NG>
+__global__ __launch_bounds__(NG * kWave, 4) void chain_kernel(Layout a, int) {
+    const int wave = uniform(threadIdx.x >> 6);
+    if (wave == 0 && lane_id() == 0) lds_cells[0] = (uint32_t)atomicAdd(chain_words(a), 1);
+    __syncthreads();
+    const int place = uniform((int)lds_cells[0]);
+    __syncthreads();
+    const int b = place % a.B, t = place / a.B - 1;            // (t = -1: the places of the unlimited recurrence)
+    // (all that is needed first in one round trip)
+    ChainIn in;
+    chain_load<TS, NG>(a, wave, b, 1, in);
+    // layer 0's costs, in the order of its list
+    const uint64_t c0 = (a.vcost + (int64_t)b * a.L * (TS * NG))[(uint32_t)(lane_id() < TS * NG ? lane_id() : TS * NG - 1)];
+    const int st = (int)read_lane((uint32_t)in.h, 0), budget = (int)read_lane((uint32_t)in.h, 1);
+    const uint32_t dmax = read_lane((uint32_t)in.h, 3);
+    if (st < 0 || t * kChainCols > budget) return;
+    const bool keys32 = st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE;
+    const bool packed = byte_status(st, dmax);
+    if (t < 0) {
+        if (!packed || wave != 0) return;
+        if (keys32)
+            chain_live<TS * NG, Key32>(layout_again(), b, dmax, budget);
+        else
+            chain_live<TS * NG, Key64>(layout_again(), b, dmax, budget);
+    } else if (st == GALV_INSTANCE_OK_FAST_U32) {
+        chain_tiles<TS, NG, uint32_t, Key32>(layout_again(), wave, b, t, dmax, in, c0);
+    } else if (packed && keys32) {
+        chain_tiles<TS, NG, uint64_t, Key32>(layout_again(), wave, b, t, dmax, in, c0);
+    } else if (packed) {
+        chain_tiles<TS, NG, uint64_t, Key64>(layout_again(), wave, b, t, dmax, in, c0);
+    } else {
+        chain_int64<TS, NG>(layout_again(), wave, b, t, budget);
+    }
+}
+constexpr unsigned chain_lds(int ts, int ng) {
+    // minima of 8-byte cells, alive rows, transition keys of 8 bytes, keys, X_l
+    const int rows = ts * ng, cols = kChainCols;
+    return (unsigned)(2 * cols * 8 + 2 * 8 + rows * rows * 8 + rows * cols * 4 + 8);
+}
+
 // ------------------------------------------------- final minimum and backtrack
 
 // C[L-1][e][s] from the un-shifted last row, as an integer (GALV_INF if none).
@@ -2297,10 +2876,17 @@ __device__ __forceinline__ int64_t last_layer_cost(const Layout &a, int b, int s
                                                    int64_t s) {
     const int64_t shift = a.m[((int64_t)b * a.L + (a.L - 1)) * a.S + s];
     if (shift > e) return kInf;
+    if (a.packed == kChain && !is_packed(a, st, b)) return chain_rows<int64_t>(a, b, a.L - 1)[s * a.e_pad + e - shift];
     if (is_packed(a, st, b)) {
         const int32_t *h = a.hdr + ((int64_t)b * a.L + (a.L - 1)) * 8;
         if (e - shift < h[5]) return kInf;
         const int64_t x = e - shift < h[6] ? e - shift : h[6];
+        if (a.packed == kChain) {
+            const int64_t at = s * a.e_pad + x;
+            if (st == GALV_INSTANCE_OK_FAST_U32) return Narrow::to_int64(chain_rows<uint32_t>(a, b, a.L - 1)[at], a.k_bits);
+            const uint64_t v = chain_rows<uint64_t>(a, b, a.L - 1)[at];
+            return v >= (uint64_t)kInf ? kInf : (int64_t)v;
+        }
         const PackTables t = pack_tables(a, (a.L - 1) & 1, b);
         const uint32_t sp = byte_rows(a, b, a.L - 1)[(int64_t)s * a.e_pad + x];
         const bool keys32 = st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE;
@@ -2577,6 +3163,31 @@ __device__ __forceinline__ void best_at_bytes(const Layout &a, int b, int e, int
     }
 }
 
+// The same from the rows of the chained sweep.
+template <class Cell>
+__device__ __forceinline__ void best_at_rows(const Layout &a, int b, int e, int64_t &opt, int32_t &last) {
+    constexpr Cell kInfCell = sizeof(Cell) == 8 ? (Cell)kInf : (Cell)kInf32;
+    const int32_t *h = a.hdr + ((int64_t)b * a.L + (a.L - 1)) * 8;
+    const int y = h[5], top = h[6];
+    opt = kInf;
+    last = -1;
+    if (y > top) return;                           // nothing reachable, nothing stored
+    const Cell *rows = chain_rows<Cell>(a, b, a.L - 1);
+    const int32_t *m = a.m + ((int64_t)b * a.L + (a.L - 1)) * a.S;
+    Cell least = kInfCell;
+#pragma unroll 4
+    for (int s = 0; s < a.S; ++s) {
+        const int at = e - m[s];
+        const bool ok = at >= y;                   // (memories are not negative, and y is not)
+        const Cell v = rows[(int64_t)s * a.e_pad + (ok && at < top ? at : top)];
+        if (ok && v < least) {
+            least = v;
+            last = s;
+        }
+    }
+    if (last >= 0) opt = (int64_t)least;
+}
+
 // The optimum of every budget column.  Grid: (column tiles, B).
 __global__ __launch_bounds__(kThreads) void best_per_budget_kernel(Layout a, int64_t *best_cost,
                                                                    int32_t *best_last) {
@@ -2589,6 +3200,10 @@ __global__ __launch_bounds__(kThreads) void best_per_budget_kernel(Layout a, int
     if (st >= 0 && e <= a.budget[b]) {
         if (!is_packed(a, st, b))
             best_at(a, b, st, e, opt, last);
+        else if (a.packed == kChain && st == GALV_INSTANCE_OK_FAST_U32)
+            best_at_rows<uint32_t>(a, b, (int)e, opt, last);
+        else if (a.packed == kChain)
+            best_at_rows<uint64_t>(a, b, (int)e, opt, last);
         else if (st == GALV_INSTANCE_OK_FAST_U32)
             best_at_bytes<uint32_t, Key32>(a, b, (int)e, opt, last);
         else if (st == GALV_INSTANCE_OK_U32_WIDE)
@@ -2874,7 +3489,33 @@ VariantEntry variant_entry() {
             pack};
 }
 
-enum class Tiles { wide, normal, split, fine };
+enum class Tiles { wide, normal, split, fine, chain };
+
+// Shapes of the chained sweep: strategies and rows per wave, waves.  Few tiles take more, thinner waves: their time is a
+// layer's latency.  Many take fewer: what a wave does beside its rows and strategies (words, list, scalars) then keeps the
+// SIMDs busy, and the more workgroups are resident the sooner a block to the right begins.  Whole searches over the
+// time with a launch per layer, thin / fat, layers alike - deep stacks - deep stacks in nanoseconds: 12 strategies x 504 tiles
+// 0.66 0.64 0.42 / 0.70 0.66 0.46, x 2064 0.85 0.89 0.57 / 0.74 0.75 0.51; 22 x 504 0.65 0.65 0.43 / 0.74 0.70 0.48, x 1032 0.86 0.91
+// 0.64 / 0.82 0.75 0.54; 30 x 700 0.84 0.87 0.63 / 0.88 0.76 0.56; 44 x 252 0.67 0.71 0.49 / 0.77 0.76 0.55, x 504 0.85 0.86 0.65 /
+// 0.80 0.70 0.52; 60 x 252 0.75 0.69 0.49 / 0.90 0.75 0.54, x 504 0.87 0.92 0.71 / 0.85 0.76 0.58.
+struct ChainEntry {
+    int ts, ng;
+    int64_t tiles;         // up to so many tiles in a layer of the whole batch
+    SweepFn fn;
+};
+template <int TS, int NG>
+ChainEntry chain_entry(int64_t tiles) {
+    return {TS, NG, tiles, chain_kernel<TS, NG>};
+}
+const ChainEntry *pick_chain(int S, int64_t tiles) {
+    constexpr int64_t any = INT64_MAX;
+    static const ChainEntry table[] = {chain_entry<2, 4>(any),  chain_entry<2, 8>(768),  chain_entry<4, 4>(any), chain_entry<3, 8>(768),
+                                       chain_entry<6, 4>(any),  chain_entry<4, 8>(704),  chain_entry<8, 4>(any), chain_entry<3, 16>(352),
+                                       chain_entry<6, 8>(any),  chain_entry<4, 16>(352), chain_entry<8, 8>(any)};
+    for (const ChainEntry &t : table)
+        if (S <= t.ts * t.ng && tiles <= t.tiles) return &t;
+    return nullptr;
+}
 
 // wide: the launch fills the chip; take the 256-column twin where there is one.  split, fine: it
 // leaves wavefront slots idle; take the twin with more waves per tile.
@@ -2945,8 +3586,9 @@ struct Plan {
 int64_t launch_tiles(const galv_dp_desc_t &d) { return ((int64_t)d.max_budget / 128 + 1) * d.n_instances; }
 constexpr int64_t kFullChip = 3072;
 
-// `only`: the shape to take instead of the one the rules below choose (the flags still override it).
-galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, Plan *p) {
+// `only`: the shape to take instead of the one the rules below choose (the flags still override it); `chain`: the chained
+// sweep may be chosen.
+galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, bool chain, Plan *p) {
     if (!d) return fail(GALV_ERR_INVALID_ARG, "desc is NULL");
     if (d->n_instances < 1 || d->n_layers < 1 || d->n_strategies < 1 || d->max_budget < 0 ||
         d->n_transition < 1)
@@ -3023,11 +3665,31 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, Plan *p) {
         shape = Tiles::fine;
     else if (tiles <= split_to)
         shape = Tiles::split;
+    // All layers in one launch (the chained sweep), up to 64 strategies.  It wins by what a launch per layer costs, and loses
+    // where the byte table's peek leaves out most of what it reads: where a layer has many tiles and its share of the budget
+    // spans several.  Where the share is below a tile the other side keeps cost rows, and the line lies further out.  Whole
+    // searches over the time with a launch per layer, layers alike - deep stacks - independent layers - deep stacks in nanoseconds
+    // - layers alike in nanoseconds with tenfold transition costs:
+    //   share 700:  12 x 4950 0.79 0.85 0.50 0.73 0.48, x 9020 1.03 1.28 0.63 1.03 0.65; 22 x 2200 0.89 0.85 0.70 0.76 0.54, x 3520 0.91 1.04 0.70
+    //   0.87 0.61; 30 x 990 0.87 0.76 0.76 0.62 0.48, x 1540 0.95 1.02 0.75 0.93 0.56; 44 x 660 0.83 0.91 0.73 0.73 0.52, x 990 1.00 1.07 0.62 0.96
+    //   0.55, x 2200 1.03 1.54 0.37 1.43 0.73; 60 x 660 0.94 0.99 0.76 0.85 0.57, x 990 0.93 1.09 0.63 0.93 0.57
+    //   share 100:  22 x 3458 0.67 0.88 0.45 0.73 0.50; 30 x 2166 0.67 0.83 0.41 0.58 0.46, x 3458 0.70 1.06 0.44 0.87 0.57; 44 x 1368 0.73 0.96 0.42
+    //   0.65 0.54; 60 x 990 0.76 0.90 0.45 0.44 0.43.  (Beyond 64 strategies: 100 x 252 1.02 0.96 0.80 0.72, x 1032 1.43 1.79 0.56 1.87.)
+    const uint32_t other = GALV_DP_BP_U8 | GALV_DP_NO_U32 | GALV_DP_NO_PEEK | GALV_DP_FORCE_PEEK | GALV_DP_NO_PACK | GALV_DP_FORCE_PACK |
+                           GALV_DP_FORCE_WIDE_TILES | GALV_DP_NO_WIDE_TILES;        // (what these ask for is a launch per layer)
+    const int64_t chain_to = share < 128 ? 80000 : S <= 24 ? 60000 : 40000;
+    const ChainEntry *ce = S <= kWave ? pick_chain(S, tiles) : nullptr;
+    // (rows of every layer: at most 8 GB of them, and a layer's of one instance within 32 bits of offset)
+    const long double chain_bytes = ce ? 8.0L * ce->ts * ce->ng * ((int64_t)d->max_budget + kChainCols) : 0;
+    if (chain && ce && !(d->flags & other) && ((d->flags & GALV_DP_STREAMS_MASK) >> GALV_DP_STREAMS_SHIFT) <= 1 && d->n_layers > 1 &&
+        tiles * S <= chain_to && chain_bytes < 4.0e9L && chain_bytes * d->n_instances * d->n_layers <= 8.0e9L)
+        shape = Tiles::chain;
     if (only) shape = *only;
     if (d->flags & GALV_DP_FORCE_WIDE_TILES) shape = Tiles::wide;
     if (d->flags & GALV_DP_NO_WIDE_TILES) shape = Tiles::normal;
+    if (shape != Tiles::chain) ce = nullptr;
     const VariantEntry &ve = pick_variant(S, shape);
-    const Variant v = ve.v;
+    const Variant v = ce ? Variant{ce->ts, kChainCols / kWave, ce->ng, ce->ng, 1, 4, 0} : ve.v;
     Layout &a = p->lay;
     a.B = d->n_instances;
     a.L = d->n_layers;
@@ -3035,7 +3697,7 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, Plan *p) {
     a.E_max = d->max_budget;
     a.nR = d->n_transition;
     a.bp_u8 = u8 ? 1 : 0;
-    a.synth_l1 = v.share ? 1 : 0;
+    a.synth_l1 = v.share || ce ? 1 : 0;
     const int group = v.ts * v.ng;
     p->groups_y = (a.S + group - 1) / group;
     a.S_pad = p->groups_y * group;
@@ -3063,19 +3725,24 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, Plan *p) {
     if (d->flags & GALV_DP_NO_PEEK) a.peek = 0;
     if (d->flags & GALV_DP_FORCE_PEEK) a.peek = 1;
     bool packed = v.share && pays;
+    if (ce) {
+        p->lds_bytes = chain_lds(v.ts, v.ng);
+        a.peek = 0;
+        a.e_pad = (int64_t)round_up((size_t)a.E_max + 1, (size_t)a.tile_e);
+    }
     if ((d->flags & GALV_DP_FORCE_PACK) && v.share && !u8) packed = true;
     if (packed) p->lds_bytes = lds_packed;
-    p->sweep = packed ? ve.fn_pack : (u8 ? ve.fn_u8 : ve.fn);
+    p->sweep = ce ? ce->fn : packed ? ve.fn_pack : (u8 ? ve.fn_u8 : ve.fn);
     // (up to 30 strategies x 3000 tiles: two tables of 8-byte cells take 184 MB, and the caches hold 256.  With all
     // rows alive, cost rows / byte table: 30 x 3760 tiles 904 / 658 us, 34 x 3760 957 / 675, 64 x 1512 919 / 833)
-    a.packed = !packed ? 0 : !(d->flags & GALV_DP_FORCE_PACK) && tiles * S < 90000 ? kRowsIfAlive : kAllBytes;
+    a.packed = ce ? kChain : !packed ? 0 : !(d->flags & GALV_DP_FORCE_PACK) && tiles * S < 90000 ? kRowsIfAlive : kAllBytes;
     a.seen = nullptr;
     a.lead = (int64_t)round_up((size_t)a.E_max + 1, 64);
     a.row = a.lead + a.e_pad;
     p->var = v;
 
     // Sizes in long double first, to reject anything that would overflow size_t math.
-    const long double approx = (long double)a.B * a.S_pad * a.row * 16 +
+    const long double approx = (long double)a.B * a.S_pad * (ce ? a.L * a.e_pad * 8 : a.row * 16) +
                                (long double)a.B * (a.L - 1) * a.S * a.e_pad * (u8 ? 1 : 4) +
                                (long double)a.B * a.nR * a.S * a.S_pad * 8;
     if (approx > 1e15L) return fail(GALV_ERR_RANGE, "tables of %.3Lg bytes cannot be indexed", approx);
@@ -3086,9 +3753,9 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, Plan *p) {
         off = round_up(off + bytes, 256);
         return at;
     };
-    const size_t u_bytes = (size_t)a.B * a.S_pad * a.row * 8;
+    const size_t u_bytes = ce ? (size_t)a.B * a.L * a.S_pad * a.e_pad * 8 : (size_t)a.B * a.S_pad * a.row * 8;
     p->off_U[0] = take(u_bytes);
-    p->off_U[1] = take(u_bytes);
+    p->off_U[1] = take(ce ? ((size_t)a.B * a.n_tiles * kWordStep + kWave) * sizeof(int32_t) : u_bytes);
     p->off_bp = take((size_t)a.B * (a.L - 1) * a.S * a.e_pad * (u8 ? 1 : sizeof(int32_t)));
     // + slack: a group of R keys is fetched whole even when it straddles the row end
     p->off_Rk = take((size_t)a.B * a.nR * a.S * a.S_pad * sizeof(double) + 1024);
@@ -3106,18 +3773,18 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, Plan *p) {
     return GALV_OK;
 }
 
-// The plan of a handle: the shape that the rules choose, or, where it does not fit `bytes` of workspace, the plain
+// The plan for a launch per layer: the shape that the rules choose, or, where it does not fit `bytes` of workspace, the plain
 // one, and where the launch fills the chip the wide one, if that does.  (The twins with more waves pad the strategies
 // to a little more, and narrow tiles take more statistics: a workspace of the size that these shapes need, which
 // were once all there were, stays large enough.)
 galv_status_t make_plan(const galv_dp_desc_t *d, size_t bytes, Plan *p) {
-    const galv_status_t st = make_plan(d, nullptr, p);
+    const galv_status_t st = make_plan(d, nullptr, false, p);
     if (st != GALV_OK || p->total <= bytes) return st;
     const bool fills_chip = launch_tiles(*d) >= kFullChip;
     for (Tiles only : {Tiles::normal, Tiles::wide}) {
         if (only == Tiles::wide && !fills_chip) continue;
         Plan q;
-        if (make_plan(d, &only, &q) == GALV_OK && q.total <= bytes) {
+        if (make_plan(d, &only, false, &q) == GALV_OK && q.total <= bytes) {
             *p = q;
             break;
         }
@@ -3125,10 +3792,22 @@ galv_status_t make_plan(const galv_dp_desc_t *d, size_t bytes, Plan *p) {
     return GALV_OK;
 }
 
+// The plan of a handle: the chained sweep, which keeps every layer's rows, where the rules choose it and the workspace
+// holds it.  (What it takes decides nothing else: a workspace is too small or a shape too large when a launch per layer
+// would not fit.)
+galv_status_t choose_plan(const galv_dp_desc_t *d, size_t bytes, Plan *p) {
+    const galv_status_t st = make_plan(d, bytes, p);
+    if (st != GALV_OK || p->total > bytes) return st;
+    Plan q;
+    if (make_plan(d, nullptr, true, &q) == GALV_OK && q.total <= bytes) *p = q;
+    return GALV_OK;
+}
+
 // grid.x of a sweep launch for n budget tiles.
 // (the byte-table sweep's first eight workgroups are not for tiles)
 inline unsigned kGridTiles(const Layout &a) {
     const unsigned n = (unsigned)a.n_tiles;
+    if (a.packed == kChain) return (unsigned)((n + 1) * a.B);
     return (GALV_XCD_MAP || a.packed ? (n + 7) / 8 * 8 : n) + (a.packed ? 8 : 0);
 }
 
@@ -3162,7 +3841,7 @@ void bind_workspace(Layout &a, const Plan &p, char *ws) {
 // single instance every instance gets its own (16 instances of 128 strategies x 65536 columns:
 // 20.3 ms with 16 streams, 21.2 with 12, 22.1 with 11).
 int pick_streams(const galv_dp *h, int64_t tiles) {
-    if (h->n_side <= 1) return 1;
+    if (h->n_side <= 1 || h->lay.packed == kChain) return 1;
     if (!h->auto_streams) return h->n_side;
     const Layout &a = h->lay;
     // The byte-table sweep: every launch costs ~4 us on the host and the same again on the queue, so
@@ -3207,7 +3886,7 @@ galv_status_t enqueue_solve(galv_dp *h, const int64_t *c_dev, const int32_t *m_d
     const int n_use = a.L < 2 ? 1 : pick_streams(h, seen > 0 ? seen : tiles_at_most(h));
     h->n_used = n_use;
     prep_kernel<<<a.B, kPrepThreads, 0, st>>>(a, h->desc.flags);
-    {
+    if (a.packed != kChain) {
         // at most 16 cells per thread: enough blocks to write a row at full rate, few enough to cost
         // nothing when, as usual after a handle's first solve, there is nothing to write
         const int64_t blocks = (a.row + 16 * kThreads - 1) / (16 * kThreads);
@@ -3215,7 +3894,9 @@ galv_status_t enqueue_solve(galv_dp *h, const int64_t *c_dev, const int32_t *m_d
     }
     a.b_off = 0;
     a.b_step = 1;
-    if (n_use <= 1) {
+    if (a.packed == kChain) {
+        h->sweep<<<kGridTiles(a), h->var.w * kWave, h->lds_bytes, st>>>(a, 0);
+    } else if (n_use <= 1) {
         const dim3 grid(kGridTiles(a), h->groups_y, a.B);
         for (int l = 1; l < a.L; ++l) h->sweep<<<grid, h->var.w * kWave, h->lds_bytes, st>>>(a, l);
     } else {
@@ -3291,12 +3972,22 @@ galv_status_t galv_dp_workspace_bytes(const galv_dp_desc_t *desc, size_t *bytes)
     return GALV_OK;
 }
 
+galv_status_t galv_dp_workspace_bytes_preferred(const galv_dp_desc_t *desc, size_t *bytes) {
+    if (!bytes) return fail(GALV_ERR_INVALID_ARG, "bytes is NULL");
+    Plan p, q;
+    galv_status_t st = make_plan(desc, nullptr, false, &p);
+    if (st == GALV_OK) st = make_plan(desc, nullptr, true, &q);
+    if (st != GALV_OK) return st;
+    *bytes = p.total > q.total ? p.total : q.total;
+    return GALV_OK;
+}
+
 galv_status_t galv_dp_create(const galv_dp_desc_t *desc, void *workspace_dev,
                              size_t workspace_bytes, galv_dp_t **out) {
     if (!out) return fail(GALV_ERR_INVALID_ARG, "out is NULL");
     *out = nullptr;
     Plan p;
-    galv_status_t st = make_plan(desc, workspace_bytes, &p);
+    galv_status_t st = choose_plan(desc, workspace_bytes, &p);
     if (st != GALV_OK) return st;
     if (!workspace_dev) return fail(GALV_ERR_WORKSPACE, "workspace is NULL");
     if (reinterpret_cast<uintptr_t>(workspace_dev) % 256 != 0)
@@ -3418,7 +4109,7 @@ galv_status_t galv_dp_solve_static(const galv_dp_desc_t *desc, const int64_t *c_
                                    int64_t *best_cost_dev, int32_t *best_last_dev, int32_t *plan_dev,
                                    void *stream) {
     Plan p;
-    galv_status_t rc = make_plan(desc, (size_t)GALV_DP_STATIC_BYTES, &p);
+    galv_status_t rc = choose_plan(desc, (size_t)GALV_DP_STATIC_BYTES, &p);
     if (rc != GALV_OK) return rc;
     if (((desc->flags & GALV_DP_STREAMS_MASK) >> GALV_DP_STREAMS_SHIFT) > 1u)
         return fail(GALV_ERR_INVALID_ARG, "galv_dp_solve_static runs on the caller's stream only "
@@ -3527,7 +4218,7 @@ galv_status_t galv_dp_get_stats(galv_dp_t *h, int64_t *stats_dev, void *stream) 
 galv_status_t galv_dp_get_config(const galv_dp_t *h, int32_t *config) {
     if (!h) return fail(GALV_ERR_INVALID_ARG, "handle is NULL");
     if (!config) return fail(GALV_ERR_INVALID_ARG, "config is NULL");
-    config[0] = h->lay.packed ? 1 : 0;
+    config[0] = h->lay.packed && h->lay.packed != kChain ? 1 : 0;
     config[1] = h->lay.peek && h->var.share ? 1 : 0;
     config[2] = h->n_used > 0 ? h->n_used : (h->lay.L < 2 ? 1 : pick_streams(h, tiles_at_most(h)));
     config[3] = h->lay.tile_e;

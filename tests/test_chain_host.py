@@ -1,0 +1,50 @@
+"""Which handles run all layers in one launch, and what happens below the workspace that takes (no GPU work)."""
+import ctypes
+
+import pytest
+
+from paper_2211_13878_amd import binding
+
+
+@pytest.fixture(scope="module")
+def lib():
+    return binding.load_library()
+
+
+def create(lib, desc, n_bytes):
+    h = ctypes.c_void_p(None)
+    rc = lib.galv_dp_create(ctypes.byref(desc), ctypes.c_void_p(4096), n_bytes, ctypes.byref(h))
+    if rc != binding.GALV_OK:
+        return rc, None
+    config = binding.galv_dp_get_config(h)
+    lib.galv_dp_destroy(h)
+    return rc, config
+
+
+@pytest.mark.parametrize("B,L,S,E,chains", [(1, 37, 29, 9973, True), (8, 32, 22, 16384, True), (16, 48, 44, 2048, True), (1, 4, 6, 256, True),
+                                            (32, 48, 22, 24576, False), (64, 96, 44, 32768, False), (8, 32, 65, 1000, False),
+                                            (1, 1, 22, 5000, False), (40, 100, 44, 4000, True), (40, 20, 44, 4000, False)])
+def test_the_rule_and_the_workspace(lib, B, L, S, E, chains):
+    desc = binding.make_desc(B, L, S, E, 2, binding.GALV_DP_STREAMS(1))     # (no streams to create here)
+    need, best = binding.galv_dp_workspace_bytes(desc), binding.galv_dp_workspace_bytes_preferred(desc)
+    assert best >= need
+    if L > 4:
+        assert (best > need) == chains
+    # less than preferred: a launch per layer; less than needed: refused
+    for n_bytes in (best, best - 1, need):
+        if n_bytes >= need:
+            assert create(lib, desc, n_bytes)[0] == binding.GALV_OK
+    if chains and L > 4:
+        assert create(lib, desc, best)[1][:2] == (0, 0)
+    # what asks for a particular sweep, or for several streams, gets a launch per layer
+    for flags in (binding.GALV_DP_FORCE_PACK, binding.GALV_DP_NO_PACK, binding.GALV_DP_BP_U8, binding.GALV_DP_NO_WIDE_TILES,
+                  binding.GALV_DP_FORCE_WIDE_TILES, binding.GALV_DP_FORCE_PEEK, binding.GALV_DP_NO_PEEK, binding.GALV_DP_NO_U32,
+                  binding.GALV_DP_STREAMS(2)):
+        asked = binding.make_desc(B, L, S, E, 2, flags)
+        assert binding.galv_dp_workspace_bytes_preferred(asked) == binding.galv_dp_workspace_bytes(asked) or flags & binding.GALV_DP_BP_U8 and S > 255
+
+
+def test_preferred_checks_its_arguments(lib):
+    n = ctypes.c_size_t(0)
+    assert lib.galv_dp_workspace_bytes_preferred(None, ctypes.byref(n)) == binding.GALV_ERR_INVALID_ARG
+    assert lib.galv_dp_workspace_bytes_preferred(ctypes.byref(binding.make_desc(1, 4, 6, 256)), None) == binding.GALV_ERR_INVALID_ARG

@@ -1,0 +1,128 @@
+"""The sweep that takes all layers of a small search in one launch: workgroups own budget columns and pass a layer's
+cells on to their neighbours.  Edges of the strategy counts that each shape covers, of tiles and of budgets, every
+arithmetic path in one batch, more workgroups than the GPU holds at a time, and solves that overlap on several streams.
+Whole tables are compared with the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2211_13878_amd import binding, workloads
+from test_gpu_parity import check_against_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def workload(seed, B, L, S, E, m_hi=None, nR=2):
+    return workloads.random_workload(seed, B, L, S, E, nR=nR, m_range=(0, m_hi or 2 * E // L), c_range=(0, 3000), r_range=(0, 400),
+                                     infeasible=0.08, zero_diagonal=False)
+
+
+def mixed(w):
+    """Instances of every status: 32-bit keys, 8-byte cells, 64-bit keys over 32-bit and over larger costs, 64-bit
+    integers, one with an invalid value, and 64-bit keys with transition costs beyond 32 bits."""
+    w.c[1] <<= 30
+    w.R[2] <<= 20
+    w.c[3] <<= 30
+    w.R[3] <<= 20
+    w.c[4] <<= 46
+    w.R[4] <<= 34
+    w.R[5, 0, 0, 0] = -1
+    w.c[6] <<= 30
+    w.R[6] <<= 25
+    return w
+
+
+@pytest.mark.parametrize("S", [1, 2, 8, 9, 16, 17, 24, 25, 32, 33, 48, 49, 64])
+@pytest.mark.parametrize("B,E", [(7, 700), (150, 640)])      # thin waves, and from 353, 705 or 769 tiles on fat ones
+def test_strategy_counts_and_arithmetic_paths(S, B, E):
+    w = mixed(workload(17 * S + B, B, 5, S, E))
+    w.budget[:7] = (E, 383, 384, E, E, E, E)
+    some = list(range(7)) + list(range(7, B, 29))
+    bad = 5
+    cost, last, plan, status = check_against_oracle(w, table_instances=[0, 1, 2, 3, 4, 6], oracle_instances=[b for b in some if b != bad],
+                                                    threads=8, allow_vacuous=S == 1)
+    assert status[bad] == binding.GALV_INSTANCE_BAD_VALUE and cost[bad] == binding.GALV_INF and (plan[bad] == -1).all()
+    if S >= 8:
+        assert set(status[:5]) == {0, 1, 2, 3, 4}
+
+
+@pytest.mark.parametrize("E", [0, 1, 126, 127, 128, 129, 255, 256, 1023, 4099])
+@pytest.mark.parametrize("L", [2, 3, 9])
+def test_edges_of_tiles_and_budgets(L, E):
+    w = workload(1000 + 31 * L + E, 5, L, 22, E, m_hi=max(1, E // L))
+    w.budget[:] = (E, max(0, E - 1), E // 2, min(E, 128), 0)
+    w.c[1] <<= 30
+    w.r_idx[:, 1:] = np.arange(L - 1) % 2                    # the transition matrix changes from layer to layer
+    check_against_oracle(w, table_instances=list(range(5)), threads=8, allow_vacuous=True)
+
+
+@pytest.mark.parametrize("m_hi", [3, 40, 900, 6000])
+def test_memories_from_within_a_tile_to_most_of_the_budget(m_hi):
+    w = workload(77 + m_hi, 3, 12, 29, 5003, m_hi=m_hi)
+    w.m[1, 3, :] = 5004                                      # a layer without a usable strategy
+    check_against_oracle(w, table_instances=[0, 1, 2], threads=8)
+
+
+def test_nothing_can_be_left_out():
+    """Every row stays alive in every tile, with each kind of key."""
+    for S in (16, 24, 48, 64):
+        w = workloads.random_workload(300 + S, 3, 6, S, 900, nR=2, m_range=(0, 150), c_range=(0, 9), r_range=(1000, 5000),
+                                      infeasible=0.05, zero_diagonal=False)
+        w.c[1] <<= 36
+        w.R[1] <<= 18
+        check_against_oracle(w, table_instances=[0, 1], threads=8)
+
+
+@pytest.mark.parametrize("B,L,S,E", [(300, 6, 6, 3000), (1, 4, 22, 150000), (90, 7, 44, 1100)])
+def test_more_workgroups_than_the_gpu_holds(B, L, S, E):
+    w = workload(5 * B + S, B, L, S, E)
+    w.c[::3] <<= 30
+    check_against_oracle(w, oracle_instances=list(range(0, B, 37)), table_instances=[0], threads=8)
+
+
+def test_solves_that_overlap_on_several_streams():
+    """Three handles on three streams at once, with changing inputs: each solve waits for its own words only."""
+    shapes = [(2, 9, 22, 9000), (6, 14, 12, 3000), (1, 6, 48, 12000)]
+    jobs = []
+    for i, (B, L, S, E) in enumerate(shapes):
+        ws = [workload(900 + 10 * i + j, B, L, S, E) for j in range(3)]
+        jobs.append((binding.Solver(B, L, S, E, 2), [binding.upload(w) for w in ws],
+                     [oracle.solve_workload(w, threads=8) for w in ws], torch.cuda.Stream(), []))
+    torch.cuda.synchronize()
+    for rep in range(12):
+        for sol, devs, refs, stream, got in jobs:
+            with torch.cuda.stream(stream):
+                cost, _ = sol.solve(*devs[rep % 3])
+                plan = sol.backtrack()
+                got.append((cost.clone(), plan.clone()))
+    torch.cuda.synchronize()
+    for sol, devs, refs, stream, got in jobs:
+        for rep, (cost, plan) in enumerate(got):
+            for b, ref in enumerate(refs[rep % 3]):
+                assert int(cost[b]) == ref.best_cost and (plan[b].cpu().numpy() == ref.plan).all(), (rep, b)
+        sol.close()
+
+
+def test_a_graph_that_is_replayed_with_changing_inputs():
+    B, L, S, E = 4, 11, 22, 6000
+    ws = [workload(700 + j, B, L, S, E) for j in range(3)]
+    devs = [binding.upload(w) for w in ws]
+    sol = binding.Solver(B, L, S, E, 2)
+    inputs = [t.clone() for t in devs[0]]
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        sol.solve(*inputs), sol.backtrack()
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cost, _ = sol.solve(*inputs)
+        plan = sol.backtrack()
+    for rep in range(6):
+        for to, t in zip(inputs, devs[rep % 3]):
+            to.copy_(t)
+        graph.replay()
+        torch.cuda.synchronize()
+        for b, ref in enumerate(oracle.solve_workload(ws[rep % 3], threads=4)):
+            assert int(cost[b]) == ref.best_cost and (plan[b].cpu().numpy() == ref.plan).all(), (rep, b)
+    sol.close()
