@@ -1694,13 +1694,9 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
 #undef GALV_DPP_MIN
     return min(min(read_lane(v, 15), read_lane(v, 31)), min(read_lane(v, 47), read_lane(v, 63)));
 }
-__device__ __forceinline__ uint64_t wave_min(uint64_t v) {
-#pragma unroll
-    for (int w = kWave / 2; w > 0; w >>= 1) {
-        const uint64_t o = (uint64_t)__shfl_xor((long long)v, w, kWave);
-        if (o < v) v = o;
-    }
-    return read_lane(v, 0);
+__device__ __forceinline__ uint64_t wave_min(uint64_t v) {     // (the high words' minimum, then the low words' beside it)
+    const uint32_t hi = wave_min((uint32_t)(v >> 32));
+    return (uint64_t)hi << 32 | wave_min((uint32_t)(v >> 32) == hi ? (uint32_t)v : 0xffffffffu);
 }
 
 // One step of the recurrence without a memory limit, for layer l of instance b: V_l(s) and the
@@ -2420,11 +2416,8 @@ __device__ __forceinline__ void chain_live(const Layout &a, int b, uint32_t dmax
         }
         load(l + 1, next);
         const bool usable = in && m <= budget;
-        const uint64_t mine = usable ? V : ~0ull;
-        const uint32_t hi = wave_min((uint32_t)(mine >> 32));
-        const uint32_t lo = wave_min((uint32_t)(mine >> 32) == hi ? (uint32_t)mine : 0xffffffffu);
-        const uint64_t vmin = (uint64_t)hi << 32 | lo;
-        if (vmin == ~0ull) {                       // nothing reachable from here on
+        const uint64_t vmin = wave_min(usable ? V : ~(uint64_t)0);
+        if (vmin == ~(uint64_t)0) {                // nothing reachable from here on
             if (lane == 0)
                 for (int q = l > 1 ? l : 2; q < L; ++q) agent_store(hdr + q * 8 + 6, -1);
             return;
@@ -2530,6 +2523,8 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
     KeyT *Rl = reinterpret_cast<KeyT *>(alive_of + 2);                      // [kRows][kRows] transition keys
     uint32_t *keys = reinterpret_cast<uint32_t *>(Rl + kRows * kRows);      // [kRows][kCols] relative costs by list position
     int32_t *last_of = reinterpret_cast<int32_t *>(keys + kRows * kCols);   // [2] X_l, by layer modulo 2
+    uint64_t *kept_ent = reinterpret_cast<uint64_t *>(last_of + 2);         // [kRows] entries of the rows to read, and how many
+    int32_t *kept_n = reinterpret_cast<int32_t *>(kept_ent + kRows);
 
     auto load = [&](int l, ChainIn &in) { chain_load<TS, NG>(layout_again(), wave, b, l < L ? l : L - 1, in); };
     // (Here the loads have arrived.  Left to itself the compiler waits for them at the top of the loop, where it cannot
@@ -2581,14 +2576,32 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
                 const int lo = min(max(start - sh_hi, y_prev), x_prev) / kCols;
                 const int hi = start + kCols - 1 - sh_lo < y_prev ? -1 : min(min(start + kCols - 1 - sh_lo, x_prev) / kCols, t - 1);
                 told = chain_wait(flags, lo, hi, l - 1);
+                if (a.peek && told) {
+                    // Rows are non-increasing: a row's cells here are at least its cell in the last column, every column
+                    // minimum is at most the one in the first column (see sweep_u32_shared).
+                    const __amdgpu_buffer_rsrc_t rows = chain_buffer(chain_rows<Cell>(a, b, l - 1));
+                    const int first = start - (int)shift, last = first + kCols - 1;
+                    const uint32_t row = (uint32_t)in.ent * pitch;
+                    auto cell = [&](int at) -> Cell {
+                        const uint32_t off = (row + (uint32_t)min(max(at, y_prev), x_prev)) * (uint32_t)sizeof(Cell);
+                        if constexpr (sizeof(Cell) == 4)
+                            return (Cell)__builtin_amdgcn_raw_buffer_load_b32(rows, (int)off, 0, kAgent);
+                        else
+                            return __builtin_bit_cast(Cell, __builtin_amdgcn_raw_buffer_load_b64(rows, (int)off, 0, kAgent));
+                    };
+                    const Cell at_first = cell(first), at_last = cell(last);
+                    const bool listed = lane < n;
+                    const Cell upper = listed && first >= y_prev ? at_first : kInfCell;
+                    const Cell lower = listed && last >= y_prev ? at_last : kInfCell;
+                    const Cell bound = wave_min(upper);
+                    const bool kept = lower < (bound < kInfCell ? bound + (Cell)dmax : kInfCell);
+                    const uint64_t votes = __builtin_amdgcn_ballot_w64(kept);
+                    if (kept) kept_ent[__builtin_popcountll(votes & ((1ull << lane) - 1ull))] = in.ent;
+                    if (lane == 0) *kept_n = __builtin_popcountll(votes);
+                }
             }
             if (lane == 0) last_of[l & 1] = told ? x : kUnset;
         }
-        // (meanwhile: which rows of the list lie inside the stored columns, and which nowhere reachable; where they begin)
-        const int shift_of = (int)(uint32_t)(in.ent >> 32);
-        const uint64_t inside = __builtin_amdgcn_ballot_w64(start - shift_of >= y_prev && start + kCols - 1 - shift_of <= x_prev);
-        const uint64_t dead = __builtin_amdgcn_ballot_w64(start + kCols - 1 - shift_of < y_prev);
-        const uint32_t off = ((uint32_t)in.ent * pitch + (uint32_t)(start - shift_of)) * (uint32_t)sizeof(Cell);
         __syncthreads();
         const int x = uniform(last_of[l & 1]);
         if (x == kUnset) {
@@ -2604,6 +2617,12 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
             continue;
         }
         const KeyT *Rk = rkeys<KeyT>(layout_again(), b, r_sel);
+        uint64_t ent = in.ent;
+        int nk = n;
+        if (a.peek && l > 1) {
+            nk = uniform(*kept_n);
+            ent = kept_ent[lane < nk ? lane : 0];  // (beyond the list's end: not used)
+        }
         if (r_sel != r_now) {                      // (used two barriers on; last read before the latest one)
             for (int i = g; i < S; i += NG)
                 if (lane < kRows) Rl[i * kRows + lane] = (Rk + (int64_t)i * S_pad)[lane];
@@ -2613,24 +2632,28 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
         if (l == 1) {
 #pragma unroll
             for (int r = 0; r < TS; ++r) {
-                const int shift = (int)read_lane((uint32_t)(in.ent >> 32), g + NG * r);
+                const int shift = (int)read_lane((uint32_t)(ent >> 32), g + NG * r);
                 const Cell cp = (Cell)read_lane(c0, g + NG * r);
 #pragma unroll
                 for (int j = 0; j < TE; ++j) row[r][j] = e0 + j >= shift ? cp : kInfCell;
             }
         } else {
-            // (past its end the list repeats its last entry)
+            // which rows lie inside the stored columns, and which nowhere reachable; where they begin
+            const int shift_of = (int)(uint32_t)(ent >> 32);
+            const uint64_t inside = __builtin_amdgcn_ballot_w64(start - shift_of >= y_prev && start + kCols - 1 - shift_of <= x_prev);
+            const uint64_t dead = __builtin_amdgcn_ballot_w64(start + kCols - 1 - shift_of < y_prev || lane >= nk);
+            const uint32_t off = ((uint32_t)ent * pitch + (uint32_t)(start - shift_of)) * (uint32_t)sizeof(Cell);
             const __amdgpu_buffer_rsrc_t rows = chain_buffer(chain_rows<Cell>(a, b, l - 1));
 #pragma unroll
             for (int r = 0; r < TS; ++r) {
                 const int i = g + NG * r;
-                if (inside >> i & 1) {
-                    buffer_cells(rows, lane_off, read_lane(off, i), row[r]);
-                } else if (dead >> i & 1) {
+                if (dead >> i & 1) {
 #pragma unroll
                     for (int j = 0; j < TE; ++j) row[r][j] = kInfCell;
+                } else if (inside >> i & 1) {
+                    buffer_cells(rows, lane_off, read_lane(off, i), row[r]);
                 } else {
-                    const uint64_t en = read_lane(in.ent, i);
+                    const uint64_t en = read_lane(ent, i);
                     const uint32_t first = (uint32_t)en * pitch * (uint32_t)sizeof(Cell);
                     const int at = e0 - (int)(uint32_t)(en >> 32);
 #pragma unroll
@@ -2649,7 +2672,7 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
             if (unstored) store_bytes();           // (behind the loads: nobody waits for them)
             unstored = 0;
         }
-        const uint32_t list = (uint32_t)in.ent;
+        const uint32_t list = (uint32_t)ent;
         const uint64_t ck = in.ck;
         load(l + 1, in);
         Word *now = minima + turn * kCols + lane * TE;
@@ -2679,7 +2702,7 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
                 least = min(least, d[j]);
             }
             *reinterpret_cast<relv *>(keys + (g + NG * r) * kCols + lane * TE) = d;
-            if (__builtin_amdgcn_ballot_w64(least < dmax) != 0 && g + NG * r < n)      // wave-uniform
+            if (__builtin_amdgcn_ballot_w64(least < dmax) != 0 && g + NG * r < nk)     // wave-uniform
                 mine |= 1ull << (g + NG * r);
         }
         if (lane == 0 && mine) atomicOr(alive_of + turn, mine);
@@ -2731,11 +2754,11 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
                 bytes[s] = __builtin_amdgcn_perm(Key::low(acc[s][1]), Key::low(acc[s][0]), 0x0c0c0400u) & mask;
             unstored = l;
         }
-        if (g == NG - 1 && lane == 0) {            // statistics: every listed row is read
+        if (g == NG - 1 && lane == 0) {            // statistics
             const Layout &al = layout_again();
             uint32_t *st = al.stats + 2 * (((int64_t)b * (L - 1) + (l - 1)) * al.n_tiles + t);
             st[0] = (uint32_t)__builtin_popcountll(alive) << 16 | (uint32_t)n;
-            st[1] = (uint32_t)n;
+            st[1] = (uint32_t)nk;
         }
         turn ^= 1;
         if (g == NG / 2) clear(turn);              // (read a layer ago; the barrier below is before its next use)
@@ -2864,9 +2887,9 @@ __global__ __launch_bounds__(NG * kWave, 4) void chain_kernel(Layout a, int) {
     }
 }
 constexpr unsigned chain_lds(int ts, int ng) {
-    // minima of 8-byte cells, alive rows, transition keys of 8 bytes, keys, X_l
+    // minima of 8-byte cells, alive rows, transition keys of 8 bytes, relative costs, X_l, rows to read
     const int rows = ts * ng, cols = kChainCols;
-    return (unsigned)(2 * cols * 8 + 2 * 8 + rows * rows * 8 + rows * cols * 4 + 8);
+    return (unsigned)(2 * cols * 8 + 2 * 8 + rows * rows * 8 + rows * cols * 4 + 8 + rows * 8 + 8);
 }
 
 // ------------------------------------------------- final minimum and backtrack
@@ -3501,17 +3524,21 @@ enum class Tiles { wide, normal, split, fine, chain };
 struct ChainEntry {
     int ts, ng;
     int64_t tiles;         // up to so many tiles in a layer of the whole batch
+    int peek;              // the fat shapes from 17 strategies on look at two cells of a row before they read it: one more round trip,
+                           // fewer rows.  Without / with, layers alike - deep stacks - the latter with tenfold transition costs, over the
+                           // time with a launch per layer: 22 x 2244 0.86 0.92 0.71 / 0.85 0.92 0.73, x 3432 0.89 1.01 0.77 / 0.89 0.94 0.77; 30 x
+                           // 1452 0.90 0.98 0.67 / 0.90 0.97 0.69; 44 x 1056 0.96 1.04 0.66 / 0.94 1.00 0.67; 12 x 5016 0.83 0.96 0.71 / 0.88 1.00 0.76
     SweepFn fn;
 };
 template <int TS, int NG>
-ChainEntry chain_entry(int64_t tiles) {
-    return {TS, NG, tiles, chain_kernel<TS, NG>};
+ChainEntry chain_entry(int64_t tiles, int peek = 0) {
+    return {TS, NG, tiles, peek, chain_kernel<TS, NG>};
 }
 const ChainEntry *pick_chain(int S, int64_t tiles) {
     constexpr int64_t any = INT64_MAX;
     static const ChainEntry table[] = {chain_entry<2, 4>(any),  chain_entry<2, 8>(768),  chain_entry<4, 4>(any), chain_entry<3, 8>(768),
-                                       chain_entry<6, 4>(any),  chain_entry<4, 8>(704),  chain_entry<8, 4>(any), chain_entry<3, 16>(352),
-                                       chain_entry<6, 8>(any),  chain_entry<4, 16>(352), chain_entry<8, 8>(any)};
+                                       chain_entry<6, 4>(any, 1), chain_entry<4, 8>(704), chain_entry<8, 4>(any, 1), chain_entry<3, 16>(352),
+                                       chain_entry<6, 8>(any, 1), chain_entry<4, 16>(352), chain_entry<8, 8>(any, 1)};
     for (const ChainEntry &t : table)
         if (S <= t.ts * t.ng && tiles <= t.tiles) return &t;
     return nullptr;
@@ -3666,18 +3693,20 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, bool chain, 
     else if (tiles <= split_to)
         shape = Tiles::split;
     // All layers in one launch (the chained sweep), up to 64 strategies.  It wins by what a launch per layer costs, and loses
-    // where the byte table's peek leaves out most of what it reads: where a layer has many tiles and its share of the budget
+    // where the byte table writes and reads less than whole rows: where a layer has many tiles and its share of the budget
     // spans several.  Where the share is below a tile the other side keeps cost rows, and the line lies further out.  Whole
     // searches over the time with a launch per layer, layers alike - deep stacks - independent layers - deep stacks in nanoseconds
-    // - layers alike in nanoseconds with tenfold transition costs:
-    //   share 700:  12 x 4950 0.79 0.85 0.50 0.73 0.48, x 9020 1.03 1.28 0.63 1.03 0.65; 22 x 2200 0.89 0.85 0.70 0.76 0.54, x 3520 0.91 1.04 0.70
-    //   0.87 0.61; 30 x 990 0.87 0.76 0.76 0.62 0.48, x 1540 0.95 1.02 0.75 0.93 0.56; 44 x 660 0.83 0.91 0.73 0.73 0.52, x 990 1.00 1.07 0.62 0.96
-    //   0.55, x 2200 1.03 1.54 0.37 1.43 0.73; 60 x 660 0.94 0.99 0.76 0.85 0.57, x 990 0.93 1.09 0.63 0.93 0.57
-    //   share 100:  22 x 3458 0.67 0.88 0.45 0.73 0.50; 30 x 2166 0.67 0.83 0.41 0.58 0.46, x 3458 0.70 1.06 0.44 0.87 0.57; 44 x 1368 0.73 0.96 0.42
-    //   0.65 0.54; 60 x 990 0.76 0.90 0.45 0.44 0.43.  (Beyond 64 strategies: 100 x 252 1.02 0.96 0.80 0.72, x 1032 1.43 1.79 0.56 1.87.)
+    // - layers alike in nanoseconds with tenfold transition costs - deep stacks with tenfold transition costs:
+    //   share 700:  6 x 5940 0.77 0.77 0.64 0.52 0.47 0.68, x 15972 1.10 1.09 0.92 0.85 0.71 0.98; 12 x 5016 0.83 0.96 0.50 0.78 0.48 0.71, x 8976 1.17 1.39
+    //   0.66 1.12 0.72 0.95; 22 x 3432 0.89 0.94 0.66 0.80 0.58 0.77, x 6204 1.10 1.34 0.67 1.16 0.68 0.88; 30 x 1452 0.90 0.97 0.68 0.77 0.55 0.69,
+    //   x 2244 0.90 1.03 0.65 0.88 0.59 0.77; 44 x 1056 0.94 1.00 0.58 0.81 0.57 0.67, x 1584 1.03 1.24 0.63 1.04 0.62 0.79; 60 x 792 0.89 1.01 0.71 0.81
+    //   0.59 0.73, x 1452 0.91 1.13 0.39 1.07 0.51 0.56
+    //   share 100:  12 x 4940 0.78 0.94 0.49 0.67 0.59 0.69; 22 x 3458 0.64 0.79 0.46 0.68 0.49 0.66, x 6080 0.68 1.14 0.39 1.02 0.62 0.77; 30 x 2166 0.60
+    //   0.73 0.40 0.50 0.44 0.56; 44 x 2166 0.61 0.83 0.36 0.47 0.42 0.79; 60 x 1482 0.60 0.76 0.36 0.31 0.34 0.72.
+    // (Beyond 64 strategies, two waves' worth of list entries: 100 x 252 1.02 0.96 0.80 0.72, x 1032 1.43 1.79 0.56 1.87.)
     const uint32_t other = GALV_DP_BP_U8 | GALV_DP_NO_U32 | GALV_DP_NO_PEEK | GALV_DP_FORCE_PEEK | GALV_DP_NO_PACK | GALV_DP_FORCE_PACK |
                            GALV_DP_FORCE_WIDE_TILES | GALV_DP_NO_WIDE_TILES;        // (what these ask for is a launch per layer)
-    const int64_t chain_to = share < 128 ? 80000 : S <= 24 ? 60000 : 40000;
+    const int64_t chain_to = share < 128 ? 90000 : S <= 16 ? 60000 : S <= 24 ? 70000 : 46000;
     const ChainEntry *ce = S <= kWave ? pick_chain(S, tiles) : nullptr;
     // (rows of every layer: at most 8 GB of them, and a layer's of one instance within 32 bits of offset)
     const long double chain_bytes = ce ? 8.0L * ce->ts * ce->ng * ((int64_t)d->max_budget + kChainCols) : 0;
@@ -3727,7 +3756,7 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, bool chain, 
     bool packed = v.share && pays;
     if (ce) {
         p->lds_bytes = chain_lds(v.ts, v.ng);
-        a.peek = 0;
+        a.peek = ce->peek;
         a.e_pad = (int64_t)round_up((size_t)a.E_max + 1, (size_t)a.tile_e);
     }
     if ((d->flags & GALV_DP_FORCE_PACK) && v.share && !u8) packed = true;

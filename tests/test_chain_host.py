@@ -23,7 +23,7 @@ def create(lib, desc, n_bytes):
 
 @pytest.mark.parametrize("B,L,S,E,chains", [(1, 37, 29, 9973, True), (8, 32, 22, 16384, True), (16, 48, 44, 2048, True), (1, 4, 6, 256, True),
                                             (32, 48, 22, 24576, False), (64, 96, 44, 32768, False), (8, 32, 65, 1000, False),
-                                            (1, 1, 22, 5000, False), (40, 100, 44, 4000, True), (40, 20, 44, 4000, False)])
+                                            (1, 1, 22, 5000, False), (40, 100, 44, 4000, True), (40, 20, 44, 4000, False), (12, 48, 44, 16384, False), (12, 24, 22, 16384, True)])
 def test_the_rule_and_the_workspace(lib, B, L, S, E, chains):
     desc = binding.make_desc(B, L, S, E, 2, binding.GALV_DP_STREAMS(1))     # (no streams to create here)
     need, best = binding.galv_dp_workspace_bytes(desc), binding.galv_dp_workspace_bytes_preferred(desc)
