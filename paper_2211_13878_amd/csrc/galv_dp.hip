@@ -2851,15 +2851,56 @@ __device__ __forceinline__ void chain_int64(const Layout &a, int g, int b, int t
     }
 }
 
+// min over s at e = budget, lowest s first, by the wave that has an instance's last place: a lane per strategy.
+__device__ __forceinline__ void chain_final(const Layout &a, int b, int st, bool packed, int budget, int64_t *best_cost, int32_t *best_last) {
+    const int lane = lane_id();
+    const int L = a.L, S = a.S;
+    const int32_t *h = a.hdr + ((int64_t)b * L + (L - 1)) * 8;
+    uint64_t v = (uint64_t)kInf;                   // this lane's cost
+    if (st >= 0) {
+        const int e = budget - a.m[((int64_t)b * L + (L - 1)) * S + (lane < S ? lane : S - 1)];
+        int y = 0, x = budget;
+        bool there = true;
+        if (packed) {
+            y = uniform(h[5]);
+            x = uniform(agent_load(h + 6));
+            there = chain_last_column(h + 6, x);
+        }
+        const bool ok = there && lane < S && e >= y && y <= x;
+        const int at = min(e, x);
+        if (__builtin_amdgcn_ballot_w64(ok) != 0) {
+            const int lo = (int)wave_min(ok ? (uint32_t)at : ~0u), hi = (int)~wave_min(ok ? ~(uint32_t)at : ~0u);
+            there = chain_wait(chain_flags(a, b), lo / kChainCols, hi / kChainCols, L - 1);
+            const int64_t cell = (int64_t)(lane < S ? lane : 0) * a.e_pad + (ok ? at : lo);
+            if (packed && st == GALV_INSTANCE_OK_FAST_U32) {
+                const uint32_t narrow = agent_load(chain_rows<uint32_t>(a, b, L - 1) + cell);
+                if (ok && there && narrow < kInf32) v = narrow;
+            } else {
+                const uint64_t wide = agent_load(chain_rows<uint64_t>(a, b, L - 1) + cell);
+                if (ok && there && wide < (uint64_t)kInf) v = wide;
+            }
+        }
+        if (!there) a.status[b] = GALV_INSTANCE_BAD_VALUE;
+    }
+    const uint64_t least = wave_min(v);
+    const int last = least < (uint64_t)kInf ? __builtin_ctzll(__builtin_amdgcn_ballot_w64(v == least)) : -1;
+    if (lane == 0) {
+        best_cost[b] = (int64_t)least;
+        best_last[b] = last;
+        a.last[b] = last;
+    }
+}
+
 // (4 waves per SIMD at least: no vector register is spilled)
 template <int TS, int NG>
-__global__ __launch_bounds__(NG * kWave, 4) void chain_kernel(Layout a, int) {
+__global__ __launch_bounds__(NG * kWave, 4) void chain_kernel(Layout a, int64_t *best_cost, int32_t *best_last) {
     const int wave = uniform(threadIdx.x >> 6);
     if (wave == 0 && lane_id() == 0) lds_cells[0] = (uint32_t)atomicAdd(chain_words(a), 1);
     __syncthreads();
     const int place = uniform((int)lds_cells[0]);
     __syncthreads();
-    const int b = place % a.B, t = place / a.B - 1;            // (t = -1: the places of the unlimited recurrence)
+    // (block -1: the places of the unlimited recurrence; block n_tiles: those of the final minimum)
+    const int b = place % a.B, t = place / a.B - 1;
     // (all that is needed first in one round trip)
     ChainIn in;
     chain_load<TS, NG>(a, wave, b, 1, in);
@@ -2867,9 +2908,13 @@ __global__ __launch_bounds__(NG * kWave, 4) void chain_kernel(Layout a, int) {
     const uint64_t c0 = (a.vcost + (int64_t)b * a.L * (TS * NG))[(uint32_t)(lane_id() < TS * NG ? lane_id() : TS * NG - 1)];
     const int st = (int)read_lane((uint32_t)in.h, 0), budget = (int)read_lane((uint32_t)in.h, 1);
     const uint32_t dmax = read_lane((uint32_t)in.h, 3);
-    if (st < 0 || t * kChainCols > budget) return;
     const bool keys32 = st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE;
     const bool packed = byte_status(st, dmax);
+    if (t == a.n_tiles) {
+        if (wave == 0) chain_final(layout_again(), b, st, packed, budget, best_cost, best_last);
+        return;
+    }
+    if (st < 0 || t * kChainCols > budget) return;
     if (t < 0) {
         if (!packed || wave != 0) return;
         if (keys32)
@@ -3493,6 +3538,7 @@ __global__ __launch_bounds__(kThreads) void expand_plan_kernel(int B, int L, int
 }
 
 using SweepFn = void (*)(Layout, int);
+using ChainFn = void (*)(Layout, int64_t *, int32_t *);
 struct VariantEntry {
     Variant v;
     SweepFn fn, fn_u8;     // int32 and one-byte back-pointers
@@ -3528,7 +3574,7 @@ struct ChainEntry {
                            // fewer rows.  Without / with, layers alike - deep stacks - the latter with tenfold transition costs, over the
                            // time with a launch per layer: 22 x 2244 0.86 0.92 0.71 / 0.85 0.92 0.73, x 3432 0.89 1.01 0.77 / 0.89 0.94 0.77; 30 x
                            // 1452 0.90 0.98 0.67 / 0.90 0.97 0.69; 44 x 1056 0.96 1.04 0.66 / 0.94 1.00 0.67; 12 x 5016 0.83 0.96 0.71 / 0.88 1.00 0.76
-    SweepFn fn;
+    ChainFn fn;
 };
 template <int TS, int NG>
 ChainEntry chain_entry(int64_t tiles, int peek = 0) {
@@ -3581,6 +3627,7 @@ struct galv_dp {
     galv_dp_desc_t desc;
     Variant var;
     SweepFn sweep;
+    ChainFn chain;     // the chained sweep, or null
     Layout lay;        // workspace pointers filled, input pointers set per solve
     size_t ws_bytes;
     int groups_y;      // grid.y of the sweep
@@ -3602,6 +3649,7 @@ namespace {
 struct Plan {
     Variant var;
     SweepFn sweep;
+    ChainFn chain;
     Layout lay;
     size_t off_U[2], off_bp, off_Rk, off_ck, off_vlist, off_vcost, off_nvalid, off_hdr, off_status, off_last, off_dclamp,
         off_lead_mode, off_stats, total;
@@ -3761,7 +3809,8 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, bool chain, 
     }
     if ((d->flags & GALV_DP_FORCE_PACK) && v.share && !u8) packed = true;
     if (packed) p->lds_bytes = lds_packed;
-    p->sweep = ce ? ce->fn : packed ? ve.fn_pack : (u8 ? ve.fn_u8 : ve.fn);
+    p->sweep = packed ? ve.fn_pack : (u8 ? ve.fn_u8 : ve.fn);
+    p->chain = ce ? ce->fn : nullptr;
     // (up to 30 strategies x 3000 tiles: two tables of 8-byte cells take 184 MB, and the caches hold 256.  With all
     // rows alive, cost rows / byte table: 30 x 3760 tiles 904 / 658 us, 34 x 3760 957 / 675, 64 x 1512 919 / 833)
     a.packed = ce ? kChain : !packed ? 0 : !(d->flags & GALV_DP_FORCE_PACK) && tiles * S < 90000 ? kRowsIfAlive : kAllBytes;
@@ -3836,7 +3885,7 @@ galv_status_t choose_plan(const galv_dp_desc_t *d, size_t bytes, Plan *p) {
 // (the byte-table sweep's first eight workgroups are not for tiles)
 inline unsigned kGridTiles(const Layout &a) {
     const unsigned n = (unsigned)a.n_tiles;
-    if (a.packed == kChain) return (unsigned)((n + 1) * a.B);
+    if (a.packed == kChain) return (unsigned)((n + 2) * a.B);     // (and two places more per instance)
     return (GALV_XCD_MAP || a.packed ? (n + 7) / 8 * 8 : n) + (a.packed ? 8 : 0);
 }
 
@@ -3889,6 +3938,11 @@ int pick_streams(const galv_dp *h, int64_t tiles) {
 }
 int64_t tiles_at_most(const galv_dp *h) { return (int64_t)h->lay.B * (h->lay.E_max / h->lay.tile_e + 1); }
 
+// The kernel that sweeps, as the runtime knows it.
+const void *sweep_function(const galv_dp *h) {
+    return h->chain ? reinterpret_cast<const void *>(h->chain) : reinterpret_cast<const void *>(h->sweep);
+}
+
 // Enqueue one whole solve (preparation, layer 0, the L-1 sweeps, final minimum) of handle h on
 // stream st.  Shared by every entry point that solves.
 galv_status_t enqueue_solve(galv_dp *h, const int64_t *c_dev, const int32_t *m_dev,
@@ -3904,7 +3958,7 @@ galv_status_t enqueue_solve(galv_dp *h, const int64_t *c_dev, const int32_t *m_d
     h->solved = false;
 
     if (!h->lds_allowed) {     // more than the default 64 KB of dynamic LDS: say so before any launch
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(h->sweep),
+        HIP_TRY(hipFuncSetAttribute(sweep_function(h),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)h->lds_bytes));
         h->lds_allowed = true;
     }
@@ -3924,7 +3978,7 @@ galv_status_t enqueue_solve(galv_dp *h, const int64_t *c_dev, const int32_t *m_d
     a.b_off = 0;
     a.b_step = 1;
     if (a.packed == kChain) {
-        h->sweep<<<kGridTiles(a), h->var.w * kWave, h->lds_bytes, st>>>(a, 0);
+        h->chain<<<kGridTiles(a), h->var.w * kWave, h->lds_bytes, st>>>(a, best_cost_dev, best_last_dev);
     } else if (n_use <= 1) {
         const dim3 grid(kGridTiles(a), h->groups_y, a.B);
         for (int l = 1; l < a.L; ++l) h->sweep<<<grid, h->var.w * kWave, h->lds_bytes, st>>>(a, l);
@@ -3958,7 +4012,7 @@ galv_status_t enqueue_solve(galv_dp *h, const int64_t *c_dev, const int32_t *m_d
             return fail(GALV_ERR_HIP, "forking the layer sweeps over internal streams failed: %s",
                         hipGetErrorString(err));
     }
-    final_kernel<<<a.B, kWave, 0, st>>>(a, best_cost_dev, best_last_dev);
+    if (a.packed != kChain) final_kernel<<<a.B, kWave, 0, st>>>(a, best_cost_dev, best_last_dev);
     HIP_TRY(hipGetLastError());
     h->solved = true;
     h->fresh = false;
@@ -4030,6 +4084,7 @@ galv_status_t galv_dp_create(const galv_dp_desc_t *desc, void *workspace_dev,
     h->desc = *desc;
     h->var = p.var;
     h->sweep = p.sweep;
+    h->chain = p.chain;
     h->lay = p.lay;
     h->ws_bytes = p.total;
     h->groups_y = p.groups_y;
@@ -4039,7 +4094,7 @@ galv_status_t galv_dp_create(const galv_dp_desc_t *desc, void *workspace_dev,
         // More than the default 64 KB of dynamic LDS: the kernel is told here, once, rather than at
         // the first solve, which a caller may be capturing into a graph.  (Should this fail, the
         // solve tries again and reports it.)
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(h->sweep), hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute(sweep_function(h), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)h->lds_bytes) == hipSuccess)
             h->lds_allowed = true;
         else
@@ -4057,7 +4112,7 @@ galv_status_t galv_dp_create(const galv_dp_desc_t *desc, void *workspace_dev,
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
             cus = 256;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(h->sweep),
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sweep_function(h),
                                                          h->var.w * kWave, h->lds_bytes) != hipSuccess || per_cu < 1)
             per_cu = h->var.wpe * 4 / h->var.w > 0 ? h->var.wpe * 4 / h->var.w : 1;
         (void)hipGetLastError();
@@ -4159,6 +4214,7 @@ galv_status_t galv_dp_solve_static(const galv_dp_desc_t *desc, const int64_t *c_
     h.desc = *desc;
     h.var = p.var;
     h.sweep = p.sweep;
+    h.chain = p.chain;
     h.lay = p.lay;
     h.ws_bytes = p.total;
     h.groups_y = p.groups_y;
