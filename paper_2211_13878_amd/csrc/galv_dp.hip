@@ -302,6 +302,21 @@ struct Wide {
     }
 };
 
+// Smallest value over the wave's lanes, in every lane.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+#define GALV_DPP_MIN(ctrl) v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, ctrl, 0xf, 0xf, false))
+    GALV_DPP_MIN(0x111);                           // row_shr 1, 2, 4, 8: minimum of each row of 16 in its last lane
+    GALV_DPP_MIN(0x112);
+    GALV_DPP_MIN(0x114);
+    GALV_DPP_MIN(0x118);
+#undef GALV_DPP_MIN
+    return min(min(read_lane(v, 15), read_lane(v, 31)), min(read_lane(v, 47), read_lane(v, 63)));
+}
+__device__ __forceinline__ uint64_t wave_min(uint64_t v) {     // (the high words' minimum, then the low words' beside it)
+    const uint32_t hi = wave_min((uint32_t)(v >> 32));
+    return (uint64_t)hi << 32 | wave_min((uint32_t)(v >> 32) == hi ? (uint32_t)v : 0xffffffffu);
+}
+
 // ------------------------------------------------------------------ preparation
 //
 // One workgroup per instance.  Checks the value preconditions, bounds the
@@ -320,7 +335,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
 
     __shared__ int bad;
     __shared__ unsigned long long rmax[64];  // max of each transition matrix (64 at a time)
-    __shared__ unsigned long long red[2][kPrepThreads / kWave];
+    __shared__ unsigned long long red[2][kPrepThreads / kWave], red4[4][kPrepThreads / kWave];
     __shared__ int m_top;                          // layer 0's largest usable memory
     if (tid == 0) bad = 0;
     __syncthreads();
@@ -368,49 +383,72 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 
-    // sum over layers of max_s c(l,s), saturating at 2^62: a wave per layer, a lane per strategy
-    // (one thread walking a layer's strategies is a chain of loads, and with few layers most of
-    // the workgroup would idle)
-    unsigned long long part = 0;
+    // The largest entries of the first two matrices, and how many transitions use them; then the sum over layers of max_s c(l,s),
+    // saturating at 2^62: a wave per layer, a lane per strategy (one thread walking a layer's strategies is a chain of loads,
+    // and with few layers most of the workgroup would idle).  All loads are on their way before the first reduction, and
+    // one barrier reduces all four: this kernel's time is its round trips (one by one, 37 layers x 29 strategies took 12.7 us).
+    unsigned long long of[4] = {0, 0, 0, 0};       // sum of costs; matrix 0; matrix 1; transitions with 0 and, from bit 32, with 1
+    bool off = false;                              // (kept in a register: a store to `bad` inside the loops
+                                                   // would hold the next iteration's loads back)
+    for (int64_t k = 0; k < 2 && k < nR; ++k) {
+        const ConstPtr<int64_t> Rm = R + k * S * S;
+#pragma unroll 4
+        for (int64_t i = tid; i < S * S; i += kPrepThreads) {
+            const int64_t v = Rm[i];
+            off |= v < 0 || v >= kInf;
+            of[1 + k] = largest(of[1 + k], (unsigned long long)v);
+        }
+    }
+    for (int64_t l = 1 + tid; l < L; l += kPrepThreads) {
+        const int64_t k = ridx ? ridx[l] : 0;
+        off |= k < 0 || k >= nR;
+        of[3] += (k == 0 ? 1ull : 0) + (k == 1 ? 1ull << 32 : 0);
+    }
     for (int64_t l = wave; l < L; l += kPrepThreads / kWave) {
         unsigned long long mx = 0;
-        bool off = false;                          // (kept in a register: a store to `bad` inside the loop
-                                                   // would hold the next iteration's loads back)
 #pragma unroll 2
         for (int64_t s = lane; s < S; s += kWave) {
             const int64_t v = c[l * S + s];
             off |= v < 0 || v >= kInf || m[l * S + s] < 0;
             if ((unsigned long long)v > mx) mx = (unsigned long long)v;
         }
-        if (off) bad = 1;
-#pragma unroll
-        for (int w = kWave / 2; w > 0; w >>= 1) {
-            const unsigned long long o = (unsigned long long)__shfl_xor((long long)mx, w, kWave);
-            if (o > mx) mx = o;
-        }
-        if (lane == 0) {
-            if (ridx && l >= 1 && (ridx[l] < 0 || ridx[l] >= nR)) bad = 1;
-            part += mx;
-            if (part > cap) part = cap;
-        }
+        mx = ~(unsigned long long)wave_min((uint64_t)~mx);
+        if (lane == 0) of[0] = sum_to_cap(of[0], mx < cap ? mx : cap);
     }
-    const unsigned long long bound_c = reduce(part, sum_to_cap);
-
-    // plus, for every layer transition, the max of the matrix it uses
-    unsigned long long rsum = 0, rmax_all = 0;
-    for (int64_t k0 = 0; k0 < nR; k0 += 64) {
+    if (off) bad = 1;
+    auto join = [&](int q, unsigned long long x, unsigned long long y) { return q == 0 ? sum_to_cap(x, y) : q == 3 ? x + y : largest(x, y); };
+#pragma unroll
+    for (int w = kWave / 2; w > 0; w >>= 1)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) of[q] = join(q, of[q], (unsigned long long)__shfl_xor((long long)of[q], w, kWave));
+    if (lane < 4) red4[lane][wave] = lane == 0 ? of[0] : lane == 1 ? of[1] : lane == 2 ? of[2] : of[3];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) of[q] = red4[q][lane & (kPrepThreads / kWave - 1)];
+#pragma unroll
+    for (int w = kPrepThreads / kWave / 2; w > 0; w >>= 1)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) of[q] = join(q, of[q], (unsigned long long)__shfl_xor((long long)of[q], w, kWave));
+    const unsigned long long bound_c = of[0];
+    // the sum, over the layer transitions, of the largest entry of the matrix each uses
+    auto times = [&](unsigned long long n, unsigned long long x) {
+        return __umul64hi(n, x) != 0 || n * x > cap ? cap : n * x;
+    };
+    unsigned long long rmax_all = largest(of[1], of[2]);
+    unsigned long long rsum = sum_to_cap(times(of[3] & 0xffffffffull, of[1] < cap ? of[1] : cap), times(of[3] >> 32, of[2] < cap ? of[2] : cap));
+    for (int64_t k0 = 2; k0 < nR; k0 += 64) {
         const int64_t kn = (nR - k0 < 64) ? nR - k0 : 64;
         for (int64_t k = 0; k < kn; ++k) {
             unsigned long long mx = 0;
             const ConstPtr<int64_t> Rm = R + (k0 + k) * S * S;
-            bool off = false;
+            bool wrong = false;
 #pragma unroll 4
             for (int64_t i = tid; i < S * S; i += kPrepThreads) {
                 const int64_t v = Rm[i];
-                off |= v < 0 || v >= kInf;
+                wrong |= v < 0 || v >= kInf;
                 if ((unsigned long long)v > mx) mx = (unsigned long long)v;
             }
-            if (off) bad = 1;
+            if (wrong) bad = 1;
             mx = reduce(mx, largest);
             if (tid == 0) rmax[k] = mx;
             rmax_all = largest(rmax_all, mx);
@@ -429,10 +467,10 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
         rsum = sum_to_cap(rsum, reduce(part_r, sum_to_cap));
     }
 
-    __shared__ int status_s;
-    if (tid == 0) {
+    // (what was found wrong stands behind a barrier since; every thread works out the same status)
+    int st;
+    {
         const unsigned long long bound = bound_c + rsum;   // each <= 2^62: no wrap
-        int st;
         if (bad || bound >= cap) {
             st = GALV_INSTANCE_BAD_VALUE;
         } else if (flags & GALV_DP_FORCE_INT64) {
@@ -443,7 +481,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
             const bool u32 = !(flags & GALV_DP_NO_U32) &&
                              ((2 * rmax_all + 2) << a.k_bits) <= (1ull << 32);
             st = u32 ? GALV_INSTANCE_OK_FAST_U32 : GALV_INSTANCE_OK_FAST;
-        } else if (a.synth_l1 && !(flags & GALV_DP_NO_U32) &&
+        } else if (a.synth_l1 && !(flags & GALV_DP_NO_U32) && rmax_all < (1ull << 32) &&
                    ((2 * rmax_all + 2) << a.k_bits) <= (1ull << 32)) {
             // costs need 64-bit cells, but only RELATIVE costs (clamped at R_max + 1) enter the keys:
             // the 32-bit-key arithmetic and its pruning apply all the same (row-sharing variants)
@@ -453,12 +491,9 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
         } else {
             st = GALV_INSTANCE_OK_INT64;
         }
-        a.dclamp[b] = rmax_all < 0xffffffffull ? (uint32_t)(rmax_all + 1) : 0u;
-        status_s = st;
-        a.status[b] = st;
     }
-    __syncthreads();
-    const int st = status_s;
+    uint32_t clamp = rmax_all < 0xffffffffull ? (uint32_t)(rmax_all + 1) : 0u;
+    if (tid == 0) a.status[b] = st;
     // The byte table saves what the pruning lets it save.  Where transition costs dwarf the spread of the layer
     // costs, hardly a row is left out, and an instance on 64-bit keys rebuilds every cell that it could have read:
     // it keeps cost rows instead (clamp 0 says so, see byte_status), as long as these stay in the caches.  Rows of
@@ -487,24 +522,25 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
                 if (v[q] != ~0ull) seen += (1ull << 32) + (v[q] - least <= rmax_all ? 1 : 0);
         }
         seen = reduce(seen, [](unsigned long long x, unsigned long long y) { return x + y; });
-        if (tid == 0 && 4 * (seen & 0xffffffffull) > 3 * (seen >> 32)) a.dclamp[b] = 0;
-        __syncthreads();
+        if (4 * (seen & 0xffffffffull) > 3 * (seen >> 32)) clamp = 0;
     }
     // One record per layer with what a sweep workgroup needs before anything else, so that it
     // takes one load instead of a chain of them.  (The count of the former layer's usable
-    // strategies is filled in below, by the thread that builds that layer's list.)
+    // strategies is filled in below, by the wave that builds that layer's list, if any.)
+    if (tid == 0) a.dclamp[b] = clamp;
+    const bool lists = narrow_cells(st) || st == GALV_INSTANCE_OK_FAST_WIDE || st == GALV_INSTANCE_OK_U32_WIDE;
+    const bool bytes = a.packed && L > 1 && byte_status(st, clamp);
     for (int64_t l = tid; l < L; l += kPrepThreads) {
         int32_t *h = a.hdr + ((int64_t)b * L + l) * 8;
         h[0] = st;
         h[1] = budget;
-        h[2] = 0;
-        h[3] = (int32_t)a.dclamp[b];
+        if (!lists || l == 0) h[2] = 0;
+        h[3] = (int32_t)clamp;
         h[4] = (ridx && l >= 1 && st >= 0) ? ridx[l] : 0;
         h[5] = 0;
-        h[6] = a.packed == kChain && l > 1 && is_packed(a, st, b) ? kUnset : budget;
+        h[6] = a.packed == kChain && l > 1 && bytes ? kUnset : budget;
     }
-    __syncthreads();
-    if (!narrow_cells(st) && st != GALV_INSTANCE_OK_FAST_WIDE && st != GALV_INSTANCE_OK_U32_WIDE) return;
+    if (!lists) return;
 
     // R key = R * 2^k + s' (s' = row = former strategy); padded columns are +inf so
     // that they never win and never read past the caller's matrix.
@@ -530,30 +566,26 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
             }
         }
     }
-    // c(l,s) in the form the epilogue adds: the integer itself (integer cells) or the
-    // double c * 2^k (cells that hold 64-bit keys).
-    uint64_t *ck = a.ck + (int64_t)b * L * S_pad;
-    const bool c_int = narrow_cells(st) || st == GALV_INSTANCE_OK_U32_WIDE || is_packed(a, st, b);
-    for (int64_t l = wave; l < L; l += kWaves)
-        for (int sx = lane; sx < S_pad; sx += kWave) {
-            const int64_t v = (sx < (int)S) ? c[l * S + sx] : 0;
-            ck[l * S_pad + sx] = c_int ? (uint64_t)v : (uint64_t)__double_as_longlong((double)v * scale);
-        }
     // Per layer, the strategies whose memory fits the budget at all, in ascending
     // order, with their shift: the sweep of the next layer walks this list instead
     // of all S columns (a column that never fits is infinity everywhere).
     // (a wave per layer, a lane per strategy: the usable ones find their place in the list by
     // counting the usable lanes below them)
+    // Beside it c(l,s) in the form the epilogue adds: the integer itself (integer cells) or the
+    // double c * 2^k (cells that hold 64-bit keys).
+    uint64_t *ck = a.ck + (int64_t)b * L * S_pad;
+    const bool c_int = narrow_cells(st) || st == GALV_INSTANCE_OK_U32_WIDE || bytes;
     for (int64_t l = wave; l < L; l += kPrepThreads / kWave) {
         uint64_t *lst = a.vlist + ((int64_t)b * L + l) * a.S_pad;
         uint64_t *lc = a.vcost + ((int64_t)b * L + l) * a.S_pad;
         int n = 0, m_lo = budget + 1, m_hi = 0;    // usable strategies, their smallest and largest memory
         uint64_t last_ent = 0, last_c = 0;         // the list's last entry so far (wave-uniform)
-        for (int s0 = 0; s0 < (int)S; s0 += kWave) {
+        for (int s0 = 0; s0 < S_pad; s0 += kWave) {
             const int sx = s0 + lane;
             const bool in = sx < (int)S;
             const int sh = in ? m[l * S + sx] : 0;
             const uint64_t cv = in ? (uint64_t)c[l * S + sx] : 0;
+            if (sx < S_pad) ck[l * S_pad + sx] = c_int ? cv : (uint64_t)__double_as_longlong((double)(int64_t)cv * scale);
             const bool ok = in && sh <= budget;
             if (ok) {
                 m_lo = min(m_lo, sh);
@@ -573,11 +605,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
                 n += __builtin_popcountll(votes);
             }
         }
-#pragma unroll
-        for (int w = kWave / 2; w > 0; w >>= 1) {
-            m_lo = min(m_lo, __shfl_xor(m_lo, w, kWave));
-            m_hi = max(m_hi, __shfl_xor(m_hi, w, kWave));
-        }
+        m_lo = (int)wave_min((uint32_t)m_lo);      // (neither is negative)
+        m_hi = (int)~wave_min(~(uint32_t)m_hi);
         if (lane == 0) {
             a.nvalid[(int64_t)b * L + l] = n;
             a.hdr[((int64_t)b * L + l) * 8 + 7] = m_lo;
@@ -593,7 +622,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
                 lc[i] = last_c;
             }
     }
-    if (!is_packed(a, st, b)) return;
+    if (!bytes) return;
     // Columns of each layer that are worth sweeping (see the byte-table sweep): from the sum of the
     // smallest memories before it, saturating above the budget (a wave's prefix sum, 64 layers at a
     // time); layer 1 up to layer 0's largest memory, later layers as live_step finds.
@@ -1683,21 +1712,6 @@ struct Key64 {
     static __device__ __forceinline__ uint64_t cost(T key, int k) { return bits(key) >> k; }
     static __device__ __forceinline__ T least(T x, T y) { return __builtin_fmin(x, y); }
 };
-
-// Smallest value over the wave's lanes, in every lane.
-__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
-#define GALV_DPP_MIN(ctrl) v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, ctrl, 0xf, 0xf, false))
-    GALV_DPP_MIN(0x111);                           // row_shr 1, 2, 4, 8: minimum of each row of 16 in its last lane
-    GALV_DPP_MIN(0x112);
-    GALV_DPP_MIN(0x114);
-    GALV_DPP_MIN(0x118);
-#undef GALV_DPP_MIN
-    return min(min(read_lane(v, 15), read_lane(v, 31)), min(read_lane(v, 47), read_lane(v, 63)));
-}
-__device__ __forceinline__ uint64_t wave_min(uint64_t v) {     // (the high words' minimum, then the low words' beside it)
-    const uint32_t hi = wave_min((uint32_t)(v >> 32));
-    return (uint64_t)hi << 32 | wave_min((uint32_t)(v >> 32) == hi ? (uint32_t)v : 0xffffffffu);
-}
 
 // One step of the recurrence without a memory limit, for layer l of instance b: V_l(s) and the
 // memory its plan takes before layer l, from those of layer l - 1; then (tell) the last column of
