@@ -76,17 +76,22 @@ class _StageBatch:
         self.S = model.n_strategies[pp]
         B = window * pp
         self.solver = binding.Solver(B, self.Ls, self.S, budget, nR=2, device=device)
-        self.c = np.zeros((B, self.Ls, self.S), np.int64)
-        self.m = np.zeros((B, self.Ls, self.S), np.int32)
-        self.R = np.zeros((B, 2, self.S, self.S), np.int64)        # matrix 1 stays zero: padding
-        self.r_idx = np.zeros((B, self.Ls), np.int32)
+        # (costs, transition costs and memories in one piece: an upload is waited for, whatever its size)
+        nc, nR, nm = 8 * B * self.Ls * self.S, 16 * B * self.S * self.S, 4 * B * self.Ls * self.S
+        self.host = np.zeros(nc + nR + nm, np.uint8)
+        self.c = self.host[:nc].view(np.int64).reshape(B, self.Ls, self.S)
+        self.R = self.host[nc:nc + nR].view(np.int64).reshape(B, 2, self.S, self.S)      # matrix 1 stays zero: padding
+        self.m = self.host[nc + nR:].view(np.int32).reshape(B, self.Ls, self.S)
+        self.parts = (nc, nR, nm)
+        r_idx = np.zeros((B, self.Ls), np.int32)
         self.budget = torch.full((B,), budget, dtype=torch.int32, device=device)
         unusable = np.int32(budget + 1)
         for st, (lo, hi) in enumerate(self.cuts):
             n = hi - lo
             if n < self.Ls:
                 self.m[st::pp, n:, 1:] = unusable
-                self.r_idx[st::pp, n:] = 1
+                r_idx[st::pp, n:] = 1
+        self.r_idx = torch.from_numpy(r_idx).to(device)            # (the same for every window)
         self.stream = _stream(device, pp)                  # the degrees' solves are independent: one stream each
 
     def fill(self, model, batch_sizes):
@@ -101,8 +106,9 @@ class _StageBatch:
         main = torch.cuda.current_stream(device)
         self.stream.wait_stream(main)
         with torch.cuda.stream(self.stream):
-            to = lambda a: torch.from_numpy(a).to(device)
-            self.dev = (to(self.c), to(self.m), to(self.R), to(self.r_idx), self.budget)
+            c, R, m = torch.from_numpy(self.host).to(device).split(self.parts)
+            self.dev = (c.view(torch.int64).view(self.c.shape), m.view(torch.int32).view(self.m.shape),
+                        R.view(torch.int64).view(self.R.shape), self.r_idx, self.budget)
             s = self.solver
             s._inputs = self.dev
             binding.galv_dp_solve_batched(s.handle, *self.dev, stage_cost, s.best_last)
@@ -114,7 +120,8 @@ def optimize(model, n_devices: int, budget: int, batch_sizes, window: int = 8,
     device = torch.device(device)
     if not 0 <= budget < np.iinfo(np.int32).max:
         raise ValueError("budget must be in [0, 2^31 - 2]")
-    batch_sizes = [int(b) for b in batch_sizes]
+    if not isinstance(batch_sizes, range):               # (a range may be far longer than the search: 5 ms for 100000 sizes)
+        batch_sizes = [int(b) for b in batch_sizes]
     degrees = [1 << k for k in range(n_devices.bit_length()) if (1 << k) <= model.n_layers]
     skipped = n_devices.bit_length() - len(degrees)      # degrees deeper than the layer count never fit
     stages = [_StageBatch(model, pp, window, budget, device) for pp in degrees]
@@ -123,7 +130,7 @@ def optimize(model, n_devices: int, budget: int, batch_sizes, window: int = 8,
     best_index, stopped, n_explored = -1, False, 0
     batch = cost = pp_index = None
     for base in range(0, len(batch_sizes), window):
-        win = batch_sizes[base:base + window]
+        win = list(batch_sizes[base:base + window])
         n = len(win)
         padded = win + [win[-1]] * (window - n)           # a short last window repeats its last size
         stage_cost = torch.empty(window * sum(degrees), dtype=torch.int64, device=device)
