@@ -353,7 +353,7 @@ def run_config(cfg, args, torch, binding, workloads):
     fetched_share = (float(sum(f for _, _, f in stats)) / float(sum(n for _, n, _ in stats))
                      if sum(n for _, n, _ in stats) > 0 else 1.0)
     # What one layer takes, per instance on average: candidates, lane-operations, table bytes, swept columns.
-    packed = bool(main_leg["packed"])
+    packed, chained = main_leg["packed"] == 1, main_leg["packed"] == 2
     ops = OPS_PER_CANDIDATE.get(int(status[0]), 0.0)
 
     def layer_work(b):
@@ -420,6 +420,11 @@ def run_config(cfg, args, torch, binding, workloads):
                     "single_stream": single and {"launch_ms": single["launch_ms"]},
                     "note": "not priced: the library counts no rows for instances on 64-bit keys"}
 
+    if chained:
+        roofline = {"bound": None, "kernel": "chain_kernel", "launch_ms": sweep_ms,
+                    "single_stream": single and {"launch_ms": single["launch_ms"]},
+                    "note": "not priced: all layers run in one launch, whose time is the latency of the chain of layers"}
+
     kinds = {3: "u32", 4: "u32", 0: "f64", 2: "f64", 1: "int64"}
     used = sorted({kinds[int(st)] for st in status if int(st) in kinds})
     dtype = ("+".join(used) or "none") + " (exact integer keys; int64 costs in, int64 costs out)"
@@ -435,8 +440,9 @@ def run_config(cfg, args, torch, binding, workloads):
         "data": "synthetic",
         "config": {"workload": f"config {cfg} '{w.name}': B={w.B} L={w.L} S={w.S} "
                                f"E_max={w.E_max} budgets {int(w.budget.min())}..{int(w.budget.max())}",
-                   "back_pointer_bytes": 1 if args.bp_u8 or packed else 4,
+                   "back_pointer_bytes": 1 if args.bp_u8 or packed or chained else 4,
                    "byte_table": packed,
+                   "one_launch_for_all_layers": chained,
                    "internal_streams": main_leg["streams"],
                    "peek_before_fetch": bool(main_leg["peek"]),
                    "tile_columns": main_leg["tile_columns"],

@@ -269,7 +269,9 @@ galv_status_t galv_dp_get_stats(galv_dp_t *h, int64_t *stats_dev, void *stream);
 /*
  * What galv_dp_create chose for this handle from the shape and the flags (host call, no GPU work):
  *   config [4] HOST int32  [0] 1 if 32-bit-key instances keep the byte table (see
- *                              GALV_DP_FORCE_PACK), [1] 1 if the sweep peeks before it fetches a
+ *                              GALV_DP_FORCE_PACK), 2 if all layers run in one launch, which
+ *                              keeps whole costs of every layer and one-byte argmins
+ *                              (galv_dp_workspace_bytes_preferred), [1] 1 if the sweep peeks before it fetches a
  *                              row (GALV_DP_FORCE_PEEK), [2] internal streams the last solve used
  *                              (before any solve: what the first will use), [3] budget columns
  *                              per sweep workgroup.

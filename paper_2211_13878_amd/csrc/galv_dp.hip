@@ -2332,7 +2332,7 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_bytes_kernel(Layout a, i
 //
 // What bounds it is the latency of a layer's chain: words 0.6 us, rows 0.8, column minima and alive rows 0.6, min-plus and
 // new cells 0.5, until the cells have arrived 0.5.  Whole searches, a launch per layer / chained, in us: 29 strategies x 78 tiles
-// x 37 layers (`single`) 248 / 166, 22 x 1032 x 32 281 / 215, 22 x 1256 x 24 with all budgets 239 / 200, 44 x 272 x 48 482 / 327.
+// x 37 layers (`single`) 251 / 167, 22 x 1032 x 32 281 / 210, 22 x 1256 x 24 with all budgets 251 / 191, 44 x 272 x 48 482 / 294.
 constexpr int kChainCols = 128;
 constexpr int kSpins = 1 << 21;                    // of some 0.6 us: no wait ends this way unless the memory order is broken
 
@@ -4317,7 +4317,7 @@ galv_status_t galv_dp_get_stats(galv_dp_t *h, int64_t *stats_dev, void *stream) 
 galv_status_t galv_dp_get_config(const galv_dp_t *h, int32_t *config) {
     if (!h) return fail(GALV_ERR_INVALID_ARG, "handle is NULL");
     if (!config) return fail(GALV_ERR_INVALID_ARG, "config is NULL");
-    config[0] = h->lay.packed && h->lay.packed != kChain ? 1 : 0;
+    config[0] = h->lay.packed == kChain ? 2 : h->lay.packed ? 1 : 0;
     config[1] = h->lay.peek && h->var.share ? 1 : 0;
     config[2] = h->n_used > 0 ? h->n_used : (h->lay.L < 2 ? 1 : pick_streams(h, tiles_at_most(h)));
     config[3] = h->lay.tile_e;

@@ -35,7 +35,8 @@ def test_the_rule_and_the_workspace(lib, B, L, S, E, chains):
         if n_bytes >= need:
             assert create(lib, desc, n_bytes)[0] == binding.GALV_OK
     if chains and L > 4:
-        assert create(lib, desc, best)[1][:2] == (0, 0)
+        assert create(lib, desc, best)[1][:2] == (2, 0)
+        assert create(lib, desc, best - 1)[1][0] != 2
     # what asks for a particular sweep, or for several streams, gets a launch per layer
     for flags in (binding.GALV_DP_FORCE_PACK, binding.GALV_DP_NO_PACK, binding.GALV_DP_BP_U8, binding.GALV_DP_NO_WIDE_TILES,
                   binding.GALV_DP_FORCE_WIDE_TILES, binding.GALV_DP_FORCE_PEEK, binding.GALV_DP_NO_PEEK, binding.GALV_DP_NO_U32,
