@@ -277,7 +277,11 @@ class Solver:
         self.desc = make_desc(B, L, S, E_max, nR, flags)
         self.workspace_bytes = galv_dp_workspace_bytes_preferred(self.desc)
         with torch.cuda.device(self.device):
-            self.workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=self.device)
+            try:
+                self.workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=self.device)
+            except torch.cuda.OutOfMemoryError:     # rows of all layers do not fit beside what is there: a launch per layer
+                self.workspace_bytes = galv_dp_workspace_bytes(self.desc)
+                self.workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=self.device)
             self.handle = galv_dp_create(self.desc, self.workspace)
         self.best_cost = torch.empty(B, dtype=torch.int64, device=self.device)
         self.best_last = torch.empty(B, dtype=torch.int32, device=self.device)

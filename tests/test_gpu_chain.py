@@ -126,3 +126,29 @@ def test_a_graph_that_is_replayed_with_changing_inputs():
         for b, ref in enumerate(oracle.solve_workload(ws[rep % 3], threads=4)):
             assert int(cost[b]) == ref.best_cost and (plan[b].cpu().numpy() == ref.plan).all(), (rep, b)
     sol.close()
+
+
+def test_without_the_memory_for_all_layers_a_launch_per_layer(monkeypatch):
+    w = workload(5, 2, 9, 22, 4000)
+    desc = binding.make_desc(w.B, w.L, w.S, w.E_max, w.nR)
+    best, need = binding.galv_dp_workspace_bytes_preferred(desc), binding.galv_dp_workspace_bytes(desc)
+    assert best > need
+    empty = torch.empty
+
+    def scarce(*size, **options):
+        if size == (best,):
+            raise torch.cuda.OutOfMemoryError("no room")
+        return empty(*size, **options)
+
+    results = []
+    for chained in (True, False):
+        if not chained:
+            monkeypatch.setattr(binding.torch, "empty", scarce)
+        sol = binding.Solver(w.B, w.L, w.S, w.E_max, w.nR)
+        assert sol.workspace_bytes == (best if chained else need) and (sol.config()["packed"] == 2) == chained
+        dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (w.c, w.m, w.R, w.r_idx, w.budget)]
+        cost, last = sol.solve(*dev)
+        results.append([x.cpu().numpy().copy() for x in (cost, last, sol.backtrack())])
+        sol.close()
+    for x, y in zip(*results):
+        assert (x == y).all()
