@@ -2334,7 +2334,12 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_bytes_kernel(Layout a, i
 // new cells 0.5, until the cells have arrived 0.5.  Whole searches, a launch per layer / chained, in us: 29 strategies x 78 tiles
 // x 37 layers (`single`) 251 / 167, 22 x 1032 x 32 281 / 210, 22 x 1256 x 24 with all budgets 251 / 191, 44 x 272 x 48 482 / 294.
 constexpr int kChainCols = 128;
-constexpr int kSpins = 1 << 21;                    // of some 0.6 us: no wait ends this way unless the memory order is broken
+// Polls of some 0.6 us after which a wait is given up, so that no error in the memory order could hang the GPU.  A correct solve
+// must never get there, and the longest wait spans a whole search: the wave with an instance's last place may start with the
+// first layer, and blocks may run ahead of their neighbours over layers whose memories are small.  Hence the limit on layers:
+// at the slowest rate measured (360 us a layer: 64 strategies, whole costs) that many take some 600000 polls, a third of these.
+constexpr int kSpins = 1 << 21;
+constexpr int kChainLayers = 1024;
 
 template <class T>
 __device__ __forceinline__ T agent_load(const T *p) {
@@ -3770,10 +3775,11 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, bool chain, 
                            GALV_DP_FORCE_WIDE_TILES | GALV_DP_NO_WIDE_TILES;        // (what these ask for is a launch per layer)
     const int64_t chain_to = share < 128 ? 90000 : S <= 16 ? 60000 : S <= 24 ? 70000 : 46000;
     const ChainEntry *ce = S <= kWave ? pick_chain(S, tiles) : nullptr;
-    // (rows of every layer: at most 8 GB of them, and a layer's of one instance within 32 bits of offset)
+    // (rows of every layer: at most 8 GB of them, and a layer's of one instance within 32 bits of offset; at most kChainLayers
+    // layers, see there)
     const long double chain_bytes = ce ? 8.0L * ce->ts * ce->ng * ((int64_t)d->max_budget + kChainCols) : 0;
     if (chain && ce && !(d->flags & other) && ((d->flags & GALV_DP_STREAMS_MASK) >> GALV_DP_STREAMS_SHIFT) <= 1 && d->n_layers > 1 &&
-        tiles * S <= chain_to && chain_bytes < 4.0e9L && chain_bytes * d->n_instances * d->n_layers <= 8.0e9L)
+        d->n_layers <= kChainLayers && tiles * S <= chain_to && chain_bytes < 4.0e9L && chain_bytes * d->n_instances * d->n_layers <= 8.0e9L)
         shape = Tiles::chain;
     if (only) shape = *only;
     if (d->flags & GALV_DP_FORCE_WIDE_TILES) shape = Tiles::wide;

@@ -49,3 +49,13 @@ def test_preferred_checks_its_arguments(lib):
     n = ctypes.c_size_t(0)
     assert lib.galv_dp_workspace_bytes_preferred(None, ctypes.byref(n)) == binding.GALV_ERR_INVALID_ARG
     assert lib.galv_dp_workspace_bytes_preferred(ctypes.byref(binding.make_desc(1, 4, 6, 256)), None) == binding.GALV_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("S,E", [(2, 0), (8, 300), (44, 90)])
+def test_no_wait_is_longer_than_a_bounded_number_of_layers(lib, S, E):
+    """A wait inside the launch is given up after a fixed number of polls and may span a whole search: very deep searches take
+    a launch per layer."""
+    for L, chains in ((1023, True), (1024, True), (1025, False), (4096, False), (200000, False)):
+        desc = binding.make_desc(1, L, S, E, 1, binding.GALV_DP_STREAMS(1))
+        best = binding.galv_dp_workspace_bytes_preferred(desc)
+        assert create(lib, desc, best)[1][0] == 2 if chains else create(lib, desc, best)[1][0] != 2, L
