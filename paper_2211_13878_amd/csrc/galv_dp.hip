@@ -212,8 +212,12 @@ __device__ __forceinline__ bool byte_status(int st, uint32_t clamp) {
     return st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE ||
            ((st == GALV_INSTANCE_OK_FAST || st == GALV_INSTANCE_OK_FAST_WIDE) && clamp != 0);
 }
+// The same in a handle that runs all layers in one launch: relative costs may have 64 bits there (KeyBig).
+__device__ __forceinline__ bool byte_status(const Layout &a, int st, uint32_t clamp) {
+    return a.packed == kChain ? st >= 0 && st != GALV_INSTANCE_OK_INT64 : byte_status(st, clamp);
+}
 __device__ __forceinline__ bool is_packed(const Layout &a, int st, int b) {
-    return a.packed && a.L > 1 && byte_status(st, a.dclamp[b]);
+    return a.packed && a.L > 1 && byte_status(a, st, a.dclamp[b]);
 }
 
 // First row of layer l (>= 1) in the byte table.  An instance's bytes start where its 32-bit back-pointers
@@ -317,6 +321,15 @@ __device__ __forceinline__ uint64_t wave_min(uint64_t v) {     // (the high word
     return (uint64_t)hi << 32 | wave_min((uint32_t)(v >> 32) == hi ? (uint32_t)v : 0xffffffffu);
 }
 
+// Chained sweep, words that workgroups tell each other: the counter of places, then [B][n_tiles] the last layer finished, each in
+// a line of its own (a line that many ask for answers them one after the other).  Behind them the clamps of 64-bit relative costs.
+__device__ __forceinline__ int32_t *chain_words(const Layout &a) { return reinterpret_cast<int32_t *>(a.U[1]); }
+__device__ __forceinline__ int32_t *chain_flags(const Layout &a, int b) {
+    return chain_words(a) + kWave + (int64_t)b * a.n_tiles * kWordStep;
+}
+__device__ __forceinline__ uint64_t *chain_clamps(const Layout &a) { return reinterpret_cast<uint64_t *>(chain_flags(a, a.B)); }
+constexpr size_t chain_word_bytes(int64_t B, int64_t n_tiles) { return (size_t)(kWave + B * n_tiles * kWordStep) * 4 + (size_t)B * 8; }
+
 // ------------------------------------------------------------------ preparation
 //
 // One workgroup per instance.  Checks the value preconditions, bounds the
@@ -367,9 +380,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
     // word of pinned memory that the NEXT solve reads when it sizes its launches; the budgets live
     // on the device, and a solve never waits for one).
     if (a.packed == kChain) {                      // nothing told yet (see chain_words)
-        int32_t *words = reinterpret_cast<int32_t *>(a.U[1]);
-        if (b == 0 && tid == 0) words[0] = 0;
-        for (int i = tid; i < a.n_tiles; i += kPrepThreads) words[kWave + ((int64_t)b * a.n_tiles + i) * kWordStep] = 0;
+        if (b == 0 && tid == 0) *chain_words(a) = 0;
+        for (int i = tid; i < a.n_tiles; i += kPrepThreads) chain_flags(a, b)[(int64_t)i * kWordStep] = 0;
     }
     if (a.seen && b == 0) {
         unsigned long long tiles = 0;
@@ -469,8 +481,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
 
     // (what was found wrong stands behind a barrier since; every thread works out the same status)
     int st;
+    const unsigned long long bound = bound_c + rsum;       // each <= 2^62: no wrap
     {
-        const unsigned long long bound = bound_c + rsum;   // each <= 2^62: no wrap
         if (bad || bound >= cap) {
             st = GALV_INSTANCE_BAD_VALUE;
         } else if (flags & GALV_DP_FORCE_INT64) {
@@ -528,8 +540,9 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(Layout a, uint32_t f
     // takes one load instead of a chain of them.  (The count of the former layer's usable
     // strategies is filled in below, by the wave that builds that layer's list, if any.)
     if (tid == 0) a.dclamp[b] = clamp;
+    if (a.packed == kChain && tid == 0) chain_clamps(a)[b] = (rmax_all < bound ? rmax_all : bound) + 1;
     const bool lists = narrow_cells(st) || st == GALV_INSTANCE_OK_FAST_WIDE || st == GALV_INSTANCE_OK_U32_WIDE;
-    const bool bytes = a.packed && L > 1 && byte_status(st, clamp);
+    const bool bytes = a.packed && L > 1 && byte_status(a, st, clamp);
     for (int64_t l = tid; l < L; l += kPrepThreads) {
         int32_t *h = a.hdr + ((int64_t)b * L + l) * 8;
         h[0] = st;
@@ -1081,7 +1094,7 @@ __device__ __forceinline__ void minplus_u32x2(uint32_t (&acc)[TE], const uint32_
 }
 
 // Dynamic LDS of the row-sharing body below.
-extern __shared__ uint32_t lds_cells[];
+extern __shared__ __align__(16) uint32_t lds_cells[];
 
 // Plain form: NG strategy groups x (waves / NG) budget sub-tiles per workgroup, every wave
 // reads the rows it needs through the caches, twice (a first pass for the column minima, a
@@ -1695,6 +1708,11 @@ __device__ __forceinline__ const T *rkeys(const Layout &a, int b, int r) {
 // strategies x 16384 columns x 48 layers x 16 instances 3.06 ms, and with the byte table 1.27 ms.
 struct Key32 {
     using T = uint32_t;
+    using Rel = uint32_t;      // a relative cost
+    using Stored = uint32_t;   // and how the chained sweep keeps it: as it is
+    static constexpr bool kKeysInLds = true;       // chained sweep: the transition keys are kept there
+    static __device__ __forceinline__ Stored stored(Rel rel, int) { return rel; }
+    static __device__ __forceinline__ T from(Stored rel, int k) { return make(rel, k); }
     static __device__ __forceinline__ T none() { return 0xffffffffu; }
     static __device__ __forceinline__ T make(uint32_t rel, int k) { return rel << k; }
     static __device__ __forceinline__ uint32_t low(T key) { return key; }
@@ -1703,6 +1721,11 @@ struct Key32 {
 };
 struct Key64 {
     using T = double;
+    using Rel = uint32_t;
+    using Stored = uint32_t;
+    static constexpr bool kKeysInLds = true;
+    static __device__ __forceinline__ Stored stored(Rel rel, int) { return rel; }
+    static __device__ __forceinline__ T from(Stored rel, int k) { return make(rel, k); }
     static __device__ __forceinline__ T none() { return 0x1p51; }
     static __device__ __forceinline__ T make(uint32_t rel, int k) { return __builtin_ldexp((double)rel, k); }
     static __device__ __forceinline__ uint64_t bits(T key) {     // (below 2^52: the sum's mantissa is the number)
@@ -1710,6 +1733,23 @@ struct Key64 {
     }
     static __device__ __forceinline__ uint32_t low(T key) { return (uint32_t)bits(key); }
     static __device__ __forceinline__ uint64_t cost(T key, int k) { return bits(key) >> k; }
+    static __device__ __forceinline__ T least(T x, T y) { return __builtin_fmin(x, y); }
+};
+// The same with relative costs of 64 bits, for transition costs of 2^32 - 1 and more (chained sweep only).  The clamp is at most
+// the largest plan cost + 1, so a clamped key is at most 2^52 and with a transition cost 2^53; a minimum is below 2^52.  (The keys
+// themselves are kept, as bits; they take the room that the transition keys have in LDS otherwise.)
+struct KeyBig {
+    using T = double;
+    using Rel = uint64_t;
+    using Stored = uint64_t;
+    static constexpr bool kKeysInLds = false;
+    static __device__ __forceinline__ T none() { return INFINITY; }
+    static __device__ __forceinline__ Stored stored(Rel rel, int k) {
+        return (uint64_t)__double_as_longlong(__longlong_as_double((long long)(kBias + (rel << k))) - 0x1p52);
+    }
+    static __device__ __forceinline__ T from(Stored key, int) { return __longlong_as_double((long long)key); }
+    static __device__ __forceinline__ uint32_t low(T key) { return Key64::low(key); }
+    static __device__ __forceinline__ uint64_t cost(T key, int k) { return Key64::cost(key, k); }
     static __device__ __forceinline__ T least(T x, T y) { return __builtin_fmin(x, y); }
 };
 
@@ -2337,7 +2377,7 @@ constexpr int kChainCols = 128;
 // Polls of some 0.6 us after which a wait is given up, so that no error in the memory order could hang the GPU.  A correct solve
 // must never get there, and the longest wait spans a whole search: the wave with an instance's last place may start with the
 // first layer, and blocks may run ahead of their neighbours over layers whose memories are small.  Hence the limit on layers:
-// at the slowest rate measured (360 us a layer: 64 strategies, whole costs) that many take some 600000 polls, a third of these.
+// at the slowest rate measured (100 us a layer: 60 strategies, 64-bit integers) that many take some 170000 polls, a twelfth of these.
 constexpr int kSpins = 1 << 21;
 constexpr int kChainLayers = 1024;
 
@@ -2348,12 +2388,6 @@ __device__ __forceinline__ T agent_load(const T *p) {
 template <class T>
 __device__ __forceinline__ void agent_store(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// Words that workgroups tell each other: the counter of places, then [B][n_tiles] the last layer finished, each in a
-// line of its own (a line that many ask for answers them one after the other).
-__device__ __forceinline__ int32_t *chain_words(const Layout &a) { return reinterpret_cast<int32_t *>(a.U[1]); }
-__device__ __forceinline__ int32_t *chain_flags(const Layout &a, int b) {
-    return chain_words(a) + kWave + (int64_t)b * a.n_tiles * kWordStep;
 }
 template <class Cell>
 __device__ __forceinline__ Cell *chain_rows(const Layout &a, int b, int l) {
@@ -2391,7 +2425,7 @@ __device__ __forceinline__ bool chain_last_column(const int32_t *p, int32_t &x) 
 // The recurrence without a memory limit for instance b, all layers (see live_step), by one wave with a lane per strategy:
 // no exchange, the transition keys in LDS.  (1.7 us a layer at 29 strategies, half of what the sweep takes.)
 template <int ROWS, class Key>
-__device__ __forceinline__ void chain_live(const Layout &a, int b, uint32_t dmax, int budget) {
+__device__ __forceinline__ void chain_live(const Layout &a, int b, typename Key::Rel dmax, int budget) {
     using KeyT = typename Key::T;
     const int lane = lane_id();
     const int S = a.S, k = a.k_bits, L = a.L;
@@ -2445,14 +2479,14 @@ __device__ __forceinline__ void chain_live(const Layout &a, int b, uint32_t dmax
         const int32_t upto = (int32_t)(with <= budget ? with : (int64_t)budget + 1);
         // (an unusable strategy costs as much as one that is ruled out)
         const uint64_t rel = V - vmin;
-        const uint32_t dv = usable && rel < dmax ? (uint32_t)rel : dmax;
+        const typename Key::Stored dv = Key::stored(usable && rel < dmax ? (typename Key::Rel)rel : dmax, k);
         KeyT best = Key::none();
         for (int i0 = 0; i0 < S; i0 += 8) {
             KeyT row[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) row[u] = Rl[(i0 + u < S ? i0 + u : S - 1) * ROWS + at];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) best = Key::least(best, Key::make(read_lane(dv, i0 + u < S ? i0 + u : S - 1), k) + row[u]);
+            for (int u = 0; u < 8; ++u) best = Key::least(best, Key::from(read_lane(dv, i0 + u < S ? i0 + u : S - 1), k) + row[u]);
         }
         const int32_t x = __shfl(upto, (int)(Key::low(best) & ((1u << k) - 1u)), kWave);
         V = vmin + Key::cost(best, k) + now.c;
@@ -2524,14 +2558,16 @@ __device__ __forceinline__ void chain_load(const Layout &a, int wave, int b, int
 // g, g + NG, ... of the former layer's list and the strategies g * TS on; the column minima meet in LDS, and the rows
 // that are alive in the tile, all of which fit, are reduced by every wave, with the transition keys from LDS.  Wave 0 does the waiting for all.
 template <int TS, int NG, class Cell, class Key>
-__device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, int t, uint32_t dmax, ChainIn &in, uint64_t c0) {
+__device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, int t, typename Key::Rel dmax, ChainIn &in, uint64_t c0) {
     constexpr Cell kInfCell = sizeof(Cell) == 8 ? (Cell)kInf : (Cell)kInf32;
     constexpr Cell kAllOnes = ~(Cell)0;
     constexpr int kCols = kChainCols, TE = kCols / kWave, kRows = TS * NG;
     static_assert(kRows <= kWave, "list positions by lane");
     using KeyT = typename Key::T;
     using Word = std::conditional_t<sizeof(Cell) == 8, unsigned long long, uint32_t>;
-    typedef uint32_t relv __attribute__((ext_vector_type(TE)));
+    using Rel = typename Key::Rel;
+    using Stored = typename Key::Stored;
+    typedef Stored relv __attribute__((ext_vector_type(TE)));
     const int lane = lane_id();
     const int S = a.S, S_pad = kRows, L = a.L, k = a.k_bits;
     const int start = t * kCols, e0 = start + lane * TE;
@@ -2539,8 +2575,8 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
     int32_t *flags = chain_flags(a, b);
     Word *minima = reinterpret_cast<Word *>(lds_cells);                     // [2][kCols] of the columns, in turns
     unsigned long long *alive_of = reinterpret_cast<unsigned long long *>(minima + 2 * kCols);   // [2] list positions
-    KeyT *Rl = reinterpret_cast<KeyT *>(alive_of + 2);                      // [kRows][kRows] transition keys
-    uint32_t *keys = reinterpret_cast<uint32_t *>(Rl + kRows * kRows);      // [kRows][kCols] relative costs by list position
+    KeyT *Rl = reinterpret_cast<KeyT *>(alive_of + 2);                      // [kRows][kRows] transition keys, where they are kept
+    Stored *keys = reinterpret_cast<Stored *>(Rl + (Key::kKeysInLds ? kRows * kRows : 0));      // [kRows][kCols] relative costs by list position
     int32_t *last_of = reinterpret_cast<int32_t *>(keys + kRows * kCols);   // [2] X_l, by layer modulo 2
     uint64_t *kept_ent = reinterpret_cast<uint64_t *>(last_of + 2);         // [kRows] entries of the rows to read, and how many
     int32_t *kept_n = reinterpret_cast<int32_t *>(kept_ent + kRows);
@@ -2642,7 +2678,7 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
             nk = uniform(*kept_n);
             ent = kept_ent[lane < nk ? lane : 0];  // (beyond the list's end: not used)
         }
-        if (r_sel != r_now) {                      // (used two barriers on; last read before the latest one)
+        if (Key::kKeysInLds && r_sel != r_now) {   // (used two barriers on; last read before the latest one)
             for (int i = g; i < S; i += NG)
                 if (lane < kRows) Rl[i * kRows + lane] = (Rk + (int64_t)i * S_pad)[lane];
             r_now = r_sel;
@@ -2714,11 +2750,12 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
 #pragma unroll
         for (int r = 0; r < TS; ++r) {
             relv d;
-            uint32_t least = dmax;
+            Rel least = dmax;
 #pragma unroll
             for (int j = 0; j < TE; ++j) {
-                d[j] = (uint32_t)min(row[r][j] - from[j], (Cell)dmax);
-                least = min(least, d[j]);
+                const Rel rel = (Rel)min(row[r][j] - from[j], (Cell)dmax);
+                least = min(least, rel);
+                d[j] = Key::stored(rel, k);
             }
             *reinterpret_cast<relv *>(keys + (g + NG * r) * kCols + lane * TE) = d;
             if (__builtin_amdgcn_ballot_w64(least < dmax) != 0 && g + NG * r < nk)     // wave-uniform
@@ -2739,17 +2776,17 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
             left &= left - 1;                      // (0 stays 0)
             const relv da = *reinterpret_cast<const relv *>(keys + i * kCols + lane * TE);
             const relv db = *reinterpret_cast<const relv *>(keys + i2 * kCols + lane * TE);
-            const KeyT *Ra = Rl + read_lane(list, i) * kRows + s0, *Rb = Rl + read_lane(list, i2) * kRows + s0;
+            const int at_a = (int)read_lane(list, i) * kRows + s0, at_b = (int)read_lane(list, i2) * kRows + s0;
             KeyT va[TE], vb[TE], ra[TS], rb[TS];
 #pragma unroll
             for (int s = 0; s < TS; ++s) {
-                ra[s] = Ra[s];
-                rb[s] = Rb[s];
+                ra[s] = Key::kKeysInLds ? Rl[at_a + s] : as_const(Rk)[at_a + s];
+                rb[s] = Key::kKeysInLds ? Rl[at_b + s] : as_const(Rk)[at_b + s];
             }
 #pragma unroll
             for (int j = 0; j < TE; ++j) {
-                va[j] = Key::make(da[j], k);
-                vb[j] = Key::make(db[j], k);
+                va[j] = Key::from(da[j], k);
+                vb[j] = Key::from(db[j], k);
             }
 #pragma unroll
             for (int s = 0; s < TS; ++s)
@@ -2791,33 +2828,79 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
     if (unstored) store_bytes();
 }
 
-// The same for the other instances: 64-bit integers, every candidate, plain back-pointers.
+// The same for the other instances, whose costs do not fit a key: 64-bit integers, every candidate, plain back-pointers, all columns
+// up to the budget.  The waves share the rows that reach into the block through LDS, all of them under way at once.  (With every
+// wave reading every row for itself a layer was a chain of as many trips as there are strategies.  Whole searches in us, a launch
+// per layer / that / shared rows: 29 strategies x 78 tiles x 37 layers 3115 / 764 / 401, 44 x 1032 x 24 9200 / 5860 / 1640, 6 x 4104 x 24
+// 831 / 1057 / 504.)
 template <int TS, int NG>
-__device__ __forceinline__ void chain_int64(const Layout &a, int g, int b, int t, int budget) {
+__device__ __forceinline__ void chain_int64(const Layout &a, int wave, int b, int t, int budget) {
+    constexpr int kCols = kChainCols, TE = kCols / kWave;
+    static_assert(TS * NG <= kWave && TE == 2, "strategies by lane, two columns a lane");
+    typedef uint64_t cell2 __attribute__((ext_vector_type(TE)));
+    typedef int32_t arg2 __attribute__((ext_vector_type(TE)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     const int lane = lane_id();
     const int S = a.S, L = a.L;
-    const int64_t pitch = a.e_pad;
-    constexpr int TE = kChainCols / kWave;
-    const int start = t * kChainCols, s0 = g * TS;
+    const uint32_t pitch = (uint32_t)a.e_pad;      // (a layer's rows are below 4 GB, see make_plan)
+    const int start = t * kCols, e0 = start + lane * TE, s0 = wave * TS;
     if (start > budget) return;
+    const uint32_t lane_off = (uint32_t)lane * TE * 8;
     int32_t *flags = chain_flags(a, b);
     int32_t *ready = reinterpret_cast<int32_t *>(lds_cells);   // [2] by layer modulo 2
+    cell2 *shared = reinterpret_cast<cell2 *>(lds_cells + 4);  // [TS * NG][kWave] the rows that reach into the block
     for (int l = 1; l < L; ++l) {
-        if (g == 0) {
-            const bool ok = l == 1 || chain_wait(flags, 0, t - 1, l - 1);
-            if (lane == 0) ready[l & 1] = ok ? 1 : 0;
+        // the former layer's strategies that reach into these columns, in ascending order, by lane: index and memory
+        const int64_t row0 = (int64_t)b * L + l - 1;
+        const int shift_of = a.m[row0 * S + (lane < S ? lane : S - 1)];
+        const bool ok = lane < S && shift_of <= budget && shift_of <= start + kCols - 1;
+        const uint64_t votes = __builtin_amdgcn_ballot_w64(ok);
+        const int n = __builtin_popcountll(votes), below = __builtin_popcountll(votes & ((1ull << lane) - 1ull));
+        const int to = (ok ? below : n + lane - below) * 4;    // (every lane has a place of its own)
+        const int id = __builtin_amdgcn_ds_permute(to, lane), shift = __builtin_amdgcn_ds_permute(to, shift_of);
+        const int64_t c_of = l == 1 ? a.c[row0 * S + (id < S ? id : S - 1)] : 0;
+        if (wave == 0) {
+            bool there = true;
+            if (l > 1 && n > 0) {
+                // the blocks from the largest memory's shift to the smallest one's, but for the own one
+                const int sh_lo = (int)wave_min(ok ? (uint32_t)shift_of : ~0u), sh_hi = (int)~wave_min(ok ? ~(uint32_t)shift_of : ~0u);
+                there = chain_wait(flags, max(start - sh_hi, 0) / kCols, min((start + kCols - 1 - sh_lo) / kCols, t - 1), l - 1);
+            }
+            if (lane == 0) ready[l & 1] = there ? 1 : 0;
         }
         __syncthreads();
         if (uniform(ready[l & 1]) == 0) {
             a.status[b] = GALV_INSTANCE_BAD_VALUE;
             return;
         }
-        const int64_t row0 = (int64_t)b * L + l - 1;
-        const int32_t *m = a.m + row0 * S;
-        const int64_t *c = a.c + row0 * S;
-        const int r_sel = a.r_idx ? a.r_idx[row0 + 1] : 0;
-        const int64_t *R = a.R + ((int64_t)b * a.nR + r_sel) * S * S;
-        const int64_t *rows = chain_rows<int64_t>(a, b, l - 1);
+        uint64_t row[TS][TE];
+        const __amdgpu_buffer_rsrc_t rows = chain_buffer(chain_rows<uint64_t>(a, b, l - 1));
+#pragma unroll
+        for (int r = 0; r < TS; ++r) {
+            const int i = wave + NG * r;
+            if (i >= n) continue;
+            const int sh = (int)read_lane((uint32_t)shift, i);
+            const uint32_t first = read_lane((uint32_t)id, i) * pitch;
+            if (l == 1) {
+                const uint64_t cp = read_lane((uint64_t)c_of, i);
+#pragma unroll
+                for (int j = 0; j < TE; ++j) row[r][j] = e0 + j >= sh ? cp : (uint64_t)kInf;
+            } else if (start >= sh) {
+                buffer_cells(rows, lane_off, (first + (uint32_t)(start - sh)) * 8, row[r]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < TE; ++j)
+                    row[r][j] = __builtin_bit_cast(uint64_t, __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(
+                                    rows, max(e0 + j - sh, 0) * 8, (int)(first * 8), kAgent)));
+#pragma unroll
+                for (int j = 0; j < TE; ++j)
+                    if (e0 + j < sh) row[r][j] = (uint64_t)kInf;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < TS; ++r)
+            if (wave + NG * r < n) shared[(wave + NG * r) * kWave + lane] = cell2{row[r][0], row[r][1]};
+        __syncthreads();
         int64_t best[TS][TE];
         int32_t arg[TS][TE];
 #pragma unroll
@@ -2827,46 +2910,54 @@ __device__ __forceinline__ void chain_int64(const Layout &a, int g, int b, int t
                 best[s][j] = kInf;
                 arg[s][j] = -1;
             }
-        for (int sp = 0; sp < S && s0 < S; ++sp) {
-            const int shift = uniform(m[sp]);
-            if (shift > budget) continue;          // whole column is infinity
-            int64_t v[TE];
+        const int r_sel = a.r_idx ? a.r_idx[row0 + 1] : 0;
+        const ConstPtr<int64_t> R = as_const(a.R + ((int64_t)b * a.nR + r_sel) * S * S);
+        constexpr int kAhead = 4;                  // (the last row repeated: that changes no minimum)
+        for (int i0 = 0; i0 < (s0 < S ? n : 0); i0 += kAhead) {
+            int64_t rk[kAhead][TS];
+            cell2 v[kAhead];
+            int sp[kAhead];
 #pragma unroll
-            for (int j = 0; j < TE; ++j) {
-                const int e = start + lane * TE + j;
-                if (l == 1)
-                    v[j] = e >= shift ? c[sp] : kInf;
-                else
-                    v[j] = e >= shift && e <= budget ? agent_load(rows + (int64_t)sp * pitch + (e - shift)) : kInf;
+            for (int u = 0; u < kAhead; ++u) {
+                const int i = min(i0 + u, n - 1);
+                sp[u] = (int)read_lane((uint32_t)id, i);
+                v[u] = shared[i * kWave + lane];
+#pragma unroll
+                for (int s = 0; s < TS; ++s) rk[u][s] = R[sp[u] * S + min(s0 + s, S - 1)];
             }
 #pragma unroll
-            for (int s = 0; s < TS; ++s) {
-                const int64_t rk = R[(int64_t)sp * S + (s0 + s < S ? s0 + s : S - 1)];
+            for (int u = 0; u < kAhead; ++u)
 #pragma unroll
-                for (int j = 0; j < TE; ++j)
-                    if (v[j] + rk < best[s][j]) {  // strict: lowest s' keeps ties
-                        best[s][j] = v[j] + rk;
-                        arg[s][j] = sp;
+                for (int s = 0; s < TS; ++s)
+#pragma unroll
+                    for (int j = 0; j < TE; ++j) {
+                        const int64_t x = (int64_t)v[u][j] + rk[u][s];
+                        if (x < best[s][j]) {      // strict: lowest s' keeps ties
+                            best[s][j] = x;
+                            arg[s][j] = sp[u];
+                        }
                     }
-            }
         }
-        int64_t *out = chain_rows<int64_t>(a, b, l);
-        const int64_t bp0 = ((int64_t)b * (L - 1) + (l - 1)) * S * pitch;
+        const __amdgpu_buffer_rsrc_t out = chain_buffer(chain_rows<uint64_t>(a, b, l) + (int64_t)s0 * pitch + start);
+        int32_t *bp = static_cast<int32_t *>(a.bp) + (((int64_t)b * (L - 1) + (l - 1)) * S + s0) * pitch + e0;
 #pragma unroll
         for (int s = 0; s < TS; ++s)
             if (s0 + s < S) {
-                const int64_t cs = c[S + s0 + s];
+                const int64_t cs = a.c[(row0 + 1) * S + s0 + s];
+                uint64_t cell[TE];
+                arg2 from;
 #pragma unroll
                 for (int j = 0; j < TE; ++j) {
-                    const int e = start + lane * TE + j;
                     const bool dead = best[s][j] >= kInf;
-                    agent_store(out + (int64_t)(s0 + s) * pitch + e, dead ? kInf : best[s][j] + cs);
-                    static_cast<int32_t *>(a.bp)[bp0 + (int64_t)(s0 + s) * pitch + e] = dead ? -1 : arg[s][j];
+                    cell[j] = (uint64_t)(dead ? kInf : best[s][j] + cs);
+                    from[j] = dead ? -1 : arg[s][j];
                 }
+                buffer_store_cells(out, lane_off, (uint32_t)s * pitch * 8, cell);
+                *reinterpret_cast<arg2 *>(bp + (int64_t)s * pitch) = from;
             }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the cells have arrived
         __syncthreads();
-        if (g == 0 && lane == 0) agent_store(flags + (int64_t)t * kWordStep, l);
+        if (wave == 0 && lane == 0) agent_store(flags + (int64_t)t * kWordStep, l);
     }
 }
 
@@ -2928,7 +3019,7 @@ __global__ __launch_bounds__(NG * kWave, 4) void chain_kernel(Layout a, int64_t 
     const int st = (int)read_lane((uint32_t)in.h, 0), budget = (int)read_lane((uint32_t)in.h, 1);
     const uint32_t dmax = read_lane((uint32_t)in.h, 3);
     const bool keys32 = st == GALV_INSTANCE_OK_FAST_U32 || st == GALV_INSTANCE_OK_U32_WIDE;
-    const bool packed = byte_status(st, dmax);
+    const bool packed = byte_status(a, st, dmax);
     if (t == a.n_tiles) {
         if (wave == 0) chain_final(layout_again(), b, st, packed, budget, best_cost, best_last);
         return;
@@ -2938,22 +3029,28 @@ __global__ __launch_bounds__(NG * kWave, 4) void chain_kernel(Layout a, int64_t 
         if (!packed || wave != 0) return;
         if (keys32)
             chain_live<TS * NG, Key32>(layout_again(), b, dmax, budget);
-        else
+        else if (dmax != 0)
             chain_live<TS * NG, Key64>(layout_again(), b, dmax, budget);
+        else
+            chain_live<TS * NG, KeyBig>(layout_again(), b, chain_clamps(layout_again())[b], budget);
     } else if (st == GALV_INSTANCE_OK_FAST_U32) {
         chain_tiles<TS, NG, uint32_t, Key32>(layout_again(), wave, b, t, dmax, in, c0);
     } else if (packed && keys32) {
         chain_tiles<TS, NG, uint64_t, Key32>(layout_again(), wave, b, t, dmax, in, c0);
-    } else if (packed) {
+    } else if (packed && dmax != 0) {
         chain_tiles<TS, NG, uint64_t, Key64>(layout_again(), wave, b, t, dmax, in, c0);
+    } else if (packed) {
+        chain_tiles<TS, NG, uint64_t, KeyBig>(layout_again(), wave, b, t, chain_clamps(layout_again())[b], in, c0);
     } else {
         chain_int64<TS, NG>(layout_again(), wave, b, t, budget);
     }
 }
 constexpr unsigned chain_lds(int ts, int ng) {
-    // minima of 8-byte cells, alive rows, transition keys of 8 bytes, relative costs, X_l, rows to read
+    // minima of 8-byte cells, alive rows, transition keys of 8 bytes and relative costs, or keys of relative costs, X_l, rows to
+    // read.  (More than the whole rows of chain_int64.)
     const int rows = ts * ng, cols = kChainCols;
-    return (unsigned)(2 * cols * 8 + 2 * 8 + rows * rows * 8 + rows * cols * 4 + 8 + rows * 8 + 8);
+    const int small = rows * rows * 8 + rows * cols * 4, big = rows * cols * 8;
+    return (unsigned)(2 * cols * 8 + 2 * 8 + (small > big ? small : big) + 8 + rows * 8 + 8);
 }
 
 // ------------------------------------------------- final minimum and backtrack
@@ -3770,6 +3867,9 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, bool chain, 
     //   0.59 0.73, x 1452 0.91 1.13 0.39 1.07 0.51 0.56
     //   share 100:  12 x 4940 0.78 0.94 0.49 0.67 0.59 0.69; 22 x 3458 0.64 0.79 0.46 0.68 0.49 0.66, x 6080 0.68 1.14 0.39 1.02 0.62 0.77; 30 x 2166 0.60
     //   0.73 0.40 0.50 0.44 0.56; 44 x 2166 0.61 0.83 0.36 0.47 0.42 0.79; 60 x 1482 0.60 0.76 0.36 0.31 0.34 0.72.
+    // Transition costs of 2^32 and more (layers alike in nanoseconds, hundredfold, every row alive) - 64-bit integers:
+    //   6 x 4104 share 2730 0.80 0.61; 12 x 4112 share 1024 0.70 0.37; 22 x 1032 share 512 0.65 0.25, x 576 share 75 0.71 0.25; 29 x 78 share 269
+    //   0.85 0.13; 44 x 1032 share 682 0.82 0.18, x 272 share 42 0.60 0.16; 60 x 715 share 341 0.77 0.17.
     // (Beyond 64 strategies, two waves' worth of list entries: 100 x 252 1.02 0.96 0.80 0.72, x 1032 1.43 1.79 0.56 1.87.)
     const uint32_t other = GALV_DP_BP_U8 | GALV_DP_NO_U32 | GALV_DP_NO_PEEK | GALV_DP_FORCE_PEEK | GALV_DP_NO_PACK | GALV_DP_FORCE_PACK |
                            GALV_DP_FORCE_WIDE_TILES | GALV_DP_NO_WIDE_TILES;        // (what these ask for is a launch per layer)
@@ -3853,7 +3953,7 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, bool chain, 
     };
     const size_t u_bytes = ce ? (size_t)a.B * a.L * a.S_pad * a.e_pad * 8 : (size_t)a.B * a.S_pad * a.row * 8;
     p->off_U[0] = take(u_bytes);
-    p->off_U[1] = take(ce ? ((size_t)a.B * a.n_tiles * kWordStep + kWave) * sizeof(int32_t) : u_bytes);
+    p->off_U[1] = take(ce ? chain_word_bytes(a.B, a.n_tiles) : u_bytes);
     p->off_bp = take((size_t)a.B * (a.L - 1) * a.S * a.e_pad * (u8 ? 1 : sizeof(int32_t)));
     // + slack: a group of R keys is fetched whole even when it straddles the row end
     p->off_Rk = take((size_t)a.B * a.nR * a.S * a.S_pad * sizeof(double) + 1024);

@@ -152,3 +152,42 @@ def test_without_the_memory_for_all_layers_a_launch_per_layer(monkeypatch):
         sol.close()
     for x, y in zip(*results):
         assert (x == y).all()
+
+
+@pytest.mark.parametrize("S", [1, 7, 16, 22, 29, 44, 64])      # every row count that a wave covers, with and without a remainder
+@pytest.mark.parametrize("m_hi", [0, 40, 900, 5003])           # from the own block only to blocks that nothing reaches
+def test_whole_costs(S, m_hi):
+    """Transition costs beyond a relative cost of 32 bits (keys in doubles), and costs beyond a key (64-bit integers)."""
+    w = workload(4000 + 7 * S + m_hi, 4, 6, S, 1500, m_hi=max(1, m_hi))
+    if m_hi == 0:
+        w.m[:] = 0
+    w.m[:, :, S // 2:] //= 40                                  # (some strategies fit whatever m_hi is: six layers, a budget of 1500)
+    w.m[1, 2, :] = 1501                                        # a layer without a usable strategy
+    w.m[2:, 1::2, 0] = 129                                     # a shift of one column more than a block
+    w.budget[:] = (1500, 1500, 1407, 128)
+    w.r_idx[:, 1:] = np.arange(5) % 2
+    w.R[:2] = (w.R[:2] << 24) + (1 << 32)
+    w.c[2:] <<= 44
+    w.R[2:] <<= 40
+    _, _, _, status = check_against_oracle(w, table_instances=[0, 1, 2, 3], threads=8, allow_vacuous=S == 1)
+    assert list(status) == [binding.GALV_INSTANCE_OK_FAST_WIDE] * 2 + [binding.GALV_INSTANCE_OK_INT64] * 2
+
+
+@pytest.mark.parametrize("S", [3, 22, 44, 64])
+def test_the_largest_transition_costs_and_keys(S):
+    """The largest relative cost that 32 bits hold and one more; the largest plan cost that a key holds and one more; a matrix
+    that no layer uses with entries above every plan cost."""
+    k = max(1, (S - 1).bit_length())
+    w = workload(600 + S, 5, 3, S, 700)
+    w.r_idx[:] = 0
+    w.R[0, 0, 0, S - 1], w.R[1, 0, 0, S - 1] = (1 << 32) - 2, (1 << 32) - 1
+    w.c[:2] <<= 32
+    most = (1 << (52 - k)) - 1                    # bound of all plan costs: the layers' largest plus two transitions
+    for b, top in ((2, most), (3, most + 1)):
+        layers = int(w.c[b].max(axis=1).sum())
+        w.c[b, 0, np.argmax(w.c[b, 0])] += (top - layers) % 2
+        w.R[b, 0, S - 1, 0] = w.R[b, 0, 0, 0] = w.R[b, 0, 0, S - 1] = (top - layers) // 2
+    w.R[4, 1] = 1 << 55
+    _, _, _, status = check_against_oracle(w, table_instances=[0, 1, 2, 3, 4], threads=8)
+    wide, integers = binding.GALV_INSTANCE_OK_FAST_WIDE, binding.GALV_INSTANCE_OK_INT64
+    assert list(status) == [wide, wide, wide, integers, wide]
