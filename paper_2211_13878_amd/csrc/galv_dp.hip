@@ -3873,13 +3873,23 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, bool chain, 
     // (Beyond 64 strategies, two waves' worth of list entries: 100 x 252 1.02 0.96 0.80 0.72, x 1032 1.43 1.79 0.56 1.87.)
     const uint32_t other = GALV_DP_BP_U8 | GALV_DP_NO_U32 | GALV_DP_NO_PEEK | GALV_DP_FORCE_PEEK | GALV_DP_NO_PACK | GALV_DP_FORCE_PACK |
                            GALV_DP_FORCE_WIDE_TILES | GALV_DP_NO_WIDE_TILES;        // (what these ask for is a launch per layer)
-    const int64_t chain_to = share < 128 ? 90000 : S <= 16 ? 60000 : S <= 24 ? 70000 : 46000;
+    // Where a layer's share of the budget is very large the other side sweeps few columns: share 6250: 16 x 3128 1.04, 22 x 3128 1.06, 44 x
+    // 782 1.11 on deep stacks; share 14000 to 25000: 13 x 929 1.11, 24 x 1203 1.08, 27 x 1166 1.14, 44 x 782 1.20; up to 8 strategies 0.70 to 0.84.
+    const int64_t chain_to = share < 128 ? 90000 : share >= 4096 ? 10000 : S <= 16 ? 60000 : S <= 24 ? 70000 : 46000;
+    // What the launches of all layers but the first cost has to pay for one workgroup per tile, which takes its place from a counter
+    // (12 ns each, one after the other) and then starts (a thousand or two at a time, 3 us).  Few strategies, many tiles, over the
+    // time with a launch per layer for 2 - 4 - 8 - 16 - 32 layers: 1 x 3000 columns of 2000 2.29 1.52 1.02 0.72 0.53, 1 x 15000 of 16384 7.2 4.2
+    // 2.5 1.4 0.76, 1 x 60000 of 100000 19 10 5.0 2.5 -; 6 x 10000 of 2000 3.1 1.8 1.04 0.81 0.76, of 16384 4.0 2.3 1.3 1.08 0.98; 16 x 3750 of 2000 2.1
+    // 1.06 0.70 0.71 0.69.  Up to 300 workgroups a layer, 593 searches of seven kinds took 0.07 to 1.04, but for two whose transition
+    // matrices alternate (1.13, 1.15).  Below a share of 128 cost rows are the other side, and the line lies further out: up to 1000
+    // workgroups a layer 0.13 to 1.00, up to 2000 0.13 to 1.32.
+    const int64_t chain_groups = (int64_t)(share < 128 ? 1000 : 300) * (d->n_layers - 1);
     const ChainEntry *ce = S <= kWave ? pick_chain(S, tiles) : nullptr;
     // (rows of every layer: at most 8 GB of them, and a layer's of one instance within 32 bits of offset; at most kChainLayers
     // layers, see there)
     const long double chain_bytes = ce ? 8.0L * ce->ts * ce->ng * ((int64_t)d->max_budget + kChainCols) : 0;
     if (chain && ce && !(d->flags & other) && ((d->flags & GALV_DP_STREAMS_MASK) >> GALV_DP_STREAMS_SHIFT) <= 1 && d->n_layers > 1 &&
-        d->n_layers <= kChainLayers && tiles * S <= chain_to && chain_bytes < 4.0e9L && chain_bytes * d->n_instances * d->n_layers <= 8.0e9L)
+        d->n_layers <= kChainLayers && tiles * S <= chain_to && tiles + 2ll * d->n_instances <= chain_groups && chain_bytes < 4.0e9L && chain_bytes * d->n_instances * d->n_layers <= 8.0e9L)
         shape = Tiles::chain;
     if (only) shape = *only;
     if (d->flags & GALV_DP_FORCE_WIDE_TILES) shape = Tiles::wide;

@@ -74,11 +74,14 @@ def test_nothing_can_be_left_out():
         check_against_oracle(w, table_instances=[0, 1], threads=8)
 
 
-@pytest.mark.parametrize("B,L,S,E", [(300, 6, 6, 3000), (1, 4, 22, 150000), (90, 7, 44, 1100)])
+@pytest.mark.parametrize("B,L,S,E", [(300, 6, 6, 3000), (1, 4, 22, 150000), (90, 7, 44, 1100),
+                                     (300, 27, 6, 3000), (1, 70, 2, 280000), (90, 17, 44, 1100)])      # these in one launch
 def test_more_workgroups_than_the_gpu_holds(B, L, S, E):
     w = workload(5 * B + S, B, L, S, E)
     w.c[::3] <<= 30
-    check_against_oracle(w, oracle_instances=list(range(0, B, 37)), table_instances=[0], threads=8)
+    desc = binding.make_desc(B, L, S, E, 2)
+    assert L < 10 or binding.galv_dp_workspace_bytes_preferred(desc) > binding.galv_dp_workspace_bytes(desc)
+    check_against_oracle(w, oracle_instances=list(range(0, B, 37)), table_instances=[0] if L < 30 else [], threads=8)
 
 
 def test_solves_that_overlap_on_several_streams():
