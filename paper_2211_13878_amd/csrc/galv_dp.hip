@@ -2621,6 +2621,16 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
         const int n = (int)read_lane((uint32_t)in.h, 2), r_sel = (int)read_lane((uint32_t)in.h, 4);
         const int y = (int)read_lane((uint32_t)in.h, 5);
         if (start + kCols - 1 < y) break;          // nothing reachable here, in this layer and from it on
+        // Another matrix than before: its keys, fetched by the waves that would only wait for wave 0.  (Read two barriers on, last
+        // read before the latest one.  Fetched by all waves in front of the rows, deep stacks whose matrices alternate from layer to
+        // layer took, in us: 60 strategies x 539 tiles x 82 layers 1053, now 1003; 18 x 1440 x 54 544, 499; 44 x 1032 x 24 311, 281.)
+        const KeyT *Rk = rkeys<KeyT>(layout_again(), b, r_sel);
+        if (Key::kKeysInLds && r_sel != r_now) {
+            if (g != 0)
+                for (int i = g - 1; i < S; i += NG - 1)
+                    if (lane < kRows) Rl[i * kRows + lane] = (Rk + (int64_t)i * S_pad)[lane];
+            r_now = r_sel;
+        }
         if (g == 0) {
             int x = uniform(in.x);
             bool told = chain_last_column(records + l * 8 + 6, x);
@@ -2671,17 +2681,11 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
             x_prev = x;
             continue;
         }
-        const KeyT *Rk = rkeys<KeyT>(layout_again(), b, r_sel);
         uint64_t ent = in.ent;
         int nk = n;
         if (a.peek && l > 1) {
             nk = uniform(*kept_n);
             ent = kept_ent[lane < nk ? lane : 0];  // (beyond the list's end: not used)
-        }
-        if (Key::kKeysInLds && r_sel != r_now) {   // (used two barriers on; last read before the latest one)
-            for (int i = g; i < S; i += NG)
-                if (lane < kRows) Rl[i * kRows + lane] = (Rk + (int64_t)i * S_pad)[lane];
-            r_now = r_sel;
         }
         Cell row[TS][TE];
         if (l == 1) {

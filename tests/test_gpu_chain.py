@@ -194,3 +194,14 @@ def test_the_largest_transition_costs_and_keys(S):
     _, _, _, status = check_against_oracle(w, table_instances=[0, 1, 2, 3, 4], threads=8)
     wide, integers = binding.GALV_INSTANCE_OK_FAST_WIDE, binding.GALV_INSTANCE_OK_INT64
     assert list(status) == [wide, wide, wide, integers, wide]
+
+
+@pytest.mark.parametrize("S", [1, 8, 12, 16, 22, 29, 32, 44, 48, 60, 64])
+@pytest.mark.parametrize("B,E", [(3, 900), (110, 900)])        # thin and fat shapes
+def test_matrices_that_change_at_every_layer(S, B, E):
+    w = workload(800 + S + B, B, 8, S, E, nR=3)
+    w.r_idx[:, 1:] = np.arange(1, 8) % 3
+    w.r_idx[2, 1:] = (0, 0, 2, 1, 1, 2, 2)
+    w.c[1] <<= 30
+    w.R[2] <<= 20
+    check_against_oracle(w, table_instances=[0, 1, 2], oracle_instances=[0, 1, 2, B - 1], threads=8, allow_vacuous=S == 1)
