@@ -212,7 +212,7 @@ def galv_dp_get_stats(h, stats, stream=None):
 
 
 def galv_dp_get_config(h):
-    """(byte table, peek, internal streams the last solve used -- before any solve: what the first
+    """(byte table -- 2: all layers in one launch --, peek, internal streams the last solve used -- before any solve: what the first
     will use --, budget columns per workgroup) as the handle chose them."""
     out = (ctypes.c_int32 * 4)()
     _check(load_library().galv_dp_get_config(h, out))

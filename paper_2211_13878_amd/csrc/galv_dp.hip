@@ -4438,7 +4438,7 @@ galv_status_t galv_dp_get_config(const galv_dp_t *h, int32_t *config) {
     if (!h) return fail(GALV_ERR_INVALID_ARG, "handle is NULL");
     if (!config) return fail(GALV_ERR_INVALID_ARG, "config is NULL");
     config[0] = h->lay.packed == kChain ? 2 : h->lay.packed ? 1 : 0;
-    config[1] = h->lay.peek && h->var.share ? 1 : 0;
+    config[1] = h->lay.peek && (h->chain || h->var.share) ? 1 : 0;
     config[2] = h->n_used > 0 ? h->n_used : (h->lay.L < 2 ? 1 : pick_streams(h, tiles_at_most(h)));
     config[3] = h->lay.tile_e;
     return GALV_OK;

@@ -28,21 +28,39 @@ def test_the_rule_and_the_workspace(lib, B, L, S, E, chains):
     desc = binding.make_desc(B, L, S, E, 2, binding.GALV_DP_STREAMS(1))     # (no streams to create here)
     need, best = binding.galv_dp_workspace_bytes(desc), binding.galv_dp_workspace_bytes_preferred(desc)
     assert best >= need
-    if L > 4:
+    rc, config = create(lib, desc, best)
+    assert rc == binding.GALV_OK and (config[0] == 2) == chains
+    if L > 4:                                     # (with fewer layers all their rows may take less than a launch per layer)
         assert (best > need) == chains
     # less than preferred: a launch per layer; less than needed: refused
     for n_bytes in (best, best - 1, need):
         if n_bytes >= need:
             assert create(lib, desc, n_bytes)[0] == binding.GALV_OK
     if chains and L > 4:
-        assert create(lib, desc, best)[1][:2] == (2, 0)
         assert create(lib, desc, best - 1)[1][0] != 2
+    assert create(lib, desc, 4096) == (binding.GALV_ERR_WORKSPACE, None)
     # what asks for a particular sweep, or for several streams, gets a launch per layer
     for flags in (binding.GALV_DP_FORCE_PACK, binding.GALV_DP_NO_PACK, binding.GALV_DP_BP_U8, binding.GALV_DP_NO_WIDE_TILES,
                   binding.GALV_DP_FORCE_WIDE_TILES, binding.GALV_DP_FORCE_PEEK, binding.GALV_DP_NO_PEEK, binding.GALV_DP_NO_U32,
                   binding.GALV_DP_STREAMS(2)):
         asked = binding.make_desc(B, L, S, E, 2, flags)
-        assert binding.galv_dp_workspace_bytes_preferred(asked) == binding.galv_dp_workspace_bytes(asked) or flags & binding.GALV_DP_BP_U8 and S > 255
+        assert binding.galv_dp_workspace_bytes_preferred(asked) == binding.galv_dp_workspace_bytes(asked)
+        if flags != binding.GALV_DP_STREAMS(2):   # (streams are created with the handle, on a GPU)
+            asked = binding.make_desc(B, L, S, E, 2, flags | binding.GALV_DP_STREAMS(1))
+            rc, config = create(lib, asked, max(best, binding.galv_dp_workspace_bytes(asked)))
+            assert rc == binding.GALV_OK and config[0] != 2
+    # 64-bit integers asked for are an arithmetic, not a sweep
+    asked = binding.make_desc(B, L, S, E, 2, binding.GALV_DP_FORCE_INT64 | binding.GALV_DP_STREAMS(1))
+    rc, config = create(lib, asked, best)
+    assert rc == binding.GALV_OK and (config[0] == 2) == chains
+
+
+@pytest.mark.parametrize("B,L,S,E,peeks", [(1, 37, 29, 9973, 0), (3, 6, 22, 1500, 0), (1, 16, 64, 16000, 0), (16, 32, 12, 32768, 0),      # thin shapes; 16 strategies at most
+                                           (8, 32, 22, 16384, 1), (11, 40, 30, 16384, 1), (8, 40, 44, 16384, 1), (11, 40, 60, 8192, 1)])
+def test_the_configuration_says_whether_it_peeks(lib, B, L, S, E, peeks):
+    """The fat shapes from 17 strategies on look at two cells of a row before they read it."""
+    desc = binding.make_desc(B, L, S, E, 2, binding.GALV_DP_STREAMS(1))
+    assert create(lib, desc, binding.galv_dp_workspace_bytes_preferred(desc))[1] == (2, peeks, 1, 128)
 
 
 def test_preferred_checks_its_arguments(lib):
