@@ -86,3 +86,19 @@ def test_layers_pay_for_the_workgroups(lib, B, L, S, E, chains):
     """Every tile costs a workgroup's start, which few layers do not pay for; a very large share of the budget per layer."""
     desc = binding.make_desc(B, L, S, E, 2, binding.GALV_DP_STREAMS(1))
     assert (create(lib, desc, binding.galv_dp_workspace_bytes_preferred(desc))[1][0] == 2) == chains
+
+
+def test_the_larger_workspace_is_taken_only_where_there_is_room(lib):
+    large = binding.make_desc(40, 100, 44, 4000, 2)                 # 3.1 and 9.2 GB
+    need, best = binding.galv_dp_workspace_bytes(large), binding.galv_dp_workspace_bytes_preferred(large)
+    assert best > 2 * need
+    for least, free, want in ((False, 100 << 30, best), (False, 8 * (best - need), best), (False, 8 * (best - need) - 1, need),
+                              (False, 0, need), (True, 1 << 40, need)):
+        assert binding.workspace_size(large, least, lambda: free) == want
+    small = binding.make_desc(1, 20, 22, 2000, 2)                   # a few MB: nobody is asked
+    best = binding.galv_dp_workspace_bytes_preferred(small)
+    assert best > binding.galv_dp_workspace_bytes(small)
+    assert binding.workspace_size(small, False, None) == best
+    assert binding.workspace_size(small, True, None) == binding.galv_dp_workspace_bytes(small)
+    same = binding.make_desc(64, 96, 44, 32768, 2)                  # a launch per layer either way
+    assert binding.workspace_size(same, True, None) == binding.workspace_size(same, False, None) == binding.galv_dp_workspace_bytes(same)

@@ -157,6 +157,24 @@ def test_without_the_memory_for_all_layers_a_launch_per_layer(monkeypatch):
         assert (x == y).all()
 
 
+def test_the_least_workspace_on_request_and_where_little_is_left(monkeypatch):
+    w = workload(6, 4, 60, 22, 20000)
+    dev = binding.upload(w)
+    results = []
+    for least, left in ((False, None), (True, None), (False, 1 << 28)):
+        if left:
+            monkeypatch.setattr(binding, "_free_bytes", lambda device: left)
+        sol = binding.Solver(w.B, w.L, w.S, w.E_max, w.nR, least_workspace=least)
+        small = least or left is not None
+        assert sol.workspace_bytes == sol.workspace.numel()
+        assert (sol.workspace_bytes == binding.galv_dp_workspace_bytes(sol.desc)) == small and (sol.config()["packed"] == 2) == (not small)
+        cost, last = sol.solve(*dev)
+        results.append([x.cpu().numpy().copy() for x in (cost, last, sol.backtrack())])
+        sol.close()
+    for r in results[1:]:
+        assert all((x == y).all() for x, y in zip(r, results[0]))
+
+
 @pytest.mark.parametrize("S", [1, 7, 16, 22, 29, 44, 64])      # every row count that a wave covers, with and without a remainder
 @pytest.mark.parametrize("m_hi", [0, 40, 900, 5003])           # from the own block only to blocks that nothing reaches
 def test_whole_costs(S, m_hi):
