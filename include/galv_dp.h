@@ -142,6 +142,10 @@ typedef struct {
                                         and n_strategies <= 256: the same 32-bit keys of relative
                                         costs (their width depends on R only), over 64-bit cells  */
 #define GALV_INSTANCE_BAD_VALUE (-1) /* a value violates the preconditions above            */
+#define GALV_INSTANCE_GAVE_UP (-2)   /* all layers in one launch: a wait between workgroups was given
+                                        up after a second, so that nothing could hang; a fault of the
+                                        library or the machine, not of the values.  No plans, and
+                                        costs are not to be used                             */
 
 /*
  * Bytes of device workspace a handle for `desc` needs (rolling cost rows,

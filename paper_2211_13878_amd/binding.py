@@ -40,6 +40,7 @@ def GALV_DP_STREAMS(n: int) -> int:
 GALV_INSTANCE_OK_FAST, GALV_INSTANCE_OK_INT64, GALV_INSTANCE_OK_FAST_WIDE, GALV_INSTANCE_OK_FAST_U32 = 0, 1, 2, 3
 GALV_INSTANCE_OK_U32_WIDE = 4
 GALV_INSTANCE_BAD_VALUE = -1
+GALV_INSTANCE_GAVE_UP = -2
 
 EXPORTS = ("galv_dp_workspace_bytes", "galv_dp_workspace_bytes_preferred", "galv_dp_create", "galv_dp_solve_batched",
            "galv_dp_backtrack", "galv_dp_solve_static", "galv_dp_best_per_budget", "galv_dp_backtrack_queries",

@@ -2670,7 +2670,7 @@ __device__ __forceinline__ void chain_tiles(const Layout &a, int wave, int b, in
         __syncthreads();
         const int x = uniform(last_of[l & 1]);
         if (x == kUnset) {
-            a.status[b] = GALV_INSTANCE_BAD_VALUE;
+            a.status[b] = GALV_INSTANCE_GAVE_UP;
             return;
         }
         if (y > x) break;                          // nothing reachable anywhere
@@ -2874,7 +2874,7 @@ __device__ __forceinline__ void chain_int64(const Layout &a, int wave, int b, in
         }
         __syncthreads();
         if (uniform(ready[l & 1]) == 0) {
-            a.status[b] = GALV_INSTANCE_BAD_VALUE;
+            a.status[b] = GALV_INSTANCE_GAVE_UP;
             return;
         }
         uint64_t row[TS][TE];
@@ -2994,7 +2994,7 @@ __device__ __forceinline__ void chain_final(const Layout &a, int b, int st, bool
                 if (ok && there && wide < (uint64_t)kInf) v = wide;
             }
         }
-        if (!there) a.status[b] = GALV_INSTANCE_BAD_VALUE;
+        if (!there) a.status[b] = GALV_INSTANCE_GAVE_UP;
     }
     const uint64_t least = wave_min(v);
     const int last = least < (uint64_t)kInf ? __builtin_ctzll(__builtin_amdgcn_ballot_w64(v == least)) : -1;
@@ -3259,7 +3259,9 @@ __device__ __forceinline__ void walk_wave(const Layout &a, bool packed, int b, i
         out[0] = s;
 }
 __device__ __forceinline__ void walk_any(const Layout &a, int b, int64_t e, int s, int32_t *out) {
-    const bool packed = is_packed(a, a.status[b], b);
+    const int st = uniform(a.status[b]);
+    const bool packed = is_packed(a, st, b);
+    if (st < 0) s = -1;                            // (no table to walk)
     if (a.S <= kWave)
         walk_wave<1>(a, packed, b, e, s, out);
     else if (a.S <= 4 * kWave)

@@ -141,3 +141,15 @@ def test_one_byte_back_pointers_need_few_strategies(lib):
     assert "255" in binding.galv_dp_last_error()
     unknown = binding.make_desc(1, 4, 6, 256, flags=0x4000)
     assert lib.galv_dp_workspace_bytes(ctypes.byref(unknown), ctypes.byref(n)) == binding.GALV_ERR_INVALID_ARG
+
+
+def test_status_codes_match_the_header_and_a_wait_given_up_is_not_a_bad_value():
+    header = open(os.path.join(ROOT, "include", "galv_dp.h")).read()
+    declared = {n: int(v) for n, v in re.findall(r"#define (GALV_INSTANCE_\w+)\s+\(?(-?\d+)\)?", header)}
+    assert len(set(declared.values())) == len(declared) == 7
+    assert all(getattr(binding, n) == v for n, v in declared.items())
+    assert all(v < 0 for n, v in declared.items() if "OK" not in n)          # (what the kernels take for "no table")
+    # invalid values are found by the preparation kernel alone
+    source = open(os.path.join(ROOT, "paper_2211_13878_amd", "csrc", "galv_dp.hip")).read()
+    given = [m.start() for m in re.finditer("GALV_INSTANCE_BAD_VALUE", source)]
+    assert given and all(source.index("prep_kernel(Layout a") < at < source.index("init_kernel(Layout a") for at in given)
