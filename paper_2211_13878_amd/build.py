@@ -35,9 +35,14 @@ def device_isa(extra_flags=()) -> str:
 
 
 def check_isa_text(text: str) -> int:
-    """Verify what the hand-issued scalar loads assume about the compiler's output
-    (see isa_check.py); returns the number of such loads checked, raises on a violation."""
-    from .isa_check import count_requests, scalar_prefetch_violations
+    """Verify what the hand-issued scalar loads and the wide stores assume about the compiler's
+    output (see isa_check.py); returns the number of such loads checked, raises on a violation."""
+    from .isa_check import count_requests, scalar_prefetch_violations, wide_store_violations
+    lost = wide_store_violations(text)
+    if lost:
+        lines = "\n".join(f"  line {a}: {t}" for a, t in lost[:8])
+        raise RuntimeError(f"{len(lost)} wide buffer stores with a scalar offset, whose data can be overwritten before it "
+                           f"is read; this build must not run on a GPU:\n{lines}")
     bad = scalar_prefetch_violations(text)
     if bad:
         lines = "\n".join(f"  {f}: load at line {a}, line {b}: {t}" for f, a, b, t in bad[:8])

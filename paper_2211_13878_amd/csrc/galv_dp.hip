@@ -2528,7 +2528,7 @@ __device__ __forceinline__ void buffer_store_cells(__amdgpu_buffer_rsrc_t rows, 
         __builtin_amdgcn_raw_buffer_store_b64(v, rows, (int)lane_off, (int)off, kAgent);
     } else {
         // (the whole offset per lane: behind a store of 16 bytes with a scalar offset the compiler leaves no wait states
-        // before the data registers are written again, and the first cell of some lanes was then lost)
+        // before the data registers are written again, and the first cell of some lanes was then lost; the build refuses that form)
         const u32x4 v = {(uint32_t)in[0], (uint32_t)(in[0] >> 32), (uint32_t)in[1], (uint32_t)(in[1] >> 32)};
         __builtin_amdgcn_raw_buffer_store_b128(v, rows, (int)(lane_off + off), 0, kAgent);
     }

@@ -11,6 +11,11 @@ produced ISA: between every scalar load that sits inside an inline-asm block and
 no instruction may name one of the load's destination registers, and control may not leave
 the straight line (no label, no branch).  A tile shape or flag that makes the compiler break
 this fails the build instead of reaching a GPU.
+
+A second form is refused wherever it stands: a buffer store of more than 8 bytes with a scalar
+register as its offset.  The compiler leaves no wait states between such a store and an
+instruction that writes its data registers again, and the first cell of some lanes was then
+lost.  (With a constant offset it leaves them; the kernels keep the whole offset per lane.)
 """
 from __future__ import annotations
 
@@ -20,6 +25,9 @@ _LOAD = re.compile(r"\s*s_load_dwordx(?:4|8|16)\s+s\[(\d+):(\d+)\]")
 _RANGE = re.compile(r"\bs\[(\d+):(\d+)\]")
 _SINGLE = re.compile(r"\bs(\d+)\b")
 _FLOW = re.compile(r"\s*(s_cbranch|s_branch|s_endpgm|s_setpc|s_swappc|s_call)")
+
+
+_WIDE_STORE = re.compile(r"buffer_store_dwordx[34]\s+(.*)")
 
 
 def _sgprs(text: str) -> set:
@@ -80,3 +88,17 @@ def count_requests(asm_text: str) -> int:
         elif in_asm and _LOAD.match(line):
             n += 1
     return n
+
+
+def wide_store_violations(asm_text: str) -> list:
+    """Buffer stores of 12 or 16 bytes with a scalar offset, as (line number, text)."""
+    out = []
+    for i, line in enumerate(asm_text.split("\n")):
+        code = line.split(";")[0].strip()
+        m = _WIDE_STORE.match(code)
+        if m:
+            operands = [x.strip() for x in m.group(1).split(",")]       # data, address, descriptor, offset and modifiers
+            offset = operands[3].split()[0] if len(operands) > 3 else "?"
+            if not re.fullmatch(r"-?\d+|0x[0-9a-f]+", offset):
+                out.append((i + 1, code))
+    return out

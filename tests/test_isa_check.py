@@ -2,7 +2,7 @@
 import pytest
 
 from paper_2211_13878_amd import build
-from paper_2211_13878_amd.isa_check import count_requests, scalar_prefetch_violations
+from paper_2211_13878_amd.isa_check import count_requests, scalar_prefetch_violations, wide_store_violations
 
 GOOD = """
 _Zkernel:                               ; @_Zkernel
@@ -48,6 +48,20 @@ def test_weaker_wait_does_not_count_and_control_flow_is_caught():
     assert any("control flow" in x[3] for x in scalar_prefetch_violations(bad))
     bad = GOOD.replace("\ts_nop 0\n", ".LBB0_7:\n")
     assert any("label" in x[3] for x in scalar_prefetch_violations(bad))
+
+
+def test_wide_store_with_a_scalar_offset_is_refused():
+    fine = ("\tbuffer_store_dwordx4 v[2:5], v1, s[8:11], 0 offen sc1\n"        # the whole offset per lane
+            "\tbuffer_store_dwordx4 v[2:5], off, s[8:11], 0 offset:16\n"
+            "\tbuffer_store_dwordx2 v[2:3], v1, s[8:11], s20 offen sc1\n"      # 8 bytes: no such hazard
+            "\tbuffer_load_dwordx4 v[2:5], v1, s[8:11], s20 offen sc1\n"
+            "\tglobal_store_dwordx4 v[0:1], v[2:5], off\n")
+    assert wide_store_violations(fine) == []
+    for bad in ("\tbuffer_store_dwordx4 v[2:5], v1, s[8:11], s20 offen sc1 ; x", "\tbuffer_store_dwordx3 v[2:4], off, s[8:11], s3 offset:16",
+                "\tbuffer_store_dwordx4 v[2:5], v1, s[8:11], m0 offen"):
+        assert [at for at, _ in wide_store_violations(fine + bad + "\n")] == [6]
+        with pytest.raises(RuntimeError, match="wide buffer stores"):
+            build.check_isa_text(GOOD + bad)
 
 
 def test_product_device_code_is_clean():
