@@ -22,3 +22,18 @@ def test_large_transition_costs(S, c_hi, r_hi):
     w.budget[:] = (900, 255, 256, 511)
     for flags in (PACK | PEEK, PACK | NO_PEEK, PACK | PEEK | WIDE, PACK | PEEK | binding.GALV_DP_NO_U32):
         check_against_oracle(w, flags=flags, table_instances=[0, 1, 2, 3], allow_vacuous=S == 1)
+
+
+@pytest.mark.parametrize("S", [6, 22, 44, 128])
+@pytest.mark.parametrize("flags", [0, PACK | PEEK, binding.GALV_DP_NO_PACK])      # all layers in one launch (up to 64 strategies), and one each
+def test_transition_costs_whose_key_would_wrap(S, flags):
+    """(2 * largest R + 2) * 2^k is 2^64 and a little: modulo 2^64 it looks as if a 32-bit key held it."""
+    k = (S - 1).bit_length()
+    top = (1 << (63 - k)) + (1 << 10)
+    w = workloads.random_workload(77 + S, 3, 3, S, 700, m_range=(0, 200), c_range=(0, 5000), r_range=(0, 900), infeasible=0.1,
+                                  zero_diagonal=False)
+    assert ((2 * top + 2) << k) % (1 << 64) <= 1 << 32 and 2 * top < 3 << 60
+    w.R[1, 0, :, :S - 1] += top - 5000
+    w.R[0, 0, 0, S - 1] = w.R[1, 0, S - 1, 0] = top          # the largest entry
+    _, _, _, status = check_against_oracle(w, flags=flags, table_instances=[0, 1, 2])
+    assert list(status[:2]) == [binding.GALV_INSTANCE_OK_INT64] * 2
