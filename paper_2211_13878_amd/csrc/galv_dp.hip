@@ -3887,9 +3887,9 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, bool chain, 
     // time with a launch per layer for 2 - 4 - 8 - 16 - 32 layers: 1 x 3000 columns of 2000 2.29 1.52 1.02 0.72 0.53, 1 x 15000 of 16384 7.2 4.2
     // 2.5 1.4 0.76, 1 x 60000 of 100000 19 10 5.0 2.5 -; 6 x 10000 of 2000 3.1 1.8 1.04 0.81 0.76, of 16384 4.0 2.3 1.3 1.08 0.98; 16 x 3750 of 2000 2.1
     // 1.06 0.70 0.71 0.69.  Up to 300 workgroups a layer, 593 searches of seven kinds took 0.07 to 1.04, but for two whose transition
-    // matrices alternate (1.13, 1.15).  Below a share of 128 cost rows are the other side, and the line lies further out: up to 1000
-    // workgroups a layer 0.13 to 1.00, up to 2000 0.13 to 1.32.
-    const int64_t chain_groups = (int64_t)(share < 128 ? 1000 : 300) * (d->n_layers - 1);
+    // matrices alternate (1.13, 1.15); from there to 640 one strategy 0.55 to 1.06, 2 to 8 0.52 to 1.21, more 0.50 to 1.01.  Below a share
+    // of 128 cost rows are the other side, and the line lies further out: up to 1000 workgroups a layer 0.13 to 1.00, up to 2000 0.13 to 1.32.
+    const int64_t chain_groups = (int64_t)(share < 128 ? 1000 : share < 4096 && (S == 1 || S > 8) ? 640 : 300) * (d->n_layers - 1);
     const ChainEntry *ce = S <= kWave ? pick_chain(S, tiles) : nullptr;
     // (rows of every layer: at most 8 GB of them, and a layer's of one instance within 32 bits of offset; at most kChainLayers
     // layers, see there)

@@ -81,7 +81,8 @@ def test_no_wait_is_longer_than_a_bounded_number_of_layers(lib, S, E):
 
 @pytest.mark.parametrize("B,L,S,E,chains", [(465, 2, 1, 16384, False), (465, 16, 1, 16384, False), (76, 4, 1, 100000, False), (3750, 8, 1, 2000, False),
                                             (625, 4, 6, 2000, False), (234, 2, 16, 2000, False), (1, 4, 44, 100000, False), (1, 16, 44, 100000, False),
-                                            (93, 8, 2, 2000, True), (31, 16, 6, 2000, True), (3, 64, 6, 100000, True), (5000, 32, 1, 300, True)])
+                                            (93, 8, 2, 2000, True), (31, 16, 6, 2000, True), (3, 64, 6, 100000, True), (5000, 32, 1, 300, True),
+                                            (64, 6, 1, 6000, True), (64, 6, 2, 6000, False), (64, 6, 9, 6000, True)])
 def test_layers_pay_for_the_workgroups(lib, B, L, S, E, chains):
     """Every tile costs a workgroup's start, which few layers do not pay for; a very large share of the budget per layer."""
     desc = binding.make_desc(B, L, S, E, 2, binding.GALV_DP_STREAMS(1))
@@ -95,7 +96,7 @@ def test_the_larger_workspace_is_taken_only_where_there_is_room(lib):
     for least, free, want in ((False, 100 << 30, best), (False, 8 * (best - need), best), (False, 8 * (best - need) - 1, need),
                               (False, 0, need), (True, 1 << 40, need)):
         assert binding.workspace_size(large, least, lambda: free) == want
-    small = binding.make_desc(1, 20, 22, 2000, 2)                   # a few MB: nobody is asked
+    small = binding.make_desc(8, 32, 22, 16384, 2)                   # less than 1 GB more: nobody is asked
     best = binding.galv_dp_workspace_bytes_preferred(small)
     assert best > binding.galv_dp_workspace_bytes(small)
     assert binding.workspace_size(small, False, None) == best
