@@ -276,11 +276,14 @@ def _free_bytes(device) -> int:
 
 def workspace_size(desc: Desc, least: bool, free_bytes) -> int:
     """Bytes of workspace for a handle: what suits the shape best, unless the least is asked for or the difference is more
-    than an eighth of the memory that free_bytes() says is left (other handles and tensors will want some of it; up to 64 MB
-    nobody is asked)."""
-    small, best = galv_dp_workspace_bytes(desc), galv_dp_workspace_bytes_preferred(desc)
+    than an eighth of the memory that free_bytes() says is left (other handles and tensors will want some of it; up to 1 GB
+    nobody is asked: the question takes 150 us, as much as a whole search of that size)."""
+    best = galv_dp_workspace_bytes_preferred(desc)
+    if not least and best <= 1 << 30:
+        return best
+    small = galv_dp_workspace_bytes(desc)
     more = best - small
-    return small if more > 0 and (least or (more > 64 << 20 and 8 * more > free_bytes())) else best
+    return small if more > 0 and (least or (more > 1 << 30 and 8 * more > free_bytes())) else best
 
 
 class Solver:

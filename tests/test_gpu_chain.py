@@ -158,7 +158,7 @@ def test_without_the_memory_for_all_layers_a_launch_per_layer(monkeypatch):
 
 
 def test_the_least_workspace_on_request_and_where_little_is_left(monkeypatch):
-    w = workload(6, 4, 60, 22, 20000)
+    w = workload(6, 8, 60, 22, 20000)
     dev = binding.upload(w)
     results = []
     for least, left in ((False, None), (True, None), (False, 1 << 28)):
