@@ -2423,13 +2423,19 @@ __device__ __forceinline__ bool chain_last_column(const int32_t *p, int32_t &x) 
 }
 
 // The recurrence without a memory limit for instance b, all layers (see live_step), by one wave with a lane per strategy:
-// no exchange, the transition keys in LDS.  (1.7 us a layer at 29 strategies, half of what the sweep takes.)
+// no exchange, the transition keys in LDS.  (1.7 us a layer at 29 strategies, half of what the sweep takes.)  It keeps several
+// matrices: fetched anew for each of 82 layers whose matrices alternate, the keys of 60 strategies made the sweep wait for it (539
+// tiles, layers alike: 727 us, now 598; where the sweep's layers are longer, or a matrix smaller, no difference).
 template <int ROWS, class Key>
 __device__ __forceinline__ void chain_live(const Layout &a, int b, typename Key::Rel dmax, int budget) {
     using KeyT = typename Key::T;
     const int lane = lane_id();
     const int S = a.S, k = a.k_bits, L = a.L;
-    KeyT *Rl = reinterpret_cast<KeyT *>(lds_cells);                     // [S][ROWS]
+    // [slots][S][ROWS], matrix r in slot r modulo their number: as many as the keys of a block's rows take (see chain_lds)
+    constexpr int kSlots = kChainCols * 8 / (ROWS * (int)sizeof(KeyT));
+    static_assert(kSlots >= 1 && kSlots <= kWave, "the matrix of each slot by lane");
+    KeyT *slots = reinterpret_cast<KeyT *>(lds_cells);
+    int held = -1;                                 // lane i: the matrix in slot i
     int32_t *hdr = a.hdr + (int64_t)b * L * 8;
     const uint64_t *costs = a.ck + (int64_t)b * L * ROWS;
     const int32_t *mems = a.m + (int64_t)b * L * S;
@@ -2451,11 +2457,11 @@ __device__ __forceinline__ void chain_live(const Layout &a, int b, typename Key:
     load(1, next);
     uint64_t V = now.c;
     int32_t mem = 0, m = now.m;                    // memory in the layers before; of the layer at hand
-    int r_now = -1;
     for (int l = 1; l < L; ++l) {
         now = next;
-        const int r = uniform(now.r);
-        if (r != r_now) {
+        const int r = uniform(now.r), slot = r % kSlots;
+        KeyT *Rl = slots + slot * (ROWS * ROWS);
+        if ((int)read_lane((uint32_t)held, slot) != r) {
             const KeyT *Rk = rkeys<KeyT>(a, b, r);
             for (int i0 = 0; i0 < S; i0 += 8) {    // (eight rows under way at a time, the last one repeated)
                 KeyT row[8];
@@ -2465,7 +2471,7 @@ __device__ __forceinline__ void chain_live(const Layout &a, int b, typename Key:
                 for (int u = 0; u < 8; ++u)
                     if (i0 + u < S && in) Rl[(i0 + u) * ROWS + lane] = row[u];
             }
-            r_now = r;
+            if (lane == slot) held = r;
         }
         load(l + 1, next);
         const bool usable = in && m <= budget;

@@ -223,3 +223,13 @@ def test_matrices_that_change_at_every_layer(S, B, E):
     w.c[1] <<= 30
     w.R[2] <<= 20
     check_against_oracle(w, table_instances=[0, 1, 2], oracle_instances=[0, 1, 2, B - 1], threads=8, allow_vacuous=S == 1)
+
+
+@pytest.mark.parametrize("S,nR,L", [(8, 33, 70), (29, 9, 30), (64, 5, 16)])      # slots for 32 or 16, 8 or 4, 4 or 2 matrices
+def test_more_matrices_than_the_unlimited_recurrence_keeps(S, nR, L):
+    """Matrices come back after another one has taken their slot, next to ones that stay."""
+    w = workload(900 + S, 3, L, S, 1200, nR=nR)
+    w.r_idx[:, 1:] = (np.arange(L - 1) * 3 + np.arange(L - 1) // 7) % nR
+    w.r_idx[1, 1:] = np.where(np.arange(L - 1) % 2, 0, nR - 1)           # two that share a slot, in turns
+    w.R[2] <<= 20
+    check_against_oracle(w, table_instances=[0, 1, 2], threads=8)
