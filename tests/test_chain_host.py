@@ -82,7 +82,9 @@ def test_no_wait_is_longer_than_a_bounded_number_of_layers(lib, S, E):
 @pytest.mark.parametrize("B,L,S,E,chains", [(465, 2, 1, 16384, False), (465, 16, 1, 16384, False), (76, 4, 1, 100000, False), (3750, 8, 1, 2000, False),
                                             (625, 4, 6, 2000, False), (234, 2, 16, 2000, False), (1, 4, 44, 100000, False), (1, 16, 44, 100000, False),
                                             (93, 8, 2, 2000, True), (31, 16, 6, 2000, True), (3, 64, 6, 100000, True), (5000, 32, 1, 300, True),
-                                            (64, 6, 1, 6000, True), (64, 6, 2, 6000, False), (64, 6, 9, 6000, True)])
+                                            (64, 6, 1, 6000, True), (64, 6, 2, 6000, False), (64, 6, 9, 6000, True),
+                                            # shares of 2048 and more: the rows that a shape adds count (33 strategies take 48)
+                                            (3, 23, 33, 57599, False), (2, 23, 33, 57599, True), (3, 38, 33, 57599, True), (2, 23, 48, 57599, True)])
 def test_layers_pay_for_the_workgroups(lib, B, L, S, E, chains):
     """Every tile costs a workgroup's start, which few layers do not pay for; a very large share of the budget per layer."""
     desc = binding.make_desc(B, L, S, E, 2, binding.GALV_DP_STREAMS(1))
