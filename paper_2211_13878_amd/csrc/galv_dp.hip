@@ -2372,7 +2372,7 @@ __global__ __launch_bounds__(W * kWave, WPE) void sweep_bytes_kernel(Layout a, i
 //
 // What bounds it is the latency of a layer's chain: words 0.6 us, rows 0.8, column minima and alive rows 0.6, min-plus and
 // new cells 0.5, until the cells have arrived 0.5.  Whole searches, a launch per layer / chained, in us: 29 strategies x 78 tiles
-// x 37 layers (`single`) 251 / 167, 22 x 1032 x 32 281 / 210, 22 x 1256 x 24 with all budgets 251 / 191, 44 x 272 x 48 482 / 294.
+// x 37 layers (`single`) 250 / 156, 22 x 1032 x 32 282 / 186, 22 x 1256 x 24 with all budgets 249 / 192, 44 x 272 x 48 479 / 294.
 constexpr int kChainCols = 128;
 // Polls of some 0.6 us after which a wait is given up, so that no error in the memory order could hang the GPU.  A correct solve
 // must never get there, and the longest wait spans a whole search: the wave with an instance's last place may start with the
