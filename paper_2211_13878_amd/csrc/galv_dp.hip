@@ -3893,18 +3893,19 @@ galv_status_t make_plan(const galv_dp_desc_t *d, const Tiles *only, bool chain, 
     // time with a launch per layer for 2 - 4 - 8 - 16 - 32 layers: 1 x 3000 columns of 2000 2.29 1.52 1.02 0.72 0.53, 1 x 15000 of 16384 7.2 4.2
     // 2.5 1.4 0.76, 1 x 60000 of 100000 19 10 5.0 2.5 -; 6 x 10000 of 2000 3.1 1.8 1.04 0.81 0.76, of 16384 4.0 2.3 1.3 1.08 0.98; 16 x 3750 of 2000 2.1
     // 1.06 0.70 0.71 0.69.  Up to 300 workgroups a layer, 593 searches of seven kinds took 0.07 to 1.04, but for two whose transition
-    // matrices alternate (1.13, 1.15); from there to 640 one strategy 0.55 to 1.06, 2 to 8 0.52 to 1.21, more 0.50 to 1.01.  Below a share
-    // of 128 cost rows are the other side, and the line lies further out: up to 1000 workgroups a layer 0.13 to 1.00, up to 2000 0.13 to 1.32.
+    // matrices alternate (1.13, 1.15, before chain_live kept several; 260 such searches since 0.17 to 1.03); from there to 640 one
+    // strategy 0.55 to 1.06, 2 to 8 0.52 to 1.21, more 0.50 to 1.01.  Below a share of 128 cost rows are the other side, and the line lies
+    // further out: up to 1000 workgroups a layer 0.13 to 1.00, up to 2000 0.13 to 1.32.
     const int64_t chain_groups = (int64_t)(share < 128 ? 1000 : share < 4096 && (S == 1 || S > 8) ? 640 : 300) * (d->n_layers - 1);
     const ChainEntry *ce = S <= kWave ? pick_chain(S, tiles) : nullptr;
     // Near the line two kinds of inputs lose and all others gain: deep stacks and independent layers with a wide memory range (the
     // peek rules out most of their rows, and the byte table writes one byte where the chain writes eight), the more the larger the
     // share and the more strategies the shape adds to fill its rows.  Deep stacks, those layers - the mean of seven kinds of inputs: 44 x 930
     // share 258 0.93 0.98 - 0.69, share 901 1.08 1.08 - 0.86; 36 x 1134 share 343 1.10 1.05 - 0.82, 34 x 1204 share 895 1.14 1.19 - 0.90, 33 x 1350
-    // share 909 1.29 1.27 - 0.97, 17 x 3990 share 889 1.10 1.15 - 0.92, 9 x 6463 share 899 1.08 0.86 - 0.87, 9 x 6454 share 2458 1.19 1.03 - 0.97.  Sizes cannot tell these kinds from the
-    // others, so the line stays where the mean is below 1; it is not with shares of 2048 and more and many rows to fill: 35 x 1272 1.35
-    // 1.25 - 1.05, 33 x 1350 1.22 1.30 - 1.01, 17 x 3987 1.21 1.24 - 1.00; inside the line that follows 33 x 1044 1.12 1.18 - 0.88, 17 x 3087
-    // 0.99 0.96 - 0.86.
+    // share 909 1.29 1.27 - 0.97, 17 x 3990 share 889 1.10 1.15 - 0.92, 9 x 6463 share 899 1.08 0.86 - 0.87, 9 x 6454 share 2458 1.19 1.03 - 0.97.
+    // The rule knows sizes only, which do not tell these kinds from the others, so the line stays where the mean is below 1.  It is not
+    // with shares of 2048 and more and many rows to fill: 35 x 1272 1.35 1.25 - 1.05, 33 x 1350 1.22 1.30 - 1.01, 17 x 3987 1.21 1.24 - 1.00; inside
+    // the line that follows 33 x 1044 1.12 1.18 - 0.88, 17 x 3087 0.99 0.96 - 0.86.
     if (ce && S > 16 && share >= 2048 && share < 4096 && tiles * ce->ts * ce->ng > chain_to + chain_to / 4) ce = nullptr;
     // (rows of every layer: at most 8 GB of them, and a layer's of one instance within 32 bits of offset; at most kChainLayers
     // layers, see there)
